@@ -351,3 +351,104 @@ def run(s):
     update = pg.pg_sde_step_logprob if s.case["dtype"] == "fp32" else pg.pg_sde_step_logprob_bf16
     update(s.x, s.u, s.out, s.logp, s.hist, None, s.src, s.ids, s.case["kept"], s.case["d"], 0.875, -0.15, 0.35, s.seed, 3, s.partials)
     return dict(x=s.out if s.case["dtype"] == "fp32" else s.out.view(torch.bfloat16), logp=s.logp, hist=s.hist)
+
+
+# ---------------------------------------------------------------- the same values in 64 bits
+
+_MASK = 0xFFFFFFFF
+
+
+def _normals(ids, d, step, stream, seed):
+    """Noise of rows `ids`: Philox-4x32-10 on (element / 4, step, id, stream) under `seed`, Box-Muller, all in 64 bits."""
+    blocks = torch.arange(d // 4, dtype=torch.int64, device=DEV)[None, :]
+    c = [blocks.expand(len(ids), -1), torch.full_like(blocks, step), ids.to(torch.int64)[:, None], torch.full_like(blocks, stream)]
+    k0, k1 = seed & _MASK, seed >> 32 & _MASK
+    for _ in range(10):
+        p0, p1 = 0xD2511F53 * c[0], 0xCD9E8D57 * c[2]                 # modulo 2^64: only the bit pattern is used
+        c = [(p1 >> 32 & _MASK) ^ c[1] ^ k0, p1 & _MASK, (p0 >> 32 & _MASK) ^ c[3] ^ k1, p0 & _MASK]
+        k0, k1 = (k0 + 0x9E3779B9) & _MASK, (k1 + 0xBB67AE85) & _MASK
+    u = [(w.double() + 0.5) / 2.0 ** 32 for w in c]
+    r = [(-2.0 * u[0].log()).sqrt(), (-2.0 * u[2].log()).sqrt()]
+    a = [2.0 * math.pi * u[1], 2.0 * math.pi * u[3]]
+    return torch.stack([r[0] * a[0].cos(), r[0] * a[0].sin(), r[1] * a[1].cos(), r[1] * a[1].sin()], -1).reshape(len(ids), d)
+
+
+def _coefficients(case):
+    """Per step (A, B, C, P, Q): x' = A x + B u + C xi, preview = P x + Q u."""
+    T, out = case["T"], []
+    if case["sampler"] == "flow":
+        for s in range(T):
+            tau, delta = 1.0 - s / T, -1.0 / T
+            var = 0.7 ** 2 * tau / max(1.0 - tau, 1.0 / T)
+            out.append((1.0 + var * delta / (2.0 * tau), delta * (1.0 + var * (1.0 - tau) / (2.0 * tau)),
+                        math.sqrt(var * -delta), 1.0, -tau))
+        return out
+    alphas, prod = [], 1.0
+    for i in range(1000):
+        prod *= 1.0 - (1e-4 + (0.02 - 1e-4) * i / 999)
+        alphas.append(prod)
+    steps = [((T - i) * 999 + T // 2) // T for i in range(T + 1)]
+    for s in range(T):
+        at, ap = alphas[steps[s]], alphas[steps[s + 1]]
+        var = (1.0 - ap) / (1.0 - at) * (1.0 - at / ap)
+        out.append((math.sqrt(ap / at), math.sqrt(1.0 - ap - var) - math.sqrt(ap * (1.0 - at) / at), math.sqrt(var),
+                    1.0 / math.sqrt(at), -math.sqrt((1.0 - at) / at)))
+    return out
+
+
+def _logp(z, C):
+    return -0.5 * (z * z).sum(1) - z.shape[1] * (math.log(C) + 0.5 * math.log(2.0 * math.pi))
+
+
+def _highest_variance(r, k):
+    """Slots of the k members with the largest variance: the j lowest and the k - j highest, best j."""
+    order = r.argsort(stable=True)
+    picks = [torch.cat([order[:j], order[len(r) - (k - j):]]) for j in range(k + 1)]
+    return max(picks, key=lambda p: float(r[p].var(unbiased=False))).sort().values
+
+
+def exact(case, seed):
+    if case["work"] == "update":
+        s = prepare(case, seed)
+        d, out = case["d"], []
+        as_is = (lambda t: t) if case["dtype"] == "fp32" else (lambda t: t.view(torch.bfloat16))
+        x, u = as_is(s.x), as_is(s.u)
+        logp = torch.zeros(case["kept"], dtype=torch.float64, device=DEV)
+        rows = max(1, (1 << 24) // d)
+        for r in range(0, case["kept"], rows):
+            ids = s.ids[r:r + rows].long()
+            z = _normals(ids, d, 3, 1, s.seed)
+            out.append(0.875 * x[ids].double() - 0.15 * u[ids].double() + 0.35 * z)
+            logp[r:r + rows] = _logp(z, 0.35)
+        hist = torch.zeros(case["rows"], dtype=torch.float64, device=DEV)
+        hist[s.ids.long()] = logp
+        return dict(x=torch.cat(out), logp=logp, hist=hist)
+    if case["work"] != "own":
+        return None          # selections are whole numbers; a bf16 network followed in 64 bits takes far too long
+    s = prepare(case, seed)
+    P, N, T, d = case["P"], case["N"], case["T"], case["C"] * case["H"] * case["W"]
+    u, w, sched = s.buf.u.view(P * N, d).double(), s.buf.probe_w.view(-1).double(), _schedule(case)
+    ids, sizes = torch.arange(P * N, device=DEV), [N] * P
+    x = _normals(ids, d, 0, 0, s.seed)
+    logp = torch.full((T, P * N), math.nan, dtype=torch.float64, device=DEV)
+    for step, (A, B, C, pc, qc) in enumerate(_coefficients(case)):
+        src = torch.arange(len(ids), device=DEV)
+        if step in s.checkpoints:
+            reward = 0.1 + (pc * x + qc * u[:len(ids)]) @ w
+            kept, first = [], 0
+            for g in range(P):
+                slots = torch.arange(first, first + sizes[g], device=DEV)
+                first += sizes[g]
+                if step in dict(sched[g]):
+                    sizes[g] = dict(sched[g])[step]
+                    slots = slots[_highest_variance(reward[slots], sizes[g])]
+                kept.append(slots)
+            src = torch.cat(kept)
+        ids = ids[src]
+        z = _normals(ids, d, step, 1, s.seed)
+        logp[step, ids] = _logp(z, C)
+        x = A * x[src] + B * u[src] + C * z
+    rewards = 0.1 + x @ w
+    adv = torch.cat([(r - r.mean()) / (r.std(unbiased=False) + 1e-6) for r in rewards.split(sizes)])
+    offsets = torch.tensor([sum(sizes[:g]) for g in range(P + 1)], device=DEV)
+    return dict(x=x, survivors=ids, rewards=rewards, adv=adv, logp=logp, logp_sum=logp.nansum(0), offsets=offsets)
