@@ -1,11 +1,14 @@
 // Optimal Variance Filtering per group (paper Sec. 4.2, Eq. 10; in-loop form in Sec. 5.1), the
 // group-normalised advantages (Eq. 5, Eq. 18) and the small index kernels around a prune.
 //
-// One 64-lane wavefront owns one group (the paper's groups have at most 64 members, cf. the
-// group-size ablation): ranks by all-pairs comparison over lane broadcasts, fp64 prefix sums by a
-// six-step shuffle-up scan, k+1 candidate scores in lanes 0..k, a butterfly arg-max, and a ballot
-// for the survivor mask.  Why k+1 candidates are enough: with the other members fixed the variance
-// is a convex quadratic in one member's value, so some optimum is "j lowest and k-j highest".
+// Why k+1 candidates per group are enough: with the other members fixed the variance is a convex
+// quadratic in one member's value, so some optimum is "j lowest and k-j highest".
+// Two decompositions for groups of at most 64 members (the paper's groups, cf. the group-size
+// ablation), both with the same order of fp64 additions and therefore the same bits:
+//   few groups: one 64-lane wavefront owns one group: ranks by all-pairs comparison from LDS, fp64
+//   prefix sums by a six-step shuffle-up scan, k+1 candidate scores in lanes 0..k, a butterfly
+//   arg-max, a ballot for the survivor mask;
+//   many groups: one LANE owns one group (ovf_select_lanes_kernel below).
 #include <mutex>
 #include "common.hpp"
 #include "philox.hpp"
@@ -41,18 +44,79 @@ __device__ __forceinline__ void fill_bad_group(int32_t* __restrict__ sel_idx, in
   for (int i = lane; i < k; i += lanes) sel_idx[out0 + i] = n >= 1 ? b + (i < n ? i : n - 1) : 0;
 }
 
-__global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
-    const float* __restrict__ rewards, const int32_t* __restrict__ offsets, const int32_t* __restrict__ kk,
-    int n_groups, const int32_t* __restrict__ new_offsets, uint64_t* __restrict__ masks,
-    int32_t* __restrict__ sel_idx, int32_t* __restrict__ status) {
-  __shared__ float sorted[OVF_WAVES][WAVE];
-  const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-  const int g = blockIdx.x * OVF_WAVES + wv;
-  if (g >= n_groups) return;                        // whole wave leaves together
-  const int b = offsets[g];
-  const int n = offsets[g + 1] - b;
-  const int k = kk[g];
-  const int out0 = new_offsets[g];
+// ---- where a group's survivors go: new_offsets[g] = sum of k[0..g) ----
+// The selection kernels work that out themselves instead of waiting for a scan in launches of its own (three of them
+// cost more than the selection: 4096 groups took 20 us, of which the selection was 6).  OFF_GIVEN: the caller knows the
+// offsets (the sampling loop has them from its schedule).  OFF_DIRECT, up to OFF_DIRECT_MAX groups: a workgroup adds up all
+// counts before its first group (at most 16 KB, from L2).  OFF_SUMS, above that: one launch sums blocks of SCAN_BLOCK
+// counts, and a workgroup adds the sums before its block and the counts before it inside the block.
+enum OffsetsFrom { OFF_GIVEN = 0, OFF_DIRECT = 1, OFF_SUMS = 2 };
+constexpr int OFF_DIRECT_MAX = 4096;
+
+// Sum over all THREADS lanes of the workgroup, the same in every lane; `part` holds one int per wave.
+template <int THREADS>
+__device__ __forceinline__ int block_allsum(int s, int* part) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, WAVE);
+  if (THREADS == WAVE) return s;
+  if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x / WAVE] = s;
+  __syncthreads();
+  int t = 0;
+#pragma unroll
+  for (int w = 0; w < THREADS / WAVE; ++w) t += part[w];
+  return t;
+}
+
+// sum of k[0..first) by the whole workgroup (first < n_groups)
+template <int FROM, int THREADS>
+__device__ __forceinline__ int counts_before(const int32_t* __restrict__ kk, const int32_t* __restrict__ sums, int first,
+                                             int* part) {
+  int s = 0, from = 0;
+  if (FROM == OFF_SUMS) {
+    const int blk = first / SCAN_BLOCK;
+    for (int i = threadIdx.x; i < blk; i += THREADS) s += sums[i];
+    from = blk * SCAN_BLOCK;
+  }
+  int i = from + threadIdx.x;
+  for (; i + 3 * THREADS < first; i += 4 * THREADS)
+    s += (counted_k(kk[i]) + counted_k(kk[i + THREADS])) + (counted_k(kk[i + 2 * THREADS]) + counted_k(kk[i + 3 * THREADS]));
+  for (; i < first; i += THREADS) s += counted_k(kk[i]);
+  return block_allsum<THREADS>(s, part);
+}
+
+// Kernels with one wave per group: where group g's survivors start (written to new_offsets unless it is given).  Called by
+// the whole workgroup; the result of a wave past the last group is not used.
+template <int FROM>
+__device__ __forceinline__ int place_group(const int32_t* __restrict__ kk, const int32_t* __restrict__ sums, int g, int n_groups,
+                                           int32_t* new_offsets, int* part) {
+  if (FROM == OFF_GIVEN) return g < n_groups ? new_offsets[g] : 0;
+  const int g0 = blockIdx.x * OVF_WAVES;
+  int out0 = counts_before<FROM, OVF_WAVES * WAVE>(kk, sums, g0, part);
+  if (g >= n_groups) return 0;
+  for (int i = g0; i < g; ++i) out0 += counted_k(kk[i]);
+  if ((threadIdx.x & (WAVE - 1)) == 0) {
+    new_offsets[g] = out0;
+    if (g == n_groups - 1) new_offsets[n_groups] = out0 + counted_k(kk[g]);
+  }
+  return out0;
+}
+
+__global__ __launch_bounds__(SCAN_THREADS) void scan_block_sums_kernel(const int32_t* __restrict__ kk,
+                                                                       int n, int32_t* __restrict__ sums) {
+  __shared__ int part[SCAN_THREADS / WAVE];
+  int s = 0;
+  const int base = blockIdx.x * SCAN_BLOCK + threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) if (base + i * SCAN_THREADS < n) s += counted_k(kk[base + i * SCAN_THREADS]);
+  s = block_allsum<SCAN_THREADS>(s, part);
+  if (threadIdx.x == 0) sums[blockIdx.x] = s;
+}
+
+// Optimal Variance Filtering of one group by one wavefront; `vals`, `sorted`: 64 floats of LDS of this wave.
+__device__ __forceinline__ void select_one_group(const float* __restrict__ rewards, int g, int b, int n, int k, int out0,
+                                                 float* vals, float* sorted, uint64_t* __restrict__ masks,
+                                                 int32_t* __restrict__ sel_idx, int32_t* __restrict__ status) {
+  const int lane = threadIdx.x & (WAVE - 1);
   if (n < 1 || n > WAVE || k < 1 || k > n) {        // nothing to select: empty mask; flag unless the
     if (lane == 0) {                                // group is simply empty (n = k = 0)
       if (!(n == 0 && k == 0)) atomicOr(status, 2);
@@ -62,7 +126,7 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
     return;
   }
   const bool live = lane < n;
-  float v = live ? rewards[b + lane] + 0.0f : 0.0f;  // -0.0 becomes +0.0
+  const float v = live ? rewards[b + lane] + 0.0f : 0.0f;  // -0.0 becomes +0.0
   const bool bad = live && !(__builtin_fabsf(v) <= 3.4028234663852886e38f);
   if (__ballot(bad) != 0ull || k == n) {
     // k == n keeps everything; a non-finite reward is flagged and the first k slots are kept so
@@ -72,19 +136,24 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
     if (lane == 0) masks[g] = (k == WAVE) ? ~0ull : ((1ull << k) - 1ull);
     return;
   }
-  // rank under the strict order (value, slot)
+  // rank under the strict order (value, slot): every value is read from LDS by all lanes at once, four at a time
+  vals[lane] = live ? v : __builtin_huge_valf();
+  sorted[lane] = 0.0f;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
   int rank = 0;
-  for (int l = 0; l < n; ++l) {
-    const float vl = __shfl(v, l, WAVE);
-    rank += (vl < v || (vl == v && l < lane)) ? 1 : 0;
+  for (int l = 0; l < n; l += 4) {
+    const float4 q = *reinterpret_cast<const float4*>(vals + l);
+    rank += (q.x < v || (q.x == v && l < lane)) ? 1 : 0;
+    rank += (q.y < v || (q.y == v && l + 1 < lane)) ? 1 : 0;
+    rank += (q.z < v || (q.z == v && l + 2 < lane)) ? 1 : 0;
+    rank += (q.w < v || (q.w == v && l + 3 < lane)) ? 1 : 0;
   }
-  sorted[wv][lane] = 0.0f;
+  if (live) sorted[rank] = v;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  if (live) sorted[wv][rank] = v;
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  const double y = (double)sorted[wv][lane];                       // ascending, zero padded
-  const double z = live ? (double)sorted[wv][n - 1 - lane] : 0.0;  // descending, zero padded
+  const double y = (double)sorted[lane];                           // ascending, zero padded
+  const double z = live ? (double)sorted[n - 1 - lane] : 0.0;      // descending, zero padded
   const double s_lo = wave_scan_f64(y, lane);
   const double s_lo2 = wave_scan_f64(__dmul_rn(y, y), lane);
   const double s_hi = wave_scan_f64(z, lane);
@@ -115,32 +184,307 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
   if (lane == 0) masks[g] = mask;
 }
 
-// ---- the same selection for groups of up to 1024 members (beyond the paper's group sizes): one
-// workgroup of 1024 lanes per group, one member per lane.  Same evaluation order as above with the
-// prefix sums taken over S zero-padded slots, S = 64 up to 64 members, else the next power of two.
+template <int FROM>
+__global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
+    const float* __restrict__ rewards, const int32_t* __restrict__ offsets, const int32_t* __restrict__ kk,
+    int n_groups, const int32_t* __restrict__ sums, int32_t* new_offsets, uint64_t* __restrict__ masks,
+    int32_t* __restrict__ sel_idx, int32_t* __restrict__ status) {
+  __shared__ __align__(16) float vals[OVF_WAVES][WAVE];
+  __shared__ float sorted[OVF_WAVES][WAVE];
+  __shared__ int part[OVF_WAVES];
+  const int wv = threadIdx.x / WAVE;
+  const int g = blockIdx.x * OVF_WAVES + wv;
+  const int out0 = place_group<FROM>(kk, sums, g, n_groups, new_offsets, part);
+  if (g >= n_groups) return;                        // whole wave leaves together
+  const int b = offsets[g];
+  const int n = offsets[g + 1] - b;
+  const int k = kk[g];
+  select_one_group(rewards, g, b, n, k, out0, vals[wv], sorted[wv], masks, sel_idx, status);
+}
+
+// ---- many groups: one lane per group ----
+// The wave-per-group form needs about 400 wave instructions per group, most of them cross-lane traffic (an all-pairs rank and
+// four fp64 scans by shuffles); it is issue bound (2^20 groups of 64 -> 16: 1.2 ms, 3 % of the memory rate).  Here a lane
+// sorts its own group in registers by a compare-exchange network (Batcher's odd-even merge sort: 543 compare-exchanges for 64
+// slots, two instructions each, for 64 groups at once) and runs the scans of the same doubling recurrence on registers.
+// Only the values are sorted; members are picked afterwards by comparing them with the two threshold values, with
+// ties at a threshold resolved by slot.  What a lane has to index by its own n and k (the descending order, the prefix
+// sums from the top) goes through LDS as [index][lane], so that every access is conflict free.
+// Takes a wave's 64 groups when all of them have 1..64 members, finite rewards and 1 <= k < n with k <= 32; any other
+// wave runs the wave-per-group code on its groups one after another.
+constexpr int LANE_K = 32;                         // largest count of the register scans
+constexpr int LANE_ROW = WAVE * WAVE + 2 * WAVE;   // staged rewards of 64 groups: one float of padding per 64, and a margin
+constexpr int LANE_WAVES = 2;                      // waves per workgroup (33 KB of LDS)
+
+// order-preserving map between floats and integers (its own inverse on the bits)
+__device__ __forceinline__ int ordered_bits(int b) { return b ^ ((b >> 31) & 0x7FFFFFFF); }
+
+// Batcher's odd-even merge sort (Knuth, vol. 3, algorithm 5.2.2M) of N registers: P the length of the sorted runs, Q the
+// distance of the compare-exchanges.  Recursive templates, so that every index is a constant.
+template <int N, int P, int Q>
+__device__ __forceinline__ void sort_registers(int (&v)[N]) {
+  if constexpr (P < N) {
+#pragma unroll
+    for (int i = 0; i + Q < N; ++i)
+      if (i >= Q % P && (i - Q % P) % (2 * Q) < Q && i / (2 * P) == (i + Q) / (2 * P)) {
+        const int lo = min(v[i], v[i + Q]), hi = max(v[i], v[i + Q]);
+        v[i] = lo;
+        v[i + Q] = hi;
+      }
+    if constexpr (Q > 1) sort_registers<N, P, Q / 2>(v);
+    else sort_registers<N, 2 * P, 2 * P>(v);
+  }
+}
+
+// inclusive prefix sums by the doubling recurrence (see wave_scan_f64)
+template <int K, int DD = 1>
+__device__ __forceinline__ void scan_registers(double (&a)[K]) {
+  if constexpr (DD < K) {
+#pragma unroll
+    for (int i = K - 1; i >= DD; --i) a[i] = __dadd_rn(a[i], a[i - DD]);
+    scan_registers<K, 2 * DD>(a);
+  }
+}
+
+__device__ __forceinline__ void lanes_sync() {     // this wave's LDS accesses, handed over between its lanes
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ int padded(int e) { return e + (e >> 6); }
+
+// Rewards [first, first + total) of a wave's groups into its LDS row, total <= 4096; returns whether one is not finite.
+__device__ __forceinline__ bool stage_rewards(const float* __restrict__ rewards, int first, int total, int lane, float* row) {
+  bool bad = false;
+#pragma unroll
+  for (int c = 0; c < 64; c += 16) {
+    if (c * 64 >= total) break;
+    float t[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t[i] = rewards[first + min((c + i) * 64 + lane, total - 1)];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      bad = bad || !(__builtin_fabsf(t[i]) <= 3.4028234663852886e38f);
+      row[padded((c + i) * 64 + lane)] = t[i];
+    }
+  }
+  return bad;
+}
+
+// One group per lane, n <= N members at row[padded(o + i)], 1 <= k < n, k <= K.  Returns the survivor mask.
+template <int N, int K>
+__device__ __forceinline__ uint64_t select_lane(const float* __restrict__ rewards, int first, int total, int o, int n, int k,
+                                                int lane, float* row) {
+  float y[K], z[K];
+  {
+    int v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int bits = ordered_bits(__builtin_bit_cast(int, row[padded(o + i)] + 0.0f));   // -0.0 becomes +0.0
+      v[i] = i < n ? bits : 0x7FFFFFFF;
+    }
+    lanes_sync();
+    sort_registers<N, 1, 1>(v);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float f = __builtin_bit_cast(float, ordered_bits(v[i]));
+      row[i * WAVE + lane] = f;
+      if (i < K) y[i] = f;
+    }
+    lanes_sync();
+#pragma unroll
+    for (int i = 0; i < K; ++i) z[i] = row[max(n - 1 - i, 0) * WAVE + lane];
+    lanes_sync();
+  }
+  // Entries at or past n hold padding; they enter no sum that is used, because candidates take at most k < n of either end.
+  double* top = reinterpret_cast<double*>(row);      // [K][64 lanes]
+  double s1[K + 1], a[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) a[i] = (double)z[i];
+  scan_registers<K>(a);
+#pragma unroll
+  for (int i = 0; i < K; ++i) top[i * WAVE + lane] = a[i];
+  lanes_sync();
+#pragma unroll
+  for (int i = 0; i < K; ++i) a[i] = (double)y[i];
+  scan_registers<K>(a);
+#pragma unroll
+  for (int j = 0; j <= K; ++j) {
+    const int m = k - j;
+    const double hi = m >= 1 ? top[(m - 1) * WAVE + lane] : 0.0;
+    s1[j] = __dadd_rn(j ? a[j ? j - 1 : 0] : 0.0, hi);
+  }
+  lanes_sync();
+#pragma unroll
+  for (int i = 0; i < K; ++i) a[i] = __dmul_rn((double)z[i], (double)z[i]);
+  scan_registers<K>(a);
+#pragma unroll
+  for (int i = 0; i < K; ++i) top[i * WAVE + lane] = a[i];
+  lanes_sync();
+#pragma unroll
+  for (int i = 0; i < K; ++i) a[i] = __dmul_rn((double)y[i], (double)y[i]);
+  scan_registers<K>(a);
+  double score = -__builtin_huge_val();
+  int best = 0;
+  float tlo = -__builtin_huge_valf();                // largest value taken from the bottom
+#pragma unroll
+  for (int j = 0; j <= K; ++j) {
+    const int m = k - j;
+    const double hi2 = m >= 1 ? top[(m - 1) * WAVE + lane] : 0.0;
+    const double s2 = __dadd_rn(j ? a[j ? j - 1 : 0] : 0.0, hi2);
+    const double sc = __dsub_rn(__dmul_rn((double)k, s2), __dmul_rn(s1[j], s1[j]));
+    if (j <= k && sc > score) {                      // ties stay with the smaller j
+      score = sc;
+      best = j;
+      if (j) tlo = y[j ? j - 1 : 0];
+    }
+  }
+  const int take_hi = k - best;
+  float thi = __builtin_huge_valf();                 // smallest value taken from the top
+  int quota_lo = 0, quota_hi = 0;                    // members equal to a threshold that are taken
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    if (i + 1 == take_hi) thi = z[i];
+    quota_lo += (i < best && y[i] == tlo) ? 1 : 0;
+  }
+#pragma unroll
+  for (int i = 0; i < K; ++i) quota_hi += (i < take_hi && z[i] == thi) ? 1 : 0;
+  lanes_sync();
+  stage_rewards(rewards, first, total, lane, row);
+  lanes_sync();
+  // the N addresses of the row are computed again instead of being carried in N registers from the top
+  asm volatile("" : "+v"(o));
+  uint64_t mask = 0ull;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float v = row[padded(o + i)];
+    if (i < n && (v <= tlo || v >= thi)) mask |= 1ull << i;
+  }
+  if (__ballot(__popcll(mask) != k) != 0ull) {       // somewhere members tie across a threshold: lowest / highest slots first
+    mask = 0ull;
+    for (int i = 0; i < n; ++i) {
+      const float v = row[padded(o + i)];
+      const bool eq = v == tlo && quota_lo > 0;
+      if (v < tlo || eq) mask |= 1ull << i;
+      quota_lo -= eq ? 1 : 0;
+    }
+    for (int i = n - 1; i >= 0; --i) {
+      const float v = row[padded(o + i)];
+      const bool eq = v == thi && quota_hi > 0;
+      if (v > thi || eq) mask |= 1ull << i;
+      quota_hi -= eq ? 1 : 0;
+    }
+  }
+  lanes_sync();
+  return mask;
+}
+
+template <int FROM>
+__global__ __launch_bounds__(LANE_WAVES * WAVE, 2) void ovf_select_lanes_kernel(
+    const float* __restrict__ rewards, const int32_t* __restrict__ offsets, const int32_t* __restrict__ kk,
+    int n_groups, const int32_t* __restrict__ sums, int32_t* new_offsets, uint64_t* __restrict__ masks,
+    int32_t* __restrict__ sel_idx, int32_t* __restrict__ status) {
+  __shared__ __align__(16) float rows[LANE_WAVES][LANE_ROW];
+  __shared__ int part[LANE_WAVES], wave_total[LANE_WAVES];
+  const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+  const int g_wave = (blockIdx.x * LANE_WAVES + wv) * WAVE, g = g_wave + lane;
+  const int before = FROM == OFF_GIVEN ? 0 : counts_before<FROM, LANE_WAVES * WAVE>(kk, sums, blockIdx.x * LANE_WAVES * WAVE, part);
+  const bool have = g < n_groups;
+  const int k = have ? kk[g] : 0;
+  int out0 = 0;
+  if (FROM == OFF_GIVEN) {
+    out0 = have ? new_offsets[g] : 0;
+  } else {
+    int incl = counted_k(k);
+#pragma unroll
+    for (int dd = 1; dd < WAVE; dd <<= 1) {
+      const int t = __shfl_up(incl, dd, WAVE);
+      if (lane >= dd) incl += t;
+    }
+    if (lane == WAVE - 1) wave_total[wv] = incl;
+    __syncthreads();
+    out0 = before + incl - counted_k(k);
+    for (int w = 0; w < wv; ++w) out0 += wave_total[w];
+    if (have) {
+      new_offsets[g] = out0;
+      if (g == n_groups - 1) new_offsets[n_groups] = out0 + counted_k(k);
+    }
+  }
+  if (g_wave >= n_groups) return;                   // no barrier of the workgroup follows
+  const int b = have ? offsets[g] : 0;
+  const int n = have ? offsets[g + 1] - b : 0;
+  float* row = rows[wv];
+  const int members = min(WAVE, n_groups - g_wave);
+  const int first = __shfl(b, 0, WAVE), last = __shfl(b + n, members - 1, WAVE);
+  const bool fits = !have || (n >= 1 && n <= WAVE && k >= 1 && k < n && k <= LANE_K);
+  bool lanes_ok = __ballot(!fits) == 0ull;
+  if (lanes_ok) {
+    lanes_ok = __ballot(stage_rewards(rewards, first, last - first, lane, row)) == 0ull;
+    lanes_sync();
+  }
+  if (!lanes_ok) {                                   // wave-uniform
+    for (int i = 0; i < members; ++i)
+      select_one_group(rewards, g_wave + i, __shfl(b, i, WAVE), __shfl(n, i, WAVE), __shfl(k, i, WAVE), __shfl(out0, i, WAVE),
+                       row, row + WAVE, masks, sel_idx, status);
+    return;
+  }
+  int n_max = have ? n : 0, k_max = have ? k : 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    n_max = max(n_max, __shfl_xor(n_max, o, WAVE));
+    k_max = max(k_max, __shfl_xor(k_max, o, WAVE));
+  }
+  // lanes past the last group work on the first one's rewards and store nothing
+  const int o = have ? b - first : 0, nn = have ? n : 2, kq = have ? k : 1;
+  uint64_t mask;
+  if (n_max <= 16) mask = select_lane<16, 16>(rewards, first, last - first, o, nn, kq, lane, row);
+  else if (n_max <= 32) mask = k_max <= 16 ? select_lane<32, 16>(rewards, first, last - first, o, nn, kq, lane, row)
+                                           : select_lane<32, 32>(rewards, first, last - first, o, nn, kq, lane, row);
+  else mask = k_max <= 16 ? select_lane<64, 16>(rewards, first, last - first, o, nn, kq, lane, row)
+                          : select_lane<64, 32>(rewards, first, last - first, o, nn, kq, lane, row);
+  if (!have) mask = 0ull;
+  if (have) masks[g] = mask;
+  // survivors of the wave are contiguous in sel_idx: packed in LDS first (at most 64 * 32), written out coalesced
+  int* idx = reinterpret_cast<int*>(row);
+  const int out_first = __shfl(out0, 0, WAVE), out_n = __shfl(out0 + k, members - 1, WAVE) - out_first;
+  int at = out0 - out_first;
+  for (uint64_t left = mask; left; left &= left - 1ull) idx[at++] = b + __builtin_ctzll(left);
+  lanes_sync();
+  for (int i = lane; i < out_n; i += WAVE) sel_idx[out_first + i] = idx[i];
+}
+
+// ---- the same selection for groups of up to 1024 members (beyond the paper's group sizes): one workgroup of
+// THREADS lanes per group, one member per lane, THREADS the smallest of 128..1024 that the caller's mask words can
+// name.  Same evaluation order as above with the prefix sums taken over S zero-padded slots, S = 64 up to 64
+// members, else the next power of two.  A workgroup sized for 1024 members spent most of its time in the
+// barriers of idle waves; the running sums keep two copies in LDS, so that a pass costs one barrier.
 constexpr int OVF_LARGE = 1024;
 
-__global__ __launch_bounds__(OVF_LARGE) void ovf_select_large_kernel(
+template <int FROM, int THREADS>
+__global__ __launch_bounds__(THREADS) void ovf_select_large_kernel(
     const float* __restrict__ rewards, const int32_t* __restrict__ offsets, const int32_t* __restrict__ kk,
-    int n_groups, const int32_t* __restrict__ new_offsets, int mask_words, uint64_t* __restrict__ masks,
+    int n_groups, const int32_t* __restrict__ sums, int32_t* new_offsets, int mask_words, uint64_t* __restrict__ masks,
     int32_t* __restrict__ sel_idx, int32_t* __restrict__ status) {
-  __shared__ float val[OVF_LARGE];
-  __shared__ float sorted[OVF_LARGE];
-  __shared__ double sc[4][OVF_LARGE];              // running sums of y, y^2, z, z^2
-  __shared__ double red_s[OVF_LARGE / WAVE];
-  __shared__ int red_b[OVF_LARGE / WAVE];
-  __shared__ int wave_cnt[OVF_LARGE / WAVE];
+  __shared__ __align__(16) float val[THREADS];
+  __shared__ float sorted[THREADS];
+  __shared__ double sc[2][4][THREADS];             // running sums of y, y^2, z, z^2, two copies
+  __shared__ double red_s[THREADS / WAVE];
+  __shared__ int red_b[THREADS / WAVE];
+  __shared__ int wave_cnt[THREADS / WAVE];
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid / WAVE;
   const int g = blockIdx.x;
   const int b = offsets[g];
   const int n = offsets[g + 1] - b;
   const int k = kk[g];
-  const int out0 = new_offsets[g];
+  const int out0 = counts_before<FROM, THREADS>(kk, sums, g, wave_cnt);
+  if (tid == 0) {
+    new_offsets[g] = out0;
+    if (g == n_groups - 1) new_offsets[n_groups] = out0 + counted_k(k);
+  }
   uint64_t* mrow = masks + (int64_t)g * mask_words;
-  if (n < 1 || n > OVF_LARGE || n > 64 * mask_words || k < 1 || k > n) {
+  if (n < 1 || n > THREADS || n > 64 * mask_words || k < 1 || k > n) {
     if (tid == 0 && !(n == 0 && k == 0)) atomicOr(status, 2);
     if (tid < mask_words) mrow[tid] = 0ull;
-    fill_bad_group(sel_idx, out0, b, n, k, tid, OVF_LARGE);
+    fill_bad_group(sel_idx, out0, b, n, k, tid, THREADS);
     return;                                          // whole workgroup leaves together
   }
   const bool live = tid < n;
@@ -152,35 +496,41 @@ __global__ __launch_bounds__(OVF_LARGE) void ovf_select_large_kernel(
     if (any_bad && tid == 0) atomicOr(status, 1);
     keep = tid < k;
   } else {
-    val[tid] = v;
-    __syncthreads();
-    int rank = 0;
-    if (live)
-      for (int l = 0; l < n; ++l) {
-        const float vl = val[l];
-        rank += (vl < v || (vl == v && l < tid)) ? 1 : 0;
-      }
+    val[tid] = live ? v : __builtin_huge_valf();
     sorted[tid] = 0.0f;
     __syncthreads();
+    int rank = 0;
+    if (wv * WAVE < n) {
+      // slots before this wave's count when equal, slots behind it do not; its own 64 are compared by slot
+      const int own = wv * WAVE, own_end = min(own + WAVE, n);
+      for (int l = 0; l < own; l += 4) {
+        const float4 q = *reinterpret_cast<const float4*>(val + l);
+        rank += (q.x <= v ? 1 : 0) + (q.y <= v ? 1 : 0) + (q.z <= v ? 1 : 0) + (q.w <= v ? 1 : 0);
+      }
+      for (int l = own; l < own_end; ++l) rank += (val[l] < v || (val[l] == v && l < tid)) ? 1 : 0;
+      for (int l = own + WAVE; l < n; l += 4) {      // past n: +inf, never below v
+        const float4 q = *reinterpret_cast<const float4*>(val + l);
+        rank += (q.x < v ? 1 : 0) + (q.y < v ? 1 : 0) + (q.z < v ? 1 : 0) + (q.w < v ? 1 : 0);
+      }
+    }
     if (live) sorted[rank] = v;
     __syncthreads();
     int S = WAVE;
     while (S < n) S <<= 1;
-    {
-      const double y = (double)sorted[tid];
-      const double z = live ? (double)sorted[n - 1 - tid] : 0.0;
-      sc[0][tid] = y; sc[1][tid] = __dmul_rn(y, y); sc[2][tid] = z; sc[3][tid] = __dmul_rn(z, z);
-    }
+    const double y = (double)sorted[tid];
+    const double z = live ? (double)sorted[n - 1 - tid] : 0.0;
+    double run[4] = {y, __dmul_rn(y, y), z, __dmul_rn(z, z)};
+    int cur = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sc[0][q][tid] = run[q];
     __syncthreads();
     for (int dd = 1; dd < S; dd <<= 1) {             // all slots updated from the values of the previous pass
-      double t[4] = {0.0, 0.0, 0.0, 0.0};
       if (tid >= dd && tid < S)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) t[q] = sc[q][tid - dd];
-      __syncthreads();
-      if (tid >= dd && tid < S)
+        for (int q = 0; q < 4; ++q) run[q] = __dadd_rn(run[q], sc[cur][q][tid - dd]);
+      cur ^= 1;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) sc[q][tid] = __dadd_rn(sc[q][tid], t[q]);
+      for (int q = 0; q < 4; ++q) sc[cur][q][tid] = run[q];
       __syncthreads();
     }
     // candidate j = tid (0 <= j <= k): j lowest + (k - j) highest
@@ -188,8 +538,8 @@ __global__ __launch_bounds__(OVF_LARGE) void ovf_select_large_kernel(
     double score = -__builtin_huge_val();
     int best = j;
     if (j <= k) {
-      const double lo = j ? sc[0][j - 1] : 0.0, lo2 = j ? sc[1][j - 1] : 0.0;
-      const double hi = m ? sc[2][m - 1] : 0.0, hi2 = m ? sc[3][m - 1] : 0.0;
+      const double lo = j ? sc[cur][0][j - 1] : 0.0, lo2 = j ? sc[cur][1][j - 1] : 0.0;
+      const double hi = m ? sc[cur][2][m - 1] : 0.0, hi2 = m ? sc[cur][3][m - 1] : 0.0;
       const double s1 = __dadd_rn(lo, hi), s2 = __dadd_rn(lo2, hi2);
       score = __dsub_rn(__dmul_rn((double)k, s2), __dmul_rn(s1, s1));
     }
@@ -202,11 +552,12 @@ __global__ __launch_bounds__(OVF_LARGE) void ovf_select_large_kernel(
     if (lane == 0) { red_s[wv] = score; red_b[wv] = best; }
     __syncthreads();
     score = red_s[0]; best = red_b[0];
-    for (int w = 1; w < OVF_LARGE / WAVE; ++w)
+    for (int w = 1; w < THREADS / WAVE; ++w)
       if (red_s[w] > score || (red_s[w] == score && red_b[w] < best)) { score = red_s[w]; best = red_b[w]; }
     keep = live && (rank < best || rank >= n - (k - best));
   }
   const uint64_t ballot = __ballot(keep);
+  __syncthreads();                                   // every wave has read what counts_before left in wave_cnt
   if (lane == 0) {
     wave_cnt[wv] = __popcll(ballot);
     if (wv < mask_words) mrow[wv] = ballot;
@@ -217,47 +568,6 @@ __global__ __launch_bounds__(OVF_LARGE) void ovf_select_large_kernel(
     for (int w = 0; w < wv; ++w) before += wave_cnt[w];
     sel_idx[out0 + before + __popcll(ballot & ((1ull << lane) - 1ull))] = b + tid;
   }
-}
-
-// ---- exclusive scan of k over groups (new_offsets[g] = sum of k[0..g)) in three launches ----
-__global__ __launch_bounds__(SCAN_THREADS) void scan_block_sums_kernel(const int32_t* __restrict__ kk,
-                                                                       int n, int32_t* __restrict__ sums) {
-  __shared__ int part[SCAN_THREADS / WAVE];
-  int s = 0;
-  const int base = blockIdx.x * SCAN_BLOCK + threadIdx.x * SCAN_ITEMS;
-  for (int i = 0; i < SCAN_ITEMS; ++i) if (base + i < n) s += counted_k(kk[base + i]);
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, WAVE);
-  if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x / WAVE] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) sums[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
-}
-
-__global__ void scan_sums_kernel(int32_t* __restrict__ sums, int n_blocks) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    int run = 0;
-    for (int i = 0; i < n_blocks; ++i) { const int t = sums[i]; sums[i] = run; run += t; }
-    sums[n_blocks] = run;
-  }
-}
-
-__global__ __launch_bounds__(SCAN_THREADS) void scan_write_kernel(const int32_t* __restrict__ kk, int n,
-                                                                  const int32_t* __restrict__ sums,
-                                                                  int32_t* __restrict__ new_offsets) {
-  __shared__ int lane_tot[SCAN_THREADS];
-  const int base = blockIdx.x * SCAN_BLOCK + threadIdx.x * SCAN_ITEMS;
-  int loc[SCAN_ITEMS];
-  int s = 0;
-  for (int i = 0; i < SCAN_ITEMS; ++i) { loc[i] = s; if (base + i < n) s += counted_k(kk[base + i]); }
-  lane_tot[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = sums[blockIdx.x];
-    for (int i = 0; i < SCAN_THREADS; ++i) { const int t = lane_tot[i]; lane_tot[i] = run; run += t; }
-  }
-  __syncthreads();
-  const int off = lane_tot[threadIdx.x];
-  for (int i = 0; i < SCAN_ITEMS; ++i) if (base + i < n) new_offsets[base + i] = off + loc[i];
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) new_offsets[n] = sums[gridDim.x];
 }
 
 // ---- advantages: one wave per group ----
@@ -290,17 +600,19 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void group_advantages_kernel(
 // (j, draw, g, STREAM_SUBSAMPLE) under the run's seed; the k slots with the smallest (key, slot) stay.
 constexpr uint32_t STREAM_SUBSAMPLE = 2u;
 
+template <int FROM>
 __global__ __launch_bounds__(OVF_WAVES * WAVE) void uniform_select_kernel(
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ kk, int n_groups,
-    const int32_t* __restrict__ new_offsets, uint32_t k0, uint32_t k1, uint32_t draw,
+    const int32_t* __restrict__ sums, int32_t* new_offsets, uint32_t k0, uint32_t k1, uint32_t draw,
     uint64_t* __restrict__ masks, int32_t* __restrict__ sel_idx, int32_t* __restrict__ status) {
   const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
   const int g = blockIdx.x * OVF_WAVES + wv;
+  __shared__ int part[OVF_WAVES];
+  const int out0 = place_group<FROM>(kk, sums, g, n_groups, new_offsets, part);
   if (g >= n_groups) return;
   const int b = offsets[g];
   const int n = offsets[g + 1] - b;
   const int k = kk[g];
-  const int out0 = new_offsets[g];
   if (n < 1 || n > WAVE || k < 1 || k > n) {
     if (lane == 0) {
       if (!(n == 0 && k == 0)) atomicOr(status, 2);
@@ -421,34 +733,62 @@ pg_status launch_masks_to_sel(const uint64_t* masks, const int32_t* offsets, con
   return PG_OK;
 }
 
+// With offsets already known (the sampling loop knows them from its schedule) the kernels only read them.
 pg_status launch_uniform_select(const int32_t* offsets, const int32_t* k, int n_groups, const int32_t* new_offsets,
                                 uint64_t seed, uint32_t draw, uint64_t* masks, int32_t* sel_idx, int32_t* status,
                                 hipStream_t s) {
-  uniform_select_kernel<<<dim3((n_groups + OVF_WAVES - 1) / OVF_WAVES), dim3(OVF_WAVES * WAVE), 0, s>>>(
-      offsets, k, n_groups, new_offsets, (uint32_t)seed, (uint32_t)(seed >> 32), draw, masks, sel_idx, status);
+  uniform_select_kernel<OFF_GIVEN><<<dim3((n_groups + OVF_WAVES - 1) / OVF_WAVES), dim3(OVF_WAVES * WAVE), 0, s>>>(
+      offsets, k, n_groups, nullptr, const_cast<int32_t*>(new_offsets), (uint32_t)seed, (uint32_t)(seed >> 32), draw, masks,
+      sel_idx, status);
   PG_LAUNCH_CHECK("uniform_select_kernel");
   return PG_OK;
 }
 
-// exclusive scan of k into new_offsets (three launches), shared by the selection entry points
-static pg_status scan_k(const int32_t* k, int n_groups, int32_t* scratch, int32_t* new_offsets, hipStream_t s) {
-  const int n_blocks = (n_groups + SCAN_BLOCK - 1) / SCAN_BLOCK;
-  scan_block_sums_kernel<<<dim3(n_blocks), dim3(SCAN_THREADS), 0, s>>>(k, n_groups, scratch);
-  PG_LAUNCH_CHECK("scan_block_sums_kernel");
-  scan_sums_kernel<<<dim3(1), dim3(64), 0, s>>>(scratch, n_blocks);
-  PG_LAUNCH_CHECK("scan_sums_kernel");
-  scan_write_kernel<<<dim3(n_blocks), dim3(SCAN_THREADS), 0, s>>>(k, n_groups, scratch, new_offsets);
-  PG_LAUNCH_CHECK("scan_write_kernel");
-  return PG_OK;
-}
-
-// OVF with new_offsets already known (the sampling loop knows them from its schedule)
 pg_status launch_ovf(const float* rewards, const int32_t* offsets, const int32_t* k, int n_groups,
                      const int32_t* new_offsets, uint64_t* masks, int32_t* sel_idx, int32_t* status,
                      hipStream_t s) {
-  ovf_select_kernel<<<dim3((n_groups + OVF_WAVES - 1) / OVF_WAVES), dim3(OVF_WAVES * WAVE), 0, s>>>(
-      rewards, offsets, k, n_groups, new_offsets, masks, sel_idx, status);
+  ovf_select_kernel<OFF_GIVEN><<<dim3((n_groups + OVF_WAVES - 1) / OVF_WAVES), dim3(OVF_WAVES * WAVE), 0, s>>>(
+      rewards, offsets, k, n_groups, nullptr, const_cast<int32_t*>(new_offsets), masks, sel_idx, status);
   PG_LAUNCH_CHECK("ovf_select_kernel");
+  return PG_OK;
+}
+
+// block sums of k for the kernels that work out the offsets themselves (nothing to do below OFF_DIRECT_MAX groups)
+static pg_status sum_counts(const int32_t* k, int n_groups, int32_t* sums, hipStream_t s) {
+  if (n_groups <= OFF_DIRECT_MAX) return PG_OK;
+  scan_block_sums_kernel<<<dim3((n_groups + SCAN_BLOCK - 1) / SCAN_BLOCK), dim3(SCAN_THREADS), 0, s>>>(k, n_groups, sums);
+  PG_LAUNCH_CHECK("scan_block_sums_kernel");
+  return PG_OK;
+}
+
+// The stand-alone selection of groups of up to 64 members.  One lane per group from LANE_MIN_GROUPS groups on.
+constexpr int LANE_MIN_GROUPS = 32768;
+static pg_status select_groups(const float* rewards, const int32_t* offsets, const int32_t* k, int n_groups, int32_t* sums,
+                               int32_t* new_offsets, uint64_t* masks, int32_t* sel_idx, int32_t* status, hipStream_t s) {
+  PG_TRY(sum_counts(k, n_groups, sums, s));
+  const dim3 per_wave((n_groups + OVF_WAVES - 1) / OVF_WAVES), block(OVF_WAVES * WAVE);
+  if (n_groups <= OFF_DIRECT_MAX)
+    ovf_select_kernel<OFF_DIRECT><<<per_wave, block, 0, s>>>(rewards, offsets, k, n_groups, sums, new_offsets, masks, sel_idx, status);
+  else if (n_groups < LANE_MIN_GROUPS)
+    ovf_select_kernel<OFF_SUMS><<<per_wave, block, 0, s>>>(rewards, offsets, k, n_groups, sums, new_offsets, masks, sel_idx, status);
+  else
+    ovf_select_lanes_kernel<OFF_SUMS><<<dim3((n_groups + LANE_WAVES * WAVE - 1) / (LANE_WAVES * WAVE)), dim3(LANE_WAVES * WAVE), 0, s>>>(
+        rewards, offsets, k, n_groups, sums, new_offsets, masks, sel_idx, status);
+  PG_LAUNCH_CHECK("ovf_select_kernel");
+  return PG_OK;
+}
+
+template <int THREADS>
+static pg_status select_large(const float* rewards, const int32_t* offsets, const int32_t* k, int n_groups, int32_t* sums,
+                              int32_t* new_offsets, int mask_words, uint64_t* masks, int32_t* sel_idx, int32_t* status,
+                              hipStream_t s) {
+  if (n_groups <= OFF_DIRECT_MAX)
+    ovf_select_large_kernel<OFF_DIRECT, THREADS><<<dim3(n_groups), dim3(THREADS), 0, s>>>(
+        rewards, offsets, k, n_groups, sums, new_offsets, mask_words, masks, sel_idx, status);
+  else
+    ovf_select_large_kernel<OFF_SUMS, THREADS><<<dim3(n_groups), dim3(THREADS), 0, s>>>(
+        rewards, offsets, k, n_groups, sums, new_offsets, mask_words, masks, sel_idx, status);
+  PG_LAUNCH_CHECK("ovf_select_large_kernel");
   return PG_OK;
 }
 
@@ -469,8 +809,7 @@ extern "C" pg_status pg_ovf_select(const float* rewards, const int32_t* group_of
   if (!rewards || !group_offsets || !k || !masks || !sel_idx || !new_offsets || !status || !scratch)
     return fail(PG_EINVAL, "pg_ovf_select: null pointer");
   hipStream_t s = (hipStream_t)stream;
-  PG_TRY(scan_k(k, n_groups, scratch, new_offsets, s));
-  return launch_ovf(rewards, group_offsets, k, n_groups, new_offsets, masks, sel_idx, status, s);
+  return select_groups(rewards, group_offsets, k, n_groups, scratch, new_offsets, masks, sel_idx, status, s);
 }
 
 // ---- the same selection for callers that cannot allocate: the scan's block sums live in a file-scope device
@@ -518,8 +857,8 @@ extern "C" pg_status pg_ovf_select_noalloc(const float* rewards, const int32_t* 
   hipStream_t s = (hipStream_t)stream;
   int32_t* sums = nullptr;
   PG_TRY(ovf_scratch_on_current_device(s, &sums));
-  PG_TRY(scan_k(k, n_groups, sums, new_offsets, s));          // every word it reads back it has written in this call
-  return launch_ovf(rewards, group_offsets, k, n_groups, new_offsets, masks, sel_idx, status, s);
+  // every word of the scratch that the call reads back it has written itself
+  return select_groups(rewards, group_offsets, k, n_groups, sums, new_offsets, masks, sel_idx, status, s);
 }
 
 extern "C" pg_status pg_group_advantages(const float* rewards, const int32_t* group_offsets,
@@ -542,8 +881,16 @@ extern "C" pg_status pg_uniform_select(const int32_t* group_offsets, const int32
   if (!group_offsets || !k || !masks || !sel_idx || !new_offsets || !status || !scratch)
     return fail(PG_EINVAL, "pg_uniform_select: null pointer");
   hipStream_t s = (hipStream_t)stream;
-  PG_TRY(scan_k(k, n_groups, scratch, new_offsets, s));
-  return launch_uniform_select(group_offsets, k, n_groups, new_offsets, seed, draw, masks, sel_idx, status, s);
+  PG_TRY(sum_counts(k, n_groups, scratch, s));
+  const dim3 grid((n_groups + OVF_WAVES - 1) / OVF_WAVES), block(OVF_WAVES * WAVE);
+  if (n_groups <= OFF_DIRECT_MAX)
+    uniform_select_kernel<OFF_DIRECT><<<grid, block, 0, s>>>(group_offsets, k, n_groups, scratch, new_offsets, (uint32_t)seed,
+                                                             (uint32_t)(seed >> 32), draw, masks, sel_idx, status);
+  else
+    uniform_select_kernel<OFF_SUMS><<<grid, block, 0, s>>>(group_offsets, k, n_groups, scratch, new_offsets, (uint32_t)seed,
+                                                           (uint32_t)(seed >> 32), draw, masks, sel_idx, status);
+  PG_LAUNCH_CHECK("uniform_select_kernel");
+  return PG_OK;
 }
 
 extern "C" pg_status pg_group_stats(const float* rewards, const int32_t* group_offsets, int32_t n_groups,
@@ -568,9 +915,9 @@ extern "C" pg_status pg_ovf_select_large(const float* rewards, const int32_t* gr
   if (!rewards || !group_offsets || !k || !masks || !sel_idx || !new_offsets || !status || !scratch)
     return fail(PG_EINVAL, "pg_ovf_select_large: null pointer");
   hipStream_t s = (hipStream_t)stream;
-  PG_TRY(scan_k(k, n_groups, scratch, new_offsets, s));
-  ovf_select_large_kernel<<<dim3(n_groups), dim3(OVF_LARGE), 0, s>>>(rewards, group_offsets, k, n_groups, new_offsets,
-                                                                      mask_words, masks, sel_idx, status);
-  PG_LAUNCH_CHECK("ovf_select_large_kernel");
-  return PG_OK;
+  // masks of one word: groups of at most 64 members, the same sums in the same order
+  if (mask_words == 1) return select_groups(rewards, group_offsets, k, n_groups, scratch, new_offsets, masks, sel_idx, status, s);
+  PG_TRY(sum_counts(k, n_groups, scratch, s));
+  auto large = mask_words <= 2 ? select_large<128> : mask_words <= 4 ? select_large<256> : mask_words <= 8 ? select_large<512> : select_large<1024>;
+  return large(rewards, group_offsets, k, n_groups, scratch, new_offsets, mask_words, masks, sel_idx, status, s);
 }

@@ -266,6 +266,53 @@ def test_ovf_many_groups_and_schedule_sizes(lib):
     np.testing.assert_array_equal(newoff, w_off)
 
 
+@pytest.mark.parametrize("lo,hi,kmax", [(2, 16, 15), (9, 32, 16), (20, 32, 31), (33, 64, 16), (2, 64, 32), (1, 64, 64)])
+def test_ovf_one_lane_per_group(lib, lo, hi, kmax):
+    """Enough groups for the one-lane-per-group kernel, last wave and workgroup part empty: every sort width and scan
+    length, ties across the thresholds, a wave with an unsuitable group (k = n, k > 32, one member, a NaN)."""
+    G = 32768 + 77
+    say(f"ovf lanes {lo}..{hi}")
+    rng = np.random.default_rng(hi * 100 + kmax)
+    sizes = rng.integers(lo, hi + 1, G)
+    ks = np.minimum(rng.integers(1, kmax + 1, G), np.maximum(sizes - (kmax < 64), 1))
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    r = (rng.standard_normal(off[-1]) * np.where(rng.random(off[-1]) < 0.8, 0.05, 1.0)).astype(np.float32)
+    r[: off[G // 2]] = np.round(r[: off[G // 2]] * 4) / 4            # exact ties, signed zeros among them
+    masks, sel, newoff, status = _run_ovf(lib, r, off, ks)
+    w_masks, w_sel, w_off = ovf.ovf_groups(r, off, ks)
+    assert status == 0
+    np.testing.assert_array_equal(masks, w_masks)
+    np.testing.assert_array_equal(sel, w_sel)
+    np.testing.assert_array_equal(newoff, w_off)
+    r[off[70]] = np.nan                                              # second wave: flagged, the other groups as before
+    masks, sel, newoff, status = _run_ovf(lib, r, off, ks)
+    assert status == 1 and off[70] <= sel[w_off[70]] < off[71]
+    np.testing.assert_array_equal(np.delete(masks, 70), np.delete(w_masks, 70))
+
+
+@pytest.mark.parametrize("words", [1, 2, 3, 4, 5, 8, 9, 16])
+def test_ovf_large_at_every_workgroup_size(lib, words):
+    say(f"ovf large, {words} mask words")
+    rng = np.random.default_rng(words)
+    P, top = 4096 + 5, 64 * words                                    # the count sums of two launches
+    sizes = np.where(rng.random(P) < 0.02, rng.integers(1, top + 1, P), rng.integers(1, 9, P))
+    sizes[:3] = [top, max(1, top - 1), top // 2 + 1]
+    ks = np.array([rng.integers(1, n + 1) for n in sizes])
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    r = np.round(rng.standard_normal(off[-1]) * 8).astype(np.float32) / 8
+    w_masks, w_sel, w_off = ovf.ovf_groups_large(r, off, ks, words)
+    masks = torch.full((P, words), -1, dtype=torch.int64, device=DEV)
+    sel = torch.full((int(ks.sum()),), -1, dtype=torch.int32, device=DEV)
+    noff = torch.zeros(P + 1, dtype=torch.int32, device=DEV)
+    status = torch.zeros(4, dtype=torch.int32, device=DEV)
+    scratch = torch.zeros(lib.pg_ovf_scratch_ints(P), dtype=torch.int32, device=DEV)
+    lib.pg_ovf_select_large(dev(r), dev(off), dev(ks.astype(np.int32)), P, words, masks, sel, noff, status, scratch)
+    assert status[0].item() == 0
+    np.testing.assert_array_equal(masks.cpu().numpy().view(np.uint64), np.asarray(w_masks).reshape(P, words))
+    np.testing.assert_array_equal(sel.cpu().numpy(), w_sel)
+    np.testing.assert_array_equal(noff.cpu().numpy(), w_off)
+
+
 def test_ovf_flags_non_finite_and_bad_counts(lib):
     say("ovf error flags")
     r = np.array([0.1, np.nan, 0.3, 0.4, 1.0, 2.0, 3.0, 4.0], dtype=np.float32)
