@@ -191,7 +191,8 @@ static pg_status plan_workspace(pg_ctx* c) {
   c->ws_newoff = take(sizeof(int32_t) * (c->cfg.P + 1));
   c->ws_forced = take(sizeof(uint64_t) * c->cfg.P + sizeof(int32_t) * c->M0);   // masks + sel of the OVF shadow run
   c->ws_sched = take(sizeof(int32_t) * c->sched_table.size());                  // the funnel, uploaded by pg_bind
-  c->ws_off0 = take(sizeof(int32_t) * (c->cfg.P + 1));                          // offsets of the full groups
+  c->ws_tin = take(sizeof(double) * c->cfg.T);                                  // network times of the steps
+  c->ws_emb = take(c->cfg.net_kind == PG_NET_NONE ? 0 : sizeof(float) * 256 * (size_t)c->cfg.T);   // their embeddings
   c->ws_logr = take(sizeof(double) * (size_t)c->cfg.T * c->M0);                 // fp64 log-ratios of pg_policy_ratio
   c->ws_net = off;
   PG_TRY(net_plan(c));
@@ -387,13 +388,13 @@ extern "C" pg_status pg_bind(pg_ctx* c, const pg_buffers* b) {
     PG_HIP(hipHostMalloc((void**)&c->staging, (size_t)(2 * c->cfg.P + 1) * sizeof(int32_t), hipHostMallocDefault));
   if (!c->staging_read) PG_HIP(hipEventCreateWithFlags(&c->staging_read, hipEventDisableTiming));
   c->buf = *b;
-  // the schedule's counts and offsets live in the workspace from here on (synchronous copies: pg_bind is set-up)
+  // the schedule's counts and offsets and the step times live in the workspace from here on (a synchronous copy: pg_bind is set-up)
   {
-    std::vector<int32_t> off0(c->cfg.P + 1);
-    for (int g = 0; g <= c->cfg.P; ++g) off0[g] = g * c->cfg.N;
-    PG_HIP(hipMemcpy((char*)b->workspace + c->ws_sched, c->sched_table.data(), sizeof(int32_t) * c->sched_table.size(),
-                     hipMemcpyHostToDevice));
-    PG_HIP(hipMemcpy((char*)b->workspace + c->ws_off0, off0.data(), sizeof(int32_t) * off0.size(), hipMemcpyHostToDevice));
+    // one image of the two adjacent tables, one copy
+    std::vector<char> image(c->ws_emb - c->ws_sched, 0);
+    memcpy(image.data(), c->sched_table.data(), sizeof(int32_t) * c->sched_table.size());
+    memcpy(image.data() + (c->ws_tin - c->ws_sched), c->tin.data(), sizeof(double) * c->tin.size());
+    PG_HIP(hipMemcpy((char*)b->workspace + c->ws_sched, image.data(), image.size(), hipMemcpyHostToDevice));
   }
   c->bound = true;
   c->initialised = false;
@@ -424,12 +425,8 @@ extern "C" pg_status pg_init_group(pg_ctx* c, uint64_t seed, void* stream) {
   c->pending_gather = false; c->net_fresh = false;
   c->evals = 0; c->updates = 0; c->steps_done = 0; c->advantages_done = false;
   for (int g = 0; g <= f.P; ++g) c->offsets[g] = g * f.N;
-  PG_HIP(hipMemcpyAsync(c->buf.group_offsets, ws(c, c->ws_off0), sizeof(int32_t) * (f.P + 1), hipMemcpyDeviceToDevice, s));
-  PG_TRY(launch_iota(c->buf.orig_id[0], c->M0, s));
-  PG_TRY(launch_fill_group_of(c->buf.group_offsets, f.P, c->buf.group_of, s));
-  PG_TRY(launch_fill_u32(c->buf.logp_hist, 0x7FC00000u, (size_t)f.T * c->M0, s));
-  PG_TRY(launch_fill_u32(c->buf.logp_sum, 0u, (size_t)c->M0, s));
-  PG_TRY(launch_fill_u32(c->buf.status, 0u, 4, s));
+  PG_TRY(launch_init_state(f.P, f.N, c->buf.group_offsets, c->buf.orig_id[0], c->buf.group_of, c->buf.logp_hist,
+                           (size_t)f.T * c->M0, c->buf.logp_sum, c->buf.status, s));
   PG_TRY(pg_init_latents(c->buf.x[0], c->buf.orig_id[0], c->M0, c->d, seed, stream));
   if (c->buf.x_hist)
     PG_HIP(hipMemcpyAsync(c->buf.x_hist, c->buf.x[0], sizeof(float) * (size_t)c->M0 * c->d, hipMemcpyDeviceToDevice, s));
@@ -457,10 +454,9 @@ extern "C" pg_status pg_net_forward(pg_ctx* c, int32_t step, void* stream) {
 static pg_status finish_prune(pg_ctx* c, const std::vector<int>& new_off, const int32_t* new_off_dev, hipStream_t s) {
   const int P = c->cfg.P;
   const int M_new = new_off[P];
-  PG_TRY(launch_gather_ids(c->buf.orig_id[c->cur_id], c->buf.sel_idx, M_new, c->buf.orig_id[1 - c->cur_id], s));
+  PG_TRY(launch_pack_state(c->buf.orig_id[c->cur_id], c->buf.sel_idx, M_new, c->buf.orig_id[1 - c->cur_id], new_off_dev, P,
+                           c->buf.group_offsets, c->buf.group_of, s));
   c->cur_id = 1 - c->cur_id;
-  PG_HIP(hipMemcpyAsync(c->buf.group_offsets, new_off_dev, sizeof(int32_t) * (P + 1), hipMemcpyDeviceToDevice, s));
-  PG_TRY(launch_fill_group_of(c->buf.group_offsets, P, c->buf.group_of, s));
   c->offsets = new_off;
   c->M = M_new;
   c->pending_gather = true;
@@ -621,11 +617,9 @@ extern "C" pg_status pg_select_final(pg_ctx* c, int32_t mode, const int32_t* k_p
   int32_t* tmp = (int32_t*)ws(c, c->ws_partials);
   PG_TRY(launch_gather_ids((const int32_t*)c->buf.rewards, c->buf.sel_idx, M_new, tmp, s));
   PG_HIP(hipMemcpyAsync(c->buf.rewards, tmp, sizeof(float) * M_new, hipMemcpyDeviceToDevice, s));
-  PG_TRY(launch_gather_ids(c->buf.orig_id[c->cur_id], c->buf.sel_idx, M_new, c->buf.orig_id[1 - c->cur_id], s));
+  PG_TRY(launch_pack_state(c->buf.orig_id[c->cur_id], c->buf.sel_idx, M_new, c->buf.orig_id[1 - c->cur_id],
+                           (int32_t*)ws(c, c->ws_newoff), P, c->buf.group_offsets, c->buf.group_of, s));
   c->cur_id = 1 - c->cur_id;
-  PG_HIP(hipMemcpyAsync(c->buf.group_offsets, ws(c, c->ws_newoff), sizeof(int32_t) * (P + 1),
-                        hipMemcpyDeviceToDevice, s));
-  PG_TRY(launch_fill_group_of(c->buf.group_offsets, P, c->buf.group_of, s));
   c->offsets = new_off;
   c->M = M_new;
   PG_TRY(pg_group_advantages(c->buf.rewards, c->buf.group_offsets, P, c->cfg.adv_eps, c->buf.adv, stream));

@@ -20,7 +20,8 @@ struct pg_ctx {
   std::vector<WeightSlot> top;            // PG_W_COUNT entries (per-block ones hold block-0 offsets)
   int64_t block_stride = 0, weights_numel = 0;
   // workspace plan
-  size_t ws_partials = 0, ws_k = 0, ws_newoff = 0, ws_forced = 0, ws_sched = 0, ws_off0 = 0, ws_logr = 0, ws_net = 0,
+  size_t ws_partials = 0, ws_k = 0, ws_newoff = 0, ws_forced = 0, ws_sched = 0, ws_tin = 0, ws_emb = 0,
+         ws_logr = 0, ws_net = 0,
          ws_total = 0;
   NetPlan net{};
   // bound buffers
@@ -65,9 +66,11 @@ pg_status launch_surrogate(const double* log_ratio, const float* adv, const int3
                            float* J, hipStream_t s);
 // small launches (ovf_kernels.hip)
 pg_status launch_fill_u32(void* p, uint32_t v, size_t n, hipStream_t s);
-pg_status launch_iota(int32_t* p, int n, hipStream_t s);
+pg_status launch_init_state(int P, int N, int32_t* offsets, int32_t* ids, int32_t* group_of, float* logp_hist, size_t hist_n,
+                            float* logp_sum, int32_t* status, hipStream_t s);
+pg_status launch_pack_state(const int32_t* ids_in, const int32_t* sel, int n_out, int32_t* ids_out, const int32_t* new_offsets,
+                            int P, int32_t* offsets, int32_t* group_of, hipStream_t s);
 pg_status launch_gather_ids(const int32_t* in, const int32_t* sel, int n_out, int32_t* out, hipStream_t s);
-pg_status launch_fill_group_of(const int32_t* offsets, int n_groups, int32_t* group_of, hipStream_t s);
 pg_status launch_masks_to_sel(const uint64_t* masks, const int32_t* offsets, const int32_t* new_offsets,
                               int n_groups, int32_t* sel_idx, hipStream_t s);
 pg_status launch_uniform_select(const int32_t* offsets, const int32_t* k, int n_groups, const int32_t* new_offsets,

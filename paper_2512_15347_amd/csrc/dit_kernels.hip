@@ -11,6 +11,7 @@
 // GEMM operand; only q | k and V^T use the joint per-trajectory layout that attention reads.
 // The residual stream h is fp32; every GEMM operand is bf16.
 #include <cmath>
+#include <type_traits>
 #include "attention.hpp"
 #include "ctx.hpp"
 #include "gemm.hpp"
@@ -27,88 +28,159 @@ __device__ __forceinline__ float wave_allsum(float v) {
   return v;
 }
 
-// emb[0:128] = cos(t f_i), emb[128:256] = sin(t f_i), f_i = 10000^(-i/128)
-__global__ void timestep_embedding_kernel(double t_in, float* __restrict__ emb) {
-  const int i = threadIdx.x;
-  if (i < 128) {
-    const double f = exp(-9.210340371976184 * (double)i / 128.0);     // fp64: t f reaches 1000 rad
-    emb[i] = (float)cos(t_in * f);
-    emb[128 + i] = (float)sin(t_in * f);
-  }
-}
+// ---- conditioning: c = MLP(sincos(t)) + y and the modulation vectors of every block ----
+// Matrix-vector products bound by reading the weights once (fp32 accumulation).  A wave computes GEMV_ROWS outputs for up to
+// PC inputs at a time: 16-byte weight loads, GEMV_ROWS of them in flight per column block, the inputs read once for all rows.
+constexpr int GEMV_ROWS = 4, GEMV_OUT = 4 * GEMV_ROWS;      // outputs per wave, per workgroup of four waves
 
-// out[p, n] = act(bias[n] + sum_k W[n, k] in[p, k]); one wave per output n, up to 8 inputs p at a time.
-// grid.y walks `blocks` weight sets (w_stride elements apart) writing out + blockIdx.y * out_bstride.
-template <bool SILU_OUT>
-__global__ __launch_bounds__(256) void gemv_bf16_kernel(const uint16_t* __restrict__ W, int64_t ldw,
-                                                        int64_t w_stride, const uint16_t* __restrict__ bias,
-                                                        int64_t b_stride, const float* __restrict__ in,
-                                                        int64_t in_ld, float* __restrict__ out, int64_t out_ld,
-                                                        int64_t out_bstride, int P, int N, int K) {
+// acc[r][p] = sum_k w[r, k] in[p, k] in every lane; rows past `rows` repeat the last one, inputs past `P` the first
+template <int PC>
+__device__ __forceinline__ void gemv_rows(const uint16_t* __restrict__ w, int64_t ldw, int rows, const float* __restrict__ in,
+                                          int64_t in_ld, int P, int K, float (&acc)[GEMV_ROWS][PC]) {
   const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (n >= N) return;
-  const uint16_t* w = W + blockIdx.y * w_stride + (int64_t)n * ldw;
-  const float bv = bf2f(bias[blockIdx.y * b_stride + n]);
-  for (int p0 = 0; p0 < P; p0 += 8) {
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int k = lane * 2; k < K; k += 128) {
-      const uint32_t pair = *reinterpret_cast<const uint32_t*>(w + k);
-      const float w0 = __builtin_bit_cast(float, pair << 16), w1 = __builtin_bit_cast(float, pair & 0xFFFF0000u);
 #pragma unroll
-      for (int p = 0; p < 8; ++p)
-        if (p0 + p < P) {
-          const float2 v = *reinterpret_cast<const float2*>(in + (int64_t)(p0 + p) * in_ld + k);
-          acc[p] += w0 * v.x + w1 * v.y;
-        }
-    }
+  for (int r = 0; r < GEMV_ROWS; ++r)
 #pragma unroll
-    for (int p = 0; p < 8; ++p)
-      if (p0 + p < P) {
-        float s = wave_allsum(acc[p]) + bv;
-        if (SILU_OUT) s = silu(s);
-        if (lane == 0) out[blockIdx.y * out_bstride + (int64_t)(p0 + p) * out_ld + n] = s;
+    for (int p = 0; p < PC; ++p) acc[r][p] = 0.f;
+  for (int k = lane * 8; k < K; k += WAVE * 8) {            // K is a multiple of 8
+    uint4 q[GEMV_ROWS];
+#pragma unroll
+    for (int r = 0; r < GEMV_ROWS; ++r) q[r] = *reinterpret_cast<const uint4*>(w + (int64_t)min(r, rows - 1) * ldw + k);
+#pragma unroll
+    for (int p = 0; p < PC; ++p) {
+      const float* v = in + (int64_t)(p < P ? p : 0) * in_ld + k;
+      const float4 a = *reinterpret_cast<const float4*>(v), b = *reinterpret_cast<const float4*>(v + 4);
+#pragma unroll
+      for (int r = 0; r < GEMV_ROWS; ++r) {
+        auto lo = [](uint32_t x) { return __builtin_bit_cast(float, x << 16); };
+        auto hi = [](uint32_t x) { return __builtin_bit_cast(float, x & 0xFFFF0000u); };
+        acc[r][p] += ((lo(q[r].x) * a.x + hi(q[r].x) * a.y) + (lo(q[r].y) * a.z + hi(q[r].y) * a.w)) +
+                     ((lo(q[r].z) * b.x + hi(q[r].z) * b.y) + (lo(q[r].w) * b.z + hi(q[r].w) * b.w));
       }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < GEMV_ROWS; ++r)
+#pragma unroll
+    for (int p = 0; p < PC; ++p) acc[r][p] = wave_allsum(acc[r][p]);
+}
+
+// Sinusoidal embeddings of all step times, which the configuration fixes: row s of emb is
+// emb[0:128] = cos(t_s f_i), emb[128:256] = sin(t_s f_i), f_i = 10000^(-i/128)
+__global__ void timestep_embedding_kernel(const double* __restrict__ t_in, float* __restrict__ emb) {
+  const int i = threadIdx.x, s = blockIdx.x;
+  const double f = exp(-9.210340371976184 * (double)i / 128.0);     // fp64: t f reaches 1000 rad
+  emb[256 * (size_t)s + i] = (float)cos(t_in[s] * f);
+  emb[256 * (size_t)s + 128 + i] = (float)sin(t_in[s] * f);
+}
+
+// What a step's network evaluation can start from, in one launch (each part is a few microseconds of latency, and each
+// used to be a launch or two): t1 = silu(W1 emb + b1) of the time embedding, the bf16 patch tokens of the latents,
+//   tok[r, 4c + 2dy + dx] = bf16(x[m, c, 2py + dy, 2px + dx]), r = m * Li + py * Wp + px; columns >= 4C are zero,
+// and the context rows of every trajectory, h[row_base + m * row_stride + j, :] = ctx_h[group_of[m], j, :].
+struct StepInputs {
+  const uint16_t* w1; int64_t ldw1; const uint16_t* b1; const float* emb; float* t1; int D;
+  const float* x; uint16_t* tok; int M, C, H, W, Kp;
+  const float* ctx_h; float* h; const int32_t* group_of; int64_t row_base; int row_stride, Lc;
+  int t1_blocks, patch_blocks;                   // workgroups of the first two parts
+};
+__global__ __launch_bounds__(256) void step_inputs_kernel(const StepInputs a) {
+  int blk = blockIdx.x;
+  if (blk < a.t1_blocks) {
+    const int n0 = blk * GEMV_OUT + (threadIdx.x >> 6) * GEMV_ROWS;
+    if (n0 >= a.D) return;
+    float acc[GEMV_ROWS][1];
+    gemv_rows<1>(a.w1 + (int64_t)n0 * a.ldw1, a.ldw1, a.D - n0, a.emb, 0, 1, 256, acc);
+    if ((threadIdx.x & 63) == 0)
+      for (int r = 0; r < GEMV_ROWS && n0 + r < a.D; ++r) a.t1[n0 + r] = silu(acc[r][0] + bf2f(a.b1[n0 + r]));
+    return;
+  }
+  blk -= a.t1_blocks;
+  if (blk < a.patch_blocks) {
+    const int Wp = a.W / 2, Hp = a.H / 2;
+    const int cq = a.Kp / 4;                     // 4-column groups per row, channels first then padding
+    const int64_t i = (int64_t)blk * 256 + threadIdx.x;
+    if (i >= (int64_t)a.M * cq * Hp * Wp) return;
+    const int px = (int)(i % Wp);
+    const int py = (int)((i / Wp) % Hp);
+    const int c = (int)((i / ((int64_t)Wp * Hp)) % cq);
+    const int m = (int)(i / ((int64_t)Wp * Hp * cq));
+    uint32_t lo = 0u, hi = 0u;
+    if (c < a.C) {
+      const float* src = a.x + ((int64_t)m * a.C + c) * a.H * a.W + (int64_t)(2 * py) * a.W + 2 * px;
+      const float2 r0 = *reinterpret_cast<const float2*>(src);
+      const float2 r1 = *reinterpret_cast<const float2*>(src + a.W);
+      lo = (uint32_t)f2bf(r0.x) | ((uint32_t)f2bf(r0.y) << 16);
+      hi = (uint32_t)f2bf(r1.x) | ((uint32_t)f2bf(r1.y) << 16);
+    }
+    *reinterpret_cast<uint2*>(a.tok + ((int64_t)m * Hp * Wp + (int64_t)py * Wp + px) * a.Kp + 4 * c) = uint2{lo, hi};
+    return;
+  }
+  blk -= a.patch_blocks;
+  const int D4 = a.D / 4;
+  const int64_t i = (int64_t)blk * 256 + threadIdx.x;
+  if (i >= (int64_t)a.M * a.Lc * D4) return;
+  const int k = (int)(i % D4);
+  const int j = (int)((i / D4) % a.Lc);
+  const int m = (int)(i / ((int64_t)D4 * a.Lc));
+  const float4 v = reinterpret_cast<const float4*>(a.ctx_h)[((int64_t)a.group_of[m] * a.Lc + j) * D4 + k];
+  reinterpret_cast<float4*>(a.h)[(a.row_base + (int64_t)m * a.row_stride + j) * D4 + k] = v;
+}
+
+// sc[p, n] = silu(b[n] + sum_k W[n, k] t1[k] + y[p, n])
+__global__ __launch_bounds__(256) void condition_kernel(const uint16_t* __restrict__ W, int64_t ldw, const uint16_t* __restrict__ bias,
+                                                        const float* __restrict__ t1, const float* __restrict__ y,
+                                                        float* __restrict__ sc, int P, int D) {
+  const int n0 = blockIdx.x * GEMV_OUT + (threadIdx.x >> 6) * GEMV_ROWS;
+  if (n0 >= D) return;
+  float acc[GEMV_ROWS][1];
+  gemv_rows<1>(W + (int64_t)n0 * ldw, ldw, D - n0, t1, 0, 1, D, acc);
+  for (int p = threadIdx.x & 63; p < P; p += WAVE)
+#pragma unroll
+    for (int r = 0; r < GEMV_ROWS; ++r)
+      if (n0 + r < D) sc[(int64_t)p * D + n0 + r] = silu(acc[r][0] + bf2f(bias[n0 + r]) + y[(int64_t)p * D + n0 + r]);
+}
+
+// Every modulation vector of the network in one launch: blockIdx.y < sets * blocks walks the blocks of the one or two
+// streams (out[set][p, block, 0:6D]), the last one the final layer's 2D outputs.
+struct Modulation {
+  const uint16_t* w[2]; const uint16_t* b[2]; float* out[2];   // per stream, block 0
+  int64_t ldw, block_stride;
+  const uint16_t* fw; const uint16_t* fb; int64_t ldfw; float* fout;
+  const float* sc; int P, D, blocks, sets;
+};
+template <int PC>
+__global__ __launch_bounds__(256) void modulation_kernel(const Modulation a) {
+  const int set = blockIdx.y / a.blocks, blk = blockIdx.y - set * a.blocks;
+  const bool fin = set >= a.sets;
+  const int N = fin ? 2 * a.D : 6 * a.D;
+  const int n0 = blockIdx.x * GEMV_OUT + (threadIdx.x >> 6) * GEMV_ROWS;
+  if (n0 >= N) return;
+  const int64_t ld = fin ? a.ldfw : a.ldw;
+  const uint16_t* w = (fin ? a.fw : a.w[set] + blk * a.block_stride) + (int64_t)n0 * ld;
+  const uint16_t* b = fin ? a.fb : a.b[set] + blk * a.block_stride;
+  float* out = fin ? a.fout : a.out[set] + (int64_t)blk * N;
+  const int64_t out_ld = fin ? N : (int64_t)a.blocks * N;
+  const int lane = threadIdx.x & 63;
+  for (int p0 = 0; p0 < a.P; p0 += PC) {
+    float acc[GEMV_ROWS][PC];
+    gemv_rows<PC>(w, ld, N - n0, a.sc + (int64_t)p0 * a.D, a.D, a.P - p0, a.D, acc);
+    if (lane == 0)
+#pragma unroll
+      for (int p = 0; p < PC; ++p)
+        if (p0 + p < a.P)
+#pragma unroll
+          for (int r = 0; r < GEMV_ROWS; ++r)
+            if (n0 + r < N) out[(int64_t)(p0 + p) * out_ld + n0 + r] = acc[r][p] + bf2f(b[n0 + r]);
   }
 }
 
-// sc[p, n] = silu(c0[n] + y[p, n])
-__global__ void cond_silu_kernel(const float* __restrict__ c0, const float* __restrict__ y, float* __restrict__ sc,
-                                 int P, int D) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < P * D) sc[i] = silu(c0[i % D] + y[i]);
-}
-
-// tok[r, 4c + 2dy + dx] = bf16(x[m, c, 2py + dy, 2px + dx]), r = m * Li + py * Wp + px; columns >= 4C are zero
-__global__ void patchify_kernel(const float* __restrict__ x, uint16_t* __restrict__ tok, int M, int C, int H, int Wd,
-                                int Kp) {
-  const int Wp = Wd / 2, Hp = H / 2;
-  const int cq = Kp / 4;                       // 4-column groups per row, channels first then padding
-  const int64_t total = (int64_t)M * cq * Hp * Wp;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int px = (int)(i % Wp);
-  const int py = (int)((i / Wp) % Hp);
-  const int c = (int)((i / ((int64_t)Wp * Hp)) % cq);
-  const int m = (int)(i / ((int64_t)Wp * Hp * cq));
-  uint32_t lo = 0u, hi = 0u;
-  if (c < C) {
-    const float* src = x + ((int64_t)m * C + c) * H * Wd + (int64_t)(2 * py) * Wd + 2 * px;
-    const float2 r0 = *reinterpret_cast<const float2*>(src);
-    const float2 r1 = *reinterpret_cast<const float2*>(src + Wd);
-    lo = (uint32_t)f2bf(r0.x) | ((uint32_t)f2bf(r0.y) << 16);
-    hi = (uint32_t)f2bf(r1.x) | ((uint32_t)f2bf(r1.y) << 16);
-  }
-  uint32_t* dst = reinterpret_cast<uint32_t*>(tok + ((int64_t)m * Hp * Wp + (int64_t)py * Wp + px) * Kp + 4 * c);
-  dst[0] = lo;
-  dst[1] = hi;
-}
-
-// out[r', :] = bf16(LN(h[r, :]) * (1 + scale[g]) + shift[g]); one wave per row.  The row lives in
-// registers (NV float4 per lane, D = 256 * NV) so h is read once; NV = 0 is the generic route for
-// widths that are not a multiple of 256 (three cached passes).
+// out[r', :] = bf16(LN(h[r, :]) * (1 + scale[g]) + shift[g]); one wave per row.  The row lives in registers (NV float4 per
+// lane, D <= 256 NV; WHOLE: D = 256 NV, else the last float4 of some lanes lies past the row) so h is read once and every
+// access is 16 bytes wide; NV = 0 is the generic route for wider rows (three cached passes of 4-byte accesses, which
+// every width that is no multiple of 256 used to take).
 // Rows: r' = m * L_out + t for t < L_out reads h row m * L_in + t (L_out < L_in drops the context rows).
-template <int NV>
+template <int NV, bool WHOLE>
 __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restrict__ h, uint16_t* __restrict__ out,
                                                           const float* __restrict__ shift,
                                                           const float* __restrict__ scale, int64_t mod_ld,
@@ -129,10 +201,11 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
   }
   if (NV > 0) {
     float4 v[NV > 0 ? NV : 1];
+    auto inside = [&](int i) { return WHOLE || i + 1 < NV || 4 * (lane + 64 * i) < D; };
     float s = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      v[i] = reinterpret_cast<const float4*>(hr)[lane + 64 * i];
+      v[i] = inside(i) ? reinterpret_cast<const float4*>(hr)[lane + 64 * i] : float4{0.f, 0.f, 0.f, 0.f};
       s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
     }
     const float mu = wave_allsum(s) / (float)D;
@@ -140,11 +213,13 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       v[i].x -= mu; v[i].y -= mu; v[i].z -= mu; v[i].w -= mu;
-      q += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
+      const float qi = (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
+      q += inside(i) ? qi : 0.f;
     }
     const float rstd = rsqrtf(wave_allsum(q) / (float)D + 1e-6f);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
+      if (!inside(i)) continue;
       float4 o = {v[i].x * rstd, v[i].y * rstd, v[i].z * rstd, v[i].w * rstd};
       if (sh) {
         const float4 a = reinterpret_cast<const float4*>(sc)[lane + 64 * i];
@@ -172,20 +247,6 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
   }
 }
 
-// context rows of trajectory m: h[row_base + m * row_stride + j, :] = ctx_h[group_of[m], j, :]
-__global__ void scatter_context_kernel(const float* __restrict__ ctx_h, float* __restrict__ h,
-                                       const int32_t* __restrict__ group_of, int M, int64_t row_base,
-                                       int row_stride, int Lc, int D4) {
-  const int64_t total = (int64_t)M * Lc * D4;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int k = (int)(i % D4);
-  const int j = (int)((i / D4) % Lc);
-  const int m = (int)(i / ((int64_t)D4 * Lc));
-  const float4 v = reinterpret_cast<const float4*>(ctx_h)[((int64_t)group_of[m] * Lc + j) * D4 + k];
-  reinterpret_cast<float4*>(h)[(row_base + (int64_t)m * row_stride + j) * D4 + k] = v;
-}
-
 // ------------------------------------------------------------------------------------------------
 
 static size_t a256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -208,7 +269,7 @@ pg_status net_plan(pg_ctx* c) {
   n.hid = take(R0 * 4 * D * 2);
   n.tok = take((size_t)c->M0 * c->Li * Kp * 2);
   n.mod = take(((size_t)f.P * f.blocks * 6 * D * (f.net_kind == PG_NET_MMDIT ? 2 : 1) + (size_t)f.P * 2 * D) * 4);
-  n.cond = take((256 + 2 * D + (size_t)f.P * D) * 4);
+  n.cond = take((D + (size_t)f.P * D) * 4);
   if (f.net_kind == PG_NET_JOINT || f.net_kind == PG_NET_MMDIT) n.ctx_h = take((size_t)f.P * f.Lc * D * 4);
   if (f.net_kind == PG_NET_CROSS) {
     n.ckv = take((size_t)f.blocks * f.P * f.Lc * D * 2);
@@ -232,9 +293,12 @@ struct Net {
 };
 }  // namespace
 
-// Step-independent work: projected context rows (joint) or per-block context keys / values (cross).
+// Step-independent work: time embeddings, projected context rows (joint) or per-block context keys / values (cross).
 pg_status net_prepare(pg_ctx* c, const uint16_t* weights, hipStream_t s) {
   const pg_config& f = c->cfg;
+  timestep_embedding_kernel<<<dim3(f.T), dim3(128), 0, s>>>((const double*)((char*)c->buf.workspace + c->ws_tin),
+                                                           (float*)((char*)c->buf.workspace + c->ws_emb));
+  PG_LAUNCH_CHECK("timestep_embedding_kernel");
   Net n{c, s, (char*)c->buf.workspace + c->ws_net, weights};
   const int D = f.D;
   if (f.net_kind == PG_NET_JOINT || f.net_kind == PG_NET_MMDIT) {
@@ -277,68 +341,70 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
   float* cmod = fmod + (size_t)P * 2 * D;           // dual-stream variant: the context stream's modulation vectors
   const bool dual = f.net_kind == PG_NET_MMDIT;
   const int Rc = M * f.Lc;                          // context rows (dual-stream planes)
-  float* emb = n.at<float>(pl.cond);
-  float* t1 = emb + 256;
-  float* c0 = t1 + D;
-  float* sc = c0 + D;
+  float* t1 = n.at<float>(pl.cond);
+  float* sc = t1 + D;
   const int32_t* group_of = c->buf.group_of;
   const int64_t mod_ld = (int64_t)f.blocks * 6 * D;
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
 
-  // ---- conditioning: c = MLP(sincos(t)) + y, modulation vectors of every block ----
-  timestep_embedding_kernel<<<dim3(1), dim3(128), 0, s>>>(c->tin[step], emb);
-  PG_LAUNCH_CHECK("timestep_embedding_kernel");
-  gemv_bf16_kernel<true><<<dim3((D + 3) / 4, 1), dim3(256), 0, s>>>(n.w(PG_W_T_W1), n.ld(PG_W_T_W1), 0, n.w(PG_W_T_B1),
-                                                                    0, emb, 256, t1, D, 0, 1, D, 256);
-  PG_LAUNCH_CHECK("gemv t1");
-  gemv_bf16_kernel<false><<<dim3((D + 3) / 4, 1), dim3(256), 0, s>>>(n.w(PG_W_T_W2), n.ld(PG_W_T_W2), 0,
-                                                                     n.w(PG_W_T_B2), 0, t1, D, c0, D, 0, 1, D, D);
-  PG_LAUNCH_CHECK("gemv t2");
-  cond_silu_kernel<<<dim3((P * D + 255) / 256), dim3(256), 0, s>>>(c0, c->buf.y, sc, P, D);
-  PG_LAUNCH_CHECK("cond_silu_kernel");
-  gemv_bf16_kernel<false><<<dim3((6 * D + 3) / 4, f.blocks), dim3(256), 0, s>>>(
-      n.w(PG_W_MOD_W), n.ld(PG_W_MOD_W), c->block_stride, n.w(PG_W_MOD_B), c->block_stride, sc, D, mod, mod_ld, 6 * D,
-      P, 6 * D, D);
-  PG_LAUNCH_CHECK("gemv mod");
-  if (dual) {
-    gemv_bf16_kernel<false><<<dim3((6 * D + 3) / 4, f.blocks), dim3(256), 0, s>>>(
-        n.w(PG_W_C_MOD_W), n.ld(PG_W_C_MOD_W), c->block_stride, n.w(PG_W_C_MOD_B), c->block_stride, sc, D, cmod, mod_ld,
-        6 * D, P, 6 * D, D);
-    PG_LAUNCH_CHECK("gemv cmod");
-  }
-  gemv_bf16_kernel<false><<<dim3((2 * D + 3) / 4, 1), dim3(256), 0, s>>>(n.w(PG_W_FMOD_W), n.ld(PG_W_FMOD_W), 0,
-                                                                         n.w(PG_W_FMOD_B), 0, sc, D, fmod, 2 * D, 0, P,
-                                                                         2 * D, D);
-  PG_LAUNCH_CHECK("gemv fmod");
-
-  // ---- patch embedding (+ position table), context rows ----
+  // ---- conditioning, patch tokens and context rows ----
   {
-    const int64_t total = (int64_t)M * (Kp / 4) * Li;
-    patchify_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(x_in, tok, M, f.C, f.H,
-                                                                                f.W, Kp);
-    PG_LAUNCH_CHECK("patchify_kernel");
+    StepInputs a{};
+    a.w1 = n.w(PG_W_T_W1); a.ldw1 = n.ld(PG_W_T_W1); a.b1 = n.w(PG_W_T_B1); a.D = D;
+    a.emb = reinterpret_cast<const float*>((char*)c->buf.workspace + c->ws_emb) + (size_t)step * 256; a.t1 = t1;
+    a.x = x_in; a.tok = tok; a.M = M; a.C = f.C; a.H = f.H; a.W = f.W; a.Kp = Kp;
+    const bool context = f.net_kind == PG_NET_JOINT || dual;
+    a.h = h; a.group_of = group_of; a.Lc = context ? f.Lc : 0;
+    if (context) a.ctx_h = n.at<float>(pl.ctx_h);
+    a.row_base = dual ? (int64_t)Ri : (int64_t)Li; a.row_stride = dual ? f.Lc : L;
+    a.t1_blocks = (D + GEMV_OUT - 1) / GEMV_OUT;
+    a.patch_blocks = (int)(((int64_t)M * (Kp / 4) * Li + 255) / 256);
+    const int64_t context_blocks = ((int64_t)M * a.Lc * (D / 4) + 255) / 256;
+    step_inputs_kernel<<<dim3((unsigned)(a.t1_blocks + a.patch_blocks + context_blocks)), dim3(256), 0, s>>>(a);
+    PG_LAUNCH_CHECK("step_inputs_kernel");
+    condition_kernel<<<dim3((D + GEMV_OUT - 1) / GEMV_OUT), dim3(256), 0, s>>>(n.w(PG_W_T_W2), n.ld(PG_W_T_W2), n.w(PG_W_T_B2),
+                                                                               t1, c->buf.y, sc, P, D);
+    PG_LAUNCH_CHECK("condition_kernel");
+    Modulation mo{};
+    mo.w[0] = n.w(PG_W_MOD_W); mo.b[0] = n.w(PG_W_MOD_B); mo.out[0] = mod; mo.ldw = n.ld(PG_W_MOD_W); mo.block_stride = c->block_stride;
+    if (dual) { mo.w[1] = n.w(PG_W_C_MOD_W); mo.b[1] = n.w(PG_W_C_MOD_B); mo.out[1] = cmod; }
+    mo.fw = n.w(PG_W_FMOD_W); mo.fb = n.w(PG_W_FMOD_B); mo.ldfw = n.ld(PG_W_FMOD_W); mo.fout = fmod;
+    mo.sc = sc; mo.P = P; mo.D = D; mo.blocks = f.blocks; mo.sets = dual ? 2 : 1;
+    const dim3 grid((6 * D + GEMV_OUT - 1) / GEMV_OUT, mo.sets * f.blocks + 1);
+    if (P == 1) modulation_kernel<1><<<grid, dim3(256), 0, s>>>(mo);
+    else if (P <= 4) modulation_kernel<4><<<grid, dim3(256), 0, s>>>(mo);
+    else modulation_kernel<8><<<grid, dim3(256), 0, s>>>(mo);
+    PG_LAUNCH_CHECK("modulation_kernel");
+  }
+
+  // ---- patch embedding (+ position table) ----
+  {
     GemmArgs g{};
     g.A = tok; g.lda = Kp; g.W = n.w(PG_W_PE_W); g.ldw = n.ld(PG_W_PE_W); g.bias = n.w(PG_W_PE_B);
     g.M = Ri; g.N = D; g.K = Kp; g.k_algo = 4 * f.C; g.outf = h; g.ldo = D; g.L = dual ? Li : L; g.Li = Li; g.pos = n.w(PG_W_POS);
     PG_TRY(launch_gemm(g, EPI_EMBED, s));
   }
-  if (f.net_kind == PG_NET_JOINT || dual) {
-    const int64_t total = (int64_t)M * f.Lc * (D / 4);
-    scatter_context_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(
-        n.at<float>(pl.ctx_h), h, group_of, M, dual ? (int64_t)Ri : (int64_t)Li, dual ? f.Lc : L, f.Lc, D / 4);
-    PG_LAUNCH_CHECK("scatter_context_kernel");
-  }
-
   // out[m * L_out + t, :] = bf16(LN(hin[m * L_in + t, :]) * (1 + scale) + shift), t < L_out
   auto ln = [&](const float* hin, uint16_t* out, const float* shift, const float* scale, int64_t ld, int rows_out,
                 int L_in, int L_out) -> pg_status {
     if (rows_out <= 0) return PG_OK;
     const dim3 grid((rows_out + 3) / 4), block(256);
-    if (D == 768) ln_modulate_kernel<3><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
-    else if (D == 1536) ln_modulate_kernel<6><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
-    else if (D == 1024) ln_modulate_kernel<4><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
-    else if (D == 256) ln_modulate_kernel<1><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
-    else ln_modulate_kernel<0><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
+    auto run = [&](auto nv_c) {
+      constexpr int NV = decltype(nv_c)::value;
+      if (D == 256 * NV) ln_modulate_kernel<NV, true><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
+      else ln_modulate_kernel<NV, false><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
+    };
+    switch ((D + 255) / 256) {                    // D is a multiple of 64: rows of h, out and the modulation vectors stay 16-byte aligned
+      case 1: run(std::integral_constant<int, 1>{}); break;
+      case 2: run(std::integral_constant<int, 2>{}); break;
+      case 3: run(std::integral_constant<int, 3>{}); break;
+      case 4: run(std::integral_constant<int, 4>{}); break;
+      case 5: run(std::integral_constant<int, 5>{}); break;
+      case 6: run(std::integral_constant<int, 6>{}); break;
+      case 7: run(std::integral_constant<int, 7>{}); break;
+      case 8: run(std::integral_constant<int, 8>{}); break;
+      default: ln_modulate_kernel<0, false><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
+    }
     PG_LAUNCH_CHECK("ln_modulate_kernel");
     return PG_OK;
   };

@@ -9,6 +9,7 @@
 //   prefix sums by a six-step shuffle-up scan, k+1 candidate scores in lanes 0..k, a butterfly
 //   arg-max, a ballot for the survivor mask;
 //   many groups: one LANE owns one group (ovf_select_lanes_kernel below).
+#include <algorithm>
 #include <mutex>
 #include "common.hpp"
 #include "philox.hpp"
@@ -669,9 +670,36 @@ __global__ void gather_ids_kernel(const int32_t* __restrict__ ids_in, const int3
   if (r < n_out) ids_out[r] = ids_in[sel[r]];
 }
 
-__global__ void fill_group_of_kernel(const int32_t* __restrict__ offsets, int32_t* __restrict__ group_of) {
-  const int g = blockIdx.x;
-  for (int i = offsets[g] + threadIdx.x; i < offsets[g + 1]; i += blockDim.x) group_of[i] = g;
+// What a run starts from, in one launch: offsets of the full groups, ids, group of every row, no log-prob yet (NaN), zero
+// sums, clear status.  (Five fills and a copy of a few microseconds each before.)
+__global__ void init_state_kernel(int P, int N, int32_t* __restrict__ offsets, int32_t* __restrict__ ids,
+                                  int32_t* __restrict__ group_of, uint32_t* __restrict__ logp_hist, size_t hist_n,
+                                  float* __restrict__ logp_sum, int32_t* __restrict__ status) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+  if (i < 4) status[i] = 0;
+  for (size_t g = i; g <= (size_t)P; g += stride) offsets[g] = (int32_t)g * N;
+  for (size_t r = i; r < (size_t)P * N; r += stride) {
+    ids[r] = (int32_t)r;
+    group_of[r] = (int32_t)(r / N);
+    logp_sum[r] = 0.f;
+  }
+  for (size_t j = i; j < hist_n; j += stride) logp_hist[j] = 0x7FC00000u;
+}
+
+// After a selection: ids, group and offsets of the packed survivors (group of a row: binary search in the new offsets)
+__global__ void pack_state_kernel(const int32_t* __restrict__ ids_in, const int32_t* __restrict__ sel, int n_out,
+                                  int32_t* __restrict__ ids_out, const int32_t* __restrict__ new_offsets, int P,
+                                  int32_t* __restrict__ offsets, int32_t* __restrict__ group_of) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  for (int g = r; g <= P; g += gridDim.x * blockDim.x) offsets[g] = new_offsets[g];
+  if (r >= n_out) return;
+  ids_out[r] = ids_in[sel[r]];
+  int lo = 0, hi = P - 1;                          // last group that starts at or before r
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (new_offsets[mid] <= r) lo = mid; else hi = mid - 1;
+  }
+  group_of[r] = lo;
 }
 
 // survivors imposed from outside: sel_idx from masks (test hook of the sampling loop)
@@ -693,11 +721,6 @@ __global__ void fill_u32_kernel(uint32_t* __restrict__ p, uint32_t v, size_t n) 
   for (; i < n; i += stride) p[i] = v;
 }
 
-__global__ void iota_kernel(int32_t* __restrict__ p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = i;
-}
-
 pg_status launch_fill_u32(void* p, uint32_t v, size_t n, hipStream_t s) {
   if (n == 0) return PG_OK;
   const unsigned blocks = (unsigned)((n + 1023) / 1024 > 4096 ? 4096 : (n + 1023) / 1024);
@@ -706,10 +729,20 @@ pg_status launch_fill_u32(void* p, uint32_t v, size_t n, hipStream_t s) {
   return PG_OK;
 }
 
-pg_status launch_iota(int32_t* p, int n, hipStream_t s) {
-  if (n <= 0) return PG_OK;
-  iota_kernel<<<dim3((n + 255) / 256), dim3(256), 0, s>>>(p, n);
-  PG_LAUNCH_CHECK("iota_kernel");
+pg_status launch_init_state(int P, int N, int32_t* offsets, int32_t* ids, int32_t* group_of, float* logp_hist, size_t hist_n,
+                            float* logp_sum, int32_t* status, hipStream_t s) {
+  const size_t n = std::max(hist_n, (size_t)P * N) + 1;
+  init_state_kernel<<<dim3((unsigned)std::min<size_t>((n + 255) / 256, 1024)), dim3(256), 0, s>>>(
+      P, N, offsets, ids, group_of, (uint32_t*)logp_hist, hist_n, logp_sum, status);
+  PG_LAUNCH_CHECK("init_state_kernel");
+  return PG_OK;
+}
+
+pg_status launch_pack_state(const int32_t* ids_in, const int32_t* sel, int n_out, int32_t* ids_out, const int32_t* new_offsets,
+                            int P, int32_t* offsets, int32_t* group_of, hipStream_t s) {
+  pack_state_kernel<<<dim3((std::max(n_out, 1) + 255) / 256), dim3(256), 0, s>>>(ids_in, sel, n_out, ids_out, new_offsets, P,
+                                                                                offsets, group_of);
+  PG_LAUNCH_CHECK("pack_state_kernel");
   return PG_OK;
 }
 
@@ -717,12 +750,6 @@ pg_status launch_gather_ids(const int32_t* in, const int32_t* sel, int n_out, in
   if (n_out <= 0) return PG_OK;
   gather_ids_kernel<<<dim3((n_out + 255) / 256), dim3(256), 0, s>>>(in, sel, n_out, out);
   PG_LAUNCH_CHECK("gather_ids_kernel");
-  return PG_OK;
-}
-
-pg_status launch_fill_group_of(const int32_t* offsets, int n_groups, int32_t* group_of, hipStream_t s) {
-  fill_group_of_kernel<<<dim3(n_groups), dim3(64), 0, s>>>(offsets, group_of);
-  PG_LAUNCH_CHECK("fill_group_of_kernel");
   return PG_OK;
 }
 

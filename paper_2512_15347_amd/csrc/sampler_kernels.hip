@@ -128,15 +128,27 @@ __global__ __launch_bounds__(STREAM_THREADS) void sde_step_bf16_kernel(
   if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
+// Sum of one trajectory's `chunks` partials (`stride` floats apart) in fp64 by one wavefront, the same in every lane.  The
+// kernels that finish a sum are pure latency, once per step: a lane that walked its trajectory's partials one by one took
+// 4 us for 16 of them and more for more.
+__device__ __forceinline__ double wave_sum_partials(const float* __restrict__ p, int chunks, int stride) {
+  double s = 0.0;
+  for (int c = threadIdx.x & (WAVE - 1); c < chunks; c += WAVE) s += (double)p[(size_t)c * stride];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, WAVE);
+  return s;
+}
+constexpr int FINISH_ROWS = 4;                     // trajectories per workgroup of the finishing kernels
+
 // logp[r] = -1/2 sum_c partial[r, c] - d (ln C + 1/2 ln 2 pi); history and running sum by original id.
 __global__ void logprob_finish_kernel(const float* __restrict__ partials, int chunks, int n_traj,
                                       double log_norm, const int32_t* __restrict__ orig_id,
                                       float* __restrict__ logp, float* __restrict__ logp_hist,
                                       float* __restrict__ logp_sum) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  const int r = blockIdx.x * FINISH_ROWS + threadIdx.x / WAVE;
   if (r >= n_traj) return;
-  double s = 0.0;
-  for (int c = 0; c < chunks; ++c) s += (double)partials[(size_t)r * chunks + c];
+  const double s = wave_sum_partials(partials + (size_t)r * chunks, chunks, 1);
+  if ((threadIdx.x & (WAVE - 1)) != 0) return;
   const float lp = (float)(-0.5 * s - log_norm);
   if (logp) logp[r] = lp;
   const int id = orig_id[r];
@@ -177,11 +189,10 @@ __global__ __launch_bounds__(STREAM_THREADS) void preview_reward_kernel(
 
 __global__ void reward_finish_kernel(const float* __restrict__ partials, int chunks, int n_traj,
                                      double bias, float* __restrict__ rewards) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  const int r = blockIdx.x * FINISH_ROWS + threadIdx.x / WAVE;
   if (r >= n_traj) return;
-  double s = 0.0;
-  for (int c = 0; c < chunks; ++c) s += (double)partials[(size_t)r * chunks + c];
-  rewards[r] = (float)(bias + s);
+  const double s = wave_sum_partials(partials + (size_t)r * chunks, chunks, 1);
+  if ((threadIdx.x & (WAVE - 1)) == 0) rewards[r] = (float)(bias + s);
 }
 
 __global__ __launch_bounds__(STREAM_THREADS) void compact_gather_kernel(
@@ -250,13 +261,11 @@ __global__ __launch_bounds__(STREAM_THREADS) void transition_sq_kernel(
 __global__ void transition_finish_kernel(const float* __restrict__ partials, int chunks, int n_traj, double inv_2c2,
                                          double log_norm, const int32_t* __restrict__ orig_id,
                                          float* __restrict__ logp_by_id, double* __restrict__ log_ratio_by_id) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  const int r = blockIdx.x * FINISH_ROWS + threadIdx.x / WAVE;
   if (r >= n_traj) return;
-  double s = 0.0, dsum = 0.0;
-  for (int c = 0; c < chunks; ++c) {
-    s += (double)partials[2 * ((size_t)r * chunks + c)];
-    dsum += (double)partials[2 * ((size_t)r * chunks + c) + 1];
-  }
+  const float* p = partials + 2 * (size_t)r * chunks;
+  const double s = wave_sum_partials(p, chunks, 2), dsum = wave_sum_partials(p + 1, chunks, 2);
+  if ((threadIdx.x & (WAVE - 1)) != 0) return;
   logp_by_id[orig_id[r]] = (float)(-s * inv_2c2 - log_norm);
   log_ratio_by_id[orig_id[r]] = 0.5 * dsum;
 }
@@ -335,7 +344,7 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
   prof_close(rec, stream);
   PG_LAUNCH_CHECK("sde_step_kernel");
   const double log_norm = (double)d * (log(C) + 0.5 * log(2.0 * M_PI));
-  logprob_finish_kernel<<<dim3((unsigned)((n_traj + 127) / 128)), dim3(128), 0, stream>>>(
+  logprob_finish_kernel<<<dim3((unsigned)((n_traj + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS * WAVE), 0, stream>>>(
       partials, chunks, (int)n_traj, log_norm, orig_id, logp, logp_hist, logp_sum);
   PG_LAUNCH_CHECK("logprob_finish_kernel");
   return PG_OK;
@@ -352,7 +361,7 @@ pg_status launch_transition_logprob(const float* x, const float* u, const float*
       x, u, x_next_by_id, orig_id, (int)(d / 4), chunks, (float)A, (float)B, (float)C, (uint32_t)seed,
       (uint32_t)(seed >> 32), step, partials);
   PG_LAUNCH_CHECK("transition_sq_kernel");
-  transition_finish_kernel<<<dim3((unsigned)((n_traj + 127) / 128)), dim3(128), 0, stream>>>(
+  transition_finish_kernel<<<dim3((unsigned)((n_traj + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS * WAVE), 0, stream>>>(
       partials, chunks, (int)n_traj, 1.0 / (2.0 * C * C), (double)d * (log(C) + 0.5 * log(2.0 * M_PI)), orig_id,
       logp_by_id, log_ratio_by_id);
   PG_LAUNCH_CHECK("transition_finish_kernel");
@@ -397,7 +406,7 @@ extern "C" pg_status pg_sde_step_logprob_bf16(const uint16_t* x, const uint16_t*
       (uint32_t)(seed >> 32), step, partials);
   PG_LAUNCH_CHECK("sde_step_bf16_kernel");
   const double log_norm = (double)d * (log(C) + 0.5 * log(2.0 * M_PI));
-  logprob_finish_kernel<<<dim3((unsigned)((n_traj + 127) / 128)), dim3(128), 0, stream>>>(
+  logprob_finish_kernel<<<dim3((unsigned)((n_traj + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS * WAVE), 0, stream>>>(
       partials, chunks, (int)n_traj, log_norm, orig_id, logp, logp_hist, logp_sum);
   PG_LAUNCH_CHECK("logprob_finish_kernel");
   return PG_OK;
@@ -421,7 +430,7 @@ extern "C" pg_status pg_preview_reward(const float* x, const float* u, const flo
                                                                            (float)Pc, 0.f, partials);
   prof_close(rec, (hipStream_t)stream);
   PG_LAUNCH_CHECK("preview_reward_kernel");
-  reward_finish_kernel<<<dim3((unsigned)((n_traj + 127) / 128)), dim3(128), 0, (hipStream_t)stream>>>(
+  reward_finish_kernel<<<dim3((unsigned)((n_traj + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS * WAVE), 0, (hipStream_t)stream>>>(
       partials, chunks, (int)n_traj, bias, rewards);
   PG_LAUNCH_CHECK("reward_finish_kernel");
   return PG_OK;
