@@ -1,19 +1,26 @@
 // bf16 MFMA GEMM for gfx950: C[M, N] = A[M, K] W[N, K]^T with a fused epilogue.  This is where the
 // network evaluation of every denoising step spends its time (the noise-prediction row of the paper's
-// cost table, Sec. 6.2).  Built around the 32x32x16 bf16 MFMA:
+// cost table, Sec. 6.2).  Built around the 16x16x32 bf16 MFMA:
 //   both operands are K-contiguous; 16-byte chunks go from global memory straight into LDS (no register
-//   staging), two LDS stages of BK = 64 columns, one barrier per K step; the requests for tile kt+2 are
-//   interleaved with the MFMAs that follow the barrier instead of being issued in a burst; operand
-//   fragments are double buffered in registers and read one MFMA slab ahead, also across the barrier;
+//   staging), two LDS stages of 64 columns, one barrier per K step; the requests for tile kt+2 are
+//   interleaved with the MFMAs that follow the barrier, and so are the reads of the operand fragments, which
+//   are double buffered in registers and read one MFMA slab ahead, also across the barrier; the K loop
+//   itself holds no branch (the last two steps are peeled);
 //   chunk positions are XOR-swizzled so that the 16-byte operand reads are bank-conflict free while the
 //   direct loads still write 1 KB contiguous per instruction;
 //   the epilogue goes through an LDS transpose so that every lane stores 16 contiguous bytes, with the
 //   non-temporal hint; workgroup ids are spread so that the tiles resident on one XCD (one L2) form a
 //   compact block of the output and share operand panels.
-// Several tile shapes are instantiated (workgroup tile BM x BN x BK, WM x WN wavefronts); the launcher
-// picks one from the number of output tiles relative to the 256 compute units.
+// The chip draws its power limit here, so energy per flop and not issue slots decides: with the branch-free loop and raised
+// wave priority around the MFMAs the 16x16x32 instruction runs 56544 x 6144 x 1536 in 0.87 ms where 32x32x16 takes 0.93 ms
+// (0.99 ms with the fragment reads in a burst before the MFMAs and a test around every request, as it was before); the
+// smaller instruction also allows 16-row steps, so that every tile height keeps a 2 x 4 arrangement of waves.  Four waves
+// with 128 x 128 wave tiles: 1.05 ms (the compiler moves accumulators between register files inside the loop).
+// Several tile shapes are instantiated (workgroup tile BM x BN x 64, WM x WN wavefronts); the launcher
+// picks one (pick_tile).
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
 #include "gemm.hpp"
 
 namespace pg {
@@ -25,13 +32,13 @@ typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 constexpr int GROUP_M = 8;                         // tile rows per raster band
 constexpr int XCDS = 8;
 
-// byte offset of 16-byte chunk `chunk` of tile row `row` inside an operand tile with CH chunks per row
-template <int CH>
-__device__ __forceinline__ int swz(int row) {
-  return CH == 8 ? ((row ^ (row >> 3)) & 7) : (((row >> 1) ^ (row >> 3)) & 3);
-}
-template <int CH>
-__device__ __forceinline__ int lds_off(int row, int chunk) { return (row * CH + (chunk ^ swz<CH>(row))) * 16; }
+constexpr int BK = 64, CH = BK / 8;                // columns per K step, 16-byte chunks per tile row
+constexpr int MI = 16, KS = 32;                    // 16x16x32 MFMA: lane l holds row l % 16, 8 columns at 8 (l / 16)
+
+// byte offset of 16-byte chunk `chunk` of tile row `row` inside an operand tile: the 16 rows of a fragment put one chunk
+// of theirs into 16 different bank groups, and rows 16 apart share their swizzle
+__device__ __forceinline__ int swz(int row) { return (row ^ ((row >> 3) & 1)) & 7; }
+__device__ __forceinline__ int lds_off(int row, int chunk) { return (row * CH + (chunk ^ swz(row))) * 16; }
 
 // 16 bytes per lane straight from global memory into LDS (no register staging): the wave writes the
 // 1 KB starting at LDS address `lds_addr` (wave-uniform), lane l at +16 l.  Issued through inline
@@ -39,16 +46,17 @@ __device__ __forceinline__ int lds_off(int row, int chunk) { return (row * CH + 
 // is awaited explicitly (wait_dma) before the barrier that publishes the stage.  The statement overwrites m0
 // without naming it as clobbered: m0 is a reserved register for this compiler (it refuses it in a clobber list
 // and writes m0 itself directly before each instruction of its own that reads it), so no value of the
-// surrounding code lives in m0 across the statement.
-__device__ __forceinline__ void dma16(const uint16_t* g, uint32_t lds_addr) {
+// surrounding code lives in m0 across the statement.  The address is a wave-uniform base plus a 32-bit byte offset per
+// lane (no vector arithmetic per request); WIDE: a 64-bit address per lane, for rows too far apart for that.
+__device__ __forceinline__ void dma16(uint32_t off, const uint16_t* base, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr) : "memory");
+}
+__device__ __forceinline__ void dma16_wide(const uint16_t* g, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_addr) : "memory");
 }
-// wait until at most N of this wave's loads are still in flight (loads complete in order)
-template <int N>
-__device__ __forceinline__ void wait_dma() {
-  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
+constexpr int64_t NARROW_LD = 1 << 23;             // 255 rows of so many bf16, in bytes, fit 32 bits
+// wait until none of this wave's loads is in flight
+__device__ __forceinline__ void wait_dma() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // Outputs are written, and the residual stream is read, once per launch: they go through the caches
 // with the non-temporal hint so that the operand panels shared by the tiles of an XCD stay resident.
@@ -82,15 +90,6 @@ __device__ __forceinline__ uint2 pack_bf16x4(float4 v) {
   return r;
 }
 
-// f(tag<I>), f(tag<I + 2>), ... while I < N and f returns true
-template <int I> struct int_tag { static constexpr int value = I; };
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for_by2(F&& f) {
-  if constexpr (I < N) {
-    if (f(int_tag<I>{})) static_for_by2<I + 2, N>(f);
-  }
-}
-
 // orders this wave's LDS accesses around a hand-over between its lanes (LDS serves one wave's accesses in issue order;
 // this keeps the compiler from moving them across the hand-over)
 __device__ __forceinline__ void wave_lds_sync() {
@@ -101,11 +100,22 @@ __device__ __forceinline__ void wave_lds_sync() {
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
-template <int EPI, int BM, int BN, int BK, int WM, int WN, int MINW, int NST>
+// f(tag<I>, tag<n>) for consecutive groups of n = 4, 2 or 1 of the N row tiles while f returns true
+template <int I> struct int_tag { static constexpr int value = I; };
+template <int I, int N, class F>
+__device__ __forceinline__ void for_row_groups(F&& f) {
+  if constexpr (I < N) {
+    constexpr int n = N - I >= 4 ? 4 : N - I >= 2 ? 2 : 1;
+    if (f(int_tag<I>{}, int_tag<n>{})) for_row_groups<I + n, N>(f);
+  }
+}
+
+template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE>
 __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmArgs a) {
-  static_assert(NST >= 2, "LDS stages filled by direct loads");
-  constexpr int CH = BK / 8;                       // 16-byte chunks per tile row
-  constexpr int TM = BM / WM / 32, TN = BN / WN / 32;   // 32x32 MFMA tiles per wave
+  constexpr int WAVES = WM * WN;
+  constexpr int CW = BN / WN, FM = BM / WM / MI, FN = CW / MI, FR = FM + FN, MF = FM * FN;   // columns, fragments, MFMAs of a wave
+  static_assert(CW == 32 || CW == 64, "the epilogue handles 32 or 64 columns per wave");
+  static_assert((BM / WM) % MI == 0 && (BM / WM) % 8 == 0, "wave rows");
   constexpr int A_BYTES = BM * BK * 2, W_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + W_BYTES;
   extern __shared__ __align__(16) unsigned char smem[];
   const uint16_t* PA = a.A; const int64_t LDA = a.lda;
@@ -113,7 +123,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmArgs
   const uint16_t* PB = a.bias;
   const int MM = a.M, NN = a.N;
   const int per_xcd = gridDim.x / XCDS;
-  const int b = a.raster ? (blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS : blockIdx.x;
+  const int b = (blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS;
   // ---- which output tile: XCD-aware, banded raster ----
   const int tiles_m = (MM + BM - 1) / BM, tiles_n = (NN + BN - 1) / BN;
   const int total = tiles_m * tiles_n;
@@ -125,180 +135,187 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmArgs
   const int tn = (b % band) / gsz;
   const int m0 = tm * BM, n0 = tn * BN;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  const int l32 = lane & 31, half = lane >> 5;
+  const int lr = lane % MI, lk = lane / MI;
 
-  int a_row[TM], w_row[TN];
+  f32x4v acc[FM][FN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) a_row[i] = wm * (BM / WM) + i * 32 + l32;
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-  for (int j = 0; j < TN; ++j) w_row[j] = wn * (BN / WN) + j * 32 + l32;
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
 
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  const int nk = a.K / BK;
   {
-    // ---- global -> LDS directly: every wave owns N_REG / WAVES regions of 1 KB (64 / CH tile rows) ----
-    constexpr int WAVES = WM * WN, RPR = 64 / CH;
-    constexpr int A_REG = BM / RPR, N_REG = (BM + BN) / RPR, PER_WAVE = (N_REG + WAVES - 1) / WAVES;
-    static_assert(NST == 2 || N_REG % WAVES == 0, "deeper pipelines count loads per wave: regions must divide evenly");
-    const uint16_t* g_ptr[PER_WAVE];
+    // ---- global -> LDS directly: a stage is N_REG regions of 1 KB (8 tile rows), dealt to the waves in turn ----
+    constexpr int RPR = 64 / CH, A_REG = BM / RPR, N_REG = (BM + BN) / RPR, PER_WAVE = (N_REG + WAVES - 1) / WAVES;
+    const int nk = a.K / BK;
+    uint32_t g_off[WIDE ? 1 : PER_WAVE];
+    const uint16_t* g_base[PER_WAVE];                // WIDE: per lane; else wave-uniform
     uint32_t g_lds[PER_WAVE];
     const uint32_t lds_base = (uint32_t)(uintptr_t)smem;
 #pragma unroll
     for (int i = 0; i < PER_WAVE; ++i) {
-      const int g = min(wave + i * WAVES, N_REG - 1);  // wave-uniform region id (the last wave may own one fewer)
+      const int g = min(wave + i * WAVES, N_REG - 1);  // wave-uniform
       const bool is_w = g >= A_REG;
       const int rg = is_w ? g - A_REG : g;
       const int row = rg * RPR + lane / CH;
-      const int ch = (lane % CH) ^ swz<CH>(row);
-      g_ptr[i] = is_w ? PW + (int64_t)min(n0 + row, NN - 1) * LDW + ch * 8
-                      : PA + (int64_t)min(m0 + row, MM - 1) * LDA + ch * 8;
+      const int ch = (lane % CH) ^ swz(row);
+      const int r = is_w ? min(row, NN - 1 - n0) : min(row, MM - 1 - m0);
+      if (WIDE) {
+        g_base[i] = (is_w ? PW + (int64_t)(n0 + r) * LDW : PA + (int64_t)(m0 + r) * LDA) + ch * 8;
+      } else {
+        g_base[i] = is_w ? PW + (int64_t)n0 * LDW : PA + (int64_t)m0 * LDA;
+        g_off[WIDE ? 0 : i] = ((uint32_t)r * (uint32_t)(is_w ? LDW : LDA) + (uint32_t)(ch * 8)) * 2u;
+      }
       g_lds[i] = __builtin_amdgcn_readfirstlane(lds_base + (is_w ? A_BYTES : 0) + rg * 1024);
     }
-    // request region i of K tile `kt` (nothing past the last tile)
+    // request region i of K tile `kt`
     auto request = [&](int i, int kt) {
-      if (kt < nk && wave + i * WAVES < N_REG) dma16(g_ptr[i] + kt * BK, g_lds[i] + (kt % NST) * STAGE_BYTES);
+      if ((i + 1) * WAVES > N_REG && wave + i * WAVES >= N_REG) return;      // the last one of an uneven deal
+      const uint32_t dst = g_lds[i] + (kt & 1) * STAGE_BYTES;
+      if (WIDE) dma16_wide(g_base[i] + kt * BK, dst);
+      else dma16(g_off[WIDE ? 0 : i], g_base[i] + kt * BK, dst);
     };
-    // NST stages of BK columns; tile kt lives in stage kt % NST.  Per K step: SLABS MFMA slabs.  Operand
-    // fragments are double buffered in registers and read one slab ahead, also across the K-step
-    // boundary: at the last slab of tile kt every read of its stage has been issued, so the barrier that
-    // publishes tile kt+1 (and frees stage kt % NST) is passed before that slab's MFMAs, and the first
-    // slab of tile kt+1 is read while they run.  The requests for tile kt+NST are not issued in a burst
-    // (a wave's request waits for the texture path, which takes 1 KB every ~20 cycles, and the MFMAs
-    // queued behind it would wait too): they are spread between the MFMAs of the SPREAD slabs that
-    // follow the barrier, one request every few MFMAs.
-    constexpr int SLABS = BK / 16, MF = TM * TN;
-    static_assert(SLABS % 2 == 0, "fragment buffers alternate per slab");
-    constexpr int SPREAD = NST == 2 ? 2 : SLABS;                     // slabs over which one tile's requests go
-    constexpr int RPS = (PER_WAVE + SPREAD - 1) / SPREAD;            // requests per slab
-    constexpr int EVERY = MF / RPS > 0 ? MF / RPS : 1;               // one request after every EVERY-th MFMA
-    static_assert(RPS <= MF, "more requests than MFMAs in a slab");
-    constexpr int LAG = (NST - 2) * PER_WAVE;                        // requests that may stay in flight at the barrier
-    bf16x8 af[2][TM], wf[2][TN];
-    auto fetch = [&](int stage, int ks, int buf) {
-      const unsigned char* sA = smem + stage * STAGE_BYTES;
-      const unsigned char* sW = sA + A_BYTES;
+    // fragment addresses: 16 rows further down only add a constant, so one base per operand and slab serves all of them
+    constexpr int SLABS = BK / KS;
+    static_assert(SLABS == 2, "fragment buffers alternate per slab");
+    int pa[SLABS], pw[SLABS];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) af[buf][i] = *reinterpret_cast<const bf16x8*>(sA + lds_off<CH>(a_row[i], 2 * ks + half));
-#pragma unroll
-      for (int j = 0; j < TN; ++j) wf[buf][j] = *reinterpret_cast<const bf16x8*>(sW + lds_off<CH>(w_row[j], 2 * ks + half));
+    for (int ks = 0; ks < SLABS; ++ks) {
+      pa[ks] = lds_off(wm * (BM / WM) + lr, ks * (KS / 8) + lk);
+      pw[ks] = A_BYTES + lds_off(wn * CW + lr, ks * (KS / 8) + lk);
+    }
+    bf16x8 fr[2][FR];
+    auto fetch = [&](int stage, int ks, int buf, int f) {
+      const int at = f < FN ? pw[ks] + f * MI * CH * 16 : pa[ks] + (f - FN) * MI * CH * 16;
+      fr[buf][f] = *reinterpret_cast<const bf16x8*>(smem + at + stage * STAGE_BYTES);
     };
-    // prologue: tiles 0 .. NST-2 are requested, tile 0 awaited
-#pragma unroll
-    for (int t = 0; t < NST - 1; ++t)
-#pragma unroll
-      for (int i = 0; i < PER_WAVE; ++i) request(i, t);
-    if (nk >= NST - 1) wait_dma<LAG>(); else wait_dma<0>();
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < RPS; ++i) request(i, NST - 1);               // the share that position 0 would have carried
-    fetch(0, 0, 0);
-    // slab position p after a barrier: p = 0 is the last slab of the K step that passed it, p >= 1 are
-    // slabs p-1 of the next K step; position p carries requests [p RPS, (p+1) RPS) of the tile freed there
-    for (int kt = 0; kt < nk; ++kt) {
-      const int cur = kt % NST;
+    // One request after every EVERY-th MFMA and one fragment read after every FEV-th: a wave's request waits for the
+    // texture path, which takes 1 KB every ~20 cycles, and in a burst the MFMAs queued behind it would wait too.
+    constexpr int FEV = MF / FR > 0 ? MF / FR : 1, EVERY = MF / PER_WAVE > 0 ? MF / PER_WAVE : 1;
+    static_assert(MF / FEV >= FR || MF < FR, "every fragment is read");
+    // K step kt.  At its last slab every read of its stage has been issued and awaited, so the barrier that publishes tile
+    // kt+1 and frees the stage is passed before that slab's MFMAs; the first slab of tile kt+1 is read, and tile kt+2
+    // requested (REQ), while they run.
+    auto step = [&](int kt, auto req_c, auto next_c) {
+      constexpr bool REQ = decltype(req_c)::value, NEXT = decltype(next_c)::value;
 #pragma unroll
       for (int ks = 0; ks < SLABS; ++ks) {
-        if (ks + 1 < SLABS) {
-          fetch(cur, ks + 1, (ks + 1) & 1);
-        } else if (kt + 1 < nk) {
-          // tiles up to kt+NST-1 have been requested (fewer near the end: then wait for all)
-          if (kt + NST - 1 < nk) wait_dma<LAG>(); else wait_dma<0>();
-          __syncthreads();                         // tile kt+1 is visible; stage `cur` is free
-          fetch((kt + 1) % NST, 0, 0);
+        const bool last = ks + 1 == SLABS;
+        if (last && NEXT) {
+          wait_dma();
+          __syncthreads();
         }
-        const int pos = ks + 1 < SLABS ? ks + 1 : 0;                 // compile-time after unrolling
-        const int tile = ks + 1 < SLABS ? kt - 1 + NST : kt + NST;   // the tile whose stage was freed last
+        const int stage = (last ? kt + 1 : kt) & 1, to = (ks + 1) & 1;
         __builtin_amdgcn_sched_barrier(0);
-        int q = 0;
+        __builtin_amdgcn_s_setprio(1);
+        int q = 0, fetched = 0, asked = 0;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks & 1][i], wf[ks & 1][j], acc[i][j], 0, 0, 0);
-            if (pos < SPREAD && q % EVERY == 0 && q / EVERY < RPS && pos * RPS + q / EVERY < PER_WAVE) {
-              __builtin_amdgcn_sched_barrier(0);
-              request(pos * RPS + q / EVERY, tile);
-              __builtin_amdgcn_sched_barrier(0);
+          for (int j = 0; j < FN; ++j) {
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[ks & 1][FN + i], fr[ks & 1][j], acc[i][j], 0, 0, 0);
+            // (the smallest tiles have fewer MFMAs than fragments or requests: what is left follows the last one)
+            const bool end = i == FM - 1 && j == FN - 1;
+            if (!last || NEXT) {
+#pragma unroll
+              for (int f = 0; f < FR; ++f)
+                if (f == fetched && ((f == q / FEV && q % FEV == 0) || end)) {
+                  __builtin_amdgcn_sched_barrier(0);
+                  fetch(stage, last ? 0 : ks + 1, to, f);
+                  __builtin_amdgcn_sched_barrier(0);
+                  ++fetched;
+                }
+            }
+            if (REQ && last) {
+#pragma unroll
+              for (int f = 0; f < PER_WAVE; ++f)
+                if (f == asked && ((f == q / EVERY && q % EVERY == EVERY - 1) || end)) {
+                  __builtin_amdgcn_sched_barrier(0);
+                  request(f, kt + 2);
+                  __builtin_amdgcn_sched_barrier(0);
+                  ++asked;
+                }
             }
             ++q;
           }
+        __builtin_amdgcn_s_setprio(0);
       }
+    };
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) request(i, 0);
+    wait_dma();
+    __syncthreads();
+    if (nk > 1) {
+#pragma unroll
+      for (int i = 0; i < PER_WAVE; ++i) request(i, 1);
     }
+#pragma unroll
+    for (int f = 0; f < FR; ++f) fetch(0, 0, 0, f);
+    for (int kt = 0; kt + 2 < nk; ++kt) step(kt, std::true_type{}, std::true_type{});
+    if (nk > 1) step(nk - 2, std::false_type{}, std::true_type{});
+    step(nk - 1, std::false_type{}, std::false_type{});
   }
 
-  // ---- epilogue: in each 32x32 accumulator tile a lane holds ONE column (l32) and rows 8q + 4*half + t ----
+  // ---- epilogue: in each 16x16 accumulator tile a lane holds ONE column (lr) and rows 4 lk + t ----
+  const int row_w = m0 + wm * (BM / WM), col_w = n0 + wn * CW;       // first row and column of this wave
   if constexpr (EPI != EPI_UNPATCH) {
     // ---- row-major epilogues: transpose each 32-row slab of the wave tile through LDS so that a lane
     // owns 4 consecutive columns of a row and every global access is 16 bytes wide (8 for bf16) ----
-    static_assert(TN == 1 || TN == 2, "the staged epilogue handles 32 or 64 columns per wave");
-    constexpr int LPR = TN * 8, RPI = 64 / LPR, NP = 32 / RPI;   // lanes per row, rows per access, accesses per slab
-    constexpr int EST = TN * 32 + 8;                 // staging row stride in floats (half-waves hit disjoint banks)
+    constexpr int LPR = CW / 4, RPI = 64 / LPR, NP = 32 / RPI;   // lanes per row, rows per access, accesses per slab
+    constexpr int EST = CW + 4;                      // staging row stride in floats: 4 rows down are 16 banks on
+    constexpr int VP = 72;                           // pitch of the transposed staging in bf16: 64 tokens + 8 (16-byte aligned rows)
+    constexpr int STG = CW * VP * 2;                 // staging bytes per wave
+    static_assert(32 * EST * 4 <= STG && WAVES * STG <= 2 * STAGE_BYTES, "the staging areas fit");
     __syncthreads();                                 // every wave has finished reading the last stage
-    float* stg = reinterpret_cast<float*>(smem) + wave * (32 * EST);
+    float* stg = reinterpret_cast<float*>(smem + wave * STG);
     const int c4 = (lane % LPR) * 4, rsub = lane / LPR;
-    const int n = n0 + wn * (BN / WN) + c4;
+    const int n = col_w + c4;
     // columns written row-major: all of them, except the value channels of EPI_QKV
     const int n_rm = EPI == EPI_QKV ? a.v_start : NN;
     if (EPI == EPI_QKV) {
       // ---- value channels, stored TRANSPOSED: V^T[traj][channel][token].  In an accumulator tile a lane already
       // holds 4 consecutive tokens of ONE channel, so they are packed to bf16 and staged channel-major (8 bytes per
-      // LDS write), two 32-token slabs at a time; then a lane owns 4 consecutive tokens of a channel row and 16
-      // lanes write 64 consecutive tokens (128 bytes) of it.  A 32-column accumulator tile is either all value
+      // LDS write), up to 64 tokens at a time; then a lane owns 4 consecutive tokens of a channel row and 16
+      // lanes write 64 consecutive tokens (128 bytes) of it.  A 32-column group is either all value
       // channels or none (v_start is a multiple of 32). ----
-      constexpr int VP = 72;                         // staging pitch in bf16: 64 tokens + 8 (rows stay 16-byte aligned)
-      static_assert(TN * 32 * VP * 2 <= 32 * EST * 4, "the transposed staging fits the wave's staging area");
       uint16_t* stg16 = reinterpret_cast<uint16_t*>(stg);
-      const int col_w = n0 + wn * (BN / WN);         // first column of this wave
       const int Dv = NN - n_rm;
-      bool is_v[TN];
-      float vb[TN];
+      bool is_v[FN];
+      float vb[FN];
       bool any_v = false;
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = col_w + j * 32;
+      for (int j = 0; j < FN; ++j) {
+        const int col = col_w + j * MI;
         is_v[j] = col >= n_rm && col < NN;           // wave-uniform
         any_v = any_v || is_v[j];
-        vb[j] = (is_v[j] && PB) ? bf16_to_f32(PB[col + l32]) : 0.f;
+        vb[j] = (is_v[j] && PB) ? bf16_to_f32(PB[col + lr]) : 0.f;
       }
       if (any_v) {
-        static_for_by2<0, TM>([&](auto tag) {
-          constexpr int i0 = decltype(tag)::value;
-          constexpr int nsl = i0 + 1 < TM ? 2 : 1;   // slabs staged together
-          const int row0 = m0 + wm * (BM / WM) + i0 * 32;        // first token row of the group, wave-uniform
+        for_row_groups<0, FM>([&](auto first, auto count) {
+          constexpr int i0 = decltype(first)::value, nt = decltype(count)::value;    // row tiles staged together
+          const int row0 = row_w + i0 * MI;          // first token row of the group, wave-uniform
           if (row0 >= MM) return false;
 #pragma unroll
-          for (int ii = 0; ii < 2; ++ii) {
-            if (ii >= nsl) break;
+          for (int ii = 0; ii < nt; ++ii)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
+            for (int j = 0; j < FN; ++j) {
               if (!is_v[j]) continue;
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                const float4 v = {acc[i0 + ii][j][4 * q] + vb[j], acc[i0 + ii][j][4 * q + 1] + vb[j],
-                                  acc[i0 + ii][j][4 * q + 2] + vb[j], acc[i0 + ii][j][4 * q + 3] + vb[j]};
-                *reinterpret_cast<uint2*>(stg16 + (j * 32 + l32) * VP + ii * 32 + 8 * q + 4 * half) = pack_bf16x4(v);
-              }
+              const f32x4v t = acc[i0 + ii][j];
+              const float4 v = {t[0] + vb[j], t[1] + vb[j], t[2] + vb[j], t[3] + vb[j]};
+              *reinterpret_cast<uint2*>(stg16 + (j * MI + lr) * VP + ii * MI + 4 * lk) = pack_bf16x4(v);
             }
-          }
           wave_lds_sync();
-          constexpr int lpr = 8 * nsl, rpa = 64 / lpr;   // lanes per channel row, channel rows per access
+          constexpr int lpr = 4 * nt, rpa = 64 / lpr;    // lanes per channel row, channel rows per access
           const int t4 = (lane % lpr) * 4, csub = lane / lpr;
           const int r = row0 + t4;                   // the lane's first token row
           const int traj0 = r / a.L, tok0 = r - traj0 * a.L;
           const bool whole = r + 3 < MM && tok0 + 3 < a.L && ((tok0 + a.tok_off) & 1) == 0;
 #pragma unroll
-          for (int p = 0; p < TN * 32 / rpa; ++p) {
+          for (int p = 0; p < CW / rpa; ++p) {
             const int cl = p * rpa + csub;           // channel row inside the wave's columns
-            if (!is_v[cl / 32] || r >= MM) continue;
+            const bool mine = col_w + cl >= n_rm && col_w + cl < NN;
+            if (!mine || r >= MM) continue;
             const uint2 pk = *reinterpret_cast<const uint2*>(stg16 + cl * VP + t4);
             const int ch = col_w + cl - n_rm;
             uint16_t* dst = a.vt + ((int64_t)traj0 * Dv + ch) * a.Lpad + a.tok_off + tok0;
@@ -343,18 +360,20 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmArgs
             bf16_to_f32((uint16_t)(raw.y >> 16))};
     }
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int slab0 = m0 + wm * (BM / WM) + i * 32;            // wave-uniform
+    for (int i = 0; i < FM; i += 2) {
+      const int slab0 = row_w + i * MI;                          // wave-uniform
       if (slab0 >= a.M) break;
+      const int np = i + 1 < FM ? NP : NP / 2;                   // an odd last row tile is half a slab
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int ii = 0; ii < 2; ++ii)
+        if (i + ii < FM)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+          for (int j = 0; j < FN; ++j)
 #pragma unroll
-          for (int t = 0; t < 4; ++t) stg[(8 * q + 4 * half + t) * EST + j * 32 + l32] = acc[i][j][4 * q + t];
+            for (int t = 0; t < 4; ++t) stg[(ii * MI + 4 * lk + t) * EST + j * MI + lr] = acc[i + ii < FM ? i + ii : 0][j][t];
       float4 v[NP];
 #pragma unroll
-      for (int p = 0; p < NP; ++p) {
+      for (int p = 0; p < np; ++p) {
         v[p] = *reinterpret_cast<const float4*>(stg + (RPI * p + rsub) * EST + c4);
         v[p].x += b4.x; v[p].y += b4.y; v[p].z += b4.z; v[p].w += b4.w;
         if (EPI == EPI_QKV && a.norm_hd > 0) {
@@ -380,7 +399,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmArgs
         }
         float4 hv[NP], gv[NP];
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
+        for (int p = 0; p < np; ++p) {
           const int r = slab0 + RPI * p + rsub;
           const bool ok = r < a.M && n_ok;
           hv[p] = ok ? load_stream(a.outf + (int64_t)r * a.ldo + n) : float4{0.f, 0.f, 0.f, 0.f};
@@ -389,7 +408,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmArgs
             gv[p] = *reinterpret_cast<const float4*>(a.gate + (int64_t)a.group_of[r / a.L] * a.gate_ld + n);
         }
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
+        for (int p = 0; p < np; ++p) {
           const int r = slab0 + RPI * p + rsub;
           if (r < a.M && n_ok) {
             float4 o = {hv[p].x + gv[p].x * v[p].x, hv[p].y + gv[p].y * v[p].y, hv[p].z + gv[p].z * v[p].z,
@@ -400,7 +419,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmArgs
         continue;
       }
 #pragma unroll
-      for (int p = 0; p < NP; ++p) {
+      for (int p = 0; p < np; ++p) {
         const int r = slab0 + RPI * p + rsub;
         if (r >= a.M || !n_ok) continue;
         if (EPI == EPI_F32) {
@@ -426,86 +445,95 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmArgs
     return;
   }
   // ---- unpatchify: per-element scatter into the latent layout (small: N = 4C columns) ----
-  int n_j[TN];
-  float bias_j[TN];
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    n_j[j] = n0 + wn * (BN / WN) + j * 32 + l32;
-    bias_j[j] = (a.bias && n_j[j] < a.N) ? bf16_to_f32(a.bias[n_j[j]]) : 0.f;
-  }
+  for (int i = 0; i < FM; ++i) {
+    const int r0 = row_w + i * MI + 4 * lk;          // rows r0 + t
+    if (r0 >= a.M) continue;
+    const int traj0 = r0 / a.Li, tok0 = r0 - traj0 * a.Li;
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int rb = m0 + wm * (BM / WM) + i * 32 + 4 * half;       // rows rb + 8q + t
+    for (int j = 0; j < FN; ++j) {
+      const int n = col_w + j * MI + lr;
+      if (n >= a.N) continue;
+      const float bias = a.bias ? bf16_to_f32(a.bias[n]) : 0.f;
+      int traj = traj0, tok = tok0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r0 = rb + 8 * q;
-      if (r0 >= a.M) continue;
-      const int traj0 = r0 / a.Li, tok0 = r0 - traj0 * a.Li;
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n = n_j[j];
-        if (n >= a.N) continue;
-        int traj = traj0, tok = tok0;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int r = r0 + t;
-          if (r >= a.M) break;
-          const float v = acc[i][j][4 * q + t] + bias_j[j];
-          if (tok >= a.Li) { tok -= a.Li; ++traj; }
-          const int py = tok / a.Wp, px = tok - py * a.Wp;
-          const int c = n >> 2, dy = (n >> 1) & 1, dx = n & 1;
-          a.outf[(int64_t)traj * ((int64_t)(a.N >> 2) * a.HW) + (int64_t)c * a.HW + (2 * py + dy) * a.Wimg + 2 * px + dx] = v;
-          ++tok;
-        }
+      for (int t = 0; t < 4; ++t) {
+        if (r0 + t >= a.M) break;
+        if (tok >= a.Li) { tok -= a.Li; ++traj; }
+        const int py = tok / a.Wp, px = tok - py * a.Wp;
+        const int c = n >> 2, dy = (n >> 1) & 1, dx = n & 1;
+        a.outf[(int64_t)traj * ((int64_t)(a.N >> 2) * a.HW) + (int64_t)c * a.HW + (2 * py + dy) * a.Wimg + 2 * px + dx] =
+            acc[i][j][t] + bias;
+        ++tok;
       }
     }
   }
 }
 
-template <int EPI, int BM, int BN, int BK, int WM, int WN, int MINW, int NST>
+template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE = false>
 static pg_status launch_tile(const GemmArgs& a, hipStream_t s) {
-  constexpr int LDS = NST * (BM + BN) * BK * 2;
+  constexpr int LDS = 2 * (BM + BN) * BK * 2;
   static bool attr_set = false;
   if (!attr_set) {
-    PG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_kernel<EPI, BM, BN, BK, WM, WN, MINW, NST>),
+    PG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_kernel<EPI, BM, BN, WM, WN, MINW, WIDE>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
     attr_set = true;
   }
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
   const int grid = (tiles + XCDS - 1) / XCDS * XCDS;
-  gemm_kernel<EPI, BM, BN, BK, WM, WN, MINW, NST><<<dim3(grid), dim3(64 * WM * WN), LDS, s>>>(a);
+  gemm_kernel<EPI, BM, BN, WM, WN, MINW, WIDE><<<dim3(grid), dim3(64 * WM * WN), LDS, s>>>(a);
   PG_LAUNCH_CHECK("gemm_kernel");
   return PG_OK;
 }
 
-// Tile choice.  A launch runs in rounds of 256 concurrent workgroups (one per compute unit); the last
-// round is usually part empty, and with few K steps a tile's fixed prologue / epilogue weighs more.
-// Pick the shape with the best product of slot occupancy and the measured relative speed of its main
-// loop.
+// Tile choice: the shape with the smallest estimated time.  A compute unit works through w = tiles / 256 tiles (the last
+// round, part empty, counts half as empty as it is: tiles of a long launch drift apart), each a fixed part (prologue and
+// epilogue; a read-modify-write of the residual stream costs three times a bf16 store) and K / 64 steps.  Microseconds per
+// step measured with the chip full and nearly idle (what limits a full chip is power and the operand traffic, a nearly
+// idle one the latency of a step):
+//   tile             full                   idle         tiles per compute unit
+//   BM x 256   0.00553 (BM + 64)    0.55 of that    1     (256: 42.5 us per round of K = 1536, 192: 33.7, 128: 25.8)
+//   128 x 128   0.52 (0.64 alone)   0.36            2
+//   128 x  64   0.30                0.28            3
+//    64 x  64   0.18                0.18            4
+// The 64-column tiles are for launches that would otherwise leave most of the chip without work or with one long K loop per
+// compute unit: 512 x 128 x 512 takes 12.0 us with 128 x 256 tiles and 5.5 with 64 x 64; 4096 x 1024 x 1024 23.3 and 16.2
+// (128 x 64).
+struct TileShape { int bm, bn; double full, idle; };
+constexpr TileShape TILES[7] = {
+    {256, 256, 0.00553 * 320, 0.00304 * 320}, {192, 256, 0.00553 * 256, 0.00304 * 256},
+    {128, 128, 0.52, 0.36}, {160, 256, 0.00553 * 224, 0.00304 * 224}, {224, 256, 0.00553 * 288, 0.00304 * 288},
+    {128, 64, 0.30, 0.28}, {64, 64, 0.18, 0.18}};
 static int pick_tile(const GemmArgs& a, int epilogue) {
-  auto score = [&](int bm, int bn, int per_cu, double speed) {
-    const double tiles = (double)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn);
-    const double slots = 256.0 * per_cu;
-    const double useful = (double)a.M * a.N / ((double)bm * bn);      // ragged edge tiles do less work
-    return speed * useful / (ceil(tiles / slots) * slots);
-  };
-  const double sc[6] = {score(256, 256, 1, 1.00), score(192, 256, 1, 0.97), score(128, 256, 1, 0.90),
-                        score(128, 128, 2, 0.85), score(160, 256, 1, 0.92), score(224, 256, 1, 0.96)};
-  const bool wide_rows = epilogue == EPI_QKV && a.norm_hd > 32;   // the fused norm needs a whole head inside one wave's columns
+  const double nk = a.K / BK, edge = epilogue == EPI_RESID ? 12.0 : 4.0;
+  const bool whole_heads = epilogue == EPI_QKV && a.norm_hd > 32;   // the fused norm needs a whole head inside one wave's columns
   int best = 0;
-  for (int i = 1; i < 6; ++i) if (sc[i] > sc[best] * 1.02 && !(wide_rows && i >= 4)) best = i;
+  double best_us = 0.0;
+  for (int i = 0; i < 7; ++i) {
+    const TileShape& t = TILES[i];
+    if (whole_heads && t.bm == 64) continue;      // 32 columns per wave
+    const double load = ceil((double)a.M / t.bm) * ceil((double)a.N / t.bn) / 256.0;
+    const double w = load <= 1.0 ? 1.0 : 0.5 * (load + ceil(load));
+    const double full = t.bm == 128 && t.bn == 128 && load <= 1.0 ? 0.64 : t.full;
+    const double step = t.idle + (full - t.idle) * fmin(1.0, load / 0.75);
+    const double us = w * (edge * t.bm * t.bn / 65536.0 + 0.3 + nk * step);
+    if (i == 0 || us < best_us) { best = i; best_us = us; }
+  }
   return best;
 }
 
 template <int EPI>
 static pg_status launch_one(const GemmArgs& a, hipStream_t s) {
+  // operand rows so far apart that their byte offsets inside a tile need 64 bits (pg_gemm_bf16 alone takes any)
+  if (EPI == EPI_F32 && (a.lda > NARROW_LD || a.ldw > NARROW_LD)) return launch_tile<EPI_F32, 128, 128, 2, 2, 2, true>(a, s);
   switch (pick_tile(a, EPI)) {
-    case 0: return launch_tile<EPI, 256, 256, 64, 2, 4, 2, 2>(a, s);
-    case 1: return launch_tile<EPI, 192, 256, 64, 2, 4, 2, 2>(a, s);
-    case 2: return launch_tile<EPI, 128, 256, 64, 2, 4, 2, 2>(a, s);
-    case 3: return launch_tile<EPI, 128, 128, 64, 2, 2, 2, 2>(a, s);
-    case 4: return launch_tile<EPI, 160, 256, 64, 1, 8, 2, 2>(a, s);     // heights that are not a multiple of 64:
-    default: return launch_tile<EPI, 224, 256, 64, 1, 8, 2, 2>(a, s);    // one wave row, 32 columns per wave
+    case 0: return launch_tile<EPI, 256, 256, 2, 4, 2>(a, s);
+    case 1: return launch_tile<EPI, 192, 256, 2, 4, 2>(a, s);
+    case 2: return launch_tile<EPI, 128, 128, 2, 2, 2>(a, s);
+    case 3: return launch_tile<EPI, 160, 256, 2, 4, 2>(a, s);
+    case 4: return launch_tile<EPI, 224, 256, 2, 4, 2>(a, s);
+    case 5: return launch_tile<EPI, 128, 64, 4, 1, 3>(a, s);
+    default: return launch_tile<EPI, 64, 64, 2, 2, 4>(a, s);
   }
 }
 
@@ -513,7 +541,7 @@ pg_status launch_gemm(const GemmArgs& a_in, int epilogue, hipStream_t s) {
   GemmArgs a = a_in;
   // bands of 8 tile rows; of 4 when the output is at most six tiles wide (the D-wide residual GEMMs of the 1536-wide network:
   // a band then still spans the whole width, and 0.7 % of the loop's GEMM time goes away)
-  a.raster = 1; a.group_m = (a.N + 255) / 256 <= 6 ? GROUP_M / 2 : GROUP_M;
+  a.group_m = (a.N + 255) / 256 <= 6 ? GROUP_M / 2 : GROUP_M;
   if (a.M <= 0 || a.N <= 0) return PG_OK;
   if (a.K <= 0 || a.K % 64) return fail(PG_ESHAPE, "GEMM K = %d must be a positive multiple of 64", a.K);
   if (a.lda % 8 || a.ldw % 8 || a.lda < a.K || a.ldw < a.K || ((uintptr_t)a.A & 15) || ((uintptr_t)a.W & 15))

@@ -41,6 +41,32 @@ def test_gemm_matches_oracle_linear(lib, M, N, K):
     assert np.max(np.abs(got - want)) < 2e-5 * math.sqrt(K) * np.max(np.abs(want)) + 1e-6
 
 
+# the remaining tiles (256 x 256, 224, 192 and 160 rows with one to four K steps, 128 x 128, 128 x 64, 64 x 64), one row and
+# column short of or past a tile
+@pytest.mark.parametrize("M,N,K", [(3213, 4484, 256), (14100, 1540, 192), (3697, 6140, 192), (4000, 4100, 128), (5000, 1000, 64),
+                                   (4097, 1020, 192), (63, 252, 64), (65, 68, 192), (64, 64, 128)])
+def test_gemm_tiles_with_short_k(lib, M, N, K):
+    test_gemm_matches_oracle_linear(lib, M, N, K)
+
+
+@pytest.mark.parametrize("ld", [1 << 23, (1 << 23) + 64])
+def test_gemm_rows_far_apart(lib, ld):
+    """Row strides on both sides of what a 32-bit byte offset inside a tile can express."""
+    say(f"gemm ld={ld}")
+    M, N, K = 9, 12, 128
+    rng = np.random.default_rng(5)
+    A = workloads.bf16_round(rng.standard_normal((M, K), dtype=np.float32))
+    W = workloads.bf16_round(rng.standard_normal((N, K), dtype=np.float32))
+    Ad = torch.zeros(M * ld, dtype=torch.int16, device=DEV)
+    Ad.view(M, ld)[:, :K] = bf16_dev(A)
+    Wd = torch.zeros(N * ld, dtype=torch.int16, device=DEV)
+    Wd.view(N, ld)[:, :K] = bf16_dev(W)
+    out = torch.full((M, N), float("nan"), device=DEV)
+    lib.pg_gemm_bf16(Ad, ld, Wd, ld, None, out, N, M, N, K)
+    want = dit.linear(A.astype(np.float64), W, np.zeros(N, np.float32))
+    assert np.max(np.abs(out.cpu().numpy() - want)) < 2e-5 * math.sqrt(K) * np.max(np.abs(want))
+
+
 def test_gemm_rejects_bad_shapes(lib):
     A = torch.zeros(64, 96, dtype=torch.int16, device=DEV)
     out = torch.zeros(64, 64, device=DEV)
