@@ -179,25 +179,29 @@ __global__ __launch_bounds__(256) void modulation_kernel(const Modulation a) {
 // lane, D <= 256 NV; WHOLE: D = 256 NV, else the last float4 of some lanes lies past the row) so h is read once and every
 // access is 16 bytes wide; NV = 0 is the generic route for wider rows (three cached passes of 4-byte accesses, which
 // every width that is no multiple of 256 used to take).
-// Rows: r' = m * L_out + t for t < L_out reads h row m * L_in + t (L_out < L_in drops the context rows).
+// Rows: r' = m * L_out + t for t < L_out reads h row m * L_in + t (L_out < L_in drops the context rows).  From output row
+// `rows0` on (dual-stream: the context plane) rows are read in place, L2 of them per trajectory, modulated by shift2 / scale2.
+struct LnArgs {
+  const float* h; uint16_t* out; const float* shift; const float* scale; int64_t mod_ld; const int32_t* group_of;
+  int rows_out, L_in, L_out, D;
+  int rows0; const float* shift2; const float* scale2; int L2;
+};
 template <int NV, bool WHOLE>
-__global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restrict__ h, uint16_t* __restrict__ out,
-                                                          const float* __restrict__ shift,
-                                                          const float* __restrict__ scale, int64_t mod_ld,
-                                                          const int32_t* __restrict__ group_of, int rows_out,
-                                                          int L_in, int L_out, int D) {
+__global__ __launch_bounds__(256) void ln_modulate_kernel(const LnArgs a) {
+  const int D = a.D;
   const int lane = threadIdx.x & 63;
   const int ro = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (ro >= rows_out) return;
-  const int m = ro / L_out, t = ro - m * L_out;
-  const float* hr = h + ((int64_t)m * L_in + t) * D;
-  uint16_t* orow = out + (int64_t)ro * D;
+  if (ro >= a.rows_out) return;
+  const bool second = ro >= a.rows0;
+  const int m = second ? (ro - a.rows0) / a.L2 : ro / a.L_out;
+  const float* hr = a.h + (second ? (int64_t)ro : (int64_t)m * a.L_in + (ro - m * a.L_out)) * D;
+  uint16_t* orow = a.out + (int64_t)ro * D;
   const float* sh = nullptr;
   const float* sc = nullptr;
-  if (shift) {
-    const int g = group_of[m];
-    sh = shift + (int64_t)g * mod_ld;
-    sc = scale + (int64_t)g * mod_ld;
+  if (a.shift) {
+    const int64_t g = (int64_t)a.group_of[m] * a.mod_ld;
+    sh = (second ? a.shift2 : a.shift) + g;
+    sc = (second ? a.scale2 : a.scale) + g;
   }
   if (NV > 0) {
     float4 v[NV > 0 ? NV : 1];
@@ -384,15 +388,14 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
     g.M = Ri; g.N = D; g.K = Kp; g.k_algo = 4 * f.C; g.outf = h; g.ldo = D; g.L = dual ? Li : L; g.Li = Li; g.pos = n.w(PG_W_POS);
     PG_TRY(launch_gemm(g, EPI_EMBED, s));
   }
-  // out[m * L_out + t, :] = bf16(LN(hin[m * L_in + t, :]) * (1 + scale) + shift), t < L_out
-  auto ln = [&](const float* hin, uint16_t* out, const float* shift, const float* scale, int64_t ld, int rows_out,
-                int L_in, int L_out) -> pg_status {
-    if (rows_out <= 0) return PG_OK;
-    const dim3 grid((rows_out + 3) / 4), block(256);
+  // act[m * L_out + t, :] = bf16(LN(h[m * L_in + t, :]) * (1 + scale) + shift), t < L_out
+  auto ln = [&](const LnArgs& a) -> pg_status {
+    if (a.rows_out <= 0) return PG_OK;
+    const dim3 grid((a.rows_out + 3) / 4), block(256);
     auto run = [&](auto nv_c) {
       constexpr int NV = decltype(nv_c)::value;
-      if (D == 256 * NV) ln_modulate_kernel<NV, true><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
-      else ln_modulate_kernel<NV, false><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
+      if (D == 256 * NV) ln_modulate_kernel<NV, true><<<grid, block, 0, s>>>(a);
+      else ln_modulate_kernel<NV, false><<<grid, block, 0, s>>>(a);
     };
     switch ((D + 255) / 256) {                    // D is a multiple of 64: rows of h, out and the modulation vectors stay 16-byte aligned
       case 1: run(std::integral_constant<int, 1>{}); break;
@@ -403,13 +406,18 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
       case 6: run(std::integral_constant<int, 6>{}); break;
       case 7: run(std::integral_constant<int, 7>{}); break;
       case 8: run(std::integral_constant<int, 8>{}); break;
-      default: ln_modulate_kernel<0, false><<<grid, block, 0, s>>>(hin, out, shift, scale, ld, group_of, rows_out, L_in, L_out, D);
+      default: ln_modulate_kernel<0, false><<<grid, block, 0, s>>>(a);
     }
     PG_LAUNCH_CHECK("ln_modulate_kernel");
     return PG_OK;
   };
   auto layer_norm = [&](const float* shift, const float* scale, int64_t ld, int rows_out, int L_out) -> pg_status {
-    return ln(h, act, shift, scale, ld, rows_out, dual ? L_out : L, L_out);
+    return ln(LnArgs{h, act, shift, scale, ld, group_of, rows_out, dual ? L_out : L, L_out, D, rows_out, nullptr, nullptr, 1});
+  };
+  // both planes of the dual-stream network in one launch
+  auto layer_norm_pair = [&](const float* const* mods, int slot) -> pg_status {
+    return ln(LnArgs{h, act, mods[0] + slot * D, mods[0] + (slot + 1) * D, mod_ld, group_of, Ri + Rc, Li, Li, D,
+                     Ri, mods[1] + slot * D, mods[1] + (slot + 1) * D, f.Lc});
   };
 
   // ---- dual-stream blocks: two planes (image rows, context rows), joint q | k and V^T ----
@@ -426,40 +434,43 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
     const int W_FC2[2] = {PG_W_FC2_W, PG_W_C_FC2_W}, B_FC2[2] = {PG_W_FC2_B, PG_W_C_FC2_B};
     for (int b = 0; b < f.blocks; ++b) {
       const float* mbs[2] = {mod + (size_t)b * 6 * D, cmod + (size_t)b * 6 * D};
+      GemmArgs g[2];
+      PG_TRY(layer_norm_pair(mbs, 0));
       for (int st = 0; st < 2; ++st) {
-        PG_TRY(ln(hs[st], acts[st], mbs[st], mbs[st] + D, mod_ld, rows[st], Ls[st], Ls[st]));
-        GemmArgs g{};
-        g.A = acts[st]; g.lda = D; g.W = n.w(W_QKV[st], b); g.ldw = n.ld(W_QKV[st]); g.bias = n.w(B_QKV[st], b);
-        g.M = rows[st]; g.N = 3 * D; g.K = D; g.outb = qk; g.ldob = 2 * D; g.vt = vt; g.v_start = 2 * D; g.Lpad = Lpad;
-        g.L = Ls[st]; g.Lout = L; g.tok_off = toff[st];
+        g[st] = GemmArgs{};
+        g[st].A = acts[st]; g[st].lda = D; g[st].W = n.w(W_QKV[st], b); g[st].ldw = n.ld(W_QKV[st]); g[st].bias = n.w(B_QKV[st], b);
+        g[st].M = rows[st]; g[st].N = 3 * D; g[st].K = D; g[st].outb = qk; g[st].ldob = 2 * D; g[st].vt = vt; g[st].v_start = 2 * D;
+        g[st].Lpad = Lpad; g[st].L = Ls[st]; g[st].Lout = L; g[st].tok_off = toff[st];
         // queries and keys leave the projection RMS-normalised per head, queries also in the softmax's log2 units
-        g.norm_hd = hd; g.qn_g = n.w(W_QN[st], b); g.kn_g = n.w(W_KN[st], b);
-        g.out_scale = scale_log2; g.scale_cols = D;
-        PG_TRY(launch_gemm(g, EPI_QKV, s));
+        g[st].norm_hd = hd; g[st].qn_g = n.w(W_QN[st], b); g[st].kn_g = n.w(W_KN[st], b);
+        g[st].out_scale = scale_log2; g[st].scale_cols = D;
       }
+      PG_TRY(launch_gemm_pair(g[0], g[1], EPI_QKV, s));
       AttnArgs a{};
       a.q = qk; a.ldq = 2 * D; a.k = qk + D; a.ldk = 2 * D; a.k_bstride = (int64_t)L * 2 * D;
       a.vt = vt; a.vt_bstride = (int64_t)D * Lpad; a.Lkpad = Lpad; a.out = atts[0]; a.ldo = D;
       a.split = Li; a.out2 = atts[1];
       a.B = M; a.Lq = L; a.Lk = L; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1;
       PG_TRY(launch_attention(a, hd, s));
+      // the layers that add into the residual stream: `gate` is the slot of their gates among the modulation vectors
+      auto residual = [&](uint16_t* const* in, int K, const int* W, const int* B, int gate) -> pg_status {
+        for (int st = 0; st < 2; ++st) {
+          g[st] = GemmArgs{};
+          g[st].A = in[st]; g[st].lda = K; g[st].W = n.w(W[st], b); g[st].ldw = n.ld(W[st]); g[st].bias = n.w(B[st], b);
+          g[st].M = rows[st]; g[st].N = D; g[st].K = K; g[st].outf = hs[st]; g[st].ldo = D; g[st].L = Ls[st];
+          g[st].gate = mbs[st] + gate * D; g[st].gate_ld = mod_ld; g[st].group_of = group_of;
+        }
+        return launch_gemm_pair(g[0], g[1], EPI_RESID, s);
+      };
+      PG_TRY(residual(atts, D, W_O, B_O, 2));
+      PG_TRY(layer_norm_pair(mbs, 3));
       for (int st = 0; st < 2; ++st) {
-        GemmArgs o{};
-        o.A = atts[st]; o.lda = D; o.W = n.w(W_O[st], b); o.ldw = n.ld(W_O[st]); o.bias = n.w(B_O[st], b);
-        o.M = rows[st]; o.N = D; o.K = D; o.outf = hs[st]; o.ldo = D; o.L = Ls[st]; o.gate = mbs[st] + 2 * D;
-        o.gate_ld = mod_ld; o.group_of = group_of;
-        PG_TRY(launch_gemm(o, EPI_RESID, s));
-        PG_TRY(ln(hs[st], acts[st], mbs[st] + 3 * D, mbs[st] + 4 * D, mod_ld, rows[st], Ls[st], Ls[st]));
-        GemmArgs g{};
-        g.A = acts[st]; g.lda = D; g.W = n.w(W_FC1[st], b); g.ldw = n.ld(W_FC1[st]); g.bias = n.w(B_FC1[st], b);
-        g.M = rows[st]; g.N = 4 * D; g.K = D; g.outb = hids[st]; g.ldob = 4 * D;
-        PG_TRY(launch_gemm(g, EPI_GELU, s));
-        GemmArgs o2{};
-        o2.A = hids[st]; o2.lda = 4 * D; o2.W = n.w(W_FC2[st], b); o2.ldw = n.ld(W_FC2[st]); o2.bias = n.w(B_FC2[st], b);
-        o2.M = rows[st]; o2.N = D; o2.K = 4 * D; o2.outf = hs[st]; o2.ldo = D; o2.L = Ls[st]; o2.gate = mbs[st] + 5 * D;
-        o2.gate_ld = mod_ld; o2.group_of = group_of;
-        PG_TRY(launch_gemm(o2, EPI_RESID, s));
+        g[st] = GemmArgs{};
+        g[st].A = acts[st]; g[st].lda = D; g[st].W = n.w(W_FC1[st], b); g[st].ldw = n.ld(W_FC1[st]); g[st].bias = n.w(B_FC1[st], b);
+        g[st].M = rows[st]; g[st].N = 4 * D; g[st].K = D; g[st].outb = hids[st]; g[st].ldob = 4 * D;
       }
+      PG_TRY(launch_gemm_pair(g[0], g[1], EPI_GELU, s));
+      PG_TRY(residual(hids, 4 * D, W_FC2, B_FC2, 5));
     }
   }
 

@@ -110,30 +110,37 @@ __device__ __forceinline__ void for_row_groups(F&& f) {
   }
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE>
-__global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmArgs a) {
+// NP = 2: two problems of equal N and K in one launch, the tile rows of the second behind those of the first
+template <int NP> struct GemmBatch { GemmArgs g[NP]; };
+
+template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE, int NPROB>
+__global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatch<NPROB> batch) {
   constexpr int WAVES = WM * WN;
   constexpr int CW = BN / WN, FM = BM / WM / MI, FN = CW / MI, FR = FM + FN, MF = FM * FN;   // columns, fragments, MFMAs of a wave
   static_assert(CW == 32 || CW == 64, "the epilogue handles 32 or 64 columns per wave");
   static_assert((BM / WM) % MI == 0 && (BM / WM) % 8 == 0, "wave rows");
   constexpr int A_BYTES = BM * BK * 2, W_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + W_BYTES;
   extern __shared__ __align__(16) unsigned char smem[];
+  const int per_xcd = gridDim.x / XCDS;
+  const int b = (blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS;
+  // ---- which output tile: XCD-aware, banded raster ----
+  const int rows0 = (batch.g[0].M + BM - 1) / BM;
+  const int tiles_m = rows0 + (NPROB > 1 ? (batch.g[NPROB - 1].M + BM - 1) / BM : 0), tiles_n = (batch.g[0].N + BN - 1) / BN;
+  const int total = tiles_m * tiles_n;
+  if (b >= total) return;
+  const int group_m = batch.g[0].group_m;
+  const int band = group_m * tiles_n;
+  const int first_m = (b / band) * group_m;
+  const int gsz = min(tiles_m - first_m, group_m);
+  const int tm = first_m + (b % band) % gsz;
+  const int tn = (b % band) / gsz;
+  const bool second = NPROB > 1 && tm >= rows0;
+  const GemmArgs& a = batch.g[second ? NPROB - 1 : 0];
+  const int m0 = (second ? tm - rows0 : tm) * BM, n0 = tn * BN;
   const uint16_t* PA = a.A; const int64_t LDA = a.lda;
   const uint16_t* PW = a.W; const int64_t LDW = a.ldw;
   const uint16_t* PB = a.bias;
   const int MM = a.M, NN = a.N;
-  const int per_xcd = gridDim.x / XCDS;
-  const int b = (blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS;
-  // ---- which output tile: XCD-aware, banded raster ----
-  const int tiles_m = (MM + BM - 1) / BM, tiles_n = (NN + BN - 1) / BN;
-  const int total = tiles_m * tiles_n;
-  if (b >= total) return;
-  const int band = a.group_m * tiles_n;
-  const int first_m = (b / band) * a.group_m;
-  const int gsz = min(tiles_m - first_m, a.group_m);
-  const int tm = first_m + (b % band) % gsz;
-  const int tn = (b % band) / gsz;
-  const int m0 = tm * BM, n0 = tn * BN;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
@@ -470,18 +477,20 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmArgs
   }
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE = false>
-static pg_status launch_tile(const GemmArgs& a, hipStream_t s) {
+template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE = false, int NPROB>
+static pg_status launch_tile(const GemmBatch<NPROB>& batch, hipStream_t s) {
   constexpr int LDS = 2 * (BM + BN) * BK * 2;
   static bool attr_set = false;
   if (!attr_set) {
-    PG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_kernel<EPI, BM, BN, WM, WN, MINW, WIDE>),
+    PG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_kernel<EPI, BM, BN, WM, WN, MINW, WIDE, NPROB>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
     attr_set = true;
   }
-  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+  int tiles_m = 0;
+  for (const GemmArgs& g : batch.g) tiles_m += (g.M + BM - 1) / BM;
+  const int tiles = tiles_m * ((batch.g[0].N + BN - 1) / BN);
   const int grid = (tiles + XCDS - 1) / XCDS * XCDS;
-  gemm_kernel<EPI, BM, BN, WM, WN, MINW, WIDE><<<dim3(grid), dim3(64 * WM * WN), LDS, s>>>(a);
+  gemm_kernel<EPI, BM, BN, WM, WN, MINW, WIDE, NPROB><<<dim3(grid), dim3(64 * WM * WN), LDS, s>>>(batch);
   PG_LAUNCH_CHECK("gemm_kernel");
   return PG_OK;
 }
@@ -504,7 +513,9 @@ constexpr TileShape TILES[7] = {
     {256, 256, 0.00553 * 320, 0.00304 * 320}, {192, 256, 0.00553 * 256, 0.00304 * 256},
     {128, 128, 0.52, 0.36}, {160, 256, 0.00553 * 224, 0.00304 * 224}, {224, 256, 0.00553 * 288, 0.00304 * 288},
     {128, 64, 0.30, 0.28}, {64, 64, 0.18, 0.18}};
-static int pick_tile(const GemmArgs& a, int epilogue) {
+template <int NPROB>
+static int pick_tile(const GemmBatch<NPROB>& batch, int epilogue) {
+  const GemmArgs& a = batch.g[0];
   const double nk = a.K / BK, edge = epilogue == EPI_RESID ? 12.0 : 4.0;
   const bool whole_heads = epilogue == EPI_QKV && a.norm_hd > 32;   // the fused norm needs a whole head inside one wave's columns
   int best = 0;
@@ -512,7 +523,9 @@ static int pick_tile(const GemmArgs& a, int epilogue) {
   for (int i = 0; i < 7; ++i) {
     const TileShape& t = TILES[i];
     if (whole_heads && t.bm == 64) continue;      // 32 columns per wave
-    const double load = ceil((double)a.M / t.bm) * ceil((double)a.N / t.bn) / 256.0;
+    double tile_rows = 0.0;
+    for (const GemmArgs& g : batch.g) tile_rows += ceil((double)g.M / t.bm);
+    const double load = tile_rows * ceil((double)a.N / t.bn) / 256.0;
     const double w = load <= 1.0 ? 1.0 : 0.5 * (load + ceil(load));
     const double full = t.bm == 128 && t.bn == 128 && load <= 1.0 ? 0.64 : t.full;
     const double step = t.idle + (full - t.idle) * fmin(1.0, load / 0.75);
@@ -522,27 +535,24 @@ static int pick_tile(const GemmArgs& a, int epilogue) {
   return best;
 }
 
-template <int EPI>
-static pg_status launch_one(const GemmArgs& a, hipStream_t s) {
+template <int EPI, int NPROB>
+static pg_status launch_one(const GemmBatch<NPROB>& batch, hipStream_t s) {
   // operand rows so far apart that their byte offsets inside a tile need 64 bits (pg_gemm_bf16 alone takes any)
-  if (EPI == EPI_F32 && (a.lda > NARROW_LD || a.ldw > NARROW_LD)) return launch_tile<EPI_F32, 128, 128, 2, 2, 2, true>(a, s);
-  switch (pick_tile(a, EPI)) {
-    case 0: return launch_tile<EPI, 256, 256, 2, 4, 2>(a, s);
-    case 1: return launch_tile<EPI, 192, 256, 2, 4, 2>(a, s);
-    case 2: return launch_tile<EPI, 128, 128, 2, 2, 2>(a, s);
-    case 3: return launch_tile<EPI, 160, 256, 2, 4, 2>(a, s);
-    case 4: return launch_tile<EPI, 224, 256, 2, 4, 2>(a, s);
-    case 5: return launch_tile<EPI, 128, 64, 4, 1, 3>(a, s);
-    default: return launch_tile<EPI, 64, 64, 2, 2, 4>(a, s);
+  if constexpr (EPI == EPI_F32)
+    if (batch.g[0].lda > NARROW_LD || batch.g[0].ldw > NARROW_LD) return launch_tile<EPI_F32, 128, 128, 2, 2, 2, true>(batch, s);
+  switch (pick_tile(batch, EPI)) {
+    case 0: return launch_tile<EPI, 256, 256, 2, 4, 2>(batch, s);
+    case 1: return launch_tile<EPI, 192, 256, 2, 4, 2>(batch, s);
+    case 2: return launch_tile<EPI, 128, 128, 2, 2, 2>(batch, s);
+    case 3: return launch_tile<EPI, 160, 256, 2, 4, 2>(batch, s);
+    case 4: return launch_tile<EPI, 224, 256, 2, 4, 2>(batch, s);
+    case 5: return launch_tile<EPI, 128, 64, 4, 1, 3>(batch, s);
+    default: return launch_tile<EPI, 64, 64, 2, 2, 4>(batch, s);
   }
 }
 
-pg_status launch_gemm(const GemmArgs& a_in, int epilogue, hipStream_t s) {
-  GemmArgs a = a_in;
-  // bands of 8 tile rows; of 4 when the output is at most six tiles wide (the D-wide residual GEMMs of the 1536-wide network:
-  // a band then still spans the whole width, and 0.7 % of the loop's GEMM time goes away)
-  a.group_m = (a.N + 255) / 256 <= 6 ? GROUP_M / 2 : GROUP_M;
-  if (a.M <= 0 || a.N <= 0) return PG_OK;
+// what the kernels assume of one problem
+static pg_status check_gemm(const GemmArgs& a, int epilogue) {
   if (a.K <= 0 || a.K % 64) return fail(PG_ESHAPE, "GEMM K = %d must be a positive multiple of 64", a.K);
   if (a.lda % 8 || a.ldw % 8 || a.lda < a.K || a.ldw < a.K || ((uintptr_t)a.A & 15) || ((uintptr_t)a.W & 15))
     return fail(PG_ESHAPE, "GEMM operands need 16-byte aligned rows (lda %lld, ldw %lld)", (long long)a.lda, (long long)a.ldw);
@@ -567,17 +577,54 @@ pg_status launch_gemm(const GemmArgs& a_in, int epilogue, hipStream_t s) {
         (a.N - vs) % 32 || !a.outb)
       return fail(PG_ESHAPE, "GEMM: bad transposed-value output (L %d, Lpad %d, v_start %d)", a.L, a.Lpad, a.v_start);
   }
-  const int rec = prof_open(PROF_GEMM, 2.0 * a.M * (double)a.N * (a.k_algo > 0 ? a.k_algo : a.K), s);
+  return PG_OK;
+}
+
+// bands of 8 tile rows; of 4 when the output is at most six tiles wide (the D-wide residual GEMMs of the 1536-wide network:
+// a band then still spans the whole width, and 0.7 % of the loop's GEMM time goes away)
+static int raster_band(int N) { return (N + 255) / 256 <= 6 ? GROUP_M / 2 : GROUP_M; }
+static double gemm_flops(const GemmArgs& a) { return 2.0 * a.M * (double)a.N * (a.k_algo > 0 ? a.k_algo : a.K); }
+
+pg_status launch_gemm(const GemmArgs& a_in, int epilogue, hipStream_t s) {
+  GemmBatch<1> batch{{a_in}};
+  GemmArgs& a = batch.g[0];
+  a.group_m = raster_band(a.N);
+  if (a.M <= 0 || a.N <= 0) return PG_OK;
+  PG_TRY(check_gemm(a, epilogue));
+  const int rec = prof_open(PROF_GEMM, gemm_flops(a), s);
   pg_status st = PG_EINVAL;
   switch (epilogue) {
-    case EPI_F32: st = launch_one<EPI_F32>(a, s); break;
-    case EPI_EMBED: st = launch_one<EPI_EMBED>(a, s); break;
-    case EPI_BF16: st = launch_one<EPI_BF16>(a, s); break;
-    case EPI_QKV: st = launch_one<EPI_QKV>(a, s); break;
-    case EPI_GELU: st = launch_one<EPI_GELU>(a, s); break;
-    case EPI_RESID: st = launch_one<EPI_RESID>(a, s); break;
-    case EPI_UNPATCH: st = launch_one<EPI_UNPATCH>(a, s); break;
+    case EPI_F32: st = launch_one<EPI_F32>(batch, s); break;
+    case EPI_EMBED: st = launch_one<EPI_EMBED>(batch, s); break;
+    case EPI_BF16: st = launch_one<EPI_BF16>(batch, s); break;
+    case EPI_QKV: st = launch_one<EPI_QKV>(batch, s); break;
+    case EPI_GELU: st = launch_one<EPI_GELU>(batch, s); break;
+    case EPI_RESID: st = launch_one<EPI_RESID>(batch, s); break;
+    case EPI_UNPATCH: st = launch_one<EPI_UNPATCH>(batch, s); break;
     default: st = fail(PG_EINVAL, "unknown GEMM epilogue %d", epilogue);
+  }
+  prof_close(rec, s);
+  return st;
+}
+
+// Two problems of equal N and K (the same layer of the two streams of the dual-stream network) in one launch: the context
+// stream alone is a few dozen tiles, which left most of the 256 compute units idle for as long as the image stream's tiles take.
+pg_status launch_gemm_pair(const GemmArgs& first, const GemmArgs& second, int epilogue, hipStream_t s) {
+  if (first.M <= 0 || second.M <= 0) return launch_gemm(first.M > 0 ? first : second, epilogue, s);
+  if (first.N != second.N || first.K != second.K) return fail(PG_EINVAL, "GEMM pair: different layers");
+  GemmBatch<2> batch{{first, second}};
+  for (GemmArgs& g : batch.g) {
+    PG_TRY(check_gemm(g, epilogue));
+    if (g.lda > NARROW_LD || g.ldw > NARROW_LD) return fail(PG_ESHAPE, "GEMM pair: operand rows too far apart");
+    g.group_m = raster_band(g.N);
+  }
+  const int rec = prof_open(PROF_GEMM, gemm_flops(first) + gemm_flops(second), s);
+  pg_status st = PG_EINVAL;
+  switch (epilogue) {
+    case EPI_QKV: st = launch_one<EPI_QKV>(batch, s); break;
+    case EPI_GELU: st = launch_one<EPI_GELU>(batch, s); break;
+    case EPI_RESID: st = launch_one<EPI_RESID>(batch, s); break;
+    default: st = fail(PG_EINVAL, "GEMM pair: epilogue %d", epilogue);
   }
   prof_close(rec, s);
   return st;

@@ -36,5 +36,7 @@ struct GemmArgs {
 };
 
 pg_status launch_gemm(const GemmArgs& a, int epilogue, hipStream_t s);
+// two problems of equal N and K in one launch (EPI_QKV, EPI_GELU, EPI_RESID)
+pg_status launch_gemm_pair(const GemmArgs& first, const GemmArgs& second, int epilogue, hipStream_t s);
 
 }  // namespace pg
