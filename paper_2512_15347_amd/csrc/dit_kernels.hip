@@ -450,7 +450,7 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
       a.q = qk; a.ldq = 2 * D; a.k = qk + D; a.ldk = 2 * D; a.k_bstride = (int64_t)L * 2 * D;
       a.vt = vt; a.vt_bstride = (int64_t)D * Lpad; a.Lkpad = Lpad; a.out = atts[0]; a.ldo = D;
       a.split = Li; a.out2 = atts[1];
-      a.B = M; a.Lq = L; a.Lk = L; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1;
+      a.B = M; a.Lq = L; a.Lk = L; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1; a.v_swapped = 1;
       PG_TRY(launch_attention(a, hd, s));
       // the layers that add into the residual stream: `gate` is the slot of their gates among the modulation vectors
       auto residual = [&](uint16_t* const* in, int K, const int* W, const int* B, int gate) -> pg_status {
@@ -487,7 +487,7 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
       AttnArgs a{};
       a.q = qk; a.ldq = 2 * D; a.k = qk + D; a.ldk = 2 * D; a.k_bstride = (int64_t)L * 2 * D;
       a.vt = vt; a.vt_bstride = (int64_t)D * Lpad; a.Lkpad = Lpad; a.out = att; a.ldo = D;
-      a.B = M; a.Lq = L; a.Lk = L; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1;
+      a.B = M; a.Lq = L; a.Lk = L; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1; a.v_swapped = 1;
       PG_TRY(launch_attention(a, hd, s));
       GemmArgs o{};
       o.A = att; o.lda = D; o.W = n.w(PG_W_O_W, b); o.ldw = n.ld(PG_W_O_W); o.bias = n.w(PG_W_O_B, b);
@@ -508,7 +508,7 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
       a.k = n.at<uint16_t>(pl.ckv) + (size_t)b * P * f.Lc * D; a.ldk = D; a.k_bstride = (int64_t)f.Lc * D;
       a.vt = n.at<uint16_t>(pl.ckvt) + (size_t)b * P * D * Lcpad; a.vt_bstride = (int64_t)D * Lcpad; a.Lkpad = Lcpad;
       a.out = att; a.ldo = D; a.kv_map = group_of;
-      a.B = M; a.Lq = L; a.Lk = f.Lc; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1;
+      a.B = M; a.Lq = L; a.Lk = f.Lc; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1; a.v_swapped = 1;
       PG_TRY(launch_attention(a, hd, s));
       GemmArgs o{};
       o.A = att; o.lda = D; o.W = n.w(PG_W_CO_W, b); o.ldw = n.ld(PG_W_CO_W); o.bias = n.w(PG_W_CO_B, b);

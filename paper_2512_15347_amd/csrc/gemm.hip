@@ -90,6 +90,11 @@ __device__ __forceinline__ uint2 pack_bf16x4(float4 v) {
   return r;
 }
 
+// Where token t of a transposed value row is stored: in every 16 tokens the second and third group of four change places,
+// which puts the eight tokens that a lane of the attention kernel multiplies at a time (4 h .. 4 h + 3 and 8 + 4 h .. 8 + 4 h + 3,
+// the order in which the score accumulators hold the keys) into one 16-byte chunk.
+__device__ __forceinline__ int value_slot(int t) { return (t & ~12) | ((t & 4) << 1) | ((t & 8) >> 1); }
+
 // orders this wave's LDS accesses around a hand-over between its lanes (LDS serves one wave's accesses in issue order;
 // this keeps the compiler from moving them across the hand-over)
 __device__ __forceinline__ void wave_lds_sync() {
@@ -186,21 +191,17 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
     // fragment addresses: 16 rows further down only add a constant, so one base per operand and slab serves all of them
     constexpr int SLABS = BK / KS;
     static_assert(SLABS == 2, "fragment buffers alternate per slab");
-    int pa[SLABS], pw[SLABS];
-#pragma unroll
-    for (int ks = 0; ks < SLABS; ++ks) {
-      pa[ks] = lds_off(wm * (BM / WM) + lr, ks * (KS / 8) + lk);
-      pw[ks] = A_BYTES + lds_off(wn * CW + lr, ks * (KS / 8) + lk);
-    }
+    const int pa0 = lds_off(wm * (BM / WM) + lr, lk), pa1 = lds_off(wm * (BM / WM) + lr, KS / 8 + lk);
+    const int pw0 = A_BYTES + lds_off(wn * CW + lr, lk), pw1 = A_BYTES + lds_off(wn * CW + lr, KS / 8 + lk);
     bf16x8 fr[2][FR];
     auto fetch = [&](int stage, int ks, int buf, int f) {
-      const int at = f < FN ? pw[ks] + f * MI * CH * 16 : pa[ks] + (f - FN) * MI * CH * 16;
+      const int at = f < FN ? (ks ? pw1 : pw0) + f * MI * CH * 16 : (ks ? pa1 : pa0) + (f - FN) * MI * CH * 16;
       fr[buf][f] = *reinterpret_cast<const bf16x8*>(smem + at + stage * STAGE_BYTES);
     };
     // One request after every EVERY-th MFMA and one fragment read after every FEV-th: a wave's request waits for the
     // texture path, which takes 1 KB every ~20 cycles, and in a burst the MFMAs queued behind it would wait too.
-    constexpr int FEV = MF / FR > 0 ? MF / FR : 1, EVERY = MF / PER_WAVE > 0 ? MF / PER_WAVE : 1;
-    static_assert(MF / FEV >= FR || MF < FR, "every fragment is read");
+    static_assert(MF >= FR && MF >= PER_WAVE, "every fragment and every request has an MFMA to follow");
+    constexpr int FEV = MF / FR, EVERY = MF / PER_WAVE;
     // K step kt.  At its last slab every read of its stage has been issued and awaited, so the barrier that publishes tile
     // kt+1 and frees the stage is passed before that slab's MFMAs; the first slab of tile kt+1 is read, and tile kt+2
     // requested (REQ), while they run.
@@ -216,33 +217,21 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
         const int stage = (last ? kt + 1 : kt) & 1, to = (ks + 1) & 1;
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(1);
-        int q = 0, fetched = 0, asked = 0;
+        int q = 0;
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
           for (int j = 0; j < FN; ++j) {
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[ks & 1][FN + i], fr[ks & 1][j], acc[i][j], 0, 0, 0);
-            // (the smallest tiles have fewer MFMAs than fragments or requests: what is left follows the last one)
-            const bool end = i == FM - 1 && j == FN - 1;
-            if (!last || NEXT) {
-#pragma unroll
-              for (int f = 0; f < FR; ++f)
-                if (f == fetched && ((f == q / FEV && q % FEV == 0) || end)) {
-                  __builtin_amdgcn_sched_barrier(0);
-                  fetch(stage, last ? 0 : ks + 1, to, f);
-                  __builtin_amdgcn_sched_barrier(0);
-                  ++fetched;
-                }
+            if ((!last || NEXT) && q % FEV == 0 && q / FEV < FR) {
+              __builtin_amdgcn_sched_barrier(0);
+              fetch(stage, last ? 0 : ks + 1, to, q / FEV);
+              __builtin_amdgcn_sched_barrier(0);
             }
-            if (REQ && last) {
-#pragma unroll
-              for (int f = 0; f < PER_WAVE; ++f)
-                if (f == asked && ((f == q / EVERY && q % EVERY == EVERY - 1) || end)) {
-                  __builtin_amdgcn_sched_barrier(0);
-                  request(f, kt + 2);
-                  __builtin_amdgcn_sched_barrier(0);
-                  ++asked;
-                }
+            if (REQ && last && q % EVERY == EVERY - 1 && q / EVERY < PER_WAVE) {
+              __builtin_amdgcn_sched_barrier(0);
+              request(q / EVERY, kt + 2);
+              __builtin_amdgcn_sched_barrier(0);
             }
             ++q;
           }
@@ -325,14 +314,13 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
             if (!mine || r >= MM) continue;
             const uint2 pk = *reinterpret_cast<const uint2*>(stg16 + cl * VP + t4);
             const int ch = col_w + cl - n_rm;
-            uint16_t* dst = a.vt + ((int64_t)traj0 * Dv + ch) * a.Lpad + a.tok_off + tok0;
-            if (whole) {
-              if (((uintptr_t)dst & 7) == 0) {
-                store_stream(dst, pk);
-              } else {
-                reinterpret_cast<uint32_t*>(dst)[0] = pk.x;
-                reinterpret_cast<uint32_t*>(dst)[1] = pk.y;
-              }
+            uint16_t* dst = a.vt + ((int64_t)traj0 * Dv + ch) * a.Lpad;
+            const int at = a.tok_off + tok0;
+            if (whole && (at & 3) == 0) {                                // one unit of four tokens
+              store_stream(dst + value_slot(at), pk);
+            } else if (whole) {                                        // two pairs: tok_off + tok0 is even
+              *reinterpret_cast<uint32_t*>(dst + value_slot(at)) = pk.x;
+              *reinterpret_cast<uint32_t*>(dst + value_slot(at + 2)) = pk.y;
             } else {
               const uint16_t e[4] = {(uint16_t)pk.x, (uint16_t)(pk.x >> 16), (uint16_t)pk.y, (uint16_t)(pk.y >> 16)};
               int traj = traj0, tok = tok0;
@@ -340,7 +328,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
               for (int k = 0; k < 4; ++k) {
                 if (r + k < MM) {
                   if (tok >= a.L) { tok -= a.L; ++traj; }
-                  a.vt[((int64_t)traj * Dv + ch) * a.Lpad + a.tok_off + tok] = e[k];
+                  a.vt[((int64_t)traj * Dv + ch) * a.Lpad + value_slot(a.tok_off + tok)] = e[k];
                   ++tok;
                 }
               }
@@ -573,7 +561,7 @@ static pg_status check_gemm(const GemmArgs& a, int epilogue) {
   }
   if (epilogue == EPI_QKV) {
     const int vs = a.v_start;
-    if (!a.vt || a.L < 1 || a.Lpad < a.L || (a.Lpad & 1) || ((uintptr_t)a.vt & 3) || vs < 0 || vs > a.N || vs % 32 ||
+    if (!a.vt || a.L < 1 || a.tok_off + a.L > a.Lpad || (a.Lpad & 15) || ((uintptr_t)a.vt & 7) || vs < 0 || vs > a.N || vs % 32 ||
         (a.N - vs) % 32 || !a.outb)
       return fail(PG_ESHAPE, "GEMM: bad transposed-value output (L %d, Lpad %d, v_start %d)", a.L, a.Lpad, a.v_start);
   }

@@ -231,6 +231,34 @@ def test_network_output_with_every_tile_height_of_the_projection(lib, P, N, tile
     lib.pg_destroy(ctx)
 
 
+# enough trajectories and tokens for the 64-queries-per-wave attention (four query tiles of 128 against two of 256, 1.67 rounds
+# against one): whole key tiles (484 + 28 tokens), a last tile that ends in its second (484 + 26) or first (462 + 18) half,
+# separate streams; query and key weights scaled until later scores pass the reference that the first tile set
+@pytest.mark.parametrize("kind,W,Lc,gain", [("joint", 44, 28, 1.0), ("joint", 42, 18, 7.0), ("joint", 44, 26, 1.0), ("mmdit", 42, 26, 1.0)])
+def test_network_output_with_wide_attention(lib, kind, W, Lc, gain):
+    from oracle import dit
+    say(f"wide attention {kind} W={W} Lc={Lc} gain={gain}")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind=kind, N=64, H=44, W=W, D=256, heads=4, Lc=Lc, Dc=256, blocks=1, T=1, schedule=[[]], Li=11 * W, d=4 * 44 * W)
+    w = workloads.make_weights(cfg)
+    if gain != 1.0:
+        w["blocks"][0]["qkv_w"][:512] = workloads.bf16_round(w["blocks"][0]["qkv_w"][:512] * np.float32(gain))
+    inp = workloads.make_inputs(cfg, w)
+    tables = sampler.flow_sde_tables(1, 0.7)
+    c, keep = lib.make_config(cfg, probe_bias=inp["probe_b"])
+    ctx = lib.pg_create(c)
+    buf = lib.Buffers(ctx, cfg, inputs=inp, weights_flat=lib.pack_weights(ctx, cfg, w))
+    lib.pg_bind(ctx, buf)
+    lib.pg_init_group(ctx, 77)
+    lib.pg_net_forward(ctx, 0)
+    got = buf.u.cpu().numpy().astype(np.float64)
+    x = buf.x[0].cpu().numpy().astype(np.float64)
+    for i in (0, 63):
+        want = dit.forward(w, cfg, x[i][None], tables["t_in"][0], inp["y"][0], inp["ctx"][0])[0]
+        assert np.max(np.abs(got[i] - want)) < 2e-2 * np.max(np.abs(want)), i
+    lib.pg_destroy(ctx)
+
+
 @pytest.mark.parametrize("name", ["cfg1", "cfg2_small", "cfg3_small", "cfg4_small", "cfg3_mmdit_small"])
 def test_full_loop_with_own_network(lib, name):
     """Free-running library loop against the free-running oracle: the survivor sets must be the
