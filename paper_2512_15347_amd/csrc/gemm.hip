@@ -14,8 +14,9 @@
 // The chip draws its power limit here, so energy per flop and not issue slots decides: with the branch-free loop and raised
 // wave priority around the MFMAs the 16x16x32 instruction runs 56544 x 6144 x 1536 in 0.87 ms where 32x32x16 takes 0.93 ms
 // (0.99 ms with the fragment reads in a burst before the MFMAs and a test around every request, as it was before); the
-// smaller instruction also allows 16-row steps, so that every tile height keeps a 2 x 4 arrangement of waves.  Four waves
-// with 128 x 128 wave tiles: 1.05 ms (the compiler moves accumulators between register files inside the loop).
+// smaller instruction also allows 16-row steps, so that every tile height keeps a 2 x 4 arrangement of waves.  Four waves with
+// 128 x 128 wave tiles and accumulators in AGPRs read a third less from LDS, but one wave per SIMD exposes the epilogue:
+// 0.92 ms (0.855 against 0.872 ms at K = 6144, N = 1536).  Storing the accumulators without the pass through LDS: 1.03 ms.
 // Several tile shapes are instantiated (workgroup tile BM x BN x 64, WM x WN wavefronts); the launcher
 // picks one (pick_tile).
 #include <cmath>

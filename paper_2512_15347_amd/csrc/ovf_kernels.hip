@@ -205,7 +205,8 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
 
 // ---- many groups: one lane per group ----
 // The wave-per-group form needs about 400 wave instructions per group, most of them cross-lane traffic (an all-pairs rank and
-// four fp64 scans by shuffles); it is issue bound (2^20 groups of 64 -> 16: 1.2 ms, 3 % of the memory rate).  Here a lane
+// four fp64 scans by shuffles); it is issue bound (2^20 groups of 64 -> 16: 1.5 ms, 3 % of the memory rate; here 0.21 ms, bound by
+// issue at two waves per SIMD, 256 registers).  Here a lane
 // sorts its own group in registers by a compare-exchange network (Batcher's odd-even merge sort: 543 compare-exchanges for 64
 // slots, two instructions each, for 64 groups at once) and runs the scans of the same doubling recurrence on registers.
 // Only the values are sorted; members are picked afterwards by comparing them with the two threshold values, with
@@ -788,8 +789,10 @@ static pg_status sum_counts(const int32_t* k, int n_groups, int32_t* sums, hipSt
   return PG_OK;
 }
 
-// The stand-alone selection of groups of up to 64 members.  One lane per group from LANE_MIN_GROUPS groups on.
-constexpr int LANE_MIN_GROUPS = 32768;
+// The stand-alone selection of groups of up to 64 members.  One lane per group from LANE_MIN_GROUPS groups on, where enough
+// waves of 64 groups exist to pay for each one's 20 us: wave per group against lane per group, us per call, at 8192 groups
+// 15.5 / 21.0 (64 -> 16), 13.4 / 14.2 (24 -> 12), 13.0 / 10.9 (16 -> 4), at 16384 groups 24.4 / 21.2, 21.4 / 14.4, 20.8 / 11.2.
+constexpr int LANE_MIN_GROUPS = 16384;
 static pg_status select_groups(const float* rewards, const int32_t* offsets, const int32_t* k, int n_groups, int32_t* sums,
                                int32_t* new_offsets, uint64_t* masks, int32_t* sel_idx, int32_t* status, hipStream_t s) {
   PG_TRY(sum_counts(k, n_groups, sums, s));
