@@ -284,11 +284,11 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(const AttnArg
 // nothing): a key tile is a chain of LDS reads, scores, exponentials and value products between two barriers, which three
 // waves per SIMD do not hide.  Here a wave owns two blocks of 32 queries, A and B: key and value operands are read from LDS once
 // for both, V P_A runs beside the exponentials of B, and keys and values go straight from global memory into one of two LDS
-// stages with one barrier per tile.  The softmax reference of a query (m_run) is only raised when a lane's probabilities
-// of a tile sum to more than 2^13 (the sum is needed anyway; no single one can then have been above the 2^8 that the kernel
-// above allows by more than 2^5), so a tile has no maximum; the first tile, which sets the reference, the masked last one and
-// a tile that raises it take the general route, one block of queries at a time.  48 x 24 heads x 1178 tokens: 563 us with the
-// kernel above on values in natural order, 547 with it on swapped ones, 519 here.
+// stages with one barrier per tile.  The softmax reference of a query (m_run) is raised by the rule of the kernel above, block
+// by block of 32 queries, so that a query's result does not depend on which of the two a batch size selects: bit for bit the
+// same.  A tile forms its maximum beside the exponentials instead of before them (no cost: 537 to 543 us for 48 x 24 heads x
+// 1178 tokens, 544 to 547 when the sum of the probabilities was tested instead); the first tile, which sets the reference, the
+// masked last one and a tile that raises it take the general route, one block of queries at a time.
 constexpr int WQ = 64, WIDE_QTILE = 4 * WQ;      // queries per wave, per workgroup
 constexpr int WIDE_STAGE = 2 * KTILE * 64 * 2;   // keys [64][64] and values [64][64] of one tile
 
@@ -394,6 +394,15 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_wide_kernel(const At
       }
     return psum;
   };
+  // whether a score of the block lies more than 2^8 above its query's reference
+  auto passes_reference = [&](const f32x16 (&s)[2]) {
+    float mx = s[0][0];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[t][e]);
+    return __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0ull;
+  };
   auto value_frag = [&](const unsigned char* st, int t, int jj, int ot) {
     const int g = 2 * t + jj;
     return *reinterpret_cast<const bf16x8*>(st + (ot ? va[g ^ 2] + 4096 : va[g]));
@@ -462,8 +471,9 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_wide_kernel(const At
       }
     }
     const float suma = probabilities(sa, pa);
+    const bool raise_a = passes_reference(sa);
     __builtin_amdgcn_sched_barrier(0);
-    if (__builtin_amdgcn_ballot_w64(suma > 8192.0f) != 0ull) return 2;
+    if (raise_a) return 2;
     l_run[0] += suma;
     // V P_A beside exp_B
     bf16x8 vf[2][2][OT];
@@ -477,8 +487,9 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_wide_kernel(const At
           o[0][ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][jj][ot], pa[t][jj], o[0][ot], 0, 0, 0);
         }
     const float sumb = probabilities(sb, pb);
+    const bool raise_b = passes_reference(sb);
     __builtin_amdgcn_sched_barrier(0);
-    if (__builtin_amdgcn_ballot_w64(sumb > 8192.0f) != 0ull) return 1;
+    if (raise_b) return 1;
     l_run[1] += sumb;
 #pragma unroll
     for (int t = 0; t < 2; ++t)

@@ -259,6 +259,34 @@ def test_network_output_with_wide_attention(lib, kind, W, Lc, gain):
     lib.pg_destroy(ctx)
 
 
+@pytest.mark.parametrize("kind", ["joint", "mmdit"])
+def test_network_output_of_a_trajectory_does_not_depend_on_the_batch(lib, kind):
+    """64 trajectories of 480 tokens take the attention with 64 queries per wave, 48 and 5 the one with 32: the same bits,
+    also where scores pass the reference that a query's first key tile set (query and key scales of 8)."""
+    say(f"batch independence {kind}")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind=kind, H=44, W=42, D=256, heads=4, Lc=18, Dc=256, blocks=2, T=1, schedule=[[]], Li=22 * 21, d=4 * 44 * 42)
+    w = workloads.make_weights(cfg)
+    for blk in w["blocks"]:
+        if kind == "joint":
+            blk["qkv_w"][:512] *= 8
+        else:
+            for name in ("qn_g", "kn_g", "c_qn_g", "c_kn_g"):
+                blk[name] *= 8
+    inp = workloads.make_inputs(cfg, w)
+    u = {}
+    for N in (64, 48, 5):
+        cfg["N"] = N
+        ctx, buf = _gpu_ctx(lib, cfg, w, inp)
+        lib.pg_init_group(ctx, 9)
+        lib.pg_net_forward(ctx, 0)
+        u[N] = buf.u.cpu().numpy()
+        lib.pg_destroy(ctx)
+    assert np.isfinite(u[64]).all()
+    np.testing.assert_array_equal(u[64][:48], u[48])
+    np.testing.assert_array_equal(u[64][:5], u[5])
+
+
 @pytest.mark.parametrize("name", ["cfg1", "cfg2_small", "cfg3_small", "cfg4_small", "cfg3_mmdit_small"])
 def test_full_loop_with_own_network(lib, name):
     """Free-running library loop against the free-running oracle: the survivor sets must be the
