@@ -202,7 +202,8 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(const AttnArg
     mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
     if (kt == 0 || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0ull) {   // wave-uniform: rare after the first tile
       const float delta = kt == 0 ? mx : fmaxf(mx, 0.f);               // the first tile sets the reference
-      const float alpha = __builtin_amdgcn_exp2f(-delta);
+      // (which may lie so far below zero that 2^-delta is infinite; there is nothing to rescale yet)
+      const float alpha = kt == 0 ? 1.0f : __builtin_amdgcn_exp2f(-delta);
       m_run += delta;
       l_run *= alpha;
 #pragma unroll

@@ -96,3 +96,26 @@ def test_attention_matches_oracle(lib, B, Lq, Lk, heads, hd):
     # probabilities and outputs are rounded to bf16 (2^-9 relative)
     assert np.max(np.abs(got - want)) < 1.5e-2 * np.max(np.abs(want))
     assert np.sqrt(np.mean((got - want) ** 2)) < 4e-3 * np.sqrt(np.mean(want ** 2))
+
+
+@pytest.mark.parametrize("hd,Lk", [(64, 128), (64, 20), (32, 77)])
+def test_attention_with_every_score_far_below_zero(lib, hd, Lk):
+    """The first key tile sets a query's reference exponent; here it lies at -1000 or below, and 2^1000 has no fp32 value."""
+    say(f"attention far below zero hd={hd} Lk={Lk}")
+    rng = np.random.default_rng(hd + Lk)
+    B, Lq, heads = 1, 40, 2
+    D = heads * hd
+    q = workloads.bf16_round(8.0 + rng.standard_normal((B, Lq, D), dtype=np.float32) * 0.1)
+    k = workloads.bf16_round(-90.0 * (1.0 if hd == 64 else 1.5) / math.sqrt(hd) + rng.standard_normal((B, Lk, D), dtype=np.float32) * 0.05)
+    v = workloads.bf16_round(rng.standard_normal((B, Lk, D), dtype=np.float32))
+    Lkpad = (Lk + 63) // 64 * 64
+    vt = np.zeros((B, D, Lkpad), dtype=np.float32)
+    vt[:, :, :Lk] = v.transpose(0, 2, 1)
+    out = torch.zeros(B, Lq, D, dtype=torch.int16, device=DEV)
+    lib.pg_attention_bf16(bf16_dev(q), bf16_dev(k), bf16_dev(vt), out, B, Lq, Lk, heads, hd)
+    got = out.view(torch.bfloat16).float().cpu().numpy().astype(np.float64)
+    want = dit.attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), heads)
+    assert np.isfinite(got).all()
+    # rounding of the scaled queries to bf16 moves the output by 2e-3 of its maximum (the part common to all keys cancels), fp32
+    # scores of this size (ulp 1e-4) by less; probabilities and outputs are rounded to bf16
+    assert np.max(np.abs(got - want)) < 1.5e-2 * np.max(np.abs(want))
