@@ -102,29 +102,34 @@ __device__ __forceinline__ int place_group(const int32_t* __restrict__ kk, const
   return out0;
 }
 
-__global__ __launch_bounds__(SCAN_THREADS) void scan_block_sums_kernel(const int32_t* __restrict__ kk,
-                                                                       int n, int32_t* __restrict__ sums) {
-  __shared__ int part[SCAN_THREADS / WAVE];
+// sums[blk] = the counts of block blk, by a workgroup of SCAN_THREADS lanes
+__device__ __forceinline__ void sum_block_of_counts(const int32_t* __restrict__ kk, int n, int blk, int32_t* __restrict__ sums, int* part) {
   int s = 0;
-  const int base = blockIdx.x * SCAN_BLOCK + threadIdx.x;
+  const int base = blk * SCAN_BLOCK + threadIdx.x;
 #pragma unroll
   for (int i = 0; i < SCAN_ITEMS; ++i) if (base + i * SCAN_THREADS < n) s += counted_k(kk[base + i * SCAN_THREADS]);
   s = block_allsum<SCAN_THREADS>(s, part);
-  if (threadIdx.x == 0) sums[blockIdx.x] = s;
+  if (threadIdx.x == 0) sums[blk] = s;
+}
+__global__ __launch_bounds__(SCAN_THREADS) void scan_block_sums_kernel(const int32_t* __restrict__ kk,
+                                                                       int n, int32_t* __restrict__ sums) {
+  __shared__ int part[SCAN_THREADS / WAVE];
+  sum_block_of_counts(kk, n, blockIdx.x, sums, part);
 }
 
-// Optimal Variance Filtering of one group by one wavefront; `vals`, `sorted`: 64 floats of LDS of this wave.
-__device__ __forceinline__ void select_one_group(const float* __restrict__ rewards, int g, int b, int n, int k, int out0,
-                                                 float* vals, float* sorted, uint64_t* __restrict__ masks,
-                                                 int32_t* __restrict__ sel_idx, int32_t* __restrict__ status) {
+// a group that the selection cannot take (an empty group that keeps nothing is none: its mask is simply empty)
+__device__ __forceinline__ bool bad_group(int n, int k) { return (n < 1 || n > WAVE || k < 1 || k > n) && !(n == 0 && k == 0); }
+// the first k slots (1 <= k <= 64)
+__device__ __forceinline__ uint64_t first_slots(int k) { return k == WAVE ? ~0ull : (1ull << k) - 1ull; }
+
+// Optimal Variance Filtering of one group by one wavefront: the survivor mask, in every lane; `vals`, `sorted`: 64 floats of LDS
+// of this wave.
+__device__ __forceinline__ uint64_t survivors_by_wave(const float* __restrict__ rewards, int b, int n, int k, float* vals,
+                                                      float* sorted, int32_t* __restrict__ status) {
   const int lane = threadIdx.x & (WAVE - 1);
-  if (n < 1 || n > WAVE || k < 1 || k > n) {        // nothing to select: empty mask; flag unless the
-    if (lane == 0) {                                // group is simply empty (n = k = 0)
-      if (!(n == 0 && k == 0)) atomicOr(status, 2);
-      masks[g] = 0ull;
-    }
-    fill_bad_group(sel_idx, out0, b, n, k, lane, WAVE);
-    return;
+  if (n < 1 || n > WAVE || k < 1 || k > n) {        // nothing to select: empty mask
+    if (lane == 0 && bad_group(n, k)) atomicOr(status, 2);
+    return 0ull;
   }
   const bool live = lane < n;
   const float v = live ? rewards[b + lane] + 0.0f : 0.0f;  // -0.0 becomes +0.0
@@ -133,9 +138,7 @@ __device__ __forceinline__ void select_one_group(const float* __restrict__ rewar
     // k == n keeps everything; a non-finite reward is flagged and the first k slots are kept so
     // that every index written stays valid for the kernels that follow
     if (__ballot(bad) != 0ull && lane == 0) atomicOr(status, 1);
-    if (lane < k) sel_idx[out0 + lane] = b + lane;
-    if (lane == 0) masks[g] = (k == WAVE) ? ~0ull : ((1ull << k) - 1ull);
-    return;
+    return first_slots(k);
   }
   // rank under the strict order (value, slot): every value is read from LDS by all lanes at once, four at a time
   vals[lane] = live ? v : __builtin_huge_valf();
@@ -179,10 +182,7 @@ __device__ __forceinline__ void select_one_group(const float* __restrict__ rewar
     const int ob = __shfl_xor(best, o, WAVE);
     if (os > score || (os == score && ob < best)) { score = os; best = ob; }
   }
-  const bool keep = live && (rank < best || rank >= n - (k - best));
-  const uint64_t mask = __ballot(keep);
-  if (keep) sel_idx[out0 + __popcll(mask & ((1ull << lane) - 1ull))] = b + lane;
-  if (lane == 0) masks[g] = mask;
+  return __ballot(live && (rank < best || rank >= n - (k - best)));
 }
 
 template <int FROM>
@@ -193,14 +193,17 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
   __shared__ __align__(16) float vals[OVF_WAVES][WAVE];
   __shared__ float sorted[OVF_WAVES][WAVE];
   __shared__ int part[OVF_WAVES];
-  const int wv = threadIdx.x / WAVE;
+  const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
   const int g = blockIdx.x * OVF_WAVES + wv;
   const int out0 = place_group<FROM>(kk, sums, g, n_groups, new_offsets, part);
   if (g >= n_groups) return;                        // whole wave leaves together
   const int b = offsets[g];
   const int n = offsets[g + 1] - b;
   const int k = kk[g];
-  select_one_group(rewards, g, b, n, k, out0, vals[wv], sorted[wv], masks, sel_idx, status);
+  const uint64_t mask = survivors_by_wave(rewards, b, n, k, vals[wv], sorted[wv], status);
+  if (lane == 0) masks[g] = mask;
+  if (bad_group(n, k)) fill_bad_group(sel_idx, out0, b, n, k, lane, WAVE);
+  else if ((mask >> lane) & 1ull) sel_idx[out0 + __popcll(mask & ((1ull << lane) - 1ull))] = b + lane;
 }
 
 // ---- many groups: one lane per group ----
@@ -212,8 +215,10 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
 // Only the values are sorted; members are picked afterwards by comparing them with the two threshold values, with
 // ties at a threshold resolved by slot.  What a lane has to index by its own n and k (the descending order, the prefix
 // sums from the top) goes through LDS as [index][lane], so that every access is conflict free.
-// Takes a wave's 64 groups when all of them have 1..64 members, finite rewards and 1 <= k < n with k <= 32; any other
-// wave runs the wave-per-group code on its groups one after another.
+// A lane takes counts k <= 32 by that route, and everything that needs no sorting: k = n, an empty group, a group with a reward
+// that is not finite, a bad count.  Groups with 32 < k < n are the wave-per-group code's, in the launch that sums the counts
+// (counts_and_rest_kernel), which leaves their masks for the lanes to place; so are all 64 groups of a wave when one has a size
+// outside 0..64, because the wave's rewards are then no run that fits its LDS.
 constexpr int LANE_K = 32;                         // largest count of the register scans
 constexpr int LANE_ROW = WAVE * WAVE + 2 * WAVE;   // staged rewards of 64 groups: one float of padding per 64, and a margin
 constexpr int LANE_WAVES = 2;                      // waves per workgroup (33 KB of LDS)
@@ -380,72 +385,114 @@ __device__ __forceinline__ uint64_t select_lane(const float* __restrict__ reward
   return mask;
 }
 
-template <int FROM>
+// whether the wave-per-group code computes the mask of a group (n members, k kept; `odd`: of a wave with a size outside 0..64)
+__device__ __forceinline__ bool by_wave(int n, int k, bool odd) { return !bad_group(n, k) && (odd || (k > LANE_K && k < n)); }
+
+// The launch before ovf_select_lanes_kernel: the first `sum_blocks` workgroups sum blocks of counts; in the others a wave looks
+// at `per_wave` groups (a divisor of 64) and computes the masks of those that the lanes do not take.  Groups of that kind come
+// in whole batches (a schedule that keeps 40 of 64) as well as one here and there, so they are spread over as many waves as the
+// chip holds: in the wave that meets them, one after another, 16384 groups of 64 -> 40 took 234 us (here 33).
+__global__ __launch_bounds__(OVF_WAVES * WAVE) void counts_and_rest_kernel(
+    const float* __restrict__ rewards, const int32_t* __restrict__ offsets, const int32_t* __restrict__ kk, int n_groups,
+    int32_t* __restrict__ sums, int sum_blocks, int per_wave, uint64_t* __restrict__ masks, int32_t* __restrict__ status) {
+  __shared__ __align__(16) float vals[OVF_WAVES][WAVE];
+  __shared__ float sorted[OVF_WAVES][WAVE];
+  __shared__ int part[SCAN_THREADS / WAVE];
+  if ((int)blockIdx.x < sum_blocks) {
+    sum_block_of_counts(kk, n_groups, blockIdx.x, sums, part);
+    return;
+  }
+  const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+  const int64_t first = ((int64_t)(blockIdx.x - sum_blocks) * OVF_WAVES + wv) * per_wave;
+  if (first >= n_groups) return;
+  const int chunk = (int)(first / WAVE) * WAVE, g = chunk + lane;     // the 64 groups of one wave of the lane kernel
+  const bool have = g < n_groups;
+  const int k = have ? kk[g] : 0, b = have ? offsets[g] : 0, n = have ? offsets[g + 1] - b : 0;
+  const bool odd = __ballot(n < 0 || n > WAVE) != 0ull;
+  const int own = (int)first - chunk;
+  uint64_t left = __ballot(lane >= own && lane < own + per_wave && have && by_wave(n, k, odd));
+  for (; left; left &= left - 1ull) {
+    const int i = __builtin_ctzll(left);
+    const uint64_t mask = survivors_by_wave(rewards, __shfl(b, i, WAVE), __shfl(n, i, WAVE), __shfl(k, i, WAVE), vals[wv], sorted[wv],
+                                            status);
+    if (lane == 0) masks[chunk + i] = mask;
+  }
+}
+
 __global__ __launch_bounds__(LANE_WAVES * WAVE, 2) void ovf_select_lanes_kernel(
     const float* __restrict__ rewards, const int32_t* __restrict__ offsets, const int32_t* __restrict__ kk,
-    int n_groups, const int32_t* __restrict__ sums, int32_t* new_offsets, uint64_t* __restrict__ masks,
+    int n_groups, const int32_t* __restrict__ sums, int32_t* __restrict__ new_offsets, uint64_t* masks,
     int32_t* __restrict__ sel_idx, int32_t* __restrict__ status) {
   __shared__ __align__(16) float rows[LANE_WAVES][LANE_ROW];
   __shared__ int part[LANE_WAVES], wave_total[LANE_WAVES];
   const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
   const int g_wave = (blockIdx.x * LANE_WAVES + wv) * WAVE, g = g_wave + lane;
-  const int before = FROM == OFF_GIVEN ? 0 : counts_before<FROM, LANE_WAVES * WAVE>(kk, sums, blockIdx.x * LANE_WAVES * WAVE, part);
+  const int before = counts_before<OFF_SUMS, LANE_WAVES * WAVE>(kk, sums, blockIdx.x * LANE_WAVES * WAVE, part);
   const bool have = g < n_groups;
   const int k = have ? kk[g] : 0;
-  int out0 = 0;
-  if (FROM == OFF_GIVEN) {
-    out0 = have ? new_offsets[g] : 0;
-  } else {
-    int incl = counted_k(k);
+  int incl = counted_k(k);
 #pragma unroll
-    for (int dd = 1; dd < WAVE; dd <<= 1) {
-      const int t = __shfl_up(incl, dd, WAVE);
-      if (lane >= dd) incl += t;
-    }
-    if (lane == WAVE - 1) wave_total[wv] = incl;
-    __syncthreads();
-    out0 = before + incl - counted_k(k);
-    for (int w = 0; w < wv; ++w) out0 += wave_total[w];
-    if (have) {
-      new_offsets[g] = out0;
-      if (g == n_groups - 1) new_offsets[n_groups] = out0 + counted_k(k);
-    }
+  for (int dd = 1; dd < WAVE; dd <<= 1) {
+    const int t = __shfl_up(incl, dd, WAVE);
+    if (lane >= dd) incl += t;
+  }
+  if (lane == WAVE - 1) wave_total[wv] = incl;
+  __syncthreads();
+  int out0 = before + incl - counted_k(k);
+  for (int w = 0; w < wv; ++w) out0 += wave_total[w];
+  if (have) {
+    new_offsets[g] = out0;
+    if (g == n_groups - 1) new_offsets[n_groups] = out0 + counted_k(k);
   }
   if (g_wave >= n_groups) return;                   // no barrier of the workgroup follows
   const int b = have ? offsets[g] : 0;
   const int n = have ? offsets[g + 1] - b : 0;
   float* row = rows[wv];
   const int members = min(WAVE, n_groups - g_wave);
-  const int first = __shfl(b, 0, WAVE), last = __shfl(b + n, members - 1, WAVE);
-  const bool fits = !have || (n >= 1 && n <= WAVE && k >= 1 && k < n && k <= LANE_K);
-  bool lanes_ok = __ballot(!fits) == 0ull;
-  if (lanes_ok) {
-    lanes_ok = __ballot(stage_rewards(rewards, first, last - first, lane, row)) == 0ull;
+  const int first = __shfl(b, 0, WAVE), total = __shfl(b + n, members - 1, WAVE) - first;
+  const bool odd = __ballot(n < 0 || n > WAVE) != 0ull;
+  const bool bad = have && bad_group(n, k), given = have && by_wave(n, k, odd);
+  bool infinite = false;                             // the group holds a reward that is not finite
+  if (!odd) {
+    const bool some = __ballot(stage_rewards(rewards, first, total, lane, row)) != 0ull;
     lanes_sync();
+    if (some)
+      for (int i = 0; i < n; ++i) infinite = infinite || !(__builtin_fabsf(row[padded(b - first + i)]) <= 3.4028234663852886e38f);
   }
-  if (!lanes_ok) {                                   // wave-uniform
-    for (int i = 0; i < members; ++i)
-      select_one_group(rewards, g_wave + i, __shfl(b, i, WAVE), __shfl(n, i, WAVE), __shfl(k, i, WAVE), __shfl(out0, i, WAVE),
-                       row, row + WAVE, masks, sel_idx, status);
+  const bool sorts = !odd && have && !bad && !given && !infinite && k >= 1 && k < n;
+  const bool any = __ballot(sorts) != 0ull;
+  uint64_t mask = 0ull;
+  if (any) {
+    int n_max = sorts ? n : 0, k_max = sorts ? k : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      n_max = max(n_max, __shfl_xor(n_max, o, WAVE));
+      k_max = max(k_max, __shfl_xor(k_max, o, WAVE));
+    }
+    // lanes with nothing to sort work on the first rewards of the wave, and the result is not used
+    const int o = sorts ? b - first : 0, nn = sorts ? n : 2, kq = sorts ? k : 1;
+    if (n_max <= 16) mask = select_lane<16, 16>(rewards, first, total, o, nn, kq, lane, row);
+    else if (n_max <= 32) mask = k_max <= 16 ? select_lane<32, 16>(rewards, first, total, o, nn, kq, lane, row)
+                                             : select_lane<32, 32>(rewards, first, total, o, nn, kq, lane, row);
+    else mask = k_max <= 16 ? select_lane<64, 16>(rewards, first, total, o, nn, kq, lane, row)
+                            : select_lane<64, 32>(rewards, first, total, o, nn, kq, lane, row);
+  }
+  if (!sorts) mask = have && !bad && k >= 1 ? (given ? masks[g] : first_slots(k)) : 0ull;
+  if (have) masks[g] = mask;
+  const uint64_t bads = __ballot(bad);
+  const bool flag_infinite = __ballot(infinite && !bad) != 0ull;
+  if (lane == 0 && (bads != 0ull || flag_infinite)) atomicOr(status, (bads != 0ull ? 2 : 0) | (flag_infinite ? 1 : 0));
+  lanes_sync();
+  if (bads != 0ull) {
+    int at = out0;
+    for (uint64_t left = mask; left; left &= left - 1ull) sel_idx[at++] = b + __builtin_ctzll(left);
+    for (uint64_t left = bads; left; left &= left - 1ull) {
+      const int i = __builtin_ctzll(left);
+      fill_bad_group(sel_idx, __shfl(out0, i, WAVE), __shfl(b, i, WAVE), __shfl(n, i, WAVE), __shfl(k, i, WAVE), lane, WAVE);
+    }
     return;
   }
-  int n_max = have ? n : 0, k_max = have ? k : 0;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    n_max = max(n_max, __shfl_xor(n_max, o, WAVE));
-    k_max = max(k_max, __shfl_xor(k_max, o, WAVE));
-  }
-  // lanes past the last group work on the first one's rewards and store nothing
-  const int o = have ? b - first : 0, nn = have ? n : 2, kq = have ? k : 1;
-  uint64_t mask;
-  if (n_max <= 16) mask = select_lane<16, 16>(rewards, first, last - first, o, nn, kq, lane, row);
-  else if (n_max <= 32) mask = k_max <= 16 ? select_lane<32, 16>(rewards, first, last - first, o, nn, kq, lane, row)
-                                           : select_lane<32, 32>(rewards, first, last - first, o, nn, kq, lane, row);
-  else mask = k_max <= 16 ? select_lane<64, 16>(rewards, first, last - first, o, nn, kq, lane, row)
-                          : select_lane<64, 32>(rewards, first, last - first, o, nn, kq, lane, row);
-  if (!have) mask = 0ull;
-  if (have) masks[g] = mask;
-  // survivors of the wave are contiguous in sel_idx: packed in LDS first (at most 64 * 32), written out coalesced
+  // survivors of the wave are contiguous in sel_idx: packed in LDS first (at most 64 * 64), written out coalesced
   int* idx = reinterpret_cast<int*>(row);
   const int out_first = __shfl(out0, 0, WAVE), out_n = __shfl(out0 + k, members - 1, WAVE) - out_first;
   int at = out0 - out_first;
@@ -793,17 +840,31 @@ static pg_status sum_counts(const int32_t* k, int n_groups, int32_t* sums, hipSt
 // waves of 64 groups exist to pay for each one's 20 us: wave per group against lane per group, us per call, at 8192 groups
 // 15.5 / 21.0 (64 -> 16), 13.4 / 14.2 (24 -> 12), 13.0 / 10.9 (16 -> 4), at 16384 groups 24.4 / 21.2, 21.4 / 14.4, 20.8 / 11.2.
 constexpr int LANE_MIN_GROUPS = 16384;
+// Groups per wave of the rest, at least, and the waves that are enough to fill the chip where groups are many.  When all groups
+// are the rest's (64 -> 40), 8 / 4 / 2 a wave take 43.6 / 32.7 / 30.1 us at 16384 groups and 54 / 49 / 46 at 32768 (one wave per
+// group and no lanes: 38 and 62); when none is (16 -> 4 at 65536 groups) 13.8 / 14.3 / 14.3.
+constexpr int REST_GROUPS = 4, REST_WAVES = 16384;
 static pg_status select_groups(const float* rewards, const int32_t* offsets, const int32_t* k, int n_groups, int32_t* sums,
                                int32_t* new_offsets, uint64_t* masks, int32_t* sel_idx, int32_t* status, hipStream_t s) {
-  PG_TRY(sum_counts(k, n_groups, sums, s));
-  const dim3 per_wave((n_groups + OVF_WAVES - 1) / OVF_WAVES), block(OVF_WAVES * WAVE);
-  if (n_groups <= OFF_DIRECT_MAX)
-    ovf_select_kernel<OFF_DIRECT><<<per_wave, block, 0, s>>>(rewards, offsets, k, n_groups, sums, new_offsets, masks, sel_idx, status);
-  else if (n_groups < LANE_MIN_GROUPS)
-    ovf_select_kernel<OFF_SUMS><<<per_wave, block, 0, s>>>(rewards, offsets, k, n_groups, sums, new_offsets, masks, sel_idx, status);
-  else
-    ovf_select_lanes_kernel<OFF_SUMS><<<dim3((n_groups + LANE_WAVES * WAVE - 1) / (LANE_WAVES * WAVE)), dim3(LANE_WAVES * WAVE), 0, s>>>(
+  if (n_groups >= LANE_MIN_GROUPS) {
+    static_assert(SCAN_THREADS == OVF_WAVES * WAVE, "both parts of the first launch");
+    int per_wave = REST_GROUPS;
+    while (per_wave < WAVE && n_groups / per_wave > REST_WAVES) per_wave *= 2;
+    const int sum_blocks = (n_groups + SCAN_BLOCK - 1) / SCAN_BLOCK, per_block = OVF_WAVES * per_wave;
+    counts_and_rest_kernel<<<dim3(sum_blocks + (n_groups + per_block - 1) / per_block), dim3(SCAN_THREADS), 0, s>>>(
+        rewards, offsets, k, n_groups, sums, sum_blocks, per_wave, masks, status);
+    PG_LAUNCH_CHECK("counts_and_rest_kernel");
+    ovf_select_lanes_kernel<<<dim3((n_groups + LANE_WAVES * WAVE - 1) / (LANE_WAVES * WAVE)), dim3(LANE_WAVES * WAVE), 0, s>>>(
         rewards, offsets, k, n_groups, sums, new_offsets, masks, sel_idx, status);
+    PG_LAUNCH_CHECK("ovf_select_lanes_kernel");
+    return PG_OK;
+  }
+  PG_TRY(sum_counts(k, n_groups, sums, s));
+  const dim3 grid((n_groups + OVF_WAVES - 1) / OVF_WAVES), block(OVF_WAVES * WAVE);
+  if (n_groups <= OFF_DIRECT_MAX)
+    ovf_select_kernel<OFF_DIRECT><<<grid, block, 0, s>>>(rewards, offsets, k, n_groups, sums, new_offsets, masks, sel_idx, status);
+  else
+    ovf_select_kernel<OFF_SUMS><<<grid, block, 0, s>>>(rewards, offsets, k, n_groups, sums, new_offsets, masks, sel_idx, status);
   PG_LAUNCH_CHECK("ovf_select_kernel");
   return PG_OK;
 }

@@ -290,6 +290,89 @@ def test_ovf_one_lane_per_group(lib, lo, hi, kmax):
     np.testing.assert_array_equal(np.delete(masks, 70), np.delete(w_masks, 70))
 
 
+@pytest.mark.parametrize("sizes_of", ["proper", "any"])
+def test_ovf_one_lane_per_group_against_one_wave_per_group(lib, sizes_of):
+    """Groups that need no selection, keep more than 32, hold a reward that is not finite or have a bad count, mixed into one
+    call that is large enough for the one-lane-per-group kernel: what the calls below its threshold give, slice by slice.
+    `any`: some sizes lie outside 0..64 as well."""
+    say(f"ovf lanes against waves, {sizes_of} sizes")
+    G, part = 16384 + 333, 8000
+    rng = np.random.default_rng(31)
+    sizes = rng.integers(1, 65, G)
+    sizes[rng.random(G) < 0.05] = 0
+    ks = np.minimum(rng.integers(1, 33, G), sizes)
+    form = rng.integers(0, 60, G)
+    ks = np.where(form < 3, sizes, ks)                               # keeps all
+    ks = np.where((form == 3) & (sizes > 34), sizes - 1, ks)         # more than 32
+    ks[(form == 4) | (sizes == 0) & (form == 5)] = 3                 # bad where larger than the group
+    ks[form == 6] = 0
+    ks[form == 7] = -2
+    ks[form == 8] += 70
+    ks[2048:2048 + 640] = np.maximum(sizes[2048:2048 + 640] - 1, 0)  # whole waves that keep nearly all
+    ks[4096:4096 + 640] = sizes[4096:4096 + 640]
+    sizes[6400:6464], ks[6400:6464] = 0, 0                           # a wave of empty groups
+    if sizes_of == "any":
+        odd = rng.choice(G - 1, 40, replace=False) + 1
+        sizes[odd] = rng.integers(65, 200, 40)
+        sizes[odd - 1] = -5
+    off = np.concatenate([[300], 300 + np.cumsum(sizes)])
+    r = rng.standard_normal(int(off.max()) + 1).astype(np.float32)
+    r[rng.random(len(r)) < 2e-4] = np.nan
+    r[rng.random(len(r)) < 1e-4] = -np.inf
+    rd, od, kd = dev(r), dev(off.astype(np.int32)), dev(ks.astype(np.int32))
+
+    def select(first, last):
+        n = last - first
+        masks = torch.full((n,), -1, dtype=torch.int64, device=DEV)
+        sel = torch.full((int(np.maximum(ks[first:last], 0).sum()),), -1, dtype=torch.int32, device=DEV)
+        noff = torch.full((n + 1,), -1, dtype=torch.int32, device=DEV)
+        status = torch.zeros(4, dtype=torch.int32, device=DEV)
+        scratch = torch.zeros(lib.pg_ovf_scratch_ints(n), dtype=torch.int32, device=DEV)
+        lib.pg_ovf_select(rd, od[first:last + 1], kd[first:last], n, masks, sel, noff, status, scratch)
+        return masks.cpu().numpy(), sel.cpu().numpy(), noff.cpu().numpy(), status.cpu().numpy()
+
+    masks, sel, noff, status = select(0, G)
+    assert status.tolist() == [3, 0, 0, 0]
+    np.testing.assert_array_equal(noff, np.concatenate([[0], np.cumsum(np.maximum(ks, 0))]))
+    for first in range(0, G, part):
+        last = min(first + part, G)
+        w_masks, w_sel, _, _ = select(first, last)
+        np.testing.assert_array_equal(masks[first:last], w_masks)
+        np.testing.assert_array_equal(sel[noff[first]:noff[last]], w_sel)
+
+
+def test_ovf_unsuited_groups_do_not_hold_up_a_batch(lib):
+    """A batch whose groups all keep more than 32, or in which every 64th group keeps everything, takes no longer than a few
+    times the batch that suits the one-lane-per-group kernel best (about 1.5 and 1.1 times; 11 times when the wave that met
+    such a group did its 64 groups one after another)."""
+    say("ovf lanes, time with unsuited groups")
+    G = 16384
+    off = torch.arange(G + 1, dtype=torch.int32, device=DEV) * 64
+    r = torch.randn(G * 64, device=DEV)
+    masks, noff = torch.zeros(G, dtype=torch.int64, device=DEV), torch.zeros(G + 1, dtype=torch.int32, device=DEV)
+    status, scratch = torch.zeros(4, dtype=torch.int32, device=DEV), torch.zeros(lib.pg_ovf_scratch_ints(G), dtype=torch.int32, device=DEV)
+
+    def micros(k):
+        sel = torch.zeros(int(k.sum()), dtype=torch.int32, device=DEV)
+        a, b, best = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), 1e9
+        for _ in range(6):
+            a.record()
+            for _ in range(20):
+                lib.pg_ovf_select(r, off, k, G, masks, sel, noff, status, scratch)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 50)
+        return best
+
+    suited = micros(torch.full((G,), 16, dtype=torch.int32, device=DEV))
+    many = micros(torch.full((G,), 40, dtype=torch.int32, device=DEV))
+    one_in_64 = torch.full((G,), 16, dtype=torch.int32, device=DEV)
+    one_in_64[5::64] = 64
+    unpruned = micros(one_in_64)
+    say(f"  {suited:.1f} us, all keep 40: {many:.1f} us, one in 64 keeps all: {unpruned:.1f} us")
+    assert many < 4 * suited and unpruned < 4 * suited
+
+
 @pytest.mark.parametrize("words", [1, 2, 3, 4, 5, 8, 9, 16])
 def test_ovf_large_at_every_workgroup_size(lib, words):
     say(f"ovf large, {words} mask words")
