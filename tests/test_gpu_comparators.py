@@ -43,6 +43,55 @@ def test_uniform_select_matches_oracle_bit_for_bit(lib, seed, draw, n_groups):
     np.testing.assert_array_equal(sel.cpu().numpy(), want_sel)
 
 
+@pytest.mark.parametrize("n_groups", [65536 + 3, 524288 + 77])
+def test_uniform_select_of_very_many_groups(lib, n_groups):
+    """Several groups to a wave (two and sixteen): offsets and packing of all groups, the subsets of sampled ones."""
+    say(f"uniform_select groups {n_groups}")
+    rng = np.random.default_rng(n_groups)
+    sizes = rng.integers(0, 10, n_groups)
+    k = np.minimum(rng.integers(1, 6, n_groups), sizes)              # empty groups among them
+    offs = np.concatenate([[0], np.cumsum(sizes)])
+    t = lambda a, dt: torch.from_numpy(np.asarray(a).astype(dt)).to(DEV)
+    masks = torch.full((n_groups,), -1, dtype=torch.int64, device=DEV)
+    sel = torch.full((int(k.sum()),), -1, dtype=torch.int32, device=DEV)
+    noff = torch.full((n_groups + 1,), -1, dtype=torch.int32, device=DEV)
+    status = torch.zeros(4, dtype=torch.int32, device=DEV)
+    scratch = torch.zeros(lib.pg_ovf_scratch_ints(n_groups), dtype=torch.int32, device=DEV)
+    lib.pg_uniform_select(t(offs, np.int32), t(k, np.int32), n_groups, 11, 4, masks, sel, noff, status, scratch)
+    assert status[0].item() == 0
+    np.testing.assert_array_equal(noff.cpu().numpy(), np.concatenate([[0], np.cumsum(k)]))
+    m = masks.cpu().numpy()
+    bits = (m[:, None] >> np.arange(10)) & 1
+    np.testing.assert_array_equal(bits.sum(1), k)
+    g, slot = np.nonzero(bits)
+    np.testing.assert_array_equal(sel.cpu().numpy(), offs[g] + slot)
+    for i in np.concatenate([np.arange(70), rng.integers(0, n_groups, 60), np.arange(n_groups - 70, n_groups)]):
+        if sizes[i]:
+            assert m[i] == cmp.uniform_subset(11, 4, int(i), int(sizes[i]), int(k[i]))[0], i
+
+
+def test_uniform_select_time_grows_with_the_groups(lib):
+    """16 times the groups take 16 times as long (25 times when every four groups added up all counts before them)."""
+    say("uniform_select time")
+    def micros(n_groups):
+        offs = torch.arange(n_groups + 1, dtype=torch.int32, device=DEV) * 8
+        k = torch.full((n_groups,), 4, dtype=torch.int32, device=DEV)
+        masks, sel = torch.zeros(n_groups, dtype=torch.int64, device=DEV), torch.zeros(4 * n_groups, dtype=torch.int32, device=DEV)
+        noff, status = torch.zeros(n_groups + 1, dtype=torch.int32, device=DEV), torch.zeros(4, dtype=torch.int32, device=DEV)
+        scratch = torch.zeros(lib.pg_ovf_scratch_ints(n_groups), dtype=torch.int32, device=DEV)
+        a, b, best = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), 1e9
+        for _ in range(6):
+            a.record()
+            lib.pg_uniform_select(offs, k, n_groups, 1, 2, masks, sel, noff, status, scratch)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3)
+        return best
+    million, sixteen = micros(1 << 20), micros(1 << 24)
+    say(f"  {million:.0f} us, {sixteen:.0f} us")
+    assert sixteen < 20 * million
+
+
 def test_uniform_select_flags_bad_k_and_oversized_groups(lib):
     offs = torch.tensor([0, 5, 5, 75, 80], dtype=torch.int32, device=DEV)        # sizes 5, 0, 70, 5
     k = torch.tensor([6, 0, 3, 2], dtype=torch.int32, device=DEV)
