@@ -231,6 +231,51 @@ def test_network_output_with_every_tile_height_of_the_projection(lib, P, N, tile
     lib.pg_destroy(ctx)
 
 
+@pytest.mark.parametrize("P,D,blocks", [(203, 128, 1), (70, 64, 2)])
+def test_network_output_of_many_groups(lib, P, D, blocks):
+    """Conditioning and modulation vectors of more groups than one workgroup takes, the last workgroup part empty."""
+    from oracle import dit
+    say(f"network forward, {P} groups of width {D}")
+    cfg = workloads.get_config("cfg1")
+    cfg.update(P=P, N=2, H=8, W=8, D=D, heads=2, blocks=blocks, T=1, schedule=[[] for _ in range(P)], Li=16, d=4 * 64)
+    w = workloads.make_weights(cfg)
+    inp = workloads.make_inputs(cfg, w)
+    ctx, buf = _gpu_ctx(lib, cfg, w, inp)
+    lib.pg_init_group(ctx, 5)
+    lib.pg_net_forward(ctx, 0)
+    u, x = buf.u.cpu().numpy().astype(np.float64), buf.x[0].cpu().numpy().astype(np.float64)
+    t_in = sampler.flow_sde_tables(1, cfg["sampler"]["a"])["t_in"][0]
+    for g in (*range(0, P, 7), P - 2, P - 1):
+        want = dit.forward(w, cfg, x[2 * g:2 * g + 2], t_in, inp["y"][g], None)
+        assert np.max(np.abs(u[2 * g:2 * g + 2] - want)) < 2e-2 * np.max(np.abs(want)), g
+    lib.pg_destroy(ctx)
+
+
+def test_network_time_does_not_depend_on_the_grouping(lib):
+    """4096 trajectories in 1024 groups and in 64 of a one-block network: the same work but for the modulation vectors (1.1
+    times; 2.9 times when few workgroups walked all groups)."""
+    say("network forward, time with many groups")
+    def micros(P, N):
+        cfg = workloads.get_config("cfg1")
+        cfg.update(P=P, N=N, D=64, heads=2, blocks=1, T=1, schedule=[[] for _ in range(P)])
+        w = workloads.make_weights(cfg)
+        ctx, buf = _gpu_ctx(lib, cfg, w, workloads.make_inputs(cfg, w))
+        lib.pg_init_group(ctx, 5)
+        a, b, best = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), 1e9
+        for _ in range(6):
+            a.record()
+            for _ in range(5):
+                lib.pg_net_forward(ctx, 0)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 200)
+        lib.pg_destroy(ctx)
+        return best
+    many, few = micros(1024, 4), micros(64, 64)
+    say(f"  1024 groups {many:.0f} us, 64 groups {few:.0f} us")
+    assert many < 1.6 * few
+
+
 # enough trajectories and tokens for the 64-queries-per-wave attention (four query tiles of 128 against two of 256, 1.67 rounds
 # against one): whole key tiles (484 + 28 tokens), a last tile that ends in its second (484 + 26) or first (462 + 18) half,
 # separate streams; query and key weights scaled until later scores pass the reference that the first tile set
