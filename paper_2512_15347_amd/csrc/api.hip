@@ -396,6 +396,12 @@ extern "C" pg_status pg_bind(pg_ctx* c, const pg_buffers* b) {
     memcpy(image.data() + (c->ws_tin - c->ws_sched), c->tin.data(), sizeof(double) * c->tin.size());
     PG_HIP(hipMemcpy((char*)b->workspace + c->ws_sched, image.data(), image.size(), hipMemcpyHostToDevice));
   }
+  // so do the embeddings of these times: complete when the call returns, whatever stream the loop then runs on, and also if its
+  // first run is only recorded into a graph
+  if (c->cfg.net_kind != PG_NET_NONE) {
+    PG_TRY(net_embed_times(c, nullptr));
+    PG_HIP(hipStreamSynchronize(nullptr));
+  }
   c->bound = true;
   c->initialised = false;
   c->context_ready = false;

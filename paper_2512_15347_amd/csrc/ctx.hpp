@@ -49,6 +49,7 @@ struct pg_ctx {
 namespace pg {
 // network (dit_kernels.hip)
 pg_status net_plan(pg_ctx* c);                                  // fills c->net, returns bytes in net.total
+pg_status net_embed_times(pg_ctx* c, hipStream_t s);             // tables of the step times, at pg_bind
 pg_status net_prepare(pg_ctx* c, const uint16_t* weights, hipStream_t s);   // step-independent precomputation
 // u = net(x) for the M active rows of `x` under `weights`
 pg_status net_forward(pg_ctx* c, int step, const float* x, const uint16_t* weights, hipStream_t s);

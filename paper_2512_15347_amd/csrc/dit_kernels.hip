@@ -303,12 +303,17 @@ struct Net {
 };
 }  // namespace
 
-// Step-independent work: time embeddings, projected context rows (joint) or per-block context keys / values (cross).
+// time embeddings of all steps from their network times, both in the workspace (set-up, see pg_bind)
+pg_status net_embed_times(pg_ctx* c, hipStream_t s) {
+  timestep_embedding_kernel<<<dim3(c->cfg.T), dim3(128), 0, s>>>((const double*)((char*)c->buf.workspace + c->ws_tin),
+                                                                (float*)((char*)c->buf.workspace + c->ws_emb));
+  PG_LAUNCH_CHECK("timestep_embedding_kernel");
+  return PG_OK;
+}
+
+// Step-independent work: projected context rows (joint) or per-block context keys / values (cross).
 pg_status net_prepare(pg_ctx* c, const uint16_t* weights, hipStream_t s) {
   const pg_config& f = c->cfg;
-  timestep_embedding_kernel<<<dim3(f.T), dim3(128), 0, s>>>((const double*)((char*)c->buf.workspace + c->ws_tin),
-                                                           (float*)((char*)c->buf.workspace + c->ws_emb));
-  PG_LAUNCH_CHECK("timestep_embedding_kernel");
   Net n{c, s, (char*)c->buf.workspace + c->ws_net, weights};
   const int D = f.D;
   if (f.net_kind == PG_NET_JOINT || f.net_kind == PG_NET_MMDIT) {

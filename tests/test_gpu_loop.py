@@ -475,3 +475,40 @@ def test_whole_loop_replays_from_a_hip_graph(lib):
         assert torch.equal(buf.logp_hist.view(torch.int32), want["hist"].view(torch.int32))
         assert int(buf.status[0]) == 0
     lib.pg_destroy(ctx)
+
+
+def test_first_run_recorded_but_not_yet_replayed(lib):
+    """A context whose first run is recorded into a HIP graph: an eager run before any replay gives what a context that was never
+    captured gives, and so does the replay.  (The workspace starts as NaN patterns, so nothing can pass on its old contents.)"""
+    name, seed = "cfg1", 91
+    say(f"capture first {name}")
+    cfg = workloads.get_config(name)
+    w = workloads.make_weights(cfg); inp = workloads.make_inputs(cfg, w)
+    c, keep = lib.make_config(cfg, probe_bias=inp["probe_b"])
+    runs = []
+    for captured in (False, True):
+        ctx = lib.pg_create(c)
+        buf = lib.Buffers(ctx, cfg, inputs=inp, weights_flat=lib.pack_weights(ctx, cfg, w))
+        buf.workspace.fill_(255)
+        lib.pg_bind(ctx, buf)
+        if captured:
+            side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+            with torch.cuda.stream(side):
+                graph.capture_begin()
+                lib.pg_sample_group(ctx, seed)
+                graph.capture_end()
+            torch.cuda.synchronize()
+        lib.pg_sample_group(ctx, seed + 1)
+        lib.pg_check(ctx)
+        st = lib.pg_state(ctx, cfg["P"])
+        runs.append(buf.x[st["cur_x"]][:st["M"]].clone())
+        if not captured:
+            lib.pg_sample_group(ctx, seed)
+            lib.pg_check(ctx)
+            want = buf.x[st["cur_x"]][:st["M"]].clone()
+        else:
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(buf.x[st["cur_x"]][:st["M"]], want)
+        lib.pg_destroy(ctx)
+    assert torch.equal(runs[0], runs[1])
