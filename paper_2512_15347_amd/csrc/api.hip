@@ -438,7 +438,10 @@ extern "C" pg_status pg_init_group(pg_ctx* c, uint64_t seed, void* stream) {
     PG_HIP(hipMemcpyAsync(c->buf.x_hist, c->buf.x[0], sizeof(float) * (size_t)c->M0 * c->d, hipMemcpyDeviceToDevice, s));
   if (f.net_kind != PG_NET_NONE && !c->context_ready) {
     PG_TRY(net_prepare(c, c->buf.weights, s));
-    c->context_ready = true;
+    // a pass that is being recorded has computed nothing yet: a later run prepares the context itself
+    hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+    PG_HIP(hipStreamIsCapturing(s, &recording));
+    c->context_ready = recording == hipStreamCaptureStatusNone;
   }
   c->initialised = true;
   return PG_OK;

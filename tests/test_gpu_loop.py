@@ -477,10 +477,11 @@ def test_whole_loop_replays_from_a_hip_graph(lib):
     lib.pg_destroy(ctx)
 
 
-def test_first_run_recorded_but_not_yet_replayed(lib):
+@pytest.mark.parametrize("name", ["cfg1", "cfg2_small", "cfg3_small", "cfg3_mmdit_small"])
+def test_first_run_recorded_but_not_yet_replayed(lib, name):
     """A context whose first run is recorded into a HIP graph: an eager run before any replay gives what a context that was never
     captured gives, and so does the replay.  (The workspace starts as NaN patterns, so nothing can pass on its old contents.)"""
-    name, seed = "cfg1", 91
+    seed = 91
     say(f"capture first {name}")
     cfg = workloads.get_config(name)
     w = workloads.make_weights(cfg); inp = workloads.make_inputs(cfg, w)
