@@ -324,6 +324,15 @@ pg_status pg_attention_bf16(const uint16_t *q, const uint16_t *k, const uint16_t
                             int32_t B, int32_t Lq, int32_t Lk, int32_t heads, int32_t hd,
                             void *stream);
 
+/* Test hooks: the attention kernels as the network launches them.  q is already multiplied by log2(e)/sqrt(hd); in a row of vt
+ * [B, heads*hd, Lk_pad] (Lk_pad >= Lk, a multiple of 64) key t lies at position t with its bits 2 and 3 exchanged; kernel 1 gives
+ * a wave 32 queries, kernel 2 gives it 64 (hd 64 only), 0 is the launcher's choice for these sizes, which pg_attention_kernel
+ * tells without a launch (0 for sizes below 1).  The result does not depend on the kernel. */
+int32_t pg_attention_kernel(int32_t B, int32_t Lq, int32_t Lk, int32_t heads, int32_t hd);
+pg_status pg_attention_network(const uint16_t *q, const uint16_t *k, const uint16_t *vt, uint16_t *out,
+                               int32_t B, int32_t Lq, int32_t Lk, int32_t Lk_pad, int32_t heads, int32_t hd,
+                               int32_t kernel, void *stream);
+
 /* ---- measurement hooks (process-wide, not thread-safe) ----
  * Between pg_profile_begin and pg_profile_end every launch of the heavy kernels is bracketed by a
  * pair of HIP events on the stream it is launched on (at most max_records launches are recorded).

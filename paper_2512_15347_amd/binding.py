@@ -100,6 +100,8 @@ _SIGNATURES = {
     "pg_group_advantages": (_i32, [_vp, _vp, _i32, _f64, _vp, _vp]),
     "pg_gemm_bf16": (_i32, [_vp, _i64, _vp, _i64, _vp, _vp, _i64, _i64, _i64, _i64, _vp]),
     "pg_attention_bf16": (_i32, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _vp]),
+    "pg_attention_kernel": (_i32, [_i32] * 5),
+    "pg_attention_network": (_i32, [_vp, _vp, _vp, _vp] + [_i32] * 7 + [_vp]),
     "pg_mfma_probe": (_i32, [_i32, _i32, C.c_float, _vp, _dp, _vp]),
     "pg_profile_begin": (_i32, [_i32]),
     "pg_profile_read": (_i32, [_i32, _dp, _dp, C.POINTER(_i64)]),
@@ -419,6 +421,14 @@ def pg_gemm_bf16(A, lda, W, ldw, bias, Cout, ldc, M, N, K, stream=None):
 
 def pg_attention_bf16(q, k, vt, out, B, Lq, Lk, heads, hd, stream=None):
     _check(_lib.pg_attention_bf16(_ptr(q), _ptr(k), _ptr(vt), _ptr(out), B, Lq, Lk, heads, hd, _stream(stream)))
+
+
+def pg_attention_kernel(B, Lq, Lk, heads, hd):
+    return int(_lib.pg_attention_kernel(B, Lq, Lk, heads, hd))
+
+
+def pg_attention_network(q, k, vt, out, B, Lq, Lk, Lk_pad, heads, hd, kernel=0, stream=None):
+    _check(_lib.pg_attention_network(_ptr(q), _ptr(k), _ptr(vt), _ptr(out), B, Lq, Lk, Lk_pad, heads, hd, kernel, _stream(stream)))
 
 
 def pg_mfma_probe(blocks, iters, operand_scale, out, stream=None):

@@ -550,18 +550,27 @@ static bool use_wide(int64_t wgs, int64_t wide_wgs, int Lk) {
   return Lk >= 480 && rounds(wide_wgs / 512.0) <= 0.8 * rounds(wgs / 768.0);
 }
 
+int pick_attention(int B, int Lq, int Lk, int heads, int hd, int v_swapped) {
+  const int64_t wgs = (int64_t)((Lq + QTILE - 1) / QTILE) * heads * B, wide_wgs = (int64_t)((Lq + WIDE_QTILE - 1) / WIDE_QTILE) * heads * B;
+  return hd == 64 && v_swapped && use_wide(wgs, wide_wgs, Lk) ? 2 : 1;
+}
+
 pg_status launch_attention(const AttnArgs& a, int hd, hipStream_t s) {
   if (a.B <= 0 || a.Lq <= 0 || a.heads <= 0) return PG_OK;
   if (a.Lk <= 0) return fail(PG_EINVAL, "attention: no keys");
   if (hd != 32 && hd != 64) return fail(PG_ESHAPE, "attention: head width %d not supported (32 or 64)", hd);
-  if (a.Lkpad % 8 || a.Lkpad < a.Lk || a.ldq % 8 || a.ldk % 8 || a.ldo % 4 ||
+  // the kernels read value rows in whole tiles of KTILE keys
+  if (a.Lkpad % KTILE || a.Lkpad < a.Lk || a.ldq % 8 || a.ldk % 8 || a.ldo % 4 ||
       ((uintptr_t)a.q & 15) || ((uintptr_t)a.k & 15) || ((uintptr_t)a.vt & 15) || ((uintptr_t)a.out & 7))
-    return fail(PG_ESHAPE, "attention: operands need 16-byte aligned rows");
-  const int64_t wgs = (int64_t)((a.Lq + QTILE - 1) / QTILE) * a.heads * a.B;
-  const int64_t wide_wgs = (int64_t)((a.Lq + WIDE_QTILE - 1) / WIDE_QTILE) * a.heads * a.B;
-  if (wgs > (1ll << 30)) return fail(PG_ESHAPE, "attention: grid limit");
-  const bool wide = hd == 64 && a.v_swapped && a.Lkpad % KTILE == 0 && use_wide(wgs, wide_wgs, a.Lk);
-  const dim3 grid((unsigned)(((wide ? wide_wgs : wgs) + 7) / 8 * 8)), block(ATT_THREADS);
+    return fail(PG_ESHAPE, "attention: operands need 16-byte aligned rows, value rows a multiple of %d keys (%d)", KTILE, a.Lkpad);
+  const int kernel = a.kernel ? a.kernel : pick_attention(a.B, a.Lq, a.Lk, a.heads, hd, a.v_swapped);
+  const bool wide = kernel == 2;
+  if (kernel < 1 || kernel > 2 || (wide && (hd != 64 || !a.v_swapped)))
+    return fail(PG_EINVAL, "attention: kernel %d does not take head width %d", kernel, hd);
+  const int q_tile = wide ? WIDE_QTILE : QTILE;
+  const int64_t wgs = (int64_t)((a.Lq + q_tile - 1) / q_tile) * a.heads * a.B;
+  if (wgs > (wide ? 1ll << 29 : 1ll << 30)) return fail(PG_ESHAPE, "attention: grid limit");
+  const dim3 grid((unsigned)((wgs + 7) / 8 * 8)), block(ATT_THREADS);
   const int rec = prof_open(PROF_ATTENTION, 4.0 * a.B * (double)a.heads * a.Lq * (double)a.Lk * hd, s);
   if (wide) attention_wide_kernel<<<grid, block, 0, s>>>(a);
   else if (hd == 64 && a.v_swapped) attention_kernel<64, true><<<grid, block, 0, s>>>(a);
@@ -590,5 +599,25 @@ extern "C" pg_status pg_attention_bf16(const uint16_t* q, const uint16_t* k, con
   a.out = out; a.ldo = D; a.kv_map = nullptr;
   a.B = B; a.Lq = Lq; a.Lk = Lk; a.heads = heads;
   a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)hd));
+  return launch_attention(a, hd, (hipStream_t)stream);
+}
+
+extern "C" int32_t pg_attention_kernel(int32_t B, int32_t Lq, int32_t Lk, int32_t heads, int32_t hd) {
+  return B < 1 || Lq < 1 || Lk < 1 || heads < 1 ? 0 : pick_attention(B, Lq, Lk, heads, hd, 1);
+}
+
+extern "C" pg_status pg_attention_network(const uint16_t* q, const uint16_t* k, const uint16_t* vt, uint16_t* out,
+                                          int32_t B, int32_t Lq, int32_t Lk, int32_t Lk_pad, int32_t heads, int32_t hd,
+                                          int32_t kernel, void* stream) {
+  if (B < 0 || Lq < 0 || Lk < 0 || heads < 1) return fail(PG_EINVAL, "pg_attention_network: bad sizes");
+  if (B == 0 || Lq == 0) return PG_OK;
+  if (!q || !k || !vt || !out) return fail(PG_EINVAL, "pg_attention_network: null pointer");
+  if (kernel < 0 || kernel > 2) return fail(PG_EINVAL, "pg_attention_network: kernel %d", kernel);
+  const int D = heads * hd;
+  AttnArgs a{};
+  a.q = q; a.ldq = D; a.k = k; a.ldk = D; a.k_bstride = (int64_t)Lk * D;
+  a.vt = vt; a.Lkpad = Lk_pad; a.vt_bstride = (int64_t)D * Lk_pad;
+  a.out = out; a.ldo = D; a.kernel = kernel; a.q_prescaled = 1; a.v_swapped = 1;
+  a.B = B; a.Lq = Lq; a.Lk = Lk; a.heads = heads;
   return launch_attention(a, hd, (hipStream_t)stream);
 }

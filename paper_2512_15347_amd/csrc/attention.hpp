@@ -13,10 +13,13 @@ struct AttnArgs {
   int B, Lq, Lk, heads;
   float scale_log2;                               // log2(e) / sqrt(hd)
   int q_prescaled;                                // the producer of q has already multiplied it by scale_log2
-  int v_swapped;                                  // tokens t of vt are stored at value_slot(t) (gemm.hip), Lkpad a multiple of 64
+  int v_swapped;                                  // tokens t of vt are stored at value_slot(t) (gemm.hip)
+  int kernel;                                     // 0: the launcher's choice, 1 / 2: 32 / 64 queries per wave (tests)
   int split; uint16_t* out2;                      // split > 0: queries >= split go to out2[b * (Lq - split) + q - split, :]
 };
 
+// which kernel the launcher takes: 1 (32 queries per wave) or 2 (64)
+int pick_attention(int B, int Lq, int Lk, int heads, int hd, int v_swapped);
 pg_status launch_attention(const AttnArgs& a, int hd, hipStream_t s);
 
 }  // namespace pg

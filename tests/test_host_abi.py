@@ -191,3 +191,17 @@ def test_context_free_argument_checks_need_no_gpu():
     assert pg._lib.pg_group_advantages(None, None, 3, -1.0, None, None) == pg.PG_EINVAL
     assert pg.pg_step_scratch_floats(1024, 262144) == 1024 * 64
     assert "null" in pg.pg_last_error().lower() or len(pg.pg_last_error()) > 0
+
+
+def test_attention_refuses_value_rows_that_end_inside_a_tile():
+    """The kernels read value rows in whole tiles of 64 keys: a shorter padding is an error before anything is launched."""
+    for kernel in (0, 1, 2):
+        for Lk, pad in ((77, 80), (64, 72), (100, 64), (64, 0)):
+            with pytest.raises(pg.PgError) as e:
+                pg.pg_attention_network(256, 256, 256, 256, 1, 32, Lk, pad, 2, 64, kernel, stream=0)
+            assert e.value.status == pg.PG_ESHAPE, (kernel, Lk, pad)
+    with pytest.raises(pg.PgError) as e:
+        pg.pg_attention_network(256, 256, 256, 256, 1, 32, 64, 64, 2, 32, 2, stream=0)     # 64 queries per wave: head width 64 only
+    assert e.value.status == pg.PG_EINVAL
+    assert pg.pg_attention_kernel(48, 1178, 1178, 24, 64) == 2 and pg.pg_attention_kernel(1, 1178, 1178, 24, 64) == 1
+    assert pg.pg_attention_kernel(48, 1178, 1178, 24, 32) == 1 and pg.pg_attention_kernel(48, 1178, 77, 24, 64) == 1
