@@ -204,9 +204,9 @@ def test_network_output_at_step_0(lib, name):
 
 @pytest.mark.parametrize("P,N,tile_rows", [(5, 51, 192), (5, 42, 160), (6, 49, 224)])
 def test_network_output_with_every_tile_height_of_the_projection(lib, P, N, tile_rows):
-    """The fused query / key / value projection stages its value channels through LDS in groups of two 32-row
-    slabs; tiles of 192, 160 and 224 rows end in a single slab.  Row counts P * N * 64 chosen so that the
-    launcher picks that height for the 768-column projection (255, 252 and 252 tiles for 256 compute units);
+    """The fused query / key / value projection stages its value channels through LDS in groups of four, two and one 16-row
+    tiles of a wave; tiles of 192, 160 and 224 rows leave 6 = 4 + 2, 5 = 4 + 1 and 7 = 4 + 2 + 1.  Row counts P * N * 64 chosen
+    so that the launcher picks that height for the 768-column projection (255, 252 and 252 tiles for 256 compute units);
     sampled trajectories (first, last, and two whose rows straddle tile boundaries) against the oracle."""
     from oracle import dit, philox
     say(f"network forward with {P * N * 64} rows ({tile_rows}-row tiles in the projection)")
@@ -276,32 +276,76 @@ def test_network_time_does_not_depend_on_the_grouping(lib):
     assert many < 1.6 * few
 
 
-# enough trajectories and tokens for the 64-queries-per-wave attention (four query tiles of 128 against two of 256, 1.67 rounds
-# against one): whole key tiles (484 + 28 tokens), a last tile that ends in its second (484 + 26) or first (462 + 18) half,
-# separate streams; query and key weights scaled until later scores pass the reference that the first tile set
-@pytest.mark.parametrize("kind,W,Lc,gain", [("joint", 44, 28, 1.0), ("joint", 42, 18, 7.0), ("joint", 44, 26, 1.0), ("mmdit", 42, 26, 1.0)])
-def test_network_output_with_wide_attention(lib, kind, W, Lc, gain):
+def _sharpen_attention(w, kind, gain):
+    """Makes the attention decide the network output: with weights of 0.02 the softmax is nearly flat and its branch small, and a
+    wrong value order or a missing key tile moves u by less than its tolerance.  With sharp scores and values and outputs four
+    times as large the oracle's u moves by 0.35 of its maximum or more when the scores are ignored or the values stored in another order,
+    by 0.18 when the last 16 keys are left out and, with less than 100 tokens, by 0.04 when one value is wrong (rounding of the
+    attention's operands to bf16: 0.01)."""
+    def scale(a, factor):
+        a[:] = workloads.bf16_round(a * np.float32(factor))
+    for blk in w["blocks"]:
+        D = len(blk["o_w"])
+        for pre in ("", "c_") if kind == "mmdit" else ("",):
+            if kind == "mmdit":
+                scale(blk[pre + "qn_g"], 1.5)
+                scale(blk[pre + "kn_g"], 1.5)
+            else:
+                scale(blk["qkv_w"][:2 * D], gain)
+            scale(blk[pre + "qkv_w"][2 * D:], 4)
+            scale(blk[pre + "o_w"], 4)
+        if kind == "cross":
+            scale(blk["cq_w"], gain)
+            scale(blk["ckv_w"][:D], gain)
+            scale(blk["ckv_w"][D:], 4)
+            scale(blk["co_w"], 4)
+
+
+def _check_sharp_network(lib, cfg, kind, gain, trajectories):
     from oracle import dit
-    say(f"wide attention {kind} W={W} Lc={Lc} gain={gain}")
-    cfg = workloads.get_config("cfg3_small")
-    cfg.update(kind=kind, N=64, H=44, W=W, D=256, heads=4, Lc=Lc, Dc=256, blocks=1, T=1, schedule=[[]], Li=11 * W, d=4 * 44 * W)
     w = workloads.make_weights(cfg)
-    if gain != 1.0:
-        w["blocks"][0]["qkv_w"][:512] = workloads.bf16_round(w["blocks"][0]["qkv_w"][:512] * np.float32(gain))
+    _sharpen_attention(w, kind, gain)
     inp = workloads.make_inputs(cfg, w)
-    tables = sampler.flow_sde_tables(1, 0.7)
-    c, keep = lib.make_config(cfg, probe_bias=inp["probe_b"])
-    ctx = lib.pg_create(c)
-    buf = lib.Buffers(ctx, cfg, inputs=inp, weights_flat=lib.pack_weights(ctx, cfg, w))
-    lib.pg_bind(ctx, buf)
+    ctx, buf = _gpu_ctx(lib, cfg, w, inp)
     lib.pg_init_group(ctx, 77)
     lib.pg_net_forward(ctx, 0)
     got = buf.u.cpu().numpy().astype(np.float64)
     x = buf.x[0].cpu().numpy().astype(np.float64)
-    for i in (0, 63):
-        want = dit.forward(w, cfg, x[i][None], tables["t_in"][0], inp["y"][0], inp["ctx"][0])[0]
-        assert np.max(np.abs(got[i] - want)) < 2e-2 * np.max(np.abs(want)), i
+    t_in = sampler.flow_sde_tables(1, 0.7)["t_in"][0]
+    for i in trajectories:
+        g = i // cfg["N"]
+        want = dit.forward(w, cfg, x[i][None], t_in, inp["y"][g], inp["ctx"][g] if cfg["Lc"] else None)[0]
+        err = np.max(np.abs(got[i] - want)) / np.max(np.abs(want))
+        say(f"  trajectory {i}: max err / max|u| = {err:.2e}")
+        assert err < 2e-2, i
     lib.pg_destroy(ctx)
+
+
+# token counts that store the transposed values in units of four, in pairs (30 image tokens before the context's) and one by one
+# (35; context rows of 13, 21, 27 and 77 tokens), at both head widths
+@pytest.mark.parametrize("kind,H,W,Lc,heads,gain", [
+    ("adaln", 16, 16, 0, 4, 7), ("adaln", 10, 14, 0, 4, 10), ("cross", 10, 14, 13, 2, 7), ("cross", 16, 16, 77, 2, 7),
+    ("joint", 10, 14, 26, 2, 7), ("joint", 16, 16, 27, 2, 7), ("mmdit", 10, 14, 18, 2, 1), ("mmdit", 10, 12, 21, 2, 1),
+    ("mmdit", 16, 16, 26, 2, 1)])
+def test_network_output_with_sharp_attention(lib, kind, H, W, Lc, heads, gain):
+    say(f"sharp attention {kind} {H}x{W} Lc={Lc}")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind=kind, P=2, N=5, H=H, W=W, D=128, heads=heads, Lc=Lc, Dc=128 if Lc else 0, blocks=1, T=1, schedule=[[], []],
+               Li=H * W // 4, d=4 * H * W)
+    _check_sharp_network(lib, cfg, kind, gain, (0, 4, 5, 9))
+
+
+# enough trajectories and tokens for the 64-queries-per-wave attention (four query tiles of 128 against two of 256, 1.67 rounds
+# against one): whole key tiles (484 + 28 tokens), a last tile that ends in its second (484 + 26) or first (462 + 18) half,
+# separate streams (462 + 26)
+@pytest.mark.parametrize("kind,W,Lc,gain", [("joint", 44, 28, 4), ("joint", 42, 18, 7), ("joint", 44, 26, 4), ("mmdit", 42, 26, 1)])
+def test_network_output_with_wide_attention(lib, kind, W, Lc, gain):
+    say(f"wide attention {kind} W={W} Lc={Lc} gain={gain}")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind=kind, N=64, H=44, W=W, D=256, heads=4, Lc=Lc, Dc=256, blocks=1, T=1, schedule=[[]], Li=11 * W, d=4 * 44 * W)
+    L = cfg["Li"] + Lc
+    assert lib.pg_attention_kernel(64, L, L, 4, 64) == 2
+    _check_sharp_network(lib, cfg, kind, gain, (0, 63))
 
 
 @pytest.mark.parametrize("kind", ["joint", "mmdit"])
@@ -320,7 +364,8 @@ def test_network_output_of_a_trajectory_does_not_depend_on_the_batch(lib, kind):
                 blk[name] *= 8
     inp = workloads.make_inputs(cfg, w)
     u = {}
-    for N in (64, 48, 5):
+    for N, kernel in ((64, 2), (48, 1), (5, 1)):
+        assert lib.pg_attention_kernel(N, 480, 480, 4, 64) == kernel
         cfg["N"] = N
         ctx, buf = _gpu_ctx(lib, cfg, w, inp)
         lib.pg_init_group(ctx, 9)

@@ -20,8 +20,7 @@ def bf16_dev(a):
     return torch.from_numpy(workloads.bf16_bits(a).view(np.int16)).to(DEV)
 
 
-# the later shapes are sized so that the launcher's tile heuristic takes each of its tile heights (160, 192, 224,
-# 256 rows, and the 128x128 tile) with a ragged last tile in both directions
+# ragged last tiles in both directions; the launcher takes its tiles of 160, 192 and 224 rows, of 128 x 64 and of 64 x 64 here
 @pytest.mark.parametrize("M,N,K", [(300, 200, 128), (2356, 384, 512), (256, 256, 64), (1, 16, 64), (777, 4608, 1536),
                                    (12251, 768, 128), (12251, 2304, 64), (12283, 3072, 128), (24571, 1532, 64),
                                    (18848, 1536, 64), (9001, 520, 192)])
@@ -41,10 +40,10 @@ def test_gemm_matches_oracle_linear(lib, M, N, K):
     assert np.max(np.abs(got - want)) < 2e-5 * math.sqrt(K) * np.max(np.abs(want)) + 1e-6
 
 
-# the remaining tiles (256 x 256, 224, 192 and 160 rows with one to four K steps, 128 x 128, 128 x 64, 64 x 64), one row and
-# column short of or past a tile
+# every tile that the launcher has (256 x 256, 224, 192 and 160 rows, 128 x 128 with one and with five K steps, 128 x 64, 64 x 64),
+# one row and column short of or past a tile
 @pytest.mark.parametrize("M,N,K", [(3213, 4484, 256), (14100, 1540, 192), (3697, 6140, 192), (4000, 4100, 128), (5000, 1000, 64),
-                                   (4097, 1020, 192), (63, 252, 64), (65, 68, 192), (64, 64, 128)])
+                                   (4099, 1404, 320), (4097, 1020, 192), (63, 252, 64), (65, 68, 192), (64, 64, 128)])
 def test_gemm_tiles_with_short_k(lib, M, N, K):
     test_gemm_matches_oracle_linear(lib, M, N, K)
 
@@ -119,3 +118,47 @@ def test_attention_with_every_score_far_below_zero(lib, hd, Lk):
     # rounding of the scaled queries to bf16 moves the output by 2e-3 of its maximum (the part common to all keys cancels), fp32
     # scores of this size (ulp 1e-4) by less; probabilities and outputs are rounded to bf16
     assert np.max(np.abs(got - want)) < 1.5e-2 * np.max(np.abs(want))
+
+
+def _network_attention(lib, q, k, v, heads, kernel):
+    """Output [B, Lq, D] of the kernel on queries already in the softmax's log2 units; values in the network's key order, NaN in
+    the padding."""
+    B, Lq, D = q.shape
+    Lk, Lkpad = k.shape[1], (k.shape[1] + 63) // 64 * 64
+    vt = np.full((B, D, Lkpad), np.nan, dtype=np.float32)
+    t = np.arange(Lk)
+    vt[:, :, (t & ~12) | ((t & 4) << 1) | ((t & 8) >> 1)] = v.transpose(0, 2, 1)
+    out = torch.full((B, Lq, D), -1, dtype=torch.int16, device=DEV)
+    lib.pg_attention_network(bf16_dev(q), bf16_dev(k), bf16_dev(vt), out, B, Lq, Lk, Lkpad, heads, D // heads, kernel)
+    return out.view(torch.bfloat16).float().cpu().numpy().astype(np.float64)
+
+
+# whole key tiles, last tiles that end in their first and second half, on and inside a group of 16 and of 4 keys, one key; query
+# counts that leave a wave's second 32, whole waves, or nearly a workgroup without work.  gain: scale of the scores; rising: later
+# keys score higher, so that tile after tile raises the reference
+@pytest.mark.parametrize("B,Lq,Lk,heads,hd,gain,rising", [
+    (1, 256, 128, 2, 64, 1.0, False), (2, 90, 90, 2, 64, 1.0, False), (1, 300, 1178, 3, 64, 1.0, False), (3, 33, 211, 1, 64, 1.0, False),
+    (1, 130, 77, 2, 64, 1.0, False), (1, 64, 13, 2, 64, 1.0, False), (2, 5, 1, 2, 64, 1.0, False), (1, 260, 506, 2, 64, 12.0, False),
+    (1, 257, 484, 2, 64, 1.0, True), (1, 100, 330, 2, 64, 12.0, True), (2, 130, 77, 2, 32, 1.0, False), (3, 64, 64, 4, 32, 1.0, False),
+    (1, 140, 186, 3, 32, 12.0, True), (1, 40, 29, 2, 32, 1.0, False)])
+def test_network_attention_kernels_match_oracle(lib, B, Lq, Lk, heads, hd, gain, rising):
+    say(f"network attention B={B} Lq={Lq} Lk={Lk} heads={heads} hd={hd} gain={gain} rising={rising}")
+    rng = np.random.default_rng(Lq * 7 + Lk)
+    D = heads * hd
+    scale = np.float32(1.4426950408889634 / math.sqrt(hd))
+    q = workloads.bf16_round(rng.standard_normal((B, Lq, D), dtype=np.float32) * (1.5 * gain * scale))
+    k = rng.standard_normal((B, Lk, D), dtype=np.float32)
+    if rising:                                         # one channel of every head: 0 .. 40 in log2 units over the keys
+        q[:, :, ::hd] = 1.0
+        k[:, :, ::hd] = np.linspace(0, 40, Lk, dtype=np.float32)[None, :, None]
+    k = workloads.bf16_round(k)
+    v = workloads.bf16_round(rng.standard_normal((B, Lk, D), dtype=np.float32))
+    want = dit.attention(q.astype(np.float64) / float(scale), k.astype(np.float64), v.astype(np.float64), heads)
+    outs = {kernel: _network_attention(lib, q, k, v, heads, kernel) for kernel in ((1, 2) if hd == 64 else (1,))}
+    for got in outs.values():
+        assert np.isfinite(got).all()
+        # probabilities and outputs are rounded to bf16 (2^-9 relative)
+        assert np.max(np.abs(got - want)) < 1.5e-2 * np.max(np.abs(want))
+        assert np.sqrt(np.mean((got - want) ** 2)) < 4e-3 * np.sqrt(np.mean(want ** 2))
+    if hd == 64:
+        np.testing.assert_array_equal(outs[1], outs[2])            # the choice is made by size and may not show
