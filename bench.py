@@ -362,7 +362,7 @@ def recorded_gemm_traffic(workload):
     if not (m_t and m_h):
         return None
     h = hashlib.sha256()
-    for fn in ("gemm.hip", "gemm.hpp"):
+    for fn in ("gemm.hip", "gemm.hpp", "operands.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2512_15347_amd", "csrc", fn), "rb").read())
     return int(m_t.group(1)) if h.hexdigest() == m_h.group(1) else None
 

@@ -18,6 +18,7 @@
 #include <cmath>
 #include <type_traits>
 #include "attention.hpp"
+#include "operands.hpp"
 
 namespace pg {
 
@@ -32,22 +33,19 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 constexpr int ATT_THREADS = 256;
 constexpr int QTILE = 128, KTILE = 64;
 
-// The value rows of the network keep their keys in the order in which the score accumulators hold them: in every 16 keys the
-// second and third group of four change places (VSWAP; value_slot in gemm.hip), so that a lane reads its eight keys as one
-// 16-byte chunk without bank conflicts instead of as two 8-byte pieces with two-way conflicts.  The public entry point
-// takes them in natural order.  Key of element i of the chunk that holds position kc (a multiple of 8):
+// The value rows of the network keep their keys in the order in which the score accumulators hold them (VSWAP; value_slot),
+// so that a lane reads its eight keys as one 16-byte chunk without bank conflicts instead of as two 8-byte pieces with two-way
+// conflicts.  The public entry point takes them in natural order.  Key at a position of a value row:
 template <bool VSWAP>
-__device__ __forceinline__ int key_at(int kc, int i) {
-  return VSWAP ? (kc & ~15) + ((kc >> 3) & 1) * 4 + (i & 3) + (i >> 2) * 8 : kc + i;
-}
-// zeroes the values of keys past the end in a chunk (the padding may hold anything)
+__device__ __forceinline__ int key_at(int position) { return VSWAP ? value_slot(position) : position; }
+// zeroes the values of keys past the end in the chunk at position kc, a multiple of 8 (the padding may hold anything)
 template <bool VSWAP>
 __device__ __forceinline__ u32x4v zero_past_end(u32x4v v, int kc, int Lk) {
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
     uint32_t x = v[w];
-    if (key_at<VSWAP>(kc, 2 * w) >= Lk) x &= 0xFFFF0000u;
-    if (key_at<VSWAP>(kc, 2 * w + 1) >= Lk) x &= 0x0000FFFFu;
+    if (key_at<VSWAP>(kc + 2 * w) >= Lk) x &= 0xFFFF0000u;
+    if (key_at<VSWAP>(kc + 2 * w + 1) >= Lk) x &= 0x0000FFFFu;
     v[w] = x;
   }
   return v;
@@ -293,10 +291,6 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(const AttnArg
 constexpr int WQ = 64, WIDE_QTILE = 4 * WQ;      // queries per wave, per workgroup
 constexpr int WIDE_STAGE = 2 * KTILE * 64 * 2;   // keys [64][64] and values [64][64] of one tile
 
-__device__ __forceinline__ void dma16(uint32_t off, const void* base, uint32_t lds_addr) {   // see gemm.hip
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr) : "memory");
-}
-
 __global__ __launch_bounds__(ATT_THREADS, 2) void attention_wide_kernel(const AttnArgs a) {
   constexpr int HD = 64, SLABS = 4, OT = 2;
   __shared__ __align__(16) unsigned char smem[2 * WIDE_STAGE];
@@ -355,6 +349,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_wide_kernel(const At
   };
   // values of keys past the end (padding may hold anything) are zeroed by the wave that fetched them
   auto zero_padding = [&](int kt) {
+    asm volatile("" ::: "memory");               // not read before the wait that the call follows
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int kc = kt * KTILE + s_ch[i] * 8;
@@ -504,7 +499,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_wide_kernel(const At
 
   request(0);
   for (int kt = 0; kt < n_tiles; ++kt) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);          // this wave's part of tile kt has arrived
+    wait_dma();                                  // this wave's part of tile kt has arrived
     const int rest = a.Lk - kt * KTILE;
     if (rest < KTILE) zero_padding(kt);
     __syncthreads();                             // everybody's part has, and everybody is done with the other stage

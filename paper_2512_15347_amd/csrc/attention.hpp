@@ -13,7 +13,7 @@ struct AttnArgs {
   int B, Lq, Lk, heads;
   float scale_log2;                               // log2(e) / sqrt(hd)
   int q_prescaled;                                // the producer of q has already multiplied it by scale_log2
-  int v_swapped;                                  // tokens t of vt are stored at value_slot(t) (gemm.hip)
+  int v_swapped;                                  // tokens t of vt are stored at value_slot(t) (operands.hpp)
   int kernel;                                     // 0: the launcher's choice, 1 / 2: 32 / 64 queries per wave (tests)
   int split; uint16_t* out2;                      // split > 0: queries >= split go to out2[b * (Lq - split) + q - split, :]
 };

@@ -23,6 +23,7 @@
 #include <cstdlib>
 #include <type_traits>
 #include "gemm.hpp"
+#include "operands.hpp"
 
 namespace pg {
 
@@ -41,23 +42,11 @@ constexpr int MI = 16, KS = 32;                    // 16x16x32 MFMA: lane l hold
 __device__ __forceinline__ int swz(int row) { return (row ^ ((row >> 3) & 1)) & 7; }
 __device__ __forceinline__ int lds_off(int row, int chunk) { return (row * CH + (chunk ^ swz(row))) * 16; }
 
-// 16 bytes per lane straight from global memory into LDS (no register staging): the wave writes the
-// 1 KB starting at LDS address `lds_addr` (wave-uniform), lane l at +16 l.  Issued through inline
-// assembly so that the operand reads of the other LDS stage are not made to wait for it; completion
-// is awaited explicitly (wait_dma) before the barrier that publishes the stage.  The statement overwrites m0
-// without naming it as clobbered: m0 is a reserved register for this compiler (it refuses it in a clobber list
-// and writes m0 itself directly before each instruction of its own that reads it), so no value of the
-// surrounding code lives in m0 across the statement.  The address is a wave-uniform base plus a 32-bit byte offset per
-// lane (no vector arithmetic per request); WIDE: a 64-bit address per lane, for rows too far apart for that.
-__device__ __forceinline__ void dma16(uint32_t off, const uint16_t* base, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr) : "memory");
-}
+// dma16 (operands.hpp) with a 64-bit address per lane, for rows too far apart for a 32-bit offset
 __device__ __forceinline__ void dma16_wide(const uint16_t* g, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_addr) : "memory");
 }
 constexpr int64_t NARROW_LD = 1 << 23;             // 255 rows of so many bf16, in bytes, fit 32 bits
-// wait until none of this wave's loads is in flight
-__device__ __forceinline__ void wait_dma() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // Outputs are written, and the residual stream is read, once per launch: they go through the caches
 // with the non-temporal hint so that the operand panels shared by the tiles of an XCD stay resident.
@@ -90,11 +79,6 @@ __device__ __forceinline__ uint2 pack_bf16x4(float4 v) {
   r.y = (uint32_t)f32_to_bf16_bits(v.z) | ((uint32_t)f32_to_bf16_bits(v.w) << 16);
   return r;
 }
-
-// Where token t of a transposed value row is stored: in every 16 tokens the second and third group of four change places,
-// which puts the eight tokens that a lane of the attention kernel multiplies at a time (4 h .. 4 h + 3 and 8 + 4 h .. 8 + 4 h + 3,
-// the order in which the score accumulators hold the keys) into one 16-byte chunk.
-__device__ __forceinline__ int value_slot(int t) { return (t & ~12) | ((t & 4) << 1) | ((t & 8) >> 1); }
 
 // orders this wave's LDS accesses around a hand-over between its lanes (LDS serves one wave's accesses in issue order;
 // this keeps the compiler from moving them across the hand-over)
@@ -490,7 +474,7 @@ static pg_status launch_tile(const GemmBatch<NPROB>& batch, hipStream_t s) {
 // step measured with the chip full and nearly idle (what limits a full chip is power and the operand traffic, a nearly
 // idle one the latency of a step):
 //   tile             full                   idle         tiles per compute unit
-//   BM x 256   0.00553 (BM + 64)    0.55 of that    1     (256: 42.5 us per round of K = 1536, 192: 33.7, 128: 25.8)
+//   BM x 256   0.00553 (BM + 64)    0.55 of that    1     (256: 42.5 us per round of K = 1536, 192: 33.7)
 //   128 x 128   0.52 (0.64 alone)   0.36            2
 //   128 x  64   0.30                0.28            3
 //    64 x  64   0.18                0.18            4
