@@ -538,8 +538,8 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_wide_kernel(const At
 // Rounds of workgroups through the chip (two wide or three narrow ones per compute unit; a part-empty last round counts half
 // as empty as it is) take the same time per key tile with either kernel, so the wide one wins where it needs clearly fewer:
 // measured from 0.8 of the narrow kernel's rounds down, and for sequences long enough that the tiles that take its general
-// route do not count (48 x 24 heads x 1178 tokens 547 -> 519 us at a ratio of 0.78, 30 x 4 x 2048 157 -> 143 at 0.71; but
-// 24 x 12 x 1024 98 -> 102 at 0.88, 96 x 10 x 410 77 -> 79 at 0.78).
+// route do not count.  Narrow / wide, us: 48 x 24 heads x 1178 tokens 536 / 504 and 16 x 24 x 1178 171 / 169 at a ratio of 0.78,
+// 30 x 4 x 2048 153 / 141 at 0.70, 64 x 4 x 512 27.8 / 28.0 at 0.6; but 24 x 12 x 1024 93 / 98 at 0.88, 96 x 10 x 410 76 / 80 at 0.78.
 static bool use_wide(int64_t wgs, int64_t wide_wgs, int Lk) {
   auto rounds = [](double load) { return load <= 1.0 ? 1.0 : 0.5 * (load + ceil(load)); };
   return Lk >= 480 && rounds(wide_wgs / 512.0) <= 0.8 * rounds(wgs / 768.0);

@@ -208,8 +208,9 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
 
 // ---- many groups: one lane per group ----
 // The wave-per-group form needs about 400 wave instructions per group, most of them cross-lane traffic (an all-pairs rank and
-// four fp64 scans by shuffles); it is issue bound (2^20 groups of 64 -> 16: 1.5 ms, 3 % of the memory rate; here 0.21 ms, bound by
-// issue at two waves per SIMD, 256 registers).  Here a lane
+// four fp64 scans by shuffles): 2^20 groups of 64 -> 16 took 1.53 ms, here 0.21 (64 groups in 4462 vector, 358 LDS and 141 load
+// instructions; with two waves per SIMD, 256 registers, the vector ALU issues in 0.56 of the cycles, some instruction is active in
+// 0.77, and a wave waits for memory and LDS for 0.43 of its time: instructions and exposed staging bound it together).  Here a lane
 // sorts its own group in registers by a compare-exchange network (Batcher's odd-even merge sort: 543 compare-exchanges for 64
 // slots, two instructions each, for 64 groups at once) and runs the scans of the same doubling recurrence on registers.
 // Only the values are sorted; members are picked afterwards by comparing them with the two threshold values, with
