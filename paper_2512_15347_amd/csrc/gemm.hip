@@ -65,7 +65,6 @@ __device__ __forceinline__ float4 load_stream(const float* p) {
 
 // gelu_tanh(x) = x/2 (1 + tanh(y)) = x / (1 + exp(-2y)),  y = sqrt(2/pi) (x + 0.044715 x^3);
 // the exponent is taken in base 2: -2 y log2(e) = x (K1 + K3 x^2)
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float gelu_tanh(float x) {
   constexpr float K1 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;
   constexpr float K3 = K1 * 0.044715f;
@@ -73,12 +72,13 @@ __device__ __forceinline__ float gelu_tanh(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z));
 }
 
-__device__ __forceinline__ uint2 pack_bf16x4(float4 v) {
-  uint2 r;
-  r.x = (uint32_t)f32_to_bf16_bits(v.x) | ((uint32_t)f32_to_bf16_bits(v.y) << 16);
-  r.y = (uint32_t)f32_to_bf16_bits(v.z) | ((uint32_t)f32_to_bf16_bits(v.w) << 16);
-  return r;
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// as vectors, so that one conversion takes two values (converted one by one they are put together by two more instructions)
+__device__ __forceinline__ uint32_t pack_bf16x2(float x, float y) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{x, y}, bf16x2));
 }
+__device__ __forceinline__ uint2 pack_bf16x4(float4 v) { return uint2{pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)}; }
 
 // orders this wave's LDS accesses around a hand-over between its lanes (LDS serves one wave's accesses in issue order;
 // this keeps the compiler from moving them across the hand-over)
@@ -87,8 +87,22 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Sum over 16 (wide) or 8 adjacent lanes, the same in each of them: a butterfly of data-parallel-primitive adds inside a row of
+// 16 lanes (quad permutations, then the mirrored half row and row, whose lanes hold the other quads' equal sums).  Shuffles
+// through LDS cost the dual-stream QKV launch of 28272 rows 80 of its 428 us.
+template <int CTRL>
+__device__ __forceinline__ float add_permuted(float v) {
+  const int w = __builtin_bit_cast(int, v);
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(w, w, CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float head_sum(float v, bool wide) {
+  v = add_permuted<0xB1>(v);                        // lane ^ 1
+  v = add_permuted<0x4E>(v);                        // lane ^ 2
+  v = add_permuted<0x141>(v);                       // 7 - lane inside 8 lanes
+  return wide ? add_permuted<0x140>(v) : v;         // 15 - lane inside 16 lanes
+}
+
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 // f(tag<I>, tag<n>) for consecutive groups of n = 4, 2 or 1 of the N row tiles while f returns true
 template <int I> struct int_tag { static constexpr int value = I; };
@@ -102,6 +116,20 @@ __device__ __forceinline__ void for_row_groups(F&& f) {
 
 // NP = 2: two problems of equal N and K in one launch, the tile rows of the second behind those of the first
 template <int NP> struct GemmBatch { GemmArgs g[NP]; };
+// The problem that a workgroup works on, chosen field by field: an array element picked at run time is read again from the
+// kernel arguments at every use (24576 + 3696 rows, GELU: 490 us, 455 like this; QKV with the head norm 410 and XXX).
+__device__ __forceinline__ GemmArgs chosen(const GemmBatch<1>& b, bool) { return b.g[0]; }
+__device__ __forceinline__ GemmArgs chosen(const GemmBatch<2>& b, bool second) {
+  const GemmArgs &x = b.g[0], &y = b.g[1];
+  GemmArgs a = x;                                    // N, K, the head norm's width, the scaled columns and Lout are equal
+#define PG_CHOOSE(field) a.field = second ? y.field : x.field
+  PG_CHOOSE(A); PG_CHOOSE(lda); PG_CHOOSE(W); PG_CHOOSE(ldw); PG_CHOOSE(bias); PG_CHOOSE(M);
+  PG_CHOOSE(outf); PG_CHOOSE(ldo); PG_CHOOSE(outb); PG_CHOOSE(ldob); PG_CHOOSE(L);
+  PG_CHOOSE(vt); PG_CHOOSE(Lpad); PG_CHOOSE(gate); PG_CHOOSE(gate_ld); PG_CHOOSE(group_of);
+  PG_CHOOSE(tok_off); PG_CHOOSE(qn_g); PG_CHOOSE(kn_g);
+#undef PG_CHOOSE
+  return a;
+}
 
 template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE, int NPROB>
 __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatch<NPROB> batch) {
@@ -122,10 +150,10 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
   const int band = group_m * tiles_n;
   const int first_m = (b / band) * group_m;
   const int gsz = min(tiles_m - first_m, group_m);
-  const int tm = first_m + (b % band) % gsz;
-  const int tn = (b % band) / gsz;
+  const int tm = __builtin_amdgcn_readfirstlane(first_m + (b % band) % gsz);
+  const int tn = __builtin_amdgcn_readfirstlane((b % band) / gsz);
   const bool second = NPROB > 1 && tm >= rows0;
-  const GemmArgs& a = batch.g[second ? NPROB - 1 : 0];
+  const GemmArgs a = chosen(batch, second);
   const int m0 = (second ? tm - rows0 : tm) * BM, n0 = tn * BN;
   const uint16_t* PA = a.A; const int64_t LDA = a.lda;
   const uint16_t* PW = a.W; const int64_t LDW = a.ldw;
@@ -136,11 +164,16 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
   const int wm = wave / WN, wn = wave % WN;
   const int lr = lane % MI, lk = lane / MI;
 
+  const int row_w = m0 + wm * (BM / WM), col_w = n0 + wn * CW;       // first row and column of this wave
+  // The accumulators start at the bias: in each 16x16 tile a lane holds one column, so it is one value per tile, loaded while
+  // the first operands are under way, instead of an add per result in the epilogue.
+  float bias[FN];
+#pragma unroll
+  for (int j = 0; j < FN; ++j) {
+    const int col = col_w + j * MI + lr;
+    bias[j] = PB && col < NN ? bf16_to_f32(PB[col]) : 0.f;
+  }
   f32x4v acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
 
   {
     // ---- global -> LDS directly: a stage is N_REG regions of 1 KB (8 tile rows), dealt to the waves in turn ----
@@ -233,13 +266,16 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
     }
 #pragma unroll
     for (int f = 0; f < FR; ++f) fetch(0, 0, 0, f);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] = f32x4v{bias[j], bias[j], bias[j], bias[j]};
     for (int kt = 0; kt + 2 < nk; ++kt) step(kt, std::true_type{}, std::true_type{});
     if (nk > 1) step(nk - 2, std::false_type{}, std::true_type{});
     step(nk - 1, std::false_type{}, std::false_type{});
   }
 
   // ---- epilogue: in each 16x16 accumulator tile a lane holds ONE column (lr) and rows 4 lk + t ----
-  const int row_w = m0 + wm * (BM / WM), col_w = n0 + wn * CW;       // first row and column of this wave
   if constexpr (EPI != EPI_UNPATCH) {
     // ---- row-major epilogues: transpose each 32-row slab of the wave tile through LDS so that a lane
     // owns 4 consecutive columns of a row and every global access is 16 bytes wide (8 for bf16) ----
@@ -262,17 +298,11 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
       // channels or none (v_start is a multiple of 32). ----
       uint16_t* stg16 = reinterpret_cast<uint16_t*>(stg);
       const int Dv = NN - n_rm;
-      bool is_v[FN];
-      float vb[FN];
       bool any_v = false;
 #pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        const int col = col_w + j * MI;
-        is_v[j] = col >= n_rm && col < NN;           // wave-uniform
-        any_v = any_v || is_v[j];
-        vb[j] = (is_v[j] && PB) ? bf16_to_f32(PB[col + lr]) : 0.f;
-      }
+      for (int j = 0; j < FN; ++j) any_v = any_v || (col_w + j * MI >= n_rm && col_w + j * MI < NN);   // wave-uniform
       if (any_v) {
+        const bool all_v = col_w >= n_rm && col_w + CW <= NN;
         for_row_groups<0, FM>([&](auto first, auto count) {
           constexpr int i0 = decltype(first)::value, nt = decltype(count)::value;    // row tiles staged together
           const int row0 = row_w + i0 * MI;          // first token row of the group, wave-uniform
@@ -281,32 +311,42 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
           for (int ii = 0; ii < nt; ++ii)
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
-              if (!is_v[j]) continue;
               const f32x4v t = acc[i0 + ii][j];
-              const float4 v = {t[0] + vb[j], t[1] + vb[j], t[2] + vb[j], t[3] + vb[j]};
-              *reinterpret_cast<uint2*>(stg16 + (j * MI + lr) * VP + ii * MI + 4 * lk) = pack_bf16x4(v);
+              *reinterpret_cast<uint2*>(stg16 + (j * MI + lr) * VP + ii * MI + 4 * lk) = pack_bf16x4({t[0], t[1], t[2], t[3]});
             }
           wave_lds_sync();
           constexpr int lpr = 4 * nt, rpa = 64 / lpr;    // lanes per channel row, channel rows per access
           const int t4 = (lane % lpr) * 4, csub = lane / lpr;
-          const int r = row0 + t4;                   // the lane's first token row
-          const int traj0 = r / a.L, tok0 = r - traj0 * a.L;
-          const bool whole = r + 3 < MM && tok0 + 3 < a.L && ((tok0 + a.tok_off) & 1) == 0;
+          const int traj_w = row0 / a.L, tok_w = row0 - traj_w * a.L, at_w = a.tok_off + tok_w;     // wave-uniform
+          if (all_v && row0 + nt * MI <= MM && tok_w + nt * MI <= a.L && (at_w & 1) == 0) {
+            // the whole group is one trajectory's: 8 bytes per lane, or two pairs where its tokens start in the middle of four
+            const int at = at_w + t4;
+            uint16_t* dst = a.vt + ((int64_t)traj_w * Dv + (col_w - n_rm) + csub) * a.Lpad;
+            const uint16_t* src = stg16 + csub * VP + t4;
+            const int64_t step_v = (int64_t)rpa * a.Lpad;
+            if ((at_w & 3) == 0) {
+              dst += value_slot(at);
 #pragma unroll
-          for (int p = 0; p < CW / rpa; ++p) {
-            const int cl = p * rpa + csub;           // channel row inside the wave's columns
-            const bool mine = col_w + cl >= n_rm && col_w + cl < NN;
-            if (!mine || r >= MM) continue;
-            const uint2 pk = *reinterpret_cast<const uint2*>(stg16 + cl * VP + t4);
-            const int ch = col_w + cl - n_rm;
-            uint16_t* dst = a.vt + ((int64_t)traj0 * Dv + ch) * a.Lpad;
-            const int at = a.tok_off + tok0;
-            if (whole && (at & 3) == 0) {                                // one unit of four tokens
-              store_stream(dst + value_slot(at), pk);
-            } else if (whole) {                                        // two pairs: tok_off + tok0 is even
-              *reinterpret_cast<uint32_t*>(dst + value_slot(at)) = pk.x;
-              *reinterpret_cast<uint32_t*>(dst + value_slot(at + 2)) = pk.y;
+              for (int p = 0; p < CW / rpa; ++p, dst += step_v) store_stream(dst, *reinterpret_cast<const uint2*>(src + p * rpa * VP));
             } else {
+              uint16_t* dst2 = dst + value_slot(at + 2);
+              dst += value_slot(at);
+#pragma unroll
+              for (int p = 0; p < CW / rpa; ++p, dst += step_v, dst2 += step_v) {
+                const uint2 pk = *reinterpret_cast<const uint2*>(src + p * rpa * VP);
+                *reinterpret_cast<uint32_t*>(dst) = pk.x;
+                *reinterpret_cast<uint32_t*>(dst2) = pk.y;
+              }
+            }
+          } else {
+            const int r = row0 + t4;                 // the lane's first token row
+            const int traj0 = r / a.L, tok0 = r - traj0 * a.L;
+#pragma unroll 1
+            for (int p = 0; p < CW / rpa; ++p) {
+              const int cl = p * rpa + csub;         // channel row inside the wave's columns
+              const int ch = col_w + cl - n_rm;
+              if (ch < 0 || ch >= Dv) continue;
+              const uint2 pk = *reinterpret_cast<const uint2*>(stg16 + cl * VP + t4);
               const uint16_t e[4] = {(uint16_t)pk.x, (uint16_t)(pk.x >> 16), (uint16_t)pk.y, (uint16_t)(pk.y >> 16)};
               int traj = traj0, tok = tok0;
 #pragma unroll
@@ -327,101 +367,102 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
     }
     const bool n_ok = n < n_rm;                      // N is a multiple of 4
     const float col_scale = n < a.scale_cols ? a.out_scale : 1.f;   // e.g. queries pre-multiplied by the softmax scale
+    const float inv_hd = a.norm_hd == 64 ? 1.f / 64.f : 1.f / 32.f;
     float4 ng4 = {1.f, 1.f, 1.f, 1.f};               // norm scales of this lane's 4 columns
     if (EPI == EPI_QKV && a.norm_hd > 0 && n_ok) {
       const uint2 raw = *reinterpret_cast<const uint2*>((n < a.scale_cols ? a.qn_g : a.kn_g) + n % a.norm_hd);
       ng4 = {bf16_to_f32((uint16_t)raw.x), bf16_to_f32((uint16_t)(raw.x >> 16)), bf16_to_f32((uint16_t)raw.y),
              bf16_to_f32((uint16_t)(raw.y >> 16))};
     }
-    float4 b4 = {0.f, 0.f, 0.f, 0.f};
-    if (PB && n_ok) {
-      const uint2 raw = *reinterpret_cast<const uint2*>(PB + n);
-      b4 = {bf16_to_f32((uint16_t)raw.x), bf16_to_f32((uint16_t)(raw.x >> 16)), bf16_to_f32((uint16_t)raw.y),
-            bf16_to_f32((uint16_t)(raw.y >> 16))};
-    }
+    // The row map of the layers that have one is linear inside a trajectory: row r = traj * per_traj + tok of the problem goes
+    // to row r + shift + traj * gap.  A slab of 32 rows touches at most two trajectories when one has at least 32 rows; a
+    // division per row and access (`per_row`) is left to shorter ones.
+    const bool mapped = EPI == EPI_EMBED || (EPI == EPI_QKV && a.Lout > 0);
+    const int per_traj = EPI == EPI_EMBED ? a.Li : a.L;
+    const int gap = EPI == EPI_EMBED ? a.L - a.Li : a.Lout - a.L, shift = EPI == EPI_QKV ? a.tok_off : 0;
+    const bool per_row = per_traj < 32;
+    constexpr bool F32 = EPI == EPI_F32 || EPI == EPI_EMBED || EPI == EPI_RESID;
+    typedef std::conditional_t<F32, float, uint16_t> out_t;
+    const int64_t ld = F32 ? a.ldo : a.ldob;
+    out_t* const out_w = [&] { if constexpr (F32) return a.outf; else return a.outb; }() + (int64_t)(row_w + rsub) * ld + n;
+    // FULL: every row of the wave's tile and every column of the lane exist, so no access is masked
+    auto slabs = [&](auto full_c) {
+      constexpr bool FULL = decltype(full_c)::value;
 #pragma unroll
-    for (int i = 0; i < FM; i += 2) {
-      const int slab0 = row_w + i * MI;                          // wave-uniform
-      if (slab0 >= a.M) break;
-      const int np = i + 1 < FM ? NP : NP / 2;                   // an odd last row tile is half a slab
+      for (int i = 0; i < FM; i += 2) {
+        const int slab0 = row_w + i * MI;                          // wave-uniform
+        if (!FULL && slab0 >= MM) break;
+        const int np = i + 1 < FM ? NP : NP / 2;                   // an odd last row tile is half a slab
 #pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
-        if (i + ii < FM)
+        for (int ii = 0; ii < 2; ++ii)
+          if (i + ii < FM)
 #pragma unroll
-          for (int j = 0; j < FN; ++j)
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) stg[(ii * MI + 4 * lk + t) * EST + j * MI + lr] = acc[i + ii < FM ? i + ii : 0][j][t];
-      float4 v[NP];
-#pragma unroll
-      for (int p = 0; p < np; ++p) {
-        v[p] = *reinterpret_cast<const float4*>(stg + (RPI * p + rsub) * EST + c4);
-        v[p].x += b4.x; v[p].y += b4.y; v[p].z += b4.z; v[p].w += b4.w;
-        if (EPI == EPI_QKV && a.norm_hd > 0) {
-          // RMS norm over the head chunk this lane's 4 columns belong to (norm_hd / 4 adjacent lanes of the row)
-          float ss = (v[p].x * v[p].x + v[p].y * v[p].y) + (v[p].z * v[p].z + v[p].w * v[p].w);
-          for (int o = 1; o < a.norm_hd / 4; o <<= 1) ss += __shfl_xor(ss, o, 64);
-          const float rstd = rsqrtf(ss / (float)a.norm_hd + 1e-6f);
-          v[p].x *= rstd * ng4.x; v[p].y *= rstd * ng4.y; v[p].z *= rstd * ng4.z; v[p].w *= rstd * ng4.w;
-        }
-        if (EPI == EPI_BF16 || EPI == EPI_QKV) { v[p].x *= col_scale; v[p].y *= col_scale; v[p].z *= col_scale; v[p].w *= col_scale; }
-      }
-      if (EPI == EPI_RESID) {
-        // gates are per (group, column); a slab of 32 rows touches at most two trajectories when a
-        // trajectory has at least 32 rows.  All loads of the slab are issued before its stores.
-        float4 g0 = {1.f, 1.f, 1.f, 1.f}, g1 = g0;
-        const bool fast = a.L >= 32;
-        const int traj0 = slab0 / a.L;
-        const int split = (traj0 + 1) * a.L;
-        if (a.gate && fast && n_ok) {
-          const int last = (a.M - 1) / a.L;
-          g0 = *reinterpret_cast<const float4*>(a.gate + (int64_t)a.group_of[traj0] * a.gate_ld + n);
-          g1 = *reinterpret_cast<const float4*>(a.gate + (int64_t)a.group_of[min(traj0 + 1, last)] * a.gate_ld + n);
-        }
-        float4 hv[NP], gv[NP];
+              for (int t = 0; t < 4; ++t) stg[(ii * MI + 4 * lk + t) * EST + j * MI + lr] = acc[i + ii < FM ? i + ii : 0][j][t];
+        float4 v[NP];
 #pragma unroll
         for (int p = 0; p < np; ++p) {
-          const int r = slab0 + RPI * p + rsub;
-          const bool ok = r < a.M && n_ok;
-          hv[p] = ok ? load_stream(a.outf + (int64_t)r * a.ldo + n) : float4{0.f, 0.f, 0.f, 0.f};
-          gv[p] = r < split ? g0 : g1;
-          if (a.gate && !fast && ok)
-            gv[p] = *reinterpret_cast<const float4*>(a.gate + (int64_t)a.group_of[r / a.L] * a.gate_ld + n);
+          v[p] = *reinterpret_cast<const float4*>(stg + (RPI * p + rsub) * EST + c4);
+          if (EPI == EPI_QKV && a.norm_hd > 0) {
+            // RMS norm over the head chunk this lane's 4 columns belong to (norm_hd / 4 adjacent lanes of the row)
+            const float ss = (v[p].x * v[p].x + v[p].y * v[p].y) + (v[p].z * v[p].z + v[p].w * v[p].w);
+            const float rstd = rsqrtf(head_sum(ss, a.norm_hd == 64) * inv_hd + 1e-6f);
+            v[p].x *= rstd * ng4.x; v[p].y *= rstd * ng4.y; v[p].z *= rstd * ng4.z; v[p].w *= rstd * ng4.w;
+          }
+          if (EPI == EPI_BF16 || EPI == EPI_QKV) { v[p].x *= col_scale; v[p].y *= col_scale; v[p].z *= col_scale; v[p].w *= col_scale; }
         }
+        auto exists = [&](int p) { return FULL || (slab0 + RPI * p + rsub < MM && n_ok); };
+        out_t* const out_i = out_w + (int64_t)(i * MI) * ld;
+        // trajectory of the slab's first row, and the first row of the next one
+        const int traj0 = EPI == EPI_RESID || mapped ? slab0 / per_traj : 0, split = (traj0 + 1) * per_traj;
+        if constexpr (EPI == EPI_RESID) {
+          // gates are per (group, column).  All loads of the slab are issued before its stores.
+          float4 g0 = {1.f, 1.f, 1.f, 1.f}, g1 = g0;
+          if (a.gate && !per_row && n_ok) {
+            const int last = (MM - 1) / a.L;
+            g0 = *reinterpret_cast<const float4*>(a.gate + (int64_t)a.group_of[traj0] * a.gate_ld + n);
+            g1 = *reinterpret_cast<const float4*>(a.gate + (int64_t)a.group_of[min(traj0 + 1, last)] * a.gate_ld + n);
+          }
+          float4 hv[NP], gv[NP];
 #pragma unroll
-        for (int p = 0; p < np; ++p) {
-          const int r = slab0 + RPI * p + rsub;
-          if (r < a.M && n_ok) {
-            float4 o = {hv[p].x + gv[p].x * v[p].x, hv[p].y + gv[p].y * v[p].y, hv[p].z + gv[p].z * v[p].z,
-                        hv[p].w + gv[p].w * v[p].w};
-            store_stream(a.outf + (int64_t)r * a.ldo + n, o);
+          for (int p = 0; p < np; ++p) {
+            const int r = slab0 + RPI * p + rsub;
+            hv[p] = exists(p) ? load_stream(out_i + (int64_t)(RPI * p) * ld) : float4{0.f, 0.f, 0.f, 0.f};
+            gv[p] = r < split ? g0 : g1;
+            if (a.gate && per_row && exists(p))
+              gv[p] = *reinterpret_cast<const float4*>(a.gate + (int64_t)a.group_of[r / a.L] * a.gate_ld + n);
+          }
+#pragma unroll
+          for (int p = 0; p < np; ++p)
+            if (exists(p))
+              store_stream(out_i + (int64_t)(RPI * p) * ld, float4{hv[p].x + gv[p].x * v[p].x, hv[p].y + gv[p].y * v[p].y,
+                                                                   hv[p].z + gv[p].z * v[p].z, hv[p].w + gv[p].w * v[p].w});
+        } else {
+#pragma unroll
+          for (int p = 0; p < np; ++p) {
+            if (!exists(p)) continue;
+            out_t* dst = out_i + (int64_t)(RPI * p) * ld;
+            const int r = slab0 + RPI * p + rsub;
+            const int traj = mapped && per_row ? r / per_traj : r < split ? traj0 : traj0 + 1;
+            if (mapped) dst += ((int64_t)traj * gap + shift) * ld;
+            if constexpr (EPI == EPI_F32) {
+              store_stream(dst, v[p]);
+            } else if constexpr (EPI == EPI_EMBED) {
+              const uint2 raw = *reinterpret_cast<const uint2*>(a.pos + (int64_t)(r - traj * a.Li) * a.N + n);
+              store_stream(dst, float4{v[p].x + bf16_to_f32((uint16_t)raw.x), v[p].y + bf16_to_f32((uint16_t)(raw.x >> 16)),
+                                       v[p].z + bf16_to_f32((uint16_t)raw.y), v[p].w + bf16_to_f32((uint16_t)(raw.y >> 16))});
+            } else if constexpr (EPI == EPI_GELU) {
+              store_stream(dst, pack_bf16x4({gelu_tanh(v[p].x), gelu_tanh(v[p].y), gelu_tanh(v[p].z), gelu_tanh(v[p].w)}));
+            } else {
+              store_stream(dst, pack_bf16x4(v[p]));
+            }
           }
         }
-        continue;
       }
-#pragma unroll
-      for (int p = 0; p < np; ++p) {
-        const int r = slab0 + RPI * p + rsub;
-        if (r >= a.M || !n_ok) continue;
-        if (EPI == EPI_F32) {
-          store_stream(a.outf + (int64_t)r * a.ldo + n, v[p]);
-        } else if (EPI == EPI_EMBED) {
-          const int traj = r / a.Li, tok = r - traj * a.Li;
-          const uint2 raw = *reinterpret_cast<const uint2*>(a.pos + (int64_t)tok * a.N + n);
-          float4 o = {v[p].x + bf16_to_f32((uint16_t)raw.x), v[p].y + bf16_to_f32((uint16_t)(raw.x >> 16)),
-                      v[p].z + bf16_to_f32((uint16_t)raw.y), v[p].w + bf16_to_f32((uint16_t)(raw.y >> 16))};
-          store_stream(a.outf + ((int64_t)traj * a.L + tok) * a.ldo + n, o);
-        } else if (EPI == EPI_BF16) {
-          store_stream(a.outb + (int64_t)r * a.ldob + n, pack_bf16x4(v[p]));
-        } else if (EPI == EPI_QKV) {
-          int64_t ro = r;
-          if (a.Lout > 0) { const int traj = r / a.L; ro = (int64_t)traj * a.Lout + a.tok_off + (r - traj * a.L); }
-          store_stream(a.outb + ro * a.ldob + n, pack_bf16x4(v[p]));
-        } else if (EPI == EPI_GELU) {
-          const float4 gl = {gelu_tanh(v[p].x), gelu_tanh(v[p].y), gelu_tanh(v[p].z), gelu_tanh(v[p].w)};
-          store_stream(a.outb + (int64_t)r * a.ldob + n, pack_bf16x4(gl));
-        }
-      }
-    }
+    };
+    if (row_w + BM / WM <= MM && col_w + CW <= n_rm) slabs(std::true_type{});
+    else slabs(std::false_type{});
     return;
   }
   // ---- unpatchify: per-element scatter into the latent layout (small: N = 4C columns) ----
@@ -434,7 +475,6 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
     for (int j = 0; j < FN; ++j) {
       const int n = col_w + j * MI + lr;
       if (n >= a.N) continue;
-      const float bias = a.bias ? bf16_to_f32(a.bias[n]) : 0.f;
       int traj = traj0, tok = tok0;
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
@@ -443,7 +483,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
         const int py = tok / a.Wp, px = tok - py * a.Wp;
         const int c = n >> 2, dy = (n >> 1) & 1, dx = n & 1;
         a.outf[(int64_t)traj * ((int64_t)(a.N >> 2) * a.HW) + (int64_t)c * a.HW + (2 * py + dy) * a.Wimg + 2 * px + dx] =
-            acc[i][j][t] + bias;
+            acc[i][j][t];
         ++tok;
       }
     }
@@ -584,7 +624,9 @@ pg_status launch_gemm(const GemmArgs& a_in, int epilogue, hipStream_t s) {
 // stream alone is a few dozen tiles, which left most of the 256 compute units idle for as long as the image stream's tiles take.
 pg_status launch_gemm_pair(const GemmArgs& first, const GemmArgs& second, int epilogue, hipStream_t s) {
   if (first.M <= 0 || second.M <= 0) return launch_gemm(first.M > 0 ? first : second, epilogue, s);
-  if (first.N != second.N || first.K != second.K) return fail(PG_EINVAL, "GEMM pair: different layers");
+  if (first.N != second.N || first.K != second.K || first.norm_hd != second.norm_hd || first.out_scale != second.out_scale ||
+      first.scale_cols != second.scale_cols || first.v_start != second.v_start || first.Lout != second.Lout)
+    return fail(PG_EINVAL, "GEMM pair: different layers");
   GemmBatch<2> batch{{first, second}};
   for (GemmArgs& g : batch.g) {
     PG_TRY(check_gemm(g, epilogue));
