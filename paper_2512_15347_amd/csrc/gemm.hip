@@ -131,6 +131,12 @@ __device__ __forceinline__ GemmArgs chosen(const GemmBatch<2>& b, bool second) {
   return a;
 }
 
+// Slabs of the residual stream that a wave loads ahead of the epilogue (EPI_RESID): the read half of its read-modify-write then
+// runs beside the last MFMAs instead of after them, when every compute unit wants the memory at once.  The whole tile where
+// registers allow it (24576 x 768 x 768 with 160-row tiles: 57.3 -> 50.0 us, 12288 rows 28.3 -> 24.1), a third of a 192-row
+// tile (14136 x 1536 x 1536: 85.9 -> 82.3), nothing of taller ones (one slab of a 224-row tile spills: 437 -> 446 us).
+constexpr int prefetched_slabs(int bm, int slabs) { return bm >= 224 ? 0 : bm == 192 ? 1 : slabs; }
+
 template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE, int NPROB>
 __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatch<NPROB> batch) {
   constexpr int WAVES = WM * WN;
@@ -174,6 +180,22 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
     bias[j] = PB && col < NN ? bf16_to_f32(PB[col]) : 0.f;
   }
   f32x4v acc[FM][FN];
+  // EPI_RESID: PF slabs of 32 rows of the residual stream are loaded while the last one and a half K steps run (rows and columns
+  // past the end repeat existing ones)
+  constexpr int LPR = CW / 4, RPI = 64 / LPR, NP = 32 / RPI;     // epilogue: lanes per row, rows per access, accesses per slab
+  constexpr int SLABS_M = (FM + 1) / 2;
+  constexpr int PF = EPI != EPI_RESID ? 0 : prefetched_slabs(BM, SLABS_M);
+  f32x4v hpre[PF > 0 ? PF : 1][NP];
+  auto prefetch = [&] {
+    const int n = col_w + (lane % LPR) * 4, rsub = lane / LPR;
+    const float* base = a.outf + (n < NN ? n : 0);
+#pragma unroll
+    for (int i = 0; i < PF; ++i)
+#pragma unroll
+      for (int p = 0; p < (2 * i + 1 < FM ? NP : NP / 2); ++p)
+        hpre[i][p] = __builtin_nontemporal_load(reinterpret_cast<const f32x4v*>(
+            base + (int64_t)min(row_w + 32 * i + RPI * p + rsub, MM - 1) * a.ldo));
+  };
 
   {
     // ---- global -> LDS directly: a stage is N_REG regions of 1 KB (8 tile rows), dealt to the waves in turn ----
@@ -231,6 +253,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
         if (last && NEXT) {
           wait_dma();
           __syncthreads();
+          if (!REQ) prefetch();
         }
         const int stage = (last ? kt + 1 : kt) & 1, to = (ks + 1) & 1;
         __builtin_amdgcn_sched_barrier(0);
@@ -272,6 +295,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
       for (int j = 0; j < FN; ++j) acc[i][j] = f32x4v{bias[j], bias[j], bias[j], bias[j]};
     for (int kt = 0; kt + 2 < nk; ++kt) step(kt, std::true_type{}, std::true_type{});
     if (nk > 1) step(nk - 2, std::false_type{}, std::true_type{});
+    else prefetch();
     step(nk - 1, std::false_type{}, std::false_type{});
   }
 
@@ -279,15 +303,15 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
   if constexpr (EPI != EPI_UNPATCH) {
     // ---- row-major epilogues: transpose each 32-row slab of the wave tile through LDS so that a lane
     // owns 4 consecutive columns of a row and every global access is 16 bytes wide (8 for bf16) ----
-    constexpr int LPR = CW / 4, RPI = 64 / LPR, NP = 32 / RPI;   // lanes per row, rows per access, accesses per slab
     constexpr int EST = CW + 4;                      // staging row stride in floats: 4 rows down are 16 banks on
     constexpr int VP = 72;                           // pitch of the transposed staging in bf16: 64 tokens + 8 (16-byte aligned rows)
     constexpr int STG = CW * VP * 2;                 // staging bytes per wave
     static_assert(32 * EST * 4 <= STG && WAVES * STG <= 2 * STAGE_BYTES, "the staging areas fit");
     __syncthreads();                                 // every wave has finished reading the last stage
     float* stg = reinterpret_cast<float*>(smem + wave * STG);
-    const int c4 = (lane % LPR) * 4, rsub = lane / LPR;
-    const int n = col_w + c4;
+    int lane_e = lane;
+    if (PF > 0) asm volatile("" : "+v"(lane_e));     // what follows from it is not carried through the K loop
+    const int c4 = (lane_e % LPR) * 4, rsub = lane_e / LPR, n = col_w + c4;
     // columns written row-major: all of them, except the value channels of EPI_QKV
     const int n_rm = EPI == EPI_QKV ? a.v_start : NN;
     if (EPI == EPI_QKV) {
@@ -428,7 +452,8 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
 #pragma unroll
           for (int p = 0; p < np; ++p) {
             const int r = slab0 + RPI * p + rsub;
-            hv[p] = exists(p) ? load_stream(out_i + (int64_t)(RPI * p) * ld) : float4{0.f, 0.f, 0.f, 0.f};
+            if (i / 2 < PF) hv[p] = __builtin_bit_cast(float4, hpre[i / 2 < PF ? i / 2 : 0][p]);
+            else hv[p] = exists(p) ? load_stream(out_i + (int64_t)(RPI * p) * ld) : float4{0.f, 0.f, 0.f, 0.f};
             gv[p] = r < split ? g0 : g1;
             if (a.gate && per_row && exists(p))
               gv[p] = *reinterpret_cast<const float4*>(a.gate + (int64_t)a.group_of[r / a.L] * a.gate_ld + n);
