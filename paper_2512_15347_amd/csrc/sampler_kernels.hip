@@ -6,6 +6,7 @@
 // trajectory and moves it with 16-byte accesses; per-trajectory sums are written as one partial per
 // workgroup and finished by a second tiny kernel in a fixed order (fp64), so results do not depend
 // on scheduling.
+#include <type_traits>
 #include "ctx.hpp"
 #include "philox.hpp"
 
@@ -42,13 +43,65 @@ __global__ __launch_bounds__(STREAM_THREADS) void init_latents_kernel(
   }
 }
 
-// x_out[r] = A x[q] + B u[q] + C xi, q = src ? src[r] : r; partial of sum xi^2 per workgroup.
-__global__ __launch_bounds__(STREAM_THREADS) void sde_step_kernel(
+// ---- sums over a trajectory: one partial per chunk of STREAM_CHUNK elements (256 lanes), added up in fp64 in a fixed order ----
+// Two decompositions with the same partials and the same order, hence the same bits:
+//   a workgroup per chunk, whose partials a second launch adds up;
+//   a workgroup per trajectory of at most four chunks, 256 lanes for each, which adds up its own partials: no second launch, whose
+//   2 to 3 us a loop pays at every step.  Update, us a call: 64 x 1024 11.2 -> 9.4, 64 x 16384 11.2 -> 9.0, 384 x 16384
+//   15.6 -> 14.7; from about 512 trajectories on the second launch is hidden and the larger workgroups fill the chip less
+//   evenly (1024 x 16384: 36.0 -> 36.8), and a workgroup that walks more chunks is slower (256 x 65536: 36.0 -> 36.6,
+//   272 x 65536: 38.0 -> 52.2).
+constexpr int ROW_GROUPS = 4;
+static bool row_per_workgroup(int64_t n_traj, int chunks) { return chunks == 1 || (chunks <= ROW_GROUPS && n_traj <= 512); }
+
+// Sum of `chunks` values partial(c) by one wavefront, the same in every lane
+template <class F>
+__device__ __forceinline__ double wave_sum_of(int chunks, F partial) {
+  double s = 0.0;
+  for (int c = threadIdx.x & (WAVE - 1); c < chunks; c += WAVE) s += (double)partial(c);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, WAVE);
+  return s;
+}
+// A workgroup of GROUPS x 256 lanes, 256 for each of `chunks` <= GROUPS chunks: `v` is the lane's share of its chunk (0 past the last
+// one); finish(sum) is called by the first wave.
+template <int GROUPS, class Finish>
+__device__ __forceinline__ void row_sum(int chunks, float v, Finish finish) {
+  __shared__ float part[GROUPS][4];
+  v = wave_sum(v);
+  if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x / STREAM_THREADS][(threadIdx.x / WAVE) & 3] = v;
+  __syncthreads();
+  if (threadIdx.x < WAVE) finish(wave_sum_of(chunks, [&](int i) { return (part[i][0] + part[i][1]) + (part[i][2] + part[i][3]); }));
+}
+// launch(tag<GROUPS>) with the smallest workgroup that holds the chunks (0: a workgroup per chunk)
+template <int N> struct groups_tag { static constexpr int value = N; };
+template <class F>
+static void with_groups(int chunks, F launch) {
+  if (chunks == 0) launch(groups_tag<0>{});
+  else if (chunks == 1) launch(groups_tag<1>{});
+  else if (chunks == 2) launch(groups_tag<2>{});
+  else launch(groups_tag<ROW_GROUPS>{});
+}
+
+struct LogProb { float* logp; float* hist; float* sum; double log_norm; };
+// logp[r] = -1/2 s - d (ln C + 1/2 ln 2 pi); history and running sum by original id
+__device__ __forceinline__ void finish_logprob(const LogProb& o, int r, int id, double s) {
+  const float lp = (float)(-0.5 * s - o.log_norm);
+  if (o.logp) o.logp[r] = lp;
+  if (o.hist) o.hist[id] = lp;
+  if (o.sum) o.sum[id] += lp;
+}
+
+// x_out[r] = A x[q] + B u[q] + C xi, q = src ? src[r] : r; sum xi^2 per trajectory.  GROUPS 0: a workgroup per chunk,
+// which leaves its partial; else a workgroup of GROUPS x 256 lanes per trajectory.
+template <int GROUPS>
+__global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_step_kernel(
     const float* __restrict__ x, const float* __restrict__ u, float* __restrict__ x_out,
     const int32_t* __restrict__ src, const int32_t* __restrict__ orig_id, int d4, int chunks, float A,
     float B, float C, uint32_t k0, uint32_t k1, uint32_t step, float* __restrict__ partials,
-    float* __restrict__ hist_next) {
-  const int r = blockIdx.x / chunks, c = blockIdx.x - r * chunks;
+    float* __restrict__ hist_next, const LogProb out) {
+  const int r = GROUPS ? blockIdx.x : blockIdx.x / chunks, c = GROUPS ? threadIdx.x / STREAM_THREADS : blockIdx.x - r * chunks;
+  const int lane256 = GROUPS > 1 ? threadIdx.x & (STREAM_THREADS - 1) : threadIdx.x;
   const int q = src ? src[r] : r;
   const uint32_t id = (uint32_t)orig_id[r];
   f32x4* hn = hist_next ? reinterpret_cast<f32x4*>(hist_next) + (size_t)id * d4 : nullptr;
@@ -59,7 +112,7 @@ __global__ __launch_bounds__(STREAM_THREADS) void sde_step_kernel(
   int e4[STREAM_ITERS];
 #pragma unroll
   for (int it = 0; it < STREAM_ITERS; ++it) {
-    e4[it] = c * (STREAM_CHUNK / 4) + it * STREAM_THREADS + threadIdx.x;
+    e4[it] = c * (STREAM_CHUNK / 4) + it * STREAM_THREADS + lane256;
     if (e4[it] < d4) {
       xv[it] = __builtin_nontemporal_load(xq + e4[it]);
       uv[it] = __builtin_nontemporal_load(uq + e4[it]);
@@ -80,8 +133,12 @@ __global__ __launch_bounds__(STREAM_THREADS) void sde_step_kernel(
       acc += (z.x * z.x + z.y * z.y) + (z.z * z.z + z.w * z.w);
     }
   }
-  const float t = block_sum_256(acc);
-  if (threadIdx.x == 0) partials[blockIdx.x] = t;
+  if constexpr (GROUPS > 0) {
+    row_sum<GROUPS>(chunks, acc, [&](double s) { if (threadIdx.x == 0) finish_logprob(out, r, (int)id, s); });
+  } else {
+    const float t = block_sum_256(acc);
+    if (threadIdx.x == 0) partials[blockIdx.x] = t;
+  }
 }
 
 // The same update with the latents and the network output stored as bf16 (6 instead of 12 bytes per element):
@@ -94,11 +151,13 @@ __device__ __forceinline__ uint32_t bf_pack(float a, float b) {
   return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)a) | ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)b) << 16);
 }
 
-__global__ __launch_bounds__(STREAM_THREADS) void sde_step_bf16_kernel(
+template <int GROUPS>
+__global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_step_bf16_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ u, uint16_t* __restrict__ x_out,
     const int32_t* __restrict__ src, const int32_t* __restrict__ orig_id, int d8, int chunks, float A, float B,
-    float C, uint32_t k0, uint32_t k1, uint32_t step, float* __restrict__ partials) {
-  const int r = blockIdx.x / chunks, c = blockIdx.x - r * chunks;
+    float C, uint32_t k0, uint32_t k1, uint32_t step, float* __restrict__ partials, const LogProb out) {
+  const int r = GROUPS ? blockIdx.x : blockIdx.x / chunks, c = GROUPS ? threadIdx.x / STREAM_THREADS : blockIdx.x - r * chunks;
+  const int lane256 = GROUPS > 1 ? threadIdx.x & (STREAM_THREADS - 1) : threadIdx.x;
   const int q = src ? src[r] : r;
   const uint32_t id = (uint32_t)orig_id[r];
   const u32x4s* xq = reinterpret_cast<const u32x4s*>(x) + (size_t)q * d8;
@@ -108,7 +167,7 @@ __global__ __launch_bounds__(STREAM_THREADS) void sde_step_bf16_kernel(
   float acc = 0.f;
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) {
-    const int e8 = c * (STREAM_CHUNK / 8) + it * STREAM_THREADS + threadIdx.x;
+    const int e8 = c * (STREAM_CHUNK / 8) + it * STREAM_THREADS + lane256;
     if (e8 < d8) {
       const u32x4s xv = __builtin_nontemporal_load(xq + e8);
       const u32x4s uv = __builtin_nontemporal_load(uq + e8);
@@ -124,51 +183,44 @@ __global__ __launch_bounds__(STREAM_THREADS) void sde_step_bf16_kernel(
              ((z1.x * z1.x + z1.y * z1.y) + (z1.z * z1.z + z1.w * z1.w));
     }
   }
-  const float t = block_sum_256(acc);
-  if (threadIdx.x == 0) partials[blockIdx.x] = t;
+  if constexpr (GROUPS > 0) {
+    row_sum<GROUPS>(chunks, acc, [&](double s) { if (threadIdx.x == 0) finish_logprob(out, r, (int)id, s); });
+  } else {
+    const float t = block_sum_256(acc);
+    if (threadIdx.x == 0) partials[blockIdx.x] = t;
+  }
 }
 
-// Sum of one trajectory's `chunks` partials (`stride` floats apart) in fp64 by one wavefront, the same in every lane.  The
-// kernels that finish a sum are pure latency, once per step: a lane that walked its trajectory's partials one by one took
-// 4 us for 16 of them and more for more.
+// The kernels that finish a sum are pure latency, once per step: one wavefront per trajectory (a lane that walked its
+// trajectory's partials one by one took 4 us for 16 of them and more for more).
 __device__ __forceinline__ double wave_sum_partials(const float* __restrict__ p, int chunks, int stride) {
-  double s = 0.0;
-  for (int c = threadIdx.x & (WAVE - 1); c < chunks; c += WAVE) s += (double)p[(size_t)c * stride];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, WAVE);
-  return s;
+  return wave_sum_of(chunks, [&](int c) { return p[(size_t)c * stride]; });
 }
 constexpr int FINISH_ROWS = 4;                     // trajectories per workgroup of the finishing kernels
 
-// logp[r] = -1/2 sum_c partial[r, c] - d (ln C + 1/2 ln 2 pi); history and running sum by original id.
-__global__ void logprob_finish_kernel(const float* __restrict__ partials, int chunks, int n_traj,
-                                      double log_norm, const int32_t* __restrict__ orig_id,
-                                      float* __restrict__ logp, float* __restrict__ logp_hist,
-                                      float* __restrict__ logp_sum) {
+__global__ void logprob_finish_kernel(const float* __restrict__ partials, int chunks, int n_traj, const int32_t* __restrict__ orig_id,
+                                      const LogProb out) {
   const int r = blockIdx.x * FINISH_ROWS + threadIdx.x / WAVE;
   if (r >= n_traj) return;
   const double s = wave_sum_partials(partials + (size_t)r * chunks, chunks, 1);
-  if ((threadIdx.x & (WAVE - 1)) != 0) return;
-  const float lp = (float)(-0.5 * s - log_norm);
-  if (logp) logp[r] = lp;
-  const int id = orig_id[r];
-  if (logp_hist) logp_hist[id] = lp;
-  if (logp_sum) logp_sum[id] += lp;
+  if ((threadIdx.x & (WAVE - 1)) == 0) finish_logprob(out, r, orig_id[r], s);
 }
 
-// partial of <w, Pc x + Qc u> per workgroup
-template <bool WITH_U>
-__global__ __launch_bounds__(STREAM_THREADS) void preview_reward_kernel(
+// <w, Pc x + Qc u> per trajectory; GROUPS as above
+template <bool WITH_U, int GROUPS>
+__global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void preview_reward_kernel(
     const float* __restrict__ x, const float* __restrict__ u, const float* __restrict__ w, int d4,
-    int chunks, float Pc, float Qc, float* __restrict__ partials) {
-  const int r = blockIdx.x / chunks, c = blockIdx.x - r * chunks;
+    int chunks, float Pc, float Qc, float* __restrict__ partials, double bias,
+    float* __restrict__ rewards) {
+  const int r = GROUPS ? blockIdx.x : blockIdx.x / chunks, c = GROUPS ? threadIdx.x / STREAM_THREADS : blockIdx.x - r * chunks;
+  const int lane256 = GROUPS > 1 ? threadIdx.x & (STREAM_THREADS - 1) : threadIdx.x;
   const f32x4* xr = reinterpret_cast<const f32x4*>(x) + (size_t)r * d4;
   const f32x4* ur = reinterpret_cast<const f32x4*>(u) + (size_t)r * d4;
   const f32x4* w4 = reinterpret_cast<const f32x4*>(w);
   float acc = 0.f;
 #pragma unroll
   for (int it = 0; it < STREAM_ITERS; ++it) {
-    const int e4 = c * (STREAM_CHUNK / 4) + it * STREAM_THREADS + threadIdx.x;
+    const int e4 = c * (STREAM_CHUNK / 4) + it * STREAM_THREADS + lane256;
     if (e4 < d4) {
       const f32x4 xv = __builtin_nontemporal_load(xr + e4);
       const f32x4 wv = w4[e4];
@@ -183,8 +235,12 @@ __global__ __launch_bounds__(STREAM_THREADS) void preview_reward_kernel(
       acc += (wv.x * h.x + wv.y * h.y) + (wv.z * h.z + wv.w * h.w);
     }
   }
-  const float t = block_sum_256(acc);
-  if (threadIdx.x == 0) partials[blockIdx.x] = t;
+  if constexpr (GROUPS > 0) {
+    row_sum<GROUPS>(chunks, acc, [&](double s) { if (threadIdx.x == 0) rewards[r] = (float)(bias + s); });
+  } else {
+    const float t = block_sum_256(acc);
+    if (threadIdx.x == 0) partials[blockIdx.x] = t;
+  }
 }
 
 __global__ void reward_finish_kernel(const float* __restrict__ partials, int chunks, int n_traj,
@@ -327,6 +383,14 @@ extern "C" pg_status pg_init_latents(float* x, const int32_t* orig_id, int64_t n
 }
 
 namespace pg {
+static pg_status launch_logprob_finish(const float* partials, int chunks, int64_t n_traj, const int32_t* orig_id, const LogProb& out,
+                                       hipStream_t stream) {
+  logprob_finish_kernel<<<dim3((unsigned)((n_traj + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS * WAVE), 0, stream>>>(
+      partials, chunks, (int)n_traj, orig_id, out);
+  PG_LAUNCH_CHECK("logprob_finish_kernel");
+  return PG_OK;
+}
+
 pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* logp, float* logp_hist,
                           float* logp_sum, const int32_t* src, const int32_t* orig_id, int64_t n_traj, int64_t d,
                           double A, double B, double C, uint64_t seed, uint32_t step, float* partials,
@@ -337,17 +401,18 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
   if (x_out == x) return fail(PG_EINVAL, "pg_sde_step_logprob: x_out must not alias x");
   if (!(C > 0.0)) return fail(PG_EINVAL, "pg_sde_step_logprob: noise scale C = %g must be > 0", C);
   const int chunks = (int)chunks_per_traj(d);
+  const LogProb out{logp, logp_hist, logp_sum, (double)d * (log(C) + 0.5 * log(2.0 * M_PI))};
+  const bool row = row_per_workgroup(n_traj, chunks);
   const int rec = prof_open(PROF_SDE_STEP, 12.0 * (double)n_traj * (double)d, stream);
-  sde_step_kernel<<<dim3((unsigned)(n_traj * chunks)), dim3(STREAM_THREADS), 0, stream>>>(
-      x, u, x_out, src, orig_id, (int)(d / 4), chunks, (float)A, (float)B, (float)C, (uint32_t)seed,
-      (uint32_t)(seed >> 32), step, partials, hist_next);
+  with_groups(row ? chunks : 0, [&](auto groups) {
+    constexpr int G = decltype(groups)::value;
+    sde_step_kernel<G><<<dim3((unsigned)(G ? n_traj : n_traj * chunks)), dim3((G ? G : 1) * STREAM_THREADS), 0, stream>>>(
+        x, u, x_out, src, orig_id, (int)(d / 4), chunks, (float)A, (float)B, (float)C, (uint32_t)seed, (uint32_t)(seed >> 32), step,
+        partials, hist_next, out);
+  });
   prof_close(rec, stream);
   PG_LAUNCH_CHECK("sde_step_kernel");
-  const double log_norm = (double)d * (log(C) + 0.5 * log(2.0 * M_PI));
-  logprob_finish_kernel<<<dim3((unsigned)((n_traj + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS * WAVE), 0, stream>>>(
-      partials, chunks, (int)n_traj, log_norm, orig_id, logp, logp_hist, logp_sum);
-  PG_LAUNCH_CHECK("logprob_finish_kernel");
-  return PG_OK;
+  return row ? PG_OK : launch_logprob_finish(partials, chunks, n_traj, orig_id, out, stream);
 }
 
 pg_status launch_transition_logprob(const float* x, const float* u, const float* x_next_by_id,
@@ -401,15 +466,16 @@ extern "C" pg_status pg_sde_step_logprob_bf16(const uint16_t* x, const uint16_t*
   if (x_out == x) return fail(PG_EINVAL, "pg_sde_step_logprob_bf16: x_out must not alias x");
   if (!(C > 0.0)) return fail(PG_EINVAL, "pg_sde_step_logprob_bf16: noise scale C = %g must be > 0", C);
   const int chunks = (int)chunks_per_traj(d);
-  sde_step_bf16_kernel<<<dim3((unsigned)(n_traj * chunks)), dim3(STREAM_THREADS), 0, stream>>>(
-      x, u, x_out, src, orig_id, (int)(d / 8), chunks, (float)A, (float)B, (float)C, (uint32_t)seed,
-      (uint32_t)(seed >> 32), step, partials);
+  const LogProb out{logp, logp_hist, logp_sum, (double)d * (log(C) + 0.5 * log(2.0 * M_PI))};
+  const bool row = row_per_workgroup(n_traj, chunks);
+  with_groups(row ? chunks : 0, [&](auto groups) {
+    constexpr int G = decltype(groups)::value;
+    sde_step_bf16_kernel<G><<<dim3((unsigned)(G ? n_traj : n_traj * chunks)), dim3((G ? G : 1) * STREAM_THREADS), 0, stream>>>(
+        x, u, x_out, src, orig_id, (int)(d / 8), chunks, (float)A, (float)B, (float)C, (uint32_t)seed, (uint32_t)(seed >> 32), step,
+        partials, out);
+  });
   PG_LAUNCH_CHECK("sde_step_bf16_kernel");
-  const double log_norm = (double)d * (log(C) + 0.5 * log(2.0 * M_PI));
-  logprob_finish_kernel<<<dim3((unsigned)((n_traj + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS * WAVE), 0, stream>>>(
-      partials, chunks, (int)n_traj, log_norm, orig_id, logp, logp_hist, logp_sum);
-  PG_LAUNCH_CHECK("logprob_finish_kernel");
-  return PG_OK;
+  return row ? PG_OK : launch_logprob_finish(partials, chunks, n_traj, orig_id, out, stream);
 }
 
 extern "C" pg_status pg_preview_reward(const float* x, const float* u, const float* w, float* rewards,
@@ -420,17 +486,20 @@ extern "C" pg_status pg_preview_reward(const float* x, const float* u, const flo
   if (!x || !w || !rewards || !partials) return fail(PG_EINVAL, "pg_preview_reward: null pointer");
   if (!u && Qc != 0.0) return fail(PG_EINVAL, "pg_preview_reward: u is NULL but Qc = %g", Qc);
   const int chunks = (int)chunks_per_traj(d);
-  const dim3 grid((unsigned)(n_traj * chunks)), block(STREAM_THREADS);
-  const int rec = prof_open(PROF_PREVIEW, ((u && Qc != 0.0) ? 8.0 : 4.0) * (double)n_traj * (double)d, (hipStream_t)stream);
-  if (u && Qc != 0.0)
-    preview_reward_kernel<true><<<grid, block, 0, (hipStream_t)stream>>>(x, u, w, (int)(d / 4), chunks,
-                                                                          (float)Pc, (float)Qc, partials);
-  else
-    preview_reward_kernel<false><<<grid, block, 0, (hipStream_t)stream>>>(x, x, w, (int)(d / 4), chunks,
-                                                                           (float)Pc, 0.f, partials);
-  prof_close(rec, (hipStream_t)stream);
+  const bool with_u = u && Qc != 0.0;
+  hipStream_t s = (hipStream_t)stream;
+  const bool row = row_per_workgroup(n_traj, chunks);
+  const int rec = prof_open(PROF_PREVIEW, (with_u ? 8.0 : 4.0) * (double)n_traj * (double)d, s);
+  with_groups(row ? chunks : 0, [&](auto groups) {
+    constexpr int G = decltype(groups)::value;
+    const dim3 grid((unsigned)(G ? n_traj : n_traj * chunks)), block((G ? G : 1) * STREAM_THREADS);
+    if (with_u) preview_reward_kernel<true, G><<<grid, block, 0, s>>>(x, u, w, (int)(d / 4), chunks, (float)Pc, (float)Qc, partials, bias, rewards);
+    else preview_reward_kernel<false, G><<<grid, block, 0, s>>>(x, x, w, (int)(d / 4), chunks, (float)Pc, 0.f, partials, bias, rewards);
+  });
+  prof_close(rec, s);
   PG_LAUNCH_CHECK("preview_reward_kernel");
-  reward_finish_kernel<<<dim3((unsigned)((n_traj + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS * WAVE), 0, (hipStream_t)stream>>>(
+  if (row) return PG_OK;
+  reward_finish_kernel<<<dim3((unsigned)((n_traj + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS * WAVE), 0, s>>>(
       partials, chunks, (int)n_traj, bias, rewards);
   PG_LAUNCH_CHECK("reward_finish_kernel");
   return PG_OK;

@@ -84,6 +84,33 @@ def test_sde_step_with_gather_on_read(lib):
     _step_case(lib, 12, 4096 + 256, seed=9, step=5, A=0.93, B=-0.21, Cc=0.31, src=src)
 
 
+@pytest.mark.parametrize("d", [1024, 4096, 4104, 8200, 12288, 16384, 16392])
+def test_sums_over_a_trajectory_do_not_depend_on_the_batch(lib, d):
+    """Few trajectories of at most four chunks of 4096 elements are summed by one workgroup each, 513 by one per chunk and a second
+    launch: the same bits."""
+    say(f"update and preview d={d}")
+    n = 513
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d)
+    x, u = (torch.randn(n, d, device=DEV, generator=g) for _ in range(2))
+    w = torch.randn(d, device=DEV, generator=g)
+    ids = torch.arange(n, dtype=torch.int32, device=DEV)
+    part = torch.zeros(lib.pg_step_scratch_floats(n, d), device=DEV)
+    half = lambda t: t.to(torch.bfloat16).view(torch.int16).contiguous()
+    results = []
+    for m in (n, 512, 5):
+        out, lp, hist, lsum, r = torch.zeros(m, d, device=DEV), *(torch.zeros(m, device=DEV) for _ in range(4))
+        lib.pg_sde_step_logprob(x[:m], u[:m], out, lp, hist, lsum, None, ids[:m], m, d, 0.9, -0.2, 0.3, 7, 2, part)
+        lib.pg_preview_reward(x[:m], u[:m], w, r, m, d, 1.0, -0.4, 0.1, part)
+        out2, lp2 = torch.zeros(m, d, dtype=torch.int16, device=DEV), torch.zeros(m, device=DEV)
+        lib.pg_sde_step_logprob_bf16(half(x[:m]), half(u[:m]), out2, lp2, None, None, None, ids[:m], m, d, 0.9, -0.2, 0.3, 7, 2, part)
+        results.append([t[:5].cpu().numpy() for t in (out, lp, hist, lsum, r, out2, lp2)])
+    for other in results[1:]:
+        for a, b in zip(results[0], other):
+            np.testing.assert_array_equal(a, b)
+    assert np.isfinite(results[0][1]).all() and np.abs(results[0][4]).min() > 0
+
+
 @pytest.mark.parametrize("n,d,gather", [(4, 1024, False), (3, 4096 * 2 + 520, False), (12, 4096 + 256, True)])
 def test_sde_step_bf16_storage_matches_oracle(lib, n, d, gather):
     """Storage variant: bf16 latents and network output in, bf16 latents out.  The oracle takes the same
