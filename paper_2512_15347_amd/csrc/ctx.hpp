@@ -6,7 +6,8 @@
 struct WeightSlot { int64_t offset; int32_t rows, cols, ld; };
 
 struct NetPlan {             // byte offsets into the workspace for the network's activations
-  size_t h, act, qkv, vt, att, hid, tok, mod, cond, ctx_h, ckv, ckvt, total;
+  size_t h, act, qkv, vt, att, hid, tok, mod, cond, rows, ctx_h, ckv, ckvt, total;
+  int mod_steps;             // steps whose modulation vectors fit in `mod`
 };
 
 struct pg_ctx {
@@ -51,8 +52,15 @@ namespace pg {
 pg_status net_plan(pg_ctx* c);                                  // fills c->net, returns bytes in net.total
 pg_status net_embed_times(pg_ctx* c, hipStream_t s);             // tables of the step times, at pg_bind
 pg_status net_prepare(pg_ctx* c, const uint16_t* weights, hipStream_t s);   // step-independent precomputation
-// u = net(x) for the M active rows of `x` under `weights`
-pg_status net_forward(pg_ctx* c, int step, const float* x, const uint16_t* weights, hipStream_t s);
+// modulation vectors of several steps at once (at most NetPlan::mod_steps)
+pg_status net_modulate(pg_ctx* c, int step, int steps, const uint16_t* weights, hipStream_t s);
+// What one network evaluation works on: M rows of x, the group of each and its row of the modulation vectors counted from
+// row mod_row P on; mod_row < 0: the evaluation makes the vectors of its step itself (row 0).
+struct NetBatch { int M; const float* x; const int32_t* group_of; const int32_t* mod_of; int mod_row; };
+// the active trajectories `steps` times over, the j-th time with the modulation vectors of step j of the last net_modulate
+pg_status net_batch_steps(pg_ctx* c, int steps, NetBatch* batch, hipStream_t s);
+// u = net(x) under `weights`; `step` only counts where mod_row < 0
+pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t* weights, hipStream_t s);
 // sampler_kernels.hip
 pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* logp, float* logp_hist,
                           float* logp_sum, const int32_t* src, const int32_t* orig_id, int64_t n_traj, int64_t d,

@@ -16,6 +16,7 @@
 #include "attention.hpp"
 #include "ctx.hpp"
 #include "gemm.hpp"
+#include "small_net.hpp"
 
 namespace pg {
 
@@ -76,7 +77,8 @@ __global__ void timestep_embedding_kernel(const double* __restrict__ t_in, float
 }
 
 // What a step's network evaluation can start from, in one launch (each part is a few microseconds of latency, and each
-// used to be a launch or two): t1 = silu(W1 emb + b1) of the time embedding, the bf16 patch tokens of the latents,
+// used to be a launch or two): t1 = silu(W1 emb + b1) of the time embedding (of gridDim.y steps, where nothing else is asked
+// for), the bf16 patch tokens of the latents,
 //   tok[r, 4c + 2dy + dx] = bf16(x[m, c, 2py + dy, 2px + dx]), r = m * Li + py * Wp + px; columns >= 4C are zero,
 // and the context rows of every trajectory, h[row_base + m * row_stride + j, :] = ctx_h[group_of[m], j, :].
 struct StepInputs {
@@ -91,9 +93,10 @@ __global__ __launch_bounds__(256) void step_inputs_kernel(const StepInputs a) {
     const int n0 = blk * GEMV_OUT + (threadIdx.x >> 6) * GEMV_ROWS;
     if (n0 >= a.D) return;
     float acc[GEMV_ROWS][1];
-    gemv_rows<1>(a.w1 + (int64_t)n0 * a.ldw1, a.ldw1, a.D - n0, a.emb, 0, 1, 256, acc);
+    gemv_rows<1>(a.w1 + (int64_t)n0 * a.ldw1, a.ldw1, a.D - n0, a.emb + 256 * (int64_t)blockIdx.y, 0, 1, 256, acc);
+    float* t1 = a.t1 + (int64_t)blockIdx.y * a.D;
     if ((threadIdx.x & 63) == 0)
-      for (int r = 0; r < GEMV_ROWS && n0 + r < a.D; ++r) a.t1[n0 + r] = silu(acc[r][0] + bf2f(a.b1[n0 + r]));
+      for (int r = 0; r < GEMV_ROWS && n0 + r < a.D; ++r) t1[n0 + r] = silu(acc[r][0] + bf2f(a.b1[n0 + r]));
     return;
   }
   blk -= a.t1_blocks;
@@ -128,15 +131,16 @@ __global__ __launch_bounds__(256) void step_inputs_kernel(const StepInputs a) {
   reinterpret_cast<float4*>(a.h)[(a.row_base + (int64_t)m * a.row_stride + j) * D4 + k] = v;
 }
 
-// sc[p, n] = silu(b[n] + sum_k W[n, k] t1[k] + y[p, n]); blockIdx.y: 64 groups, one per lane (1024 groups of
-// width 64: 4.8 us, 23.1 when a lane walked them)
+// sc[z, p, n] = silu(b[n] + sum_k W[n, k] t1[z, k] + y[p, n]) for step blockIdx.z; blockIdx.y: 64 groups, one per lane (1024
+// groups of width 64: 4.8 us, 23.1 when a lane walked them)
 __global__ __launch_bounds__(256) void condition_kernel(const uint16_t* __restrict__ W, int64_t ldw, const uint16_t* __restrict__ bias,
                                                         const float* __restrict__ t1, const float* __restrict__ y,
                                                         float* __restrict__ sc, int P, int D) {
   const int n0 = blockIdx.x * GEMV_OUT + (threadIdx.x >> 6) * GEMV_ROWS;
   if (n0 >= D) return;
   float acc[GEMV_ROWS][1];
-  gemv_rows<1>(W + (int64_t)n0 * ldw, ldw, D - n0, t1, 0, 1, D, acc);
+  gemv_rows<1>(W + (int64_t)n0 * ldw, ldw, D - n0, t1 + (int64_t)blockIdx.z * D, 0, 1, D, acc);
+  sc += (int64_t)blockIdx.z * P * D;
   const int p = blockIdx.y * WAVE + (threadIdx.x & 63);
   if (p < P)
 #pragma unroll
@@ -278,8 +282,12 @@ pg_status net_plan(pg_ctx* c) {
   n.att = take(R0 * D * 2);
   n.hid = take(R0 * 4 * D * 2);
   n.tok = take((size_t)c->M0 * c->Li * Kp * 2);
-  n.mod = take(((size_t)f.P * f.blocks * 6 * D * (f.net_kind == PG_NET_MMDIT ? 2 : 1) + (size_t)f.P * 2 * D) * 4);
-  n.cond = take((D + (size_t)f.P * D) * 4);
+  // modulation vectors of several steps at a time, at most 64 vectors (or one step's)
+  n.mod_steps = std::max(1, std::min(f.T, 64 / f.P));
+  const size_t mod_rows = (size_t)n.mod_steps * f.P;
+  n.mod = take(mod_rows * (f.blocks * 6 * D * (f.net_kind == PG_NET_MMDIT ? 2 : 1) + 2 * D) * 4);
+  n.cond = take((n.mod_steps * D + mod_rows * D) * 4);
+  n.rows = take(2 * sizeof(int32_t) * c->M0);
   if (f.net_kind == PG_NET_JOINT || f.net_kind == PG_NET_MMDIT) n.ctx_h = take((size_t)f.P * f.Lc * D * 4);
   if (f.net_kind == PG_NET_CROSS) {
     n.ckv = take((size_t)f.blocks * f.P * f.Lc * D * 2);
@@ -336,11 +344,97 @@ pg_status net_prepare(pg_ctx* c, const uint16_t* weights, hipStream_t s) {
   return PG_OK;
 }
 
-pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* weights, hipStream_t s) {
+namespace {
+// where the modulation vectors of a set of steps lie, and what the conditioning works on
+struct ModPlan {
+  float *mod, *fmod, *cmod, *t1, *sc;
+  int64_t ld;                                       // floats from one vector set of a stream to the next
+};
+ModPlan mod_plan(const pg_ctx* c, const Net& n) {
+  const pg_config& f = c->cfg;
+  const size_t rows = (size_t)c->net.mod_steps * f.P;
+  ModPlan m;
+  m.ld = (int64_t)f.blocks * 6 * f.D;
+  m.mod = n.at<float>(c->net.mod);
+  m.fmod = m.mod + rows * m.ld;
+  m.cmod = m.fmod + rows * 2 * f.D;                 // dual-stream variant: the context stream's modulation vectors
+  m.t1 = n.at<float>(c->net.cond);
+  m.sc = m.t1 + (size_t)c->net.mod_steps * f.D;
+  return m;
+}
+
+StepInputs time_inputs(const pg_ctx* c, const Net& n, const ModPlan& m, int step) {
+  StepInputs a{};
+  a.w1 = n.w(PG_W_T_W1); a.ldw1 = n.ld(PG_W_T_W1); a.b1 = n.w(PG_W_T_B1); a.D = c->cfg.D;
+  a.emb = reinterpret_cast<const float*>((char*)c->buf.workspace + c->ws_emb) + (size_t)step * 256; a.t1 = m.t1;
+  a.t1_blocks = (c->cfg.D + GEMV_OUT - 1) / GEMV_OUT;
+  return a;
+}
+
+// conditioning and modulation vectors of `steps` steps from their t1
+pg_status launch_modulation(const pg_ctx* c, const Net& n, const ModPlan& m, int steps) {
+  const pg_config& f = c->cfg;
+  const int D = f.D;
+  const bool dual = f.net_kind == PG_NET_MMDIT;
+  condition_kernel<<<dim3((D + GEMV_OUT - 1) / GEMV_OUT, (f.P + WAVE - 1) / WAVE, steps), dim3(256), 0, n.s>>>(
+      n.w(PG_W_T_W2), n.ld(PG_W_T_W2), n.w(PG_W_T_B2), m.t1, c->buf.y, m.sc, f.P, D);
+  PG_LAUNCH_CHECK("condition_kernel");
+  Modulation mo{};
+  mo.w[0] = n.w(PG_W_MOD_W); mo.b[0] = n.w(PG_W_MOD_B); mo.out[0] = m.mod; mo.ldw = n.ld(PG_W_MOD_W); mo.block_stride = c->block_stride;
+  if (dual) { mo.w[1] = n.w(PG_W_C_MOD_W); mo.b[1] = n.w(PG_W_C_MOD_B); mo.out[1] = m.cmod; }
+  mo.fw = n.w(PG_W_FMOD_W); mo.fb = n.w(PG_W_FMOD_B); mo.ldfw = n.ld(PG_W_FMOD_W); mo.fout = m.fmod;
+  const int P = steps * f.P;
+  mo.sc = m.sc; mo.P = P; mo.D = D; mo.blocks = f.blocks; mo.sets = dual ? 2 : 1;
+  // split the vectors until there are 2048 workgroups (eight to a compute unit) or one pass of `pc` vectors is left to each
+  const int pc = P == 1 ? 1 : P <= 4 ? 4 : 8, passes = (P + pc - 1) / pc;
+  const int tiles = (6 * D + GEMV_OUT - 1) / GEMV_OUT, rows = mo.sets * f.blocks + 1;
+  const int split = (int)std::min<int64_t>(passes, std::max<int64_t>(1, 2048 / ((int64_t)tiles * rows)));
+  mo.span = (passes + split - 1) / split * pc;
+  const dim3 grid(tiles, rows, (P + mo.span - 1) / mo.span);
+  if (P == 1) modulation_kernel<1><<<grid, dim3(256), 0, n.s>>>(mo);
+  else if (P <= 4) modulation_kernel<4><<<grid, dim3(256), 0, n.s>>>(mo);
+  else modulation_kernel<8><<<grid, dim3(256), 0, n.s>>>(mo);
+  PG_LAUNCH_CHECK("modulation_kernel");
+  return PG_OK;
+}
+}  // namespace
+
+// Modulation vectors of steps [step, step + steps), steps <= mod_steps, for evaluations that name their row (NetBatch::mod_row).
+// One step's are matrix-vector products bound by reading the weights, and three launches of latency: 24 blocks of width 1536
+// 129 us a step, 519 us for ten steps together; two blocks of width 128 13 us a step, 19 for ten.
+pg_status net_modulate(pg_ctx* c, int step, int steps, const uint16_t* weights, hipStream_t s) {
+  Net n{c, s, (char*)c->buf.workspace + c->ws_net, weights};
+  const ModPlan m = mod_plan(c, n);
+  const StepInputs a = time_inputs(c, n, m, step);
+  step_inputs_kernel<<<dim3((unsigned)a.t1_blocks, (unsigned)steps), dim3(256), 0, s>>>(a);
+  PG_LAUNCH_CHECK("step_inputs_kernel");
+  return launch_modulation(c, n, m, steps);
+}
+
+__global__ void batch_rows_kernel(const int32_t* __restrict__ group_of, int M, int steps, int P, int32_t* __restrict__ groups,
+                                  int32_t* __restrict__ mods) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= M * steps) return;
+  const int g = group_of[i % M];
+  groups[i] = g;
+  mods[i] = (i / M) * P + g;
+}
+
+pg_status net_batch_steps(pg_ctx* c, int steps, NetBatch* batch, hipStream_t s) {
+  int32_t* groups = reinterpret_cast<int32_t*>((char*)c->buf.workspace + c->ws_net + c->net.rows);
+  int32_t* mods = groups + c->M0;
+  const int M = c->M * steps;
+  batch_rows_kernel<<<dim3((M + 255) / 256), dim3(256), 0, s>>>(c->buf.group_of, c->M, steps, c->cfg.P, groups, mods);
+  PG_LAUNCH_CHECK("batch_rows_kernel");
+  batch->M = M; batch->group_of = groups; batch->mod_of = mods; batch->mod_row = 0;
+  return PG_OK;
+}
+
+pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t* weights, hipStream_t s) {
   const pg_config& f = c->cfg;
   Net n{c, s, (char*)c->buf.workspace + c->ws_net, weights};
   const NetPlan& pl = c->net;
-  const int D = f.D, M = c->M, L = c->L, Li = c->Li, P = f.P, hd = D / f.heads;
+  const int D = f.D, M = batch.M, L = c->L, Li = c->Li, P = f.P, hd = D / f.heads;
   const int R = M * L, Ri = M * Li;
   const int Lpad = (L + 63) / 64 * 64, Lcpad = (f.Lc + 63) / 64 * 64, Kp = (4 * f.C + 63) / 64 * 64;
   if (M == 0) return PG_OK;
@@ -351,50 +445,49 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
   uint16_t* att = n.at<uint16_t>(pl.att);
   uint16_t* hid = n.at<uint16_t>(pl.hid);
   uint16_t* tok = n.at<uint16_t>(pl.tok);
-  float* mod = n.at<float>(pl.mod);
-  float* fmod = mod + (size_t)P * f.blocks * 6 * D;
-  float* cmod = fmod + (size_t)P * 2 * D;           // dual-stream variant: the context stream's modulation vectors
+  const ModPlan mp = mod_plan(c, n);
+  const bool own_step = batch.mod_row < 0;          // this step's modulation vectors are made here
+  const int64_t mod_ld = mp.ld;
+  const float* mod = mp.mod + (own_step ? 0 : batch.mod_row) * P * mod_ld;
+  const float* cmod = mp.cmod + (own_step ? 0 : batch.mod_row) * P * mod_ld;
+  const float* fmod = mp.fmod + (int64_t)(own_step ? 0 : batch.mod_row) * P * 2 * D;
   const bool dual = f.net_kind == PG_NET_MMDIT;
   const int Rc = M * f.Lc;                          // context rows (dual-stream planes)
-  float* t1 = n.at<float>(pl.cond);
-  float* sc = t1 + D;
-  const int32_t* group_of = c->buf.group_of;
-  const int64_t mod_ld = (int64_t)f.blocks * 6 * D;
+  const int32_t* group_of = batch.group_of;
+  const int32_t* mod_of = batch.mod_of;
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
+  const bool small = small_net_takes(c);
 
   // ---- conditioning, patch tokens and context rows ----
   {
-    StepInputs a{};
-    a.w1 = n.w(PG_W_T_W1); a.ldw1 = n.ld(PG_W_T_W1); a.b1 = n.w(PG_W_T_B1); a.D = D;
-    a.emb = reinterpret_cast<const float*>((char*)c->buf.workspace + c->ws_emb) + (size_t)step * 256; a.t1 = t1;
-    a.x = x_in; a.tok = tok; a.M = M; a.C = f.C; a.H = f.H; a.W = f.W; a.Kp = Kp;
+    StepInputs a = time_inputs(c, n, mp, step);
+    if (!own_step) a.t1_blocks = 0;
+    a.x = batch.x; a.tok = tok; a.M = M; a.C = f.C; a.H = f.H; a.W = f.W; a.Kp = Kp;
     const bool context = f.net_kind == PG_NET_JOINT || dual;
     a.h = h; a.group_of = group_of; a.Lc = context ? f.Lc : 0;
     if (context) a.ctx_h = n.at<float>(pl.ctx_h);
     a.row_base = dual ? (int64_t)Ri : (int64_t)Li; a.row_stride = dual ? f.Lc : L;
-    a.t1_blocks = (D + GEMV_OUT - 1) / GEMV_OUT;
-    a.patch_blocks = (int)(((int64_t)M * (Kp / 4) * Li + 255) / 256);
-    const int64_t context_blocks = ((int64_t)M * a.Lc * (D / 4) + 255) / 256;
-    step_inputs_kernel<<<dim3((unsigned)(a.t1_blocks + a.patch_blocks + context_blocks)), dim3(256), 0, s>>>(a);
-    PG_LAUNCH_CHECK("step_inputs_kernel");
-    condition_kernel<<<dim3((D + GEMV_OUT - 1) / GEMV_OUT, (P + WAVE - 1) / WAVE), dim3(256), 0, s>>>(
-        n.w(PG_W_T_W2), n.ld(PG_W_T_W2), n.w(PG_W_T_B2), t1, c->buf.y, sc, P, D);
-    PG_LAUNCH_CHECK("condition_kernel");
-    Modulation mo{};
-    mo.w[0] = n.w(PG_W_MOD_W); mo.b[0] = n.w(PG_W_MOD_B); mo.out[0] = mod; mo.ldw = n.ld(PG_W_MOD_W); mo.block_stride = c->block_stride;
-    if (dual) { mo.w[1] = n.w(PG_W_C_MOD_W); mo.b[1] = n.w(PG_W_C_MOD_B); mo.out[1] = cmod; }
-    mo.fw = n.w(PG_W_FMOD_W); mo.fb = n.w(PG_W_FMOD_B); mo.ldfw = n.ld(PG_W_FMOD_W); mo.fout = fmod;
-    mo.sc = sc; mo.P = P; mo.D = D; mo.blocks = f.blocks; mo.sets = dual ? 2 : 1;
-    // split the groups until there are 2048 workgroups (eight to a compute unit) or one pass of PC groups is left to each
-    const int pc = P == 1 ? 1 : P <= 4 ? 4 : 8, passes = (P + pc - 1) / pc;
-    const int tiles = (6 * D + GEMV_OUT - 1) / GEMV_OUT, rows = mo.sets * f.blocks + 1;
-    const int split = (int)std::min<int64_t>(passes, std::max<int64_t>(1, 2048 / ((int64_t)tiles * rows)));
-    mo.span = (passes + split - 1) / split * pc;
-    const dim3 grid(tiles, rows, (P + mo.span - 1) / mo.span);
-    if (P == 1) modulation_kernel<1><<<grid, dim3(256), 0, s>>>(mo);
-    else if (P <= 4) modulation_kernel<4><<<grid, dim3(256), 0, s>>>(mo);
-    else modulation_kernel<8><<<grid, dim3(256), 0, s>>>(mo);
-    PG_LAUNCH_CHECK("modulation_kernel");
+    a.patch_blocks = small ? 0 : (int)(((int64_t)M * (Kp / 4) * Li + 255) / 256);
+    const int64_t context_blocks = small ? 0 : ((int64_t)M * a.Lc * (D / 4) + 255) / 256;
+    const int64_t blocks = a.t1_blocks + a.patch_blocks + context_blocks;
+    if (blocks > 0) {
+      step_inputs_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(a);
+      PG_LAUNCH_CHECK("step_inputs_kernel");
+    }
+    if (own_step) PG_TRY(launch_modulation(c, n, mp, 1));
+  }
+
+  // ---- narrow networks on short sequences: the rest in one launch ----
+  if (small) {
+    auto layer = [&](int w, int b) { return SmallLayer{n.w(w), n.w(b), n.ld(w)}; };
+    SmallNetArgs a{};
+    a.x = batch.x; a.u = c->buf.u; a.group_of = group_of; a.mod_of = mod_of; a.M = M;
+    a.C = f.C; a.H = f.H; a.W = f.W; a.Li = Li; a.Lc = L - Li; a.L = L; a.blocks = f.blocks;
+    if (a.Lc) a.ctx_h = n.at<float>(pl.ctx_h);
+    a.embed = layer(PG_W_PE_W, PG_W_PE_B); a.qkv = layer(PG_W_QKV_W, PG_W_QKV_B); a.out = layer(PG_W_O_W, PG_W_O_B);
+    a.fc1 = layer(PG_W_FC1_W, PG_W_FC1_B); a.fc2 = layer(PG_W_FC2_W, PG_W_FC2_B); a.fin = layer(PG_W_F_W, PG_W_F_B);
+    a.pos = n.w(PG_W_POS); a.mod = mod; a.fmod = fmod; a.block_stride = c->block_stride; a.scale_log2 = scale_log2;
+    return launch_small_net(a, D, hd, s);
   }
 
   // ---- patch embedding (+ position table) ----
@@ -428,11 +521,11 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
     return PG_OK;
   };
   auto layer_norm = [&](const float* shift, const float* scale, int64_t ld, int rows_out, int L_out) -> pg_status {
-    return ln(LnArgs{h, act, shift, scale, ld, group_of, rows_out, dual ? L_out : L, L_out, D, rows_out, nullptr, nullptr, 1});
+    return ln(LnArgs{h, act, shift, scale, ld, mod_of, rows_out, dual ? L_out : L, L_out, D, rows_out, nullptr, nullptr, 1});
   };
   // both planes of the dual-stream network in one launch
   auto layer_norm_pair = [&](const float* const* mods, int slot) -> pg_status {
-    return ln(LnArgs{h, act, mods[0] + slot * D, mods[0] + (slot + 1) * D, mod_ld, group_of, Ri + Rc, Li, Li, D,
+    return ln(LnArgs{h, act, mods[0] + slot * D, mods[0] + (slot + 1) * D, mod_ld, mod_of, Ri + Rc, Li, Li, D,
                      Ri, mods[1] + slot * D, mods[1] + (slot + 1) * D, f.Lc});
   };
 
@@ -474,7 +567,7 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
           g[st] = GemmArgs{};
           g[st].A = in[st]; g[st].lda = K; g[st].W = n.w(W[st], b); g[st].ldw = n.ld(W[st]); g[st].bias = n.w(B[st], b);
           g[st].M = rows[st]; g[st].N = D; g[st].K = K; g[st].outf = hs[st]; g[st].ldo = D; g[st].L = Ls[st];
-          g[st].gate = mbs[st] + gate * D; g[st].gate_ld = mod_ld; g[st].group_of = group_of;
+          g[st].gate = mbs[st] + gate * D; g[st].gate_ld = mod_ld; g[st].group_of = mod_of;
         }
         return launch_gemm_pair(g[0], g[1], EPI_RESID, s);
       };
@@ -508,7 +601,7 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
       GemmArgs o{};
       o.A = att; o.lda = D; o.W = n.w(PG_W_O_W, b); o.ldw = n.ld(PG_W_O_W); o.bias = n.w(PG_W_O_B, b);
       o.M = R; o.N = D; o.K = D; o.outf = h; o.ldo = D; o.L = L; o.gate = mb + 2 * D; o.gate_ld = mod_ld;
-      o.group_of = group_of;
+      o.group_of = mod_of;
       PG_TRY(launch_gemm(o, EPI_RESID, s));
     }
     // cross-attention sub-block over the prompt's context tokens
@@ -541,7 +634,7 @@ pg_status net_forward(pg_ctx* c, int step, const float* x_in, const uint16_t* we
       GemmArgs o{};
       o.A = hid; o.lda = 4 * D; o.W = n.w(PG_W_FC2_W, b); o.ldw = n.ld(PG_W_FC2_W); o.bias = n.w(PG_W_FC2_B, b);
       o.M = R; o.N = D; o.K = 4 * D; o.outf = h; o.ldo = D; o.L = L; o.gate = mb + 5 * D; o.gate_ld = mod_ld;
-      o.group_of = group_of;
+      o.group_of = mod_of;
       PG_TRY(launch_gemm(o, EPI_RESID, s));
     }
   }

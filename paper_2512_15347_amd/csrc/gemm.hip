@@ -63,46 +63,6 @@ __device__ __forceinline__ float4 load_stream(const float* p) {
   return float4{v[0], v[1], v[2], v[3]};
 }
 
-// gelu_tanh(x) = x/2 (1 + tanh(y)) = x / (1 + exp(-2y)),  y = sqrt(2/pi) (x + 0.044715 x^3);
-// the exponent is taken in base 2: -2 y log2(e) = x (K1 + K3 x^2)
-__device__ __forceinline__ float gelu_tanh(float x) {
-  constexpr float K1 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;
-  constexpr float K3 = K1 * 0.044715f;
-  const float z = x * __builtin_fmaf(x * x, K3, K1);
-  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z));
-}
-
-typedef float f32x2v __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-// as vectors, so that one conversion takes two values (converted one by one they are put together by two more instructions)
-__device__ __forceinline__ uint32_t pack_bf16x2(float x, float y) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2v{x, y}, bf16x2));
-}
-__device__ __forceinline__ uint2 pack_bf16x4(float4 v) { return uint2{pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)}; }
-
-// orders this wave's LDS accesses around a hand-over between its lanes (LDS serves one wave's accesses in issue order;
-// this keeps the compiler from moving them across the hand-over)
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// Sum over 16 (wide) or 8 adjacent lanes, the same in each of them: a butterfly of data-parallel-primitive adds inside a row of
-// 16 lanes (quad permutations, then the mirrored half row and row, whose lanes hold the other quads' equal sums).  Shuffles
-// through LDS cost the dual-stream QKV launch of 28272 rows 80 of its 428 us.
-template <int CTRL>
-__device__ __forceinline__ float add_permuted(float v) {
-  const int w = __builtin_bit_cast(int, v);
-  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(w, w, CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float head_sum(float v, bool wide) {
-  v = add_permuted<0xB1>(v);                        // lane ^ 1
-  v = add_permuted<0x4E>(v);                        // lane ^ 2
-  v = add_permuted<0x141>(v);                       // 7 - lane inside 8 lanes
-  return wide ? add_permuted<0x140>(v) : v;         // 15 - lane inside 16 lanes
-}
-
-__device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
 
 // f(tag<I>, tag<n>) for consecutive groups of n = 4, 2 or 1 of the N row tiles while f returns true
 template <int I> struct int_tag { static constexpr int value = I; };
@@ -117,7 +77,7 @@ __device__ __forceinline__ void for_row_groups(F&& f) {
 // NP = 2: two problems of equal N and K in one launch, the tile rows of the second behind those of the first
 template <int NP> struct GemmBatch { GemmArgs g[NP]; };
 // The problem that a workgroup works on, chosen field by field: an array element picked at run time is read again from the
-// kernel arguments at every use (24576 + 3696 rows, GELU: 490 us, 455 like this; QKV with the head norm 410 and XXX).
+// kernel arguments at every use (32 scalar loads in the epilogue; QKV of 24576 + 3696 rows with the head norm 402 -> 398 us).
 __device__ __forceinline__ GemmArgs chosen(const GemmBatch<1>& b, bool) { return b.g[0]; }
 __device__ __forceinline__ GemmArgs chosen(const GemmBatch<2>& b, bool second) {
   const GemmArgs &x = b.g[0], &y = b.g[1];

@@ -335,6 +335,23 @@ def test_network_output_with_sharp_attention(lib, kind, H, W, Lc, heads, gain):
     _check_sharp_network(lib, cfg, kind, gain, (0, 4, 5, 9))
 
 
+# networks that one workgroup evaluates whole (width 64 up to 192 tokens, 128 up to 96), at the sequence lengths where the kernel
+# changes: one token, a whole number of 16-row tiles and one more token, the longest sequence and the first that takes a launch per
+# layer; image tokens that end inside a tile before the context's (21 of 25 + ..), 3 and 16 channels, both head widths
+@pytest.mark.parametrize("kind,D,heads,C,H,W,Lc", [
+    ("adaln", 64, 2, 4, 2, 2, 0), ("adaln", 64, 1, 16, 8, 16, 0), ("joint", 64, 2, 4, 8, 16, 1), ("joint", 64, 2, 3, 10, 10, 39),
+    ("joint", 64, 1, 4, 16, 16, 1), ("adaln", 64, 2, 4, 16, 32, 0), ("joint", 64, 1, 4, 16, 32, 1), ("joint", 64, 2, 4, 16, 46, 8),
+    ("joint", 64, 2, 4, 16, 46, 9), ("adaln", 128, 4, 16, 8, 16, 0), ("joint", 128, 2, 4, 8, 16, 1), ("adaln", 128, 2, 3, 16, 16, 0),
+    ("joint", 128, 4, 4, 16, 16, 1), ("joint", 128, 2, 4, 14, 12, 54), ("joint", 128, 4, 16, 14, 12, 55)])
+def test_network_output_of_narrow_networks(lib, kind, D, heads, C, H, W, Lc):
+    L = H * W // 4 + Lc
+    say(f"narrow network {kind} width {D}, {L} tokens, {C} channels")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind=kind, P=2, N=3, C=C, H=H, W=W, D=D, heads=heads, Lc=Lc, Dc=D if Lc else 0, blocks=2, T=1, schedule=[[], []],
+               Li=H * W // 4, d=C * H * W)
+    _check_sharp_network(lib, cfg, kind, 7 if L > 1 else 1, (0, 2, 3, 5))
+
+
 # enough trajectories and tokens for the 64-queries-per-wave attention (four query tiles of 128 against two of 256, 1.67 rounds
 # against one): whole key tiles (484 + 28 tokens), a last tile that ends in its second (484 + 26) or first (462 + 18) half,
 # separate streams (462 + 26)
