@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <mutex>
 #include "common.hpp"
+#include "operands.hpp"
 #include "philox.hpp"
 
 namespace pg {
@@ -208,9 +209,11 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
 
 // ---- many groups: one lane per group ----
 // The wave-per-group form needs about 400 wave instructions per group, most of them cross-lane traffic (an all-pairs rank and
-// four fp64 scans by shuffles): 2^20 groups of 64 -> 16 took 1.53 ms, here 0.21 (64 groups in 4462 vector, 358 LDS and 141 load
-// instructions; with two waves per SIMD, 256 registers, the vector ALU issues in 0.56 of the cycles, some instruction is active in
-// 0.77, and a wave waits for memory and LDS for 0.43 of its time: instructions and exposed staging bound it together).  Here a lane
+// four fp64 scans by shuffles): 2^20 groups of 64 -> 16 took 1.53 ms, here 0.14 (64 groups in 2812 vector, 162 LDS and 29 load
+// instructions; with two waves per SIMD, 231 registers, the vector ALU issues in 0.53 of the cycles, some instruction is active in
+// 0.71, and a wave waits for memory and LDS for 0.40 of its time: instructions and exposed latency bound it together).  What
+// took it from 0.21 ms (4462, 358 and 141 instructions): values stay floats in the sort, they stay in registers for the
+// thresholds instead of being staged a second time, and whole chunks are staged by direct loads.  Here a lane
 // sorts its own group in registers by a compare-exchange network (Batcher's odd-even merge sort: 543 compare-exchanges for 64
 // slots, two instructions each, for 64 groups at once) and runs the scans of the same doubling recurrence on registers.
 // Only the values are sorted; members are picked afterwards by comparing them with the two threshold values, with
@@ -224,18 +227,15 @@ constexpr int LANE_K = 32;                         // largest count of the regis
 constexpr int LANE_ROW = WAVE * WAVE + 2 * WAVE;   // staged rewards of 64 groups: one float of padding per 64, and a margin
 constexpr int LANE_WAVES = 2;                      // waves per workgroup (33 KB of LDS)
 
-// order-preserving map between floats and integers (its own inverse on the bits)
-__device__ __forceinline__ int ordered_bits(int b) { return b ^ ((b >> 31) & 0x7FFFFFFF); }
-
 // Batcher's odd-even merge sort (Knuth, vol. 3, algorithm 5.2.2M) of N registers: P the length of the sorted runs, Q the
 // distance of the compare-exchanges.  Recursive templates, so that every index is a constant.
 template <int N, int P, int Q>
-__device__ __forceinline__ void sort_registers(int (&v)[N]) {
+__device__ __forceinline__ void sort_registers(float (&v)[N]) {
   if constexpr (P < N) {
 #pragma unroll
     for (int i = 0; i + Q < N; ++i)
       if (i >= Q % P && (i - Q % P) % (2 * Q) < Q && i / (2 * P) == (i + Q) / (2 * P)) {
-        const int lo = min(v[i], v[i + Q]), hi = max(v[i], v[i + Q]);
+        const float lo = fminf(v[i], v[i + Q]), hi = fmaxf(v[i], v[i + Q]);
         v[i] = lo;
         v[i + Q] = hi;
       }
@@ -277,30 +277,66 @@ __device__ __forceinline__ bool stage_rewards(const float* __restrict__ rewards,
   }
   return bad;
 }
+// The same where the wave's rewards are whole 16-byte chunks and every group starts with one (WHOLE below): by direct loads, in
+// chunks whose positions are XOR-swizzled inside every sixteen, so that lanes that read the i-th chunk of their groups meet in
+// different banks.
+__device__ __forceinline__ int swizzled(int chunk) { return chunk ^ ((chunk >> 4) & 15); }
+__device__ __forceinline__ bool stage_chunks(const float* rewards, int first, int total, int lane, float* row) {
+  const float* base = rewards + __builtin_amdgcn_readfirstlane(first);
+  const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)row);
+  const int chunks = __builtin_amdgcn_readfirstlane(total) / 4, pieces = (chunks + WAVE - 1) / WAVE;
+  for (int j = 0; j < pieces; ++j) dma16((uint32_t)min(swizzled(j * WAVE + lane), chunks - 1) * 16u, base, at + j * 1024u);
+  wait_dma();
+  lanes_sync();
+  float zero = 0.f;                                  // becomes NaN with the first value that is not finite
+  for (int j = 0; j < pieces; ++j) {
+    const float4 q = *reinterpret_cast<const float4*>(row + 4 * (j * WAVE + lane));
+    zero = __builtin_fmaf(q.x, 0.f, __builtin_fmaf(q.y, 0.f, __builtin_fmaf(q.z, 0.f, __builtin_fmaf(q.w, 0.f, zero))));
+  }
+  return zero != 0.f;
+}
+// where the wave's e-th reward is staged
+template <bool WHOLE>
+__device__ __forceinline__ int staged(int e) { return WHOLE ? 4 * swizzled(e >> 2) + (e & 3) : padded(e); }
 
-// One group per lane, n <= N members at row[padded(o + i)], 1 <= k < n, k <= K.  Returns the survivor mask.
-template <int N, int K>
-__device__ __forceinline__ uint64_t select_lane(const float* __restrict__ rewards, int first, int total, int o, int n, int k,
+// One group per lane, n <= N members from the wave's o-th staged reward on, 1 <= k < n, k <= K.  `full`: every lane that matters has
+// n = N.  Returns the survivor mask.
+template <int N, int K, bool WHOLE>
+__device__ __forceinline__ uint64_t select_lane(const float* __restrict__ rewards, int first, int total, int o, int n, int k, bool full,
                                                 int lane, float* row) {
-  float y[K], z[K];
+  constexpr bool KEEP = K <= 16;                     // the members stay in registers for the thresholds (beside 32 counts they do not fit)
+  float y[K], z[K], w[N];
   {
-    int v[N];
+    float v[N];
+    if (WHOLE) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int bits = ordered_bits(__builtin_bit_cast(int, row[padded(o + i)] + 0.0f));   // -0.0 becomes +0.0
-      v[i] = i < n ? bits : 0x7FFFFFFF;
+      for (int i = 0; i < N; i += 4) {
+        const float4 q = *reinterpret_cast<const float4*>(row + 4 * swizzled((o + i) >> 2));
+        w[i] = q.x + 0.0f; w[i + 1] = q.y + 0.0f; w[i + 2] = q.z + 0.0f; w[i + 3] = q.w + 0.0f;            // -0.0 becomes +0.0
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; ++i) w[i] = row[padded(o + i)] + 0.0f;
     }
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = w[i];
+    if (!full)
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] = i < n ? v[i] : __builtin_huge_valf();
     lanes_sync();
     sort_registers<N, 1, 1>(v);
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const float f = __builtin_bit_cast(float, ordered_bits(v[i]));
-      row[i * WAVE + lane] = f;
-      if (i < K) y[i] = f;
-    }
-    lanes_sync();
+    for (int i = 0; i < K; ++i) y[i] = v[i];
+    if (KEEP && full) {
 #pragma unroll
-    for (int i = 0; i < K; ++i) z[i] = row[max(n - 1 - i, 0) * WAVE + lane];
+      for (int i = 0; i < K; ++i) z[i] = v[N - 1 - i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; ++i) row[i * WAVE + lane] = v[i];
+      lanes_sync();
+#pragma unroll
+      for (int i = 0; i < K; ++i) z[i] = row[max(n - 1 - i, 0) * WAVE + lane];
+    }
     lanes_sync();
   }
   // Entries at or past n hold padding; they enter no sum that is used, because candidates take at most k < n of either end.
@@ -357,17 +393,23 @@ __device__ __forceinline__ uint64_t select_lane(const float* __restrict__ reward
 #pragma unroll
   for (int i = 0; i < K; ++i) quota_hi += (i < take_hi && z[i] == thi) ? 1 : 0;
   lanes_sync();
-  stage_rewards(rewards, first, total, lane, row);
-  lanes_sync();
-  // the N addresses of the row are computed again instead of being carried in N registers from the top
-  asm volatile("" : "+v"(o));
   uint64_t mask = 0ull;
+  if (!KEEP) {
+    stage_rewards(rewards, first, total, lane, row);
+    lanes_sync();
+    // the N addresses of the row are computed again instead of being carried in N registers from the top
+    asm volatile("" : "+v"(o));
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const float v = row[padded(o + i)];
-    if (i < n && (v <= tlo || v >= thi)) mask |= 1ull << i;
+    for (int i = 0; i < N; ++i) w[i] = row[padded(o + i)];
   }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i < n && (w[i] <= tlo || w[i] >= thi)) mask |= 1ull << i;
   if (__ballot(__popcll(mask) != k) != 0ull) {       // somewhere members tie across a threshold: lowest / highest slots first
+    if (KEEP) {
+      stage_rewards(rewards, first, total, lane, row);
+      lanes_sync();
+    }
     mask = 0ull;
     for (int i = 0; i < n; ++i) {
       const float v = row[padded(o + i)];
@@ -384,6 +426,13 @@ __device__ __forceinline__ uint64_t select_lane(const float* __restrict__ reward
   }
   lanes_sync();
   return mask;
+}
+template <bool WHOLE>
+__device__ __forceinline__ uint64_t select_lane_sized(const float* __restrict__ rewards, int first, int total, int n_max, int k_max, int o, int n, int k, bool full16, bool full32, bool full64, int lane,
+                                                      float* row) {
+  if (n_max <= 16) return select_lane<16, 16, WHOLE>(rewards, first, total, o, n, k, full16, lane, row);
+  if (n_max <= 32) return k_max <= 16 ? select_lane<32, 16, WHOLE>(rewards, first, total, o, n, k, full32, lane, row) : select_lane<32, 32, WHOLE>(rewards, first, total, o, n, k, full32, lane, row);
+  return k_max <= 16 ? select_lane<64, 16, WHOLE>(rewards, first, total, o, n, k, full64, lane, row) : select_lane<64, 32, WHOLE>(rewards, first, total, o, n, k, full64, lane, row);
 }
 
 // whether the wave-per-group code computes the mask of a group (n members, k kept; `odd`: of a wave with a size outside 0..64)
@@ -453,12 +502,16 @@ __global__ __launch_bounds__(LANE_WAVES * WAVE, 2) void ovf_select_lanes_kernel(
   const int first = __shfl(b, 0, WAVE), total = __shfl(b + n, members - 1, WAVE) - first;
   const bool odd = __ballot(n < 0 || n > WAVE) != 0ull;
   const bool bad = have && bad_group(n, k), given = have && by_wave(n, k, odd);
+  const bool whole = !odd && __ballot(have && ((b | n) & 3) != 0) == 0ull && (((uintptr_t)(rewards + first)) & 15) == 0 && total > 0;
   bool infinite = false;                             // the group holds a reward that is not finite
   if (!odd) {
-    const bool some = __ballot(stage_rewards(rewards, first, total, lane, row)) != 0ull;
+    const bool some = __ballot(whole ? stage_chunks(rewards, first, total, lane, row) : stage_rewards(rewards, first, total, lane, row)) != 0ull;
     lanes_sync();
     if (some)
-      for (int i = 0; i < n; ++i) infinite = infinite || !(__builtin_fabsf(row[padded(b - first + i)]) <= 3.4028234663852886e38f);
+      for (int i = 0; i < n; ++i) {
+        const int e = b - first + i;
+        infinite = infinite || !(__builtin_fabsf(row[whole ? staged<true>(e) : staged<false>(e)]) <= 3.4028234663852886e38f);
+      }
   }
   const bool sorts = !odd && have && !bad && !given && !infinite && k >= 1 && k < n;
   const bool any = __ballot(sorts) != 0ull;
@@ -472,11 +525,9 @@ __global__ __launch_bounds__(LANE_WAVES * WAVE, 2) void ovf_select_lanes_kernel(
     }
     // lanes with nothing to sort work on the first rewards of the wave, and the result is not used
     const int o = sorts ? b - first : 0, nn = sorts ? n : 2, kq = sorts ? k : 1;
-    if (n_max <= 16) mask = select_lane<16, 16>(rewards, first, total, o, nn, kq, lane, row);
-    else if (n_max <= 32) mask = k_max <= 16 ? select_lane<32, 16>(rewards, first, total, o, nn, kq, lane, row)
-                                             : select_lane<32, 32>(rewards, first, total, o, nn, kq, lane, row);
-    else mask = k_max <= 16 ? select_lane<64, 16>(rewards, first, total, o, nn, kq, lane, row)
-                            : select_lane<64, 32>(rewards, first, total, o, nn, kq, lane, row);
+    const bool same = __ballot(sorts && n != n_max) == 0ull;
+    mask = whole ? select_lane_sized<true>(rewards, first, total, n_max, k_max, o, nn, kq, same && n_max == 16, same && n_max == 32, same && n_max == 64, lane, row)
+                 : select_lane_sized<false>(rewards, first, total, n_max, k_max, o, nn, kq, same && n_max == 16, same && n_max == 32, same && n_max == 64, lane, row);
   }
   if (!sorts) mask = have && !bad && k >= 1 ? (given ? masks[g] : first_slots(k)) : 0ull;
   if (have) masks[g] = mask;

@@ -368,6 +368,45 @@ def test_ovf_one_lane_per_group_against_one_wave_per_group(lib, sizes_of):
         np.testing.assert_array_equal(sel[noff[first]:noff[last]], w_sel)
 
 
+@pytest.mark.parametrize("n,k", [(64, 16), (64, 17), (64, 32), (64, 1), (32, 16), (32, 31), (16, 15), (16, 4), (48, 16), (20, 7), (4, 3)])
+def test_ovf_lanes_with_groups_of_whole_chunks(lib, n, k):
+    """Groups that start and end on 16 bytes are staged by direct loads, others through registers: the oracle's selection with
+    the rewards aligned, the same with them one float further on; equal sizes (nothing to pad when they fill the sort), then sizes
+    that are multiples of four; ties across the thresholds, a reward that is not finite, groups that keep everything."""
+    say(f"ovf lanes, whole chunks, {n} -> {k}")
+    G = 16384 + 77
+    for mixed in (False, True):
+        rng = np.random.default_rng(1000 * n + k + mixed)
+        sizes = np.full(G, n) if not mixed else 4 * rng.integers(1, n // 4 + 1, G)
+        ks = np.minimum(np.full(G, k), sizes - (sizes > 1))
+        ks[rng.random(G) < 0.01] = 1
+        ks[40:44] = sizes[40:44]
+        off = np.concatenate([[0], np.cumsum(sizes)])
+        r = rng.standard_normal(off[-1] + 1).astype(np.float32)
+        r[: off[G // 2]] = np.round(r[: off[G // 2]] * 4) / 4
+        want = ovf.ovf_groups(r[:-1], off, ks)
+        for shift in (0, 1):
+            base = dev(np.concatenate([np.zeros(shift, np.float32), r]))[shift:]
+            assert base.data_ptr() % 16 == 4 * shift
+            for bad in (False, True):
+                if bad:
+                    base[int(off[200])] = float("inf")
+                masks = torch.full((G,), -1, dtype=torch.int64, device=DEV)
+                sel = torch.full((int(ks.sum()),), -1, dtype=torch.int32, device=DEV)
+                noff, status = torch.zeros(G + 1, dtype=torch.int32, device=DEV), torch.zeros(4, dtype=torch.int32, device=DEV)
+                scratch = torch.zeros(lib.pg_ovf_scratch_ints(G), dtype=torch.int32, device=DEV)
+                lib.pg_ovf_select(base, dev(off.astype(np.int32)), dev(ks.astype(np.int32)), G, masks, sel, noff, status, scratch)
+                got = masks.cpu().numpy().view(np.uint64)
+                np.testing.assert_array_equal(noff.cpu().numpy(), want[2])
+                assert int(status[0]) == (1 if bad else 0)
+                if bad:                                             # the first slots are kept where a reward is not finite
+                    assert got[200] == np.uint64((1 << int(ks[200])) - 1)
+                    np.testing.assert_array_equal(np.delete(got, 200), np.delete(want[0], 200))
+                else:
+                    np.testing.assert_array_equal(got, want[0])
+                    np.testing.assert_array_equal(sel.cpu().numpy(), want[1])
+
+
 def test_ovf_unsuited_groups_do_not_hold_up_a_batch(lib):
     """A batch whose groups all keep more than 32, or in which every 64th group keeps everything, takes no longer than a few
     times the batch that suits the one-lane-per-group kernel best (about 1.5 and 1.1 times; 11 times when the wave that met
