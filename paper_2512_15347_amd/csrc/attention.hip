@@ -278,58 +278,51 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(const AttnArg
   }
 }
 
-// ---- head width 64, long sequences: 64 queries per wavefront ----
-// What bounds the kernel above is neither the MFMAs (0.37 of the cycles) nor the vector ALU (halving its instructions changes
-// nothing): a key tile is a chain of LDS reads, scores, exponentials and value products between two barriers, which three
-// waves per SIMD do not hide.  Here a wave owns two blocks of 32 queries, A and B: key and value operands are read from LDS once
-// for both, V P_A runs beside the exponentials of B, and keys and values go straight from global memory into one of two LDS
-// stages with one barrier per tile.  The softmax reference of a query (m_run) is raised by the rule of the kernel above, block
-// by block of 32 queries, so that a query's result does not depend on which of the two a batch size selects: bit for bit the
-// same.  A tile forms its maximum beside the exponentials instead of before them (no cost: 537 to 543 us for 48 x 24 heads x
-// 1178 tokens, 544 to 547 when the sum of the probabilities was tested instead); the first tile, which sets the reference, the
-// masked last one and a tile that raises it take the general route, one block of queries at a time.
-constexpr int WQ = 64, WIDE_QTILE = 4 * WQ;      // queries per wave, per workgroup
-constexpr int WIDE_STAGE = 2 * KTILE * 64 * 2;   // keys [64][64] and values [64][64] of one tile
+// ---- head width 64, values in the accumulators' order: what the network launches ----
+// The kernel above waits: a key tile is a chain of LDS reads, scores, exponentials and value products between two barriers.  Here
+// the chain is taken apart.  A wave owns QB blocks of 32 queries and walks the keys in steps of 32: the scores of the next step
+// run on the matrix pipe beside this step's exponentials, operands are read from LDS a phase before they are used (keys while the
+// value products run, values while the scores do), and keys and values come by direct loads a whole tile ahead, with one
+// barrier per tile of 64 keys.  Two blocks share the operand reads.
+// There is no running maximum: probabilities are 2^score as they are, which bf16 and fp32 hold with the same relative precision
+// anywhere between 2^-60 and 2^100, so no reference has to be subtracted, compared or raised.  A block of 32 queries in which a
+// normaliser leaves that range (a row's largest logit below -41 or above 69, or a value that is not finite) is done again by the
+// online softmax with a reference exponent, for that block alone, so that a query's result depends on its own block and not on QB.
+// A step and wave costs 1024 cycles of MFMA and 850 of vector ALU (32 exponentials of eight) per 64 queries and 64 keys; taken apart
+// like this it runs in about 2400 (2700 with the maximum, and with the keys read one fragment at a time before their MFMAs).  What
+// is left is power (zero operands: 1040 TFLOP/s, random ones 870) and the part-filled tiles of queries and keys.  us, before / now:
+// 48 x 24 heads x 1178 512 / 466, 24 x 24 x 1178 267 / 238, 24 x 12 x 1024 96 / 85, 24 x 12 x 1024 on 77 keys 28.5 / 24.8,
+// 10 x 16 x 340 14.2 / 12.4.
+constexpr int FAST_K = 2 * KTILE * 64 * 2, FAST_LDS = FAST_K + 3 * KTILE * 64 * 2;   // two key tiles, three value tiles
+constexpr float L_MIN = 0x1p-60f, L_MAX = 0x1p100f;
 
-__global__ __launch_bounds__(ATT_THREADS, 2) void attention_wide_kernel(const AttnArgs a) {
-  constexpr int HD = 64, SLABS = 4, OT = 2;
-  __shared__ __align__(16) unsigned char smem[2 * WIDE_STAGE];
+// the value exists from here on
+__device__ __forceinline__ void pin(bf16x8& v) {
+  u32x4v w = __builtin_bit_cast(u32x4v, v);
+  asm volatile("" : "+v"(w));
+  v = __builtin_bit_cast(bf16x8, w);
+}
+
+template <int QB>
+__global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_kernel(const AttnArgs a) {
+  constexpr int HD = 64, KS = 4, WQ = 32 * QB, QT = 4 * WQ;
+  __shared__ __align__(16) unsigned char smem[FAST_LDS];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
-  const int nq = (a.Lq + WIDE_QTILE - 1) / WIDE_QTILE;
+  const int nq = (a.Lq + QT - 1) / QT;
   const int per_xcd = gridDim.x / 8;
   const int wg = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;      // query tiles of one head share an L2, as above
   if (wg >= nq * a.heads * a.B) return;
   const int b = wg / (nq * a.heads), h = (wg / nq) % a.heads;
-  const int q0 = (wg % nq) * WIDE_QTILE + wave * WQ;
+  const int q0 = (wg % nq) * QT + wave * WQ;
   const int kb = a.kv_map ? a.kv_map[b] : b;
   const uint16_t* kbase = a.k + (int64_t)kb * a.k_bstride + h * HD;
   const uint16_t* vbase = a.vt + (int64_t)kb * a.vt_bstride + (int64_t)h * HD * a.Lkpad;
-
-  bf16x8 qf[2][SLABS];
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int qr = min(q0 + 32 * c + l32, a.Lq - 1);
-    const uint16_t* qp = a.q + ((int64_t)b * a.Lq + qr) * a.ldq + h * HD + 8 * half;
-#pragma unroll
-    for (int ks = 0; ks < SLABS; ++ks) {
-      qf[c][ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
-      if (!a.q_prescaled)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) qf[c][ks][e] = (__bf16)((float)qf[c][ks][e] * a.scale_log2);
-    }
-  }
-  f32x16 o[2][OT];
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int t = 0; t < OT; ++t) o[c][t] = f32x16{};
-  float m_run[2] = {0.f, 0.f}, l_run[2] = {0.f, 0.f};
   const bool wave_has_queries = q0 < a.Lq;       // wave-uniform
 
   // staging: a wave owns two of the eight 1 KB regions (8 rows) of either tile; lane l fills chunk l % 8 of row l / 8 of a
   // region with the source chunk that the swizzle puts there
-  const int n_tiles = (a.Lk + KTILE - 1) / KTILE;
+  const int n_tiles = (a.Lk + KTILE - 1) / KTILE, n_full = a.Lk / KTILE;
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
   int s_row[2], s_ch[2];
 #pragma unroll
@@ -337,193 +330,307 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_wide_kernel(const At
     s_row[i] = (2 * wave + i) * 8 + (lane >> 3);
     s_ch[i] = (lane & 7) ^ ((s_row[i] ^ (s_row[i] >> 3)) & 7);
   }
+  auto k_stage = [](int kt) { return (kt & 1) * 8192; };
+  auto v_stage = [](int kt) { return FAST_K + (kt % 3) * 8192; };
   auto request = [&](int kt) {
     const int k0 = kt * KTILE;
-    const uint32_t dst = lds0 + (kt & 1) * WIDE_STAGE;
+    const uint32_t kd = lds0 + k_stage(kt), vd = lds0 + v_stage(kt);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int row = min(s_row[i], a.Lk - 1 - k0);
-      dma16((uint32_t)(row * (int)a.ldk + s_ch[i] * 8) * 2u, kbase + (int64_t)k0 * a.ldk, dst + (2 * wave + i) * 1024);
-      dma16((uint32_t)(s_row[i] * a.Lkpad + s_ch[i] * 8) * 2u, vbase + k0, dst + 8192 + (2 * wave + i) * 1024);
+      dma16((uint32_t)(row * (int)a.ldk + s_ch[i] * 8) * 2u, kbase + (int64_t)k0 * a.ldk, kd + (2 * wave + i) * 1024);
+      dma16((uint32_t)(s_row[i] * a.Lkpad + s_ch[i] * 8) * 2u, vbase + k0, vd + (2 * wave + i) * 1024);
     }
   };
-  // values of keys past the end (padding may hold anything) are zeroed by the wave that fetched them
-  auto zero_padding = [&](int kt) {
-    asm volatile("" ::: "memory");               // not read before the wait that the call follows
+  // Tile kt, which this wave's loads have brought, is made whole: values of keys past the end (padding may hold anything) are
+  // zeroed by the wave that fetched them.  Then everybody's part is there, and everybody is done with what was read before.
+  auto publish = [&](int kt) {
+    wait_dma();
+    if (a.Lk - kt * KTILE < KTILE) {
+      asm volatile("" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int kc = kt * KTILE + s_ch[i] * 8;
-      if ((kc & ~15) + 16 > a.Lk) {
-        u32x4v* at = reinterpret_cast<u32x4v*>(smem + (kt & 1) * WIDE_STAGE + 8192 + (2 * wave + i) * 1024 + lane * 16);
-        *at = zero_past_end<true>(*at, kc, a.Lk);
+      for (int i = 0; i < 2; ++i) {
+        const int kc = kt * KTILE + s_ch[i] * 8;
+        if ((kc & ~15) + 16 > a.Lk) {
+          u32x4v* at = reinterpret_cast<u32x4v*>(smem + v_stage(kt) + (2 * wave + i) * 1024 + lane * 16);
+          *at = zero_past_end<true>(*at, kc, a.Lk);
+        }
       }
     }
+    __syncthreads();
   };
-  // operand addresses in a stage: the second 32 rows have the chunks permuted and lie 4 KB further
-  int ka[SLABS], va[4];
-#pragma unroll
-  for (int ks = 0; ks < SLABS; ++ks) ka[ks] = k_off<HD>(l32, 2 * ks + half);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) va[c] = 8192 + v_off(l32, 2 * c + half);
+  request(0);
+  if (n_tiles > 1) request(1);
 
-  auto scores_half = [&](f32x16& s, const unsigned char* st, int c, int t, float init) {
+  bf16x8 qf[QB][KS];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) s[e] = init;
+  for (int c = 0; c < QB; ++c) {
+    const int qr = min(q0 + 32 * c + l32, a.Lq - 1);
+    const uint16_t* qp = a.q + ((int64_t)b * a.Lq + qr) * a.ldq + h * HD + 8 * half;
 #pragma unroll
-    for (int ks = 0; ks < SLABS; ++ks) {
-      const bf16x8 kf = *reinterpret_cast<const bf16x8*>(st + (t ? ka[ks ^ 2] + 4096 : ka[ks]));
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c][ks], s, 0, 0, 0);
+    for (int ks = 0; ks < KS; ++ks) {
+      qf[c][ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
+      if (!a.q_prescaled)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qf[c][ks][e] = (__bf16)((float)qf[c][ks][e] * a.scale_log2);
     }
+  }
+  f32x16 o[QB][2];
+  float l_run[QB];
+#pragma unroll
+  for (int c = 0; c < QB; ++c) {
+    o[c][0] = o[c][1] = f32x16{};
+    l_run[c] = 0.f;
+  }
+
+  // operand addresses in a stage: the second 32 rows have the chunks permuted and lie 4 KB further
+  int ka[KS], va[4];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) ka[ks] = k_off<HD>(l32, 2 * ks + half);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) va[c] = v_off(l32, 2 * c + half);
+  // keys / values of half t of a tile
+  auto read_keys = [&](const unsigned char* st, int t, bf16x8 (&kf)[KS]) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kf[ks] = *reinterpret_cast<const bf16x8*>(st + (t ? ka[ks ^ 2] + 4096 : ka[ks]));
   };
-  auto probabilities = [&](const f32x16 (&s)[2], bf16x8 (&pf)[2][2]) {
-    float psum = 0.f;
+  auto read_values = [&](const unsigned char* st, int t, bf16x8 (&vf)[2][2]) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-      for (int e = 0; e < 16; e += 2) {
-        const f32x2v pp = {__builtin_amdgcn_exp2f(s[t][e]), __builtin_amdgcn_exp2f(s[t][e + 1])};
-        const bf16x2 pb = __builtin_convertvector(pp, bf16x2);
-        // the normaliser sums the probabilities as the value product sees them (rounded to bf16)
-        psum = __builtin_amdgcn_fdot2_f32_bf16(pb, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, psum, false);
-        pf[t][e >> 3][e & 7] = pb[0];
-        pf[t][e >> 3][(e & 7) + 1] = pb[1];
+      for (int ot = 0; ot < 2; ++ot) {
+        const int g = 2 * t + jj;
+        vf[jj][ot] = *reinterpret_cast<const bf16x8*>(st + (ot ? va[g ^ 2] + 4096 : va[g]));
       }
-    return psum;
   };
-  // whether a score of the block lies more than 2^8 above its query's reference
-  auto passes_reference = [&](const f32x16 (&s)[2]) {
-    float mx = s[0][0];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[t][e]);
-    return __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0ull;
+  auto score_mfma = [&](f32x16& s, int c, int ks, const bf16x8 (&kf)[KS]) {
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[c][ks], ks ? s : f32x16{}, 0, 0, 0);
   };
-  auto value_frag = [&](const unsigned char* st, int t, int jj, int ot) {
-    const int g = 2 * t + jj;
-    return *reinterpret_cast<const bf16x8*>(st + (ot ? va[g ^ 2] + 4096 : va[g]));
+  // probabilities 2 i and 2 i + 1 of a block
+  auto probability_pair = [](const f32x16& s, bf16x8 (&pf)[2], int i) {
+    const bf16x2 pb = __builtin_convertvector(f32x2v{__builtin_amdgcn_exp2f(s[2 * i]), __builtin_amdgcn_exp2f(s[2 * i + 1])}, bf16x2);
+    pf[i >> 2][2 * (i & 3)] = pb[0];
+    pf[i >> 2][2 * (i & 3) + 1] = pb[1];
   };
-  // any key tile for block c of the queries; `rest`: keys left from the tile's first on
-  auto general = [&](const unsigned char* st, int c, bool first, int rest) {
-    f32x16 s[2];
-    bf16x8 pf[2][2];
-    const bool upper = rest > 32;                // wave-uniform: keys in the second half of the tile
-    scores_half(s[0], st, c, 0, -m_run[c]);
-    if (upper) scores_half(s[1], st, c, 1, -m_run[c]);
-    if (rest < KTILE) {
+  // the normaliser sums the probabilities as the value product sees them (rounded to bf16)
+  auto add_pair = [](const bf16x8 (&pf)[2], int i, float sum) {
+    return __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[i >> 2][2 * (i & 3)], pf[i >> 2][2 * (i & 3) + 1]}, bf16x2{(__bf16)1.0f, (__bf16)1.0f},
+                                           sum, false);
+  };
+  bf16x8 kf[KS];
+  // One step of 32 keys: exponentials of `s`, beside them (NEXT) the scores of the following step from `kf`; then the value
+  // products, beside them (READ) the reads of the keys after those.  Eight MFMAs of either kind with two blocks; the exponentials
+  // of four scores and the packing after each score MFMA, one pair's sum after each value MFMA.
+  auto step = [&](const f32x16 (&s)[QB], f32x16 (&next)[QB], const unsigned char* v_st, int t, float (&psum)[QB], auto next_c, auto between,
+                  auto read_next) {
+    constexpr bool NEXT = decltype(next_c)::value;
+    bf16x8 vf[2][2], pf[QB][2];
+    read_values(v_st, t, vf);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int c = 0; c < QB; ++c) {
+        if (NEXT) score_mfma(next[c], c, ks, kf);
+        probability_pair(s[c], pf[c], 2 * ks);
+        probability_pair(s[c], pf[c], 2 * ks + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+    for (int c = 0; c < QB; ++c)                 // made here, not where they are used: below the barrier nothing would run beside the scores
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) pin(pf[c][jj]);
+    between();
+    read_next();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+      for (int c = 0; c < QB; ++c)
+#pragma unroll
+        for (int ot = 0; ot < 2; ++ot) {
+          o[c][ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[jj][ot], pf[c][jj], o[c][ot], 0, 0, 0);
+          psum[c] = add_pair(pf[c], 4 * jj + 2 * ot, psum[c]);
+          psum[c] = add_pair(pf[c], 4 * jj + 2 * ot + 1, psum[c]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+  };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  const auto nothing = [] {};
+
+  // a full tile; at entry s0 holds the scores of its first half and kf the keys of its second.  The barrier in the middle publishes
+  // the next tile (LAST: the last full one, after which no scores are prepared)
+  f32x16 s0[QB], s1[QB];
+  auto full_tile = [&](int kt, auto last_c) {
+    constexpr bool LAST = decltype(last_c)::value;
+    const unsigned char* v_st = smem + v_stage(kt);
+    const unsigned char* k_st = smem + k_stage(kt + 1);
+    auto turn = [&] {
+      if (kt + 1 >= n_tiles) return;
+      publish(kt + 1);
+      if (kt + 2 < n_tiles) request(kt + 2);
+    };
+    if (!wave_has_queries) {
+      turn();
+      return;
+    }
+    float psum[QB];
+#pragma unroll
+    for (int c = 0; c < QB; ++c) psum[c] = 0.f;
+    step(s0, s1, v_st, 0, psum, yes, turn, [&] { if (!LAST) read_keys(k_st, 0, kf); });
+    if constexpr (LAST) step(s1, s0, v_st, 1, psum, no, nothing, nothing);
+    else step(s1, s0, v_st, 1, psum, yes, nothing, [&] { read_keys(k_st, 1, kf); });
+#pragma unroll
+    for (int c = 0; c < QB; ++c) l_run[c] += psum[c];
+  };
+
+#pragma unroll
+  for (int c = 0; c < QB; ++c)                   // the queries are here before the loop (a wait inside it would be one for the next tile, too)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) pin(qf[c][ks]);
+  if (n_tiles > 1) wait_dma_but<4>();            // tile 1 may still be on its way
+  if (n_tiles > 1) __syncthreads();
+  else publish(0);
+  if (n_full > 0) {
+    if (wave_has_queries) {
+      read_keys(smem, 0, kf);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int c = 0; c < QB; ++c) score_mfma(s0[c], c, ks, kf);
+      read_keys(smem, 1, kf);
+    }
+    for (int kt = 0; kt + 1 < n_full; ++kt) full_tile(kt, no);
+    full_tile(n_full - 1, yes);
+  }
+  const int rest = a.Lk - n_full * KTILE;
+  if (rest > 0 && wave_has_queries) {            // the last, part-filled tile, published by the tile before it
+    const unsigned char* k_st = smem + k_stage(n_full);
+    float psum[QB];
+#pragma unroll
+    for (int c = 0; c < QB; ++c) psum[c] = 0.f;
+    for (int t = 0; t < 2 && 32 * t < rest; ++t) {
+      if (t) read_keys(k_st, 1, kf);
+      else read_keys(k_st, 0, kf);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int c = 0; c < QB; ++c) score_mfma(s0[c], c, ks, kf);
+#pragma unroll
+      for (int c = 0; c < QB; ++c)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          if (t * 32 + 8 * (e >> 2) + 4 * half + (e & 3) >= rest) s[t][e] = -__builtin_huge_valf();
+          if (t * 32 + 8 * (e >> 2) + 4 * half + (e & 3) >= rest) s0[c][e] = -__builtin_huge_valf();
+      if (t) step(s0, s1, smem + v_stage(n_full), 1, psum, no, nothing, nothing);
+      else step(s0, s1, smem + v_stage(n_full), 0, psum, no, nothing, nothing);
     }
-    float mx = s[0][0];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int c = 0; c < QB; ++c) l_run[c] += psum[c];
+  }
+
+  // ---- blocks whose sums left the range: online softmax with a reference exponent ----
+  float l_tot[QB];
+  bool again[QB], any = false;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[t][e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-    if (first || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0ull) {
-      const float delta = first ? mx : fmaxf(mx, 0.f);                 // the first tile sets the reference
-      const float alpha = __builtin_amdgcn_exp2f(-delta);
-      m_run[c] += delta;
-      if (!first) {
-        l_run[c] *= alpha;
+  for (int c = 0; c < QB; ++c) {
+    l_tot[c] = l_run[c] + __shfl_xor(l_run[c], 32, WAVE);
+    again[c] = wave_has_queries && __builtin_amdgcn_ballot_w64(!(l_tot[c] >= L_MIN && l_tot[c] <= L_MAX)) != 0ull;
+    any = any || again[c];
+  }
+  if (__syncthreads_or(any ? 1 : 0)) {
+    float m_run[QB];
 #pragma unroll
-        for (int t = 0; t < OT; ++t)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) o[c][t][e] *= alpha;
+    for (int c = 0; c < QB; ++c)
+      if (again[c]) {
+        o[c][0] = o[c][1] = f32x16{};
+        l_run[c] = m_run[c] = 0.f;
       }
+    // a key tile for block c; `left`: keys from the tile's first on
+    auto general = [&](int kt, int c, int left) {
+      const unsigned char* k_st = smem + k_stage(kt);
+      const unsigned char* v_st = smem + v_stage(kt);
+      f32x16 s[2];
+      bf16x8 pf[2][2], vf[2][2];
+      const float neg_m = -m_run[c];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        read_keys(k_st, t, kf);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[t][e] = neg_m;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[c][ks], s[t], 0, 0, 0);
+      }
+      if (left < KTILE) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (t * 32 + 8 * (e >> 2) + 4 * half + (e & 3) >= left) s[t][e] = -__builtin_huge_valf();
+      }
+      float mx = s[0][0];
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) s[t][e] -= delta;
-    }
-    l_run[c] += probabilities(s, pf);
+        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[t][e]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
+      if (kt == 0 || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0ull) {
+        const float delta = kt == 0 ? mx : fmaxf(mx, 0.f);               // the first tile sets the reference
+        const float alpha = kt == 0 ? 1.0f : __builtin_amdgcn_exp2f(-delta);
+        m_run[c] += delta;
+        l_run[c] *= alpha;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      if (t == 1 && !upper) break;
+        for (int ot = 0; ot < 2; ++ot)
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
+          for (int e = 0; e < 16; ++e) o[c][ot][e] *= alpha;
 #pragma unroll
-        for (int ot = 0; ot < OT; ++ot)
-          o[c][ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(value_frag(st, t, jj, ot), pf[t][jj], o[c][ot], 0, 0, 0);
-    }
-  };
-  // A full key tile for both blocks.  Returns how many blocks are left to general(): 2 both, 1 the second, with nothing of
-  // theirs changed.
-  auto tile = [&](const unsigned char* st) -> int {
-    f32x16 sa[2], sb[2];
-    bf16x8 pa[2][2], pb[2][2];
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { sa[t][e] = -m_run[0]; sb[t][e] = -m_run[1]; }
-#pragma unroll
-      for (int ks = 0; ks < SLABS; ++ks) {
-        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(st + (t ? ka[ks ^ 2] + 4096 : ka[ks]));
-        sa[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[0][ks], sa[t], 0, 0, 0);
-        sb[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[1][ks], sb[t], 0, 0, 0);
+          for (int e = 0; e < 16; ++e) s[t][e] -= delta;
       }
+      float psum = 0.f;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) probability_pair(s[t], pf[t], i);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) psum = add_pair(pf[t], i, psum);
+      }
+      l_run[c] += psum;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        read_values(v_st, t, vf);
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+          for (int ot = 0; ot < 2; ++ot) o[c][ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[jj][ot], pf[t][jj], o[c][ot], 0, 0, 0);
+      }
+    };
+    request(0);
+    for (int kt = 0; kt < n_tiles; ++kt) {
+      publish(kt);
+      if (kt + 1 < n_tiles) request(kt + 1);
+#pragma unroll
+      for (int c = 0; c < QB; ++c)
+        if (again[c]) general(kt, c, a.Lk - kt * KTILE);
     }
-    const float suma = probabilities(sa, pa);
-    const bool raise_a = passes_reference(sa);
-    __builtin_amdgcn_sched_barrier(0);
-    if (raise_a) return 2;
-    l_run[0] += suma;
-    // V P_A beside exp_B
-    bf16x8 vf[2][2][OT];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-        for (int ot = 0; ot < OT; ++ot) {
-          vf[t][jj][ot] = value_frag(st, t, jj, ot);
-          o[0][ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][jj][ot], pa[t][jj], o[0][ot], 0, 0, 0);
-        }
-    const float sumb = probabilities(sb, pb);
-    const bool raise_b = passes_reference(sb);
-    __builtin_amdgcn_sched_barrier(0);
-    if (raise_b) return 1;
-    l_run[1] += sumb;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-        for (int ot = 0; ot < OT; ++ot)
-          o[1][ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][jj][ot], pb[t][jj], o[1][ot], 0, 0, 0);
-    return 0;
-  };
-
-  request(0);
-  for (int kt = 0; kt < n_tiles; ++kt) {
-    wait_dma();                                  // this wave's part of tile kt has arrived
-    const int rest = a.Lk - kt * KTILE;
-    if (rest < KTILE) zero_padding(kt);
-    __syncthreads();                             // everybody's part has, and everybody is done with the other stage
-    if (kt + 1 < n_tiles) request(kt + 1);
-    if (!wave_has_queries) continue;
-    const unsigned char* st = smem + (kt & 1) * WIDE_STAGE;
-    int left = 2;
-    if (kt > 0 && rest >= KTILE) left = tile(st);
-    if (left == 2) general(st, 0, kt == 0, rest);
-    if (left >= 1) general(st, 1, kt == 0, rest);
+    for (int c = 0; c < QB; ++c)
+      if (again[c]) l_tot[c] = l_run[c] + __shfl_xor(l_run[c], 32, WAVE);
   }
   if (!wave_has_queries) return;
 
   // ---- normalise and store: lane holds head-dim rows 8*(e/4) + 4*half + e%4 of its queries ----
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const float inv = 1.0f / (l_run[c] + __shfl_xor(l_run[c], 32, WAVE));
+  for (int c = 0; c < QB; ++c) {
+    const float inv = 1.0f / l_tot[c];
     const int qr = q0 + 32 * c + l32;
     if (qr < a.Lq) {
       uint16_t* op = (a.split > 0) ? (qr < a.split ? a.out + ((int64_t)b * a.split + qr) * a.ldo + h * HD
                                                    : a.out2 + ((int64_t)b * (a.Lq - a.split) + qr - a.split) * a.ldo + h * HD)
                                    : a.out + ((int64_t)b * a.Lq + qr) * a.ldo + h * HD;
 #pragma unroll
-      for (int ot = 0; ot < OT; ++ot)
+      for (int ot = 0; ot < 2; ++ot)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           bf16x4 w;
@@ -534,12 +641,13 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_wide_kernel(const At
     }
   }
 }
+constexpr int WIDE_QTILE = 256;
 
-// Rounds of workgroups through the chip (two wide or three narrow ones per compute unit; a part-empty last round counts half
-// as empty as it is) take the same time per key tile with either kernel, so the wide one wins where it needs clearly fewer:
-// measured from 0.8 of the narrow kernel's rounds down, and for sequences long enough that the tiles that take its general
-// route do not count.  Narrow / wide, us: 48 x 24 heads x 1178 tokens 536 / 504 and 16 x 24 x 1178 171 / 169 at a ratio of 0.78,
-// 30 x 4 x 2048 153 / 141 at 0.70, 64 x 4 x 512 27.8 / 28.0 at 0.6; but 24 x 12 x 1024 93 / 98 at 0.88, 96 x 10 x 410 76 / 80 at 0.78.
+// Rounds of workgroups through the chip (two with 64 queries per wave or three with 32 per compute unit; a part-empty last round
+// counts half as empty as it is) take about the same time per key tile with either, so the wide one wins where it needs clearly
+// fewer and there are enough key tiles to share the reads of: from 0.8 of the narrow one's rounds down.  Narrow / wide, us:
+// 48 x 24 heads x 1178 tokens 488 / 466 and 12 x 24 x 1178 122 / 115 at a ratio of 0.78, 30 x 4 x 2048 143 / 133 at 0.70, 64 x 4 x 512
+// 27.8 / 27.3 at 0.6; but 24 x 12 x 1024 85 / 90 at 0.88, 96 x 10 x 410 70 / 72 at 0.78.
 static bool use_wide(int64_t wgs, int64_t wide_wgs, int Lk) {
   auto rounds = [](double load) { return load <= 1.0 ? 1.0 : 0.5 * (load + ceil(load)); };
   return Lk >= 480 && rounds(wide_wgs / 512.0) <= 0.8 * rounds(wgs / 768.0);
@@ -567,8 +675,8 @@ pg_status launch_attention(const AttnArgs& a, int hd, hipStream_t s) {
   if (wgs > (wide ? 1ll << 29 : 1ll << 30)) return fail(PG_ESHAPE, "attention: grid limit");
   const dim3 grid((unsigned)((wgs + 7) / 8 * 8)), block(ATT_THREADS);
   const int rec = prof_open(PROF_ATTENTION, 4.0 * a.B * (double)a.heads * a.Lq * (double)a.Lk * hd, s);
-  if (wide) attention_wide_kernel<<<grid, block, 0, s>>>(a);
-  else if (hd == 64 && a.v_swapped) attention_kernel<64, true><<<grid, block, 0, s>>>(a);
+  if (wide) attention_fast_kernel<2><<<grid, block, 0, s>>>(a);
+  else if (hd == 64 && a.v_swapped) attention_fast_kernel<1><<<grid, block, 0, s>>>(a);
   else if (hd == 64) attention_kernel<64, false><<<grid, block, 0, s>>>(a);
   else if (a.v_swapped) attention_kernel<32, true><<<grid, block, 0, s>>>(a);
   else attention_kernel<32, false><<<grid, block, 0, s>>>(a);

@@ -162,3 +162,33 @@ def test_network_attention_kernels_match_oracle(lib, B, Lq, Lk, heads, hd, gain,
         assert np.sqrt(np.mean((got - want) ** 2)) < 4e-3 * np.sqrt(np.mean(want ** 2))
     if hd == 64:
         np.testing.assert_array_equal(outs[1], outs[2])            # the choice is made by size and may not show
+
+
+# a constant added to the scores of the queries of one block of 32 (exact in bf16: one channel holds 1 and the constant), inside the
+# range in which probabilities are taken as they are and outside it on either side, where that block alone is done again
+@pytest.mark.parametrize("offset", [90.0, 130.0, 1000.0, -50.0, -70.0, -140.0, -1000.0])
+@pytest.mark.parametrize("Lk", [13, 64, 130, 331])
+def test_network_attention_outside_the_range_of_plain_probabilities(lib, offset, Lk):
+    say(f"network attention, scores moved by {offset}, {Lk} keys")
+    rng = np.random.default_rng(Lk)
+    B, Lq, heads, hd = 2, 300, 1, 64
+    scale = np.float32(1.4426950408889634 / math.sqrt(hd))
+    q = workloads.bf16_round(rng.standard_normal((B, Lq, hd), dtype=np.float32) * scale)
+    k = workloads.bf16_round(rng.standard_normal((B, Lk, hd), dtype=np.float32))
+    v = workloads.bf16_round(rng.standard_normal((B, Lk, hd), dtype=np.float32))
+    q[:, :, 5], k[:, :, 5] = 0.0, offset
+    plain = {kernel: _network_attention(lib, q, k, v, heads, kernel) for kernel in (1, 2)}
+    q[1, 96:128, 5] = 1.0
+    want = dit.attention(q.astype(np.float64) / float(scale), k.astype(np.float64), v.astype(np.float64), heads)
+    for kernel in (1, 2):
+        got = _network_attention(lib, q, k, v, heads, kernel)
+        assert np.isfinite(got).all()
+        # fp32 scores of size 1000 (ulp 6e-5) do not show beside probabilities and outputs rounded to bf16 (2^-9 relative)
+        assert np.max(np.abs(got - want)) < 1.5e-2 * np.max(np.abs(want))
+        others = np.ones((B, Lq), bool)
+        others[1, 96:128] = False
+        np.testing.assert_array_equal(got[others], plain[kernel][others])          # nobody else notices
+        np.testing.assert_array_equal(plain[kernel], plain[1])
+        if kernel == 1:
+            first = got
+        np.testing.assert_array_equal(got, first)
