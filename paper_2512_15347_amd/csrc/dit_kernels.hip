@@ -16,6 +16,7 @@
 #include "attention.hpp"
 #include "ctx.hpp"
 #include "gemm.hpp"
+#include "operands.hpp"
 #include "small_net.hpp"
 
 namespace pg {
@@ -23,12 +24,6 @@ namespace pg {
 __device__ __forceinline__ float bf2f(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
-
-__device__ __forceinline__ float wave_allsum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-  return v;
-}
 
 // ---- conditioning: c = MLP(sincos(t)) + y and the modulation vectors of every block ----
 // Matrix-vector products bound by reading the weights once (fp32 accumulation).  A wave computes GEMV_ROWS outputs for up to
@@ -241,10 +236,7 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const LnArgs a) {
         o.x = o.x * (1.0f + a.x) + b.x; o.y = o.y * (1.0f + a.y) + b.y;
         o.z = o.z * (1.0f + a.z) + b.z; o.w = o.w * (1.0f + a.w) + b.w;
       }
-      uint2 pk;
-      pk.x = (uint32_t)f2bf(o.x) | ((uint32_t)f2bf(o.y) << 16);
-      pk.y = (uint32_t)f2bf(o.z) | ((uint32_t)f2bf(o.w) << 16);
-      reinterpret_cast<uint2*>(orow)[lane + 64 * i] = pk;
+      reinterpret_cast<uint2*>(orow)[lane + 64 * i] = pack_bf16x4(o);
     }
     return;
   }

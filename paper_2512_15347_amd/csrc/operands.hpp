@@ -66,4 +66,19 @@ __device__ __forceinline__ float head_sum(float v, bool wide) {
   return wide ? add_permuted<0x140>(v) : v;         // 15 - lane inside 16 lanes
 }
 
+// op over the four lanes 16 apart (one of each row of 16), the same in each of them
+template <class Op>
+__device__ __forceinline__ float across_rows(float v, Op op) {
+  uint32_t b = __builtin_bit_cast(uint32_t, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(b, b, false, false);         // (own row or its neighbour's) twice
+  v = op(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
+  b = __builtin_bit_cast(uint32_t, v);
+  const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return op(__builtin_bit_cast(float, (uint32_t)q[0]), __builtin_bit_cast(float, (uint32_t)q[1]));
+}
+// sum over the wave, the same in every lane
+__device__ __forceinline__ float wave_allsum(float v) {
+  return across_rows(head_sum(v, true), [](float x, float y) { return x + y; });
+}
+
 }  // namespace pg

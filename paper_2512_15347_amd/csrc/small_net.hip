@@ -139,18 +139,6 @@ __device__ __forceinline__ void layer_norm(const float* h, uint16_t* act, const 
   }
 }
 
-// over the four lanes 16 apart that hold one query's keys
-typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
-template <class Op>
-__device__ __forceinline__ float across_rows(float v, Op op) {
-  uint32_t b = __builtin_bit_cast(uint32_t, v);
-  const auto r = __builtin_amdgcn_permlane16_swap(b, b, false, false);         // (own row or its neighbour's) twice
-  v = op(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
-  b = __builtin_bit_cast(uint32_t, v);
-  const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);
-  return op(__builtin_bit_cast(float, (uint32_t)q[0]), __builtin_bit_cast(float, (uint32_t)q[1]));
-}
-
 // Softmax attention inside the workgroup: a unit is 16 queries of one head, whose scores over all keys stay in registers.
 // Scores are computed transposed, so a lane holds one query and, of every 16 keys, four; two such tiles are the 32-key
 // operand of the value product with the keys in the order that the values are read in.
