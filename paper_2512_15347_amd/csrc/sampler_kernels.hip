@@ -8,20 +8,15 @@
 // on scheduling.
 #include <type_traits>
 #include "ctx.hpp"
+#include "operands.hpp"
 #include "philox.hpp"
 
 namespace pg {
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, WAVE);
-  return v;
-}
-
 // Sum over the 256 lanes of the workgroup; valid in lane 0 of wave 0.
 __device__ __forceinline__ float block_sum_256(float v) {
   __shared__ float part[STREAM_THREADS / WAVE];
-  v = wave_sum(v);
+  v = wave_allsum(v);
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   if (lane == 0) part[wv] = v;
   __syncthreads();
@@ -64,14 +59,19 @@ __device__ __forceinline__ double wave_sum_of(int chunks, F partial) {
   return s;
 }
 // A workgroup of GROUPS x 256 lanes, 256 for each of `chunks` <= GROUPS chunks: `v` is the lane's share of its chunk (0 past the last
-// one); finish(sum) is called by the first wave.
+// one); finish(sum) is called by the first lane.
 template <int GROUPS, class Finish>
 __device__ __forceinline__ void row_sum(int chunks, float v, Finish finish) {
   __shared__ float part[GROUPS][4];
-  v = wave_sum(v);
+  v = wave_allsum(v);
   if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x / STREAM_THREADS][(threadIdx.x / WAVE) & 3] = v;
   __syncthreads();
-  if (threadIdx.x < WAVE) finish(wave_sum_of(chunks, [&](int i) { return (part[i][0] + part[i][1]) + (part[i][2] + part[i][3]); }));
+  if (threadIdx.x == 0) {                            // in the order of wave_sum_of (whose other lanes add zeros)
+    double p[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = i < GROUPS && i < chunks ? (double)((part[i][0] + part[i][1]) + (part[i][2] + part[i][3])) : 0.0;
+    finish(GROUPS == 1 ? p[0] : (p[0] + p[2]) + (p[1] + p[3]));
+  }
 }
 // launch(tag<GROUPS>) with the smallest workgroup that holds the chunks (0: a workgroup per chunk)
 template <int N> struct groups_tag { static constexpr int value = N; };
@@ -134,7 +134,7 @@ __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_st
     }
   }
   if constexpr (GROUPS > 0) {
-    row_sum<GROUPS>(chunks, acc, [&](double s) { if (threadIdx.x == 0) finish_logprob(out, r, (int)id, s); });
+    row_sum<GROUPS>(chunks, acc, [&](double s) { finish_logprob(out, r, (int)id, s); });
   } else {
     const float t = block_sum_256(acc);
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
@@ -184,7 +184,7 @@ __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_st
     }
   }
   if constexpr (GROUPS > 0) {
-    row_sum<GROUPS>(chunks, acc, [&](double s) { if (threadIdx.x == 0) finish_logprob(out, r, (int)id, s); });
+    row_sum<GROUPS>(chunks, acc, [&](double s) { finish_logprob(out, r, (int)id, s); });
   } else {
     const float t = block_sum_256(acc);
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
@@ -236,7 +236,7 @@ __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void previe
     }
   }
   if constexpr (GROUPS > 0) {
-    row_sum<GROUPS>(chunks, acc, [&](double s) { if (threadIdx.x == 0) rewards[r] = (float)(bias + s); });
+    row_sum<GROUPS>(chunks, acc, [&](double s) { rewards[r] = (float)(bias + s); });
   } else {
     const float t = block_sum_256(acc);
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
@@ -302,8 +302,8 @@ __global__ __launch_bounds__(STREAM_THREADS) void transition_sq_kernel(
       dif += ((z.x - w0) * (z.x + w0) + (z.y - w1) * (z.y + w1)) + ((z.z - w2) * (z.z + w2) + (z.w - w3) * (z.w + w3));
     }
   }
-  acc = wave_sum(acc);
-  dif = wave_sum(dif);
+  acc = wave_allsum(acc);
+  dif = wave_allsum(dif);
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   if (lane == 0) { part[0][wv] = acc; part[1][wv] = dif; }
   __syncthreads();

@@ -57,8 +57,8 @@ __device__ __forceinline__ void load_weights(Weights<NC, K>& r, const uint16_t* 
     for (int ks = 0; ks < K / 32; ++ks) r.f[j][ks] = *reinterpret_cast<const bf16x8*>(p + 32 * ks);
   }
 }
-// [rows, K] x [cols, K]^T: out(j, column tile, row tile, acc) for every 16 x 16 tile of the wave, start(j, column tile) the first
-// value of its accumulators.  A lane holds four consecutive columns of one row; for j >= TR (transposed) four consecutive rows of
+// [rows, K] x [cols, K]^T: out(j, column tile, row tile, n, acc) for every 16 x 16 tile of the wave, the wave's n-th row tile (a
+// constant), start(j, column tile) the first value of its accumulators.  A lane holds four consecutive columns of one row; for j >= TR (transposed) four consecutive rows of
 // one column.
 template <int D, int NC, int K, int TR, int T, class Start, class Out>
 __device__ __forceinline__ void product(const uint16_t* A, int pitch, const Weights<NC, K>& w, int wc, int wr, int lane, Start start, Out out) {
@@ -95,14 +95,14 @@ __device__ __forceinline__ void product(const uint16_t* A, int pitch, const Weig
 #pragma unroll
     for (int j = 0; j < NC; ++j)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) out(j, wc + j * col_groups(D), rt + i, acc[i][j]);
+      for (int i = 0; i < 2; ++i) out(j, wc + j * col_groups(D), rt + i, 2 * (c / row_groups(D)) + i, acc[i][j]);
   }
 }
 
-__device__ __forceinline__ f32x4v bias4(const uint16_t* b) {           // b: 8-byte aligned
-  const uint2 v = *reinterpret_cast<const uint2*>(b);
+__device__ __forceinline__ f32x4v widen4(uint2 v) {
   return f32x4v{bf16_to_f32((uint16_t)v.x), bf16_to_f32((uint16_t)(v.x >> 16)), bf16_to_f32((uint16_t)v.y), bf16_to_f32((uint16_t)(v.y >> 16))};
 }
+__device__ __forceinline__ f32x4v bias4(const uint16_t* b) { return widen4(*reinterpret_cast<const uint2*>(b)); }   // 8-byte aligned
 __device__ __forceinline__ void store4(uint16_t* p, f32x4v v) { *reinterpret_cast<uint2*>(p) = pack_bf16x4({v[0], v[1], v[2], v[3]}); }
 
 // act[r, :] = bf16(LN(h[r, :]) (1 + scale) + shift), 16 lanes per row
@@ -110,7 +110,7 @@ template <int D, int ROWS>
 __device__ __forceinline__ void layer_norm(const float* h, uint16_t* act, const float* shift, const float* scale) {
   constexpr int V = D / 64;
   const int j = threadIdx.x & 15;
-#pragma unroll
+#pragma unroll 1
   for (int r0 = 0; r0 < ROWS; r0 += THREADS / 16) {
     const int r = r0 + (threadIdx.x >> 4);
     if (ROWS % (THREADS / 16) != 0 && r >= ROWS) break;
@@ -254,6 +254,14 @@ __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArg
   load_weights<D>(w_e, a.embed.w, a.embed.ld, wc, D, lane);
   Weights<3, D> w_qkv;
   load_weights<D>(w_qkv, a.qkv.w, a.qkv.ld, wc, 3 * D, lane);
+  const f32x4v b_e = bias4(a.embed.b + wc * 16 + 4 * lk);
+  uint2 pos[T];                                      // the wave's rows of the position table
+#pragma unroll
+  for (int c = 0; c < T / 2; c += row_groups(D))
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      pos[2 * (c / row_groups(D)) + i] = *reinterpret_cast<const uint2*>(
+          a.pos + (int64_t)min((2 * (c + wr) + i) * 16 + lr, a.Li - 1) * D + wc * 16 + 4 * lk);
   const float* x = a.x + (int64_t)m * a.C * HW;
   for (int i = tid; i < L16 * 16; i += THREADS) {                      // four columns (one channel) of one token
     const int tok = i % L16, c = i / L16;
@@ -276,17 +284,16 @@ __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArg
   __syncthreads();
 
   // ---- patch embedding + position table ----
-  product<D, 1, 64, 1, T>(act, a_pitch(D), w_e, wc, wr, lane, [&](int, int col) { return bias4(a.embed.b + col * 16 + 4 * lk); },
-                       [&](int, int col, int rt, const f32x4v& v) {
-                         const int tok = rt * 16 + lr, n = col * 16 + 4 * lk;
-                         if (tok < a.Li)
-                           *reinterpret_cast<f32x4v*>(h + tok * h_pitch(D) + n) = v + bias4(a.pos + (int64_t)tok * D + n);
-                       });
+  product<D, 1, 64, 1, T>(act, a_pitch(D), w_e, wc, wr, lane, [&](int, int) { return b_e; },
+                          [&](int, int col, int rt, int n, const f32x4v& v) {
+                            const int tok = rt * 16 + lr;
+                            if (tok < a.Li) *reinterpret_cast<f32x4v*>(h + tok * h_pitch(D) + col * 16 + 4 * lk) = v + widen4(pos[n]);
+                          });
   __syncthreads();
 
   // h[r, :] += gate (acc): the layers that add into the residual stream
   auto add_gated = [&](const float* gate) {
-    return [=](int, int col, int rt, const f32x4v& v) {
+    return [=](int, int col, int rt, int, const f32x4v& v) {
       const int n = col * 16 + 4 * lk;
       f32x4v* p = reinterpret_cast<f32x4v*>(h + (rt * 16 + lr) * h_pitch(D) + n);
       *p = *p + *reinterpret_cast<const f32x4v*>(gate + n) * v;
@@ -311,7 +318,7 @@ __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArg
                           const float v = bf16_to_f32(bs[col * 16 + lr]);
                           return f32x4v{v, v, v, v};
                         },
-                        [&](int j, int col, int rt, const f32x4v& v) {
+                        [&](int j, int col, int rt, int, const f32x4v& v) {
                           if (j == 2) store4(vt + (col * 16 - 2 * D + lr) * vp + rt * 16 + 4 * lk, v);   // four tokens of a channel
                           else store4(qk + (rt * 16 + lr) * q_pitch(D) + col * 16 + 4 * lk, j == 0 ? v * a.scale_log2 : v);
                         });
@@ -325,7 +332,10 @@ __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArg
     // ---- MLP sub-block, the hidden values in two halves ----
     layer_norm<D, L16>(h, act, md + 3 * D, md + 4 * D);
     const bool more = b + 1 < a.blocks;
-    if (more) {
+    if (!more) {                                     // the final layer's shift and scale, and its weights where the projection's were
+      if (tid < 2 * D / 4) md_next = *reinterpret_cast<const f32x4v*>(a.fmod + (int64_t)row * 2 * D + 4 * tid);
+      load_weights<D>(w_o, a.fin.w, a.fin.ld, wc, 4 * a.C, lane);
+    } else {
       fetch_vectors(b + 1);
       load_weights<D>(w_qkv, a.qkv.w + at + a.block_stride, a.qkv.ld, wc, 3 * D, lane);
     }
@@ -334,7 +344,7 @@ __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArg
     for (int half = 0; half < 2; ++half) {
       product<D, 2, D, 2, T>(act, a_pitch(D), w_1, wc, wr, lane,
                           [&](int, int col) { return bias4(bs + 4 * D + half * 2 * D + col * 16 + 4 * lk); },
-                          [&](int, int col, int rt, const f32x4v& v) {
+                          [&](int, int col, int rt, int, const f32x4v& v) {
                             store4(qk + (rt * 16 + lr) * q_pitch(D) + col * 16 + 4 * lk,
                                    f32x4v{gelu_tanh(v[0]), gelu_tanh(v[1]), gelu_tanh(v[2]), gelu_tanh(v[3])});
                           });
@@ -346,30 +356,27 @@ __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArg
       if (half == 0) load_weights<D>(w_2, fc2 + 2 * D, a.fc2.ld, wc, D, lane);
       __syncthreads();
     }
-    if (more) {
-      put_vectors();
-      __syncthreads();
-    }
+    put_vectors();
+    __syncthreads();
   }
 
   // ---- final layer on the image tokens, written straight into the latent layout ----
-  Weights<1, D> w_f;
-  load_weights<D>(w_f, a.fin.w, a.fin.ld, wc, 4 * a.C, lane);
-  const float* fm = a.fmod + (int64_t)row * 2 * D;
-  layer_norm<D, L16>(h, act, fm, fm + D);
+  const int c_f = wc * 4 + lk;                       // channel of the wave's columns 4 c .. 4 c + 3: one channel's 2 x 2 patch
+  f32x4v b_f = {0.f, 0.f, 0.f, 0.f};
+  if (c_f < a.C) b_f = bias4(a.fin.b + 4 * c_f);
+  layer_norm<D, L16>(h, act, md, md + D);
   __syncthreads();
   float* u = a.u + (int64_t)m * a.C * HW;
   if (wc * 16 >= 4 * a.C) return;                    // no barrier follows
-  product<D, 1, D, 1, T>(act, a_pitch(D), w_f, wc, wr, lane,
-                      [&](int, int col) { const int c = col * 4 + lk; return c < a.C ? bias4(a.fin.b + 4 * c) : f32x4v{0.f, 0.f, 0.f, 0.f}; },
-                      [&](int, int col, int rt, const f32x4v& v) {
-                        const int tok = rt * 16 + lr, c = col * 4 + lk;      // columns 4 c .. 4 c + 3: one channel's 2 x 2 patch
-                        if (tok >= a.Li || c >= a.C) return;
-                        const int py = tok / Wp, px = tok - py * Wp;
-                        float* dst = u + (int64_t)c * HW + 2 * py * a.W + 2 * px;
-                        *reinterpret_cast<float2*>(dst) = float2{v[0], v[1]};
-                        *reinterpret_cast<float2*>(dst + a.W) = float2{v[2], v[3]};
-                      });
+  product<D, 1, D, 1, T>(act, a_pitch(D), w_o, wc, wr, lane, [&](int, int) { return b_f; },
+                         [&](int, int, int rt, int, const f32x4v& v) {
+                           const int tok = rt * 16 + lr;
+                           if (tok >= a.Li || c_f >= a.C) return;
+                           const int py = tok / Wp, px = tok - py * Wp;
+                           float* dst = u + (int64_t)c_f * HW + 2 * py * a.W + 2 * px;
+                           *reinterpret_cast<float2*>(dst) = float2{v[0], v[1]};
+                           *reinterpret_cast<float2*>(dst + a.W) = float2{v[2], v[3]};
+                         });
 }
 
 // Whatever fits the LDS of a compute unit runs here, however many trajectories are active (so that a trajectory's result does not
