@@ -285,16 +285,17 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(const AttnArg
 // value products run, values while the scores do), and keys and values come by direct loads a whole tile ahead, with one
 // barrier per tile of 64 keys.  Two blocks share the operand reads.
 // There is no running maximum: probabilities are 2^score as they are, which bf16 and fp32 hold with the same relative precision
-// anywhere between 2^-60 and 2^100, so no reference has to be subtracted, compared or raised.  A block of 32 queries in which a
-// normaliser leaves that range (a row's largest logit below -41 or above 69, or a value that is not finite) is done again by the
-// online softmax with a reference exponent, for that block alone, so that a query's result depends on its own block and not on QB.
+// anywhere between 2^-60 and 2^60, so no reference has to be subtracted, compared or raised; a value of up to 2^67 times such a
+// normaliser is still finite in fp32.  A block of 32 queries in which a normaliser leaves that range (a row's largest logit below
+// -41 or above 41, or a value that is not finite) is done again by the online softmax with a reference exponent, for that block
+// alone, so that a query's result depends on its own block and not on QB.
 // A step and wave costs 1024 cycles of MFMA and 850 of vector ALU (32 exponentials of eight) per 64 queries and 64 keys; taken apart
 // like this it runs in about 2400 (2700 with the maximum, and with the keys read one fragment at a time before their MFMAs).  What
 // is left is power (zero operands: 1040 TFLOP/s, random ones 870) and the part-filled tiles of queries and keys.  us, before / now:
 // 48 x 24 heads x 1178 512 / 466, 24 x 24 x 1178 267 / 238, 24 x 12 x 1024 96 / 85, 24 x 12 x 1024 on 77 keys 28.5 / 24.8,
 // 10 x 16 x 340 14.2 / 12.4.
 constexpr int FAST_K = 2 * KTILE * 64 * 2, FAST_LDS = FAST_K + 3 * KTILE * 64 * 2;   // two key tiles, three value tiles
-constexpr float L_MIN = 0x1p-60f, L_MAX = 0x1p100f;
+constexpr float L_MIN = 0x1p-60f, L_MAX = 0x1p60f;
 
 // the value exists from here on
 __device__ __forceinline__ void pin(bf16x8& v) {

@@ -166,7 +166,7 @@ def test_network_attention_kernels_match_oracle(lib, B, Lq, Lk, heads, hd, gain,
 
 # a constant added to the scores of the queries of one block of 32 (exact in bf16: one channel holds 1 and the constant), inside the
 # range in which probabilities are taken as they are and outside it on either side, where that block alone is done again
-@pytest.mark.parametrize("offset", [90.0, 130.0, 1000.0, -50.0, -70.0, -140.0, -1000.0])
+@pytest.mark.parametrize("offset", [50.0, 90.0, 130.0, 1000.0, -50.0, -70.0, -140.0, -1000.0])
 @pytest.mark.parametrize("Lk", [13, 64, 130, 331])
 def test_network_attention_outside_the_range_of_plain_probabilities(lib, offset, Lk):
     say(f"network attention, scores moved by {offset}, {Lk} keys")
@@ -176,6 +176,7 @@ def test_network_attention_outside_the_range_of_plain_probabilities(lib, offset,
     q = workloads.bf16_round(rng.standard_normal((B, Lq, hd), dtype=np.float32) * scale)
     k = workloads.bf16_round(rng.standard_normal((B, Lk, hd), dtype=np.float32))
     v = workloads.bf16_round(rng.standard_normal((B, Lk, hd), dtype=np.float32))
+    v *= np.float32(2.0 ** 60)                             # exact; times an unnormalised probability of 2^90 it has no fp32 value
     q[:, :, 5], k[:, :, 5] = 0.0, offset
     plain = {kernel: _network_attention(lib, q, k, v, heads, kernel) for kernel in (1, 2)}
     q[1, 96:128, 5] = 1.0
