@@ -285,10 +285,10 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(const AttnArg
 // value products run, values while the scores do), and keys and values come by direct loads a whole tile ahead, with one
 // barrier per tile of 64 keys.  Two blocks share the operand reads.
 // There is no running maximum: probabilities are 2^score as they are, which bf16 and fp32 hold with the same relative precision
-// anywhere between 2^-60 and 2^60, so no reference has to be subtracted, compared or raised; a value of up to 2^67 times such a
-// normaliser is still finite in fp32.  A block of 32 queries in which a normaliser leaves that range (a row's largest logit below
-// -41 or above 41, or a value that is not finite) is done again by the online softmax with a reference exponent, for that block
-// alone, so that a query's result depends on its own block and not on QB.
+// anywhere between 2^-60 and 2^60, so no reference has to be subtracted, compared or raised.  A block of 32 queries is done again by
+// the online softmax with a reference exponent if a normaliser leaves that range (a row's largest logit below -41 or above 41) or
+// values beside it leave fp32's: a sum that is not finite, or, below normalisers of 1, one so small that products under 2^-126 could
+// be missing from it.  Block by block, so that a query's result depends on its own block and not on QB.
 // A step and wave costs 1024 cycles of MFMA and 850 of vector ALU (32 exponentials of eight) per 64 queries and 64 keys; taken apart
 // like this it runs in about 2400 (2700 with the maximum, and with the keys read one fragment at a time before their MFMAs).  What
 // is left is power (zero operands: 1040 TFLOP/s, random ones 870) and the part-filled tiles of queries and keys.  us, before / now:
@@ -296,6 +296,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(const AttnArg
 // 10 x 16 x 340 14.2 / 12.4.
 constexpr int FAST_K = 2 * KTILE * 64 * 2, FAST_LDS = FAST_K + 3 * KTILE * 64 * 2;   // two key tiles, three value tiles
 constexpr float L_MIN = 0x1p-60f, L_MAX = 0x1p60f;
+constexpr float O_MIN = 0x1p-96f;                // beside it, 2^16 lost products of 2^-126 are 2^-14
 
 // the value exists from here on
 __device__ __forceinline__ void pin(bf16x8& v) {
@@ -536,7 +537,18 @@ __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_k
 #pragma unroll
   for (int c = 0; c < QB; ++c) {
     l_tot[c] = l_run[c] + __shfl_xor(l_run[c], 32, WAVE);
-    again[c] = wave_has_queries && __builtin_amdgcn_ballot_w64(!(l_tot[c] >= L_MIN && l_tot[c] <= L_MAX)) != 0ull;
+    float most = 0.f, least = 1.f;               // of the lane's sums; NaN as soon as one of them is
+#pragma unroll
+    for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) most = __builtin_elementwise_maximum(most, __builtin_fabsf(o[c][ot][e]));
+    if (__builtin_amdgcn_ballot_w64(l_tot[c] < 1.f) != 0ull)
+#pragma unroll
+      for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) least = __builtin_elementwise_minimum(least, __builtin_fabsf(o[c][ot][e]));
+    const bool sound = l_tot[c] >= L_MIN && l_tot[c] <= L_MAX && most < __builtin_huge_valf() && (l_tot[c] >= 1.f || least >= O_MIN);
+    again[c] = wave_has_queries && __builtin_amdgcn_ballot_w64(!sound) != 0ull;
     any = any || again[c];
   }
   if (__syncthreads_or(any ? 1 : 0)) {

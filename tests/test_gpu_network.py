@@ -193,3 +193,24 @@ def test_network_attention_outside_the_range_of_plain_probabilities(lib, offset,
         if kernel == 1:
             first = got
         np.testing.assert_array_equal(got, first)
+
+
+# values so large or so small that beside a normaliser inside the range of plain probabilities (2^offset and more) their products
+# leave fp32's range: the reference exponent of the online softmax keeps them
+@pytest.mark.parametrize("offset,exponent", [(50.0, 80), (30.0, 110), (0.0, 115), (-50.0, -85), (-20.0, -115), (-58.0, -75)])
+@pytest.mark.parametrize("Lk", [13, 128, 331])
+def test_network_attention_with_values_of_any_size(lib, offset, exponent, Lk):
+    say(f"network attention, scores moved by {offset}, values of size 2^{exponent}, {Lk} keys")
+    rng = np.random.default_rng(Lk)
+    B, Lq, heads, hd = 1, 300, 1, 64
+    scale = np.float32(1.4426950408889634 / math.sqrt(hd))
+    q = workloads.bf16_round(rng.standard_normal((B, Lq, hd), dtype=np.float32) * scale)
+    k = workloads.bf16_round(rng.standard_normal((B, Lk, hd), dtype=np.float32))
+    v = workloads.bf16_round(rng.standard_normal((B, Lk, hd), dtype=np.float32)) * np.float32(2.0 ** exponent)     # exact
+    q[:, :, 5], k[:, :, 5] = 1.0, offset
+    want = dit.attention(q.astype(np.float64) / float(scale), k.astype(np.float64), v.astype(np.float64), heads)
+    outs = [_network_attention(lib, q, k, v, heads, kernel) for kernel in (1, 2)]
+    np.testing.assert_array_equal(outs[0], outs[1])
+    assert np.isfinite(outs[0]).all()
+    # probabilities and outputs are rounded to bf16 (2^-9 relative)
+    assert np.max(np.abs(outs[0] - want)) < 1.5e-2 * np.max(np.abs(want))
