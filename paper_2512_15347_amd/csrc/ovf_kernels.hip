@@ -299,11 +299,11 @@ __device__ __forceinline__ bool stage_chunks(const float* rewards, int first, in
 template <bool WHOLE>
 __device__ __forceinline__ int staged(int e) { return WHOLE ? 4 * swizzled(e >> 2) + (e & 3) : padded(e); }
 
-// One group per lane, n <= N members from the wave's o-th staged reward on, 1 <= k < n, k <= K.  `full`: every lane that matters has
-// n = N.  Returns the survivor mask.
+// One group per lane, n <= N members from the wave's o-th staged reward on, 1 <= k < n, k <= K.  `sorts`: the lane's result is
+// used; `full`: every such lane has n = N.  Returns the survivor mask.
 template <int N, int K, bool WHOLE>
-__device__ __forceinline__ uint64_t select_lane(const float* __restrict__ rewards, int first, int total, int o, int n, int k, bool full,
-                                                int lane, float* row) {
+__device__ __forceinline__ uint64_t select_lane(const float* __restrict__ rewards, int first, int total, int o, int n, int k, bool sorts,
+                                                bool full, int lane, float* row) {
   constexpr bool KEEP = K <= 16;                     // the members stay in registers for the thresholds (beside 32 counts they do not fit)
   float y[K], z[K], w[N];
   {
@@ -405,7 +405,10 @@ __device__ __forceinline__ uint64_t select_lane(const float* __restrict__ reward
 #pragma unroll
   for (int i = 0; i < N; ++i)
     if (i < n && (w[i] <= tlo || w[i] >= thi)) mask |= 1ull << i;
-  if (__ballot(__popcll(mask) != k) != 0ull) {       // somewhere members tie across a threshold: lowest / highest slots first
+  // Somewhere members tie across a threshold: lowest / highest slots first.  A lane whose result is not used has no say: without
+  // padding behind its two members its count never fits, and one group that keeps everything sent the whole wave through here
+  // (2^20 groups of 64 -> 16, every 64th unpruned: 228 -> 153 us, 64 -> 32 297 -> 240, 32 -> 8 143 -> 102, 16 -> 4 105 -> 82).
+  if (__ballot(sorts && __popcll(mask) != k) != 0ull) {
     if (KEEP) {
       stage_rewards(rewards, first, total, lane, row);
       lanes_sync();
@@ -427,12 +430,19 @@ __device__ __forceinline__ uint64_t select_lane(const float* __restrict__ reward
   lanes_sync();
   return mask;
 }
+// n_max, k_max: the largest n and k of the lanes that sort; `same`: all of them have n_max members
 template <bool WHOLE>
-__device__ __forceinline__ uint64_t select_lane_sized(const float* __restrict__ rewards, int first, int total, int n_max, int k_max, int o, int n, int k, bool full16, bool full32, bool full64, int lane,
-                                                      float* row) {
-  if (n_max <= 16) return select_lane<16, 16, WHOLE>(rewards, first, total, o, n, k, full16, lane, row);
-  if (n_max <= 32) return k_max <= 16 ? select_lane<32, 16, WHOLE>(rewards, first, total, o, n, k, full32, lane, row) : select_lane<32, 32, WHOLE>(rewards, first, total, o, n, k, full32, lane, row);
-  return k_max <= 16 ? select_lane<64, 16, WHOLE>(rewards, first, total, o, n, k, full64, lane, row) : select_lane<64, 32, WHOLE>(rewards, first, total, o, n, k, full64, lane, row);
+__device__ __forceinline__ uint64_t select_lane_sized(const float* __restrict__ rewards, int first, int total, int n_max, int k_max, int o,
+                                                      int n, int k, bool sorts, bool same, int lane, float* row) {
+  if (n_max <= 16) return select_lane<16, 16, WHOLE>(rewards, first, total, o, n, k, sorts, same && n_max == 16, lane, row);
+  if (n_max <= 32) {
+    const bool full = same && n_max == 32;
+    return k_max <= 16 ? select_lane<32, 16, WHOLE>(rewards, first, total, o, n, k, sorts, full, lane, row)
+                       : select_lane<32, 32, WHOLE>(rewards, first, total, o, n, k, sorts, full, lane, row);
+  }
+  const bool full = same && n_max == 64;
+  return k_max <= 16 ? select_lane<64, 16, WHOLE>(rewards, first, total, o, n, k, sorts, full, lane, row)
+                     : select_lane<64, 32, WHOLE>(rewards, first, total, o, n, k, sorts, full, lane, row);
 }
 
 // whether the wave-per-group code computes the mask of a group (n members, k kept; `odd`: of a wave with a size outside 0..64)
@@ -526,8 +536,8 @@ __global__ __launch_bounds__(LANE_WAVES * WAVE, 2) void ovf_select_lanes_kernel(
     // lanes with nothing to sort work on the first rewards of the wave, and the result is not used
     const int o = sorts ? b - first : 0, nn = sorts ? n : 2, kq = sorts ? k : 1;
     const bool same = __ballot(sorts && n != n_max) == 0ull;
-    mask = whole ? select_lane_sized<true>(rewards, first, total, n_max, k_max, o, nn, kq, same && n_max == 16, same && n_max == 32, same && n_max == 64, lane, row)
-                 : select_lane_sized<false>(rewards, first, total, n_max, k_max, o, nn, kq, same && n_max == 16, same && n_max == 32, same && n_max == 64, lane, row);
+    mask = whole ? select_lane_sized<true>(rewards, first, total, n_max, k_max, o, nn, kq, sorts, same, lane, row)
+                 : select_lane_sized<false>(rewards, first, total, n_max, k_max, o, nn, kq, sorts, same, lane, row);
   }
   if (!sorts) mask = have && !bad && k >= 1 ? (given ? masks[g] : first_slots(k)) : 0ull;
   if (have) masks[g] = mask;

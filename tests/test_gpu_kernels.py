@@ -439,6 +439,35 @@ def test_ovf_unsuited_groups_do_not_hold_up_a_batch(lib):
     assert many < 4 * suited and unpruned < 4 * suited
 
 
+@pytest.mark.parametrize("n,k", [(64, 16), (32, 8), (16, 4)])
+def test_ovf_groups_with_nothing_to_sort_cost_what_they_write(lib, n, k):
+    """Sizes that fill the sort, one group in 64 unpruned: the other lanes' time does not change, and the unpruned groups write n - k
+    more indices each (3 % of the batch's bytes).  One such group in a wave took it to 1.65 (64 -> 16), 1.52 and 1.35 times while its
+    lane sent the others through the route of ties."""
+    say(f"ovf lanes, time with unpruned groups, {n} -> {k}")
+    G = 1 << 18
+    off = torch.arange(G + 1, dtype=torch.int32, device=DEV) * n
+    r = torch.randn(G * n, device=DEV)
+    masks, noff = torch.zeros(G, dtype=torch.int64, device=DEV), torch.zeros(G + 1, dtype=torch.int32, device=DEV)
+    status, scratch = torch.zeros(4, dtype=torch.int32, device=DEV), torch.zeros(lib.pg_ovf_scratch_ints(G), dtype=torch.int32, device=DEV)
+    micros = []
+    for kept in (k, n):
+        ks = torch.full((G,), k, dtype=torch.int32, device=DEV)
+        ks[5::64] = kept
+        sel = torch.zeros(int(ks.sum()), dtype=torch.int32, device=DEV)
+        a, b, best = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), 1e9
+        for _ in range(8):
+            a.record()
+            for _ in range(20):
+                lib.pg_ovf_select(r, off, ks, G, masks, sel, noff, status, scratch)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 50)
+        micros.append(best)
+    say(f"  plain {micros[0]:.1f} us, one in 64 unpruned {micros[1]:.1f} us")
+    assert micros[1] < 1.2 * micros[0]
+
+
 @pytest.mark.parametrize("words", [1, 2, 3, 4, 5, 8, 9, 16])
 def test_ovf_large_at_every_workgroup_size(lib, words):
     say(f"ovf large, {words} mask words")
