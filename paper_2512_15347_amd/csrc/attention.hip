@@ -284,19 +284,41 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void attention_kernel(const AttnArg
 // run on the matrix pipe beside this step's exponentials, operands are read from LDS a phase before they are used (keys while the
 // value products run, values while the scores do), and keys and values come by direct loads a whole tile ahead, with one
 // barrier per tile of 64 keys.  Two blocks share the operand reads.
-// There is no running maximum: probabilities are 2^score as they are, which bf16 and fp32 hold with the same relative precision
-// anywhere between 2^-60 and 2^60, so no reference has to be subtracted, compared or raised.  A block of 32 queries is done again by
-// the online softmax with a reference exponent if a normaliser leaves that range (a row's largest logit below -41 or above 41) or
-// values beside it leave fp32's: a sum that is not finite, or, below normalisers of 1, one so small that products under 2^-126 could
-// be missing from it.  Block by block, so that a query's result depends on its own block and not on QB.
+// Ordinary scores need no running maximum: probabilities are 2^score as they are, which bf16 and fp32 hold with the same relative
+// precision anywhere between 2^-60 and 2^60, so no reference has to be subtracted, compared or raised.  A block of 32 queries gets a
+// reference exponent (raised by the rule of the kernel above) when the largest of a query's first 32 scores lies outside -40 .. 40, or
+// after the tile that takes a normaliser past 2^60; a wave that holds such a block does the rest of its tiles one after another
+// (`chained`).  Sharp scores (largest of a row 60 and more), us, always with a running maximum / blocks outside 2^-60 .. 2^60 done
+// twice / now: 48 x 24 heads x 1178 714 / 1009 / 610, 24 x 12 x 1024 103 / 175 / 104, on 77 keys 28.5 / 35.1 / 28.6; every score
+// moved by 70: 510 / 930 / 545.
+// Done again from its first tile is only a block that leaves fp32's range all the same: a normaliser past 2^128 inside one tile, values
+// whose sum is not finite or, below normalisers of 1, so small that products under 2^-126 could be missing from it.  All of this
+// block by block, so that a query's result depends on its own block and not on QB.
 // A step and wave costs 1024 cycles of MFMA and 850 of vector ALU (32 exponentials of eight) per 64 queries and 64 keys; taken apart
 // like this it runs in about 2400 (2700 with the maximum, and with the keys read one fragment at a time before their MFMAs).  What
 // is left is power (zero operands: 1040 TFLOP/s, random ones 870) and the part-filled tiles of queries and keys.  us, before / now:
 // 48 x 24 heads x 1178 512 / 466, 24 x 24 x 1178 267 / 238, 24 x 12 x 1024 96 / 85, 24 x 12 x 1024 on 77 keys 28.5 / 24.8,
 // 10 x 16 x 340 14.2 / 12.4.
 constexpr int FAST_K = 2 * KTILE * 64 * 2, FAST_LDS = FAST_K + 3 * KTILE * 64 * 2;   // two key tiles, three value tiles
-constexpr float L_MIN = 0x1p-60f, L_MAX = 0x1p60f;
+constexpr float S_PLAIN = 40.f, L_MIN = 0x1p-60f, L_MAX = 0x1p60f;
 constexpr float O_MIN = 0x1p-96f;                // beside it, 2^16 lost products of 2^-126 are 2^-14
+
+__device__ __forceinline__ float largest(const f32x16& s) {
+  float mx = s[0];
+#pragma unroll
+  for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
+  return mx;
+}
+
+// op over the two lanes of a query
+template <class Op>
+__device__ __forceinline__ float across_halves(float v, Op op) {
+  const uint32_t b = __builtin_bit_cast(uint32_t, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return op(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
+}
+__device__ __forceinline__ float max_of(float x, float y) { return fmaxf(x, y); }
+__device__ __forceinline__ float sum_of(float x, float y) { return x + y; }
 
 // the value exists from here on
 __device__ __forceinline__ void pin(bf16x8& v) {
@@ -309,6 +331,7 @@ template <int QB>
 __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_kernel(const AttnArgs a) {
   constexpr int HD = 64, KS = 4, WQ = 32 * QB, QT = 4 * WQ;
   __shared__ __align__(16) unsigned char smem[FAST_LDS];
+  __shared__ int left_over[4];                   // whether a wave has blocks to do again
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   const int nq = (a.Lq + QT - 1) / QT;
@@ -327,11 +350,20 @@ __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_k
   const int n_tiles = (a.Lk + KTILE - 1) / KTILE, n_full = a.Lk / KTILE;
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
   int s_row[2], s_ch[2];
+  int ka[KS], va[4];                             // operand addresses in a stage: the second 32 rows have the chunks permuted and lie 4 KB further
+  auto addresses = [&](int lane) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    s_row[i] = (2 * wave + i) * 8 + (lane >> 3);
-    s_ch[i] = (lane & 7) ^ ((s_row[i] ^ (s_row[i] >> 3)) & 7);
-  }
+    for (int i = 0; i < 2; ++i) {
+      s_row[i] = (2 * wave + i) * 8 + (lane >> 3);
+      s_ch[i] = (lane & 7) ^ ((s_row[i] ^ (s_row[i] >> 3)) & 7);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      ka[c] = k_off<HD>(lane & 31, 2 * c + (lane >> 5));
+      va[c] = v_off(lane & 31, 2 * c + (lane >> 5));
+    }
+  };
+  addresses(lane);
   auto k_stage = [](int kt) { return (kt & 1) * 8192; };
   auto v_stage = [](int kt) { return FAST_K + (kt % 3) * 8192; };
   auto request = [&](int kt) {
@@ -361,6 +393,12 @@ __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_k
     }
     __syncthreads();
   };
+  // in tile kt, when its keys have been read: the next one is published, the one after it asked for
+  auto turn = [&](int kt) {
+    if (kt + 1 >= n_tiles) return;
+    publish(kt + 1);
+    if (kt + 2 < n_tiles) request(kt + 2);
+  };
   request(0);
   if (n_tiles > 1) request(1);
 
@@ -378,19 +416,38 @@ __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_k
     }
   }
   f32x16 o[QB][2];
-  float l_run[QB];
+  float l_run[QB], m_run[QB];                    // m_run: reference exponent of the lane's query, 0 in a block without
+  bool ref[QB];                                  // wave-uniform: whether the block has one
 #pragma unroll
   for (int c = 0; c < QB; ++c) {
     o[c][0] = o[c][1] = f32x16{};
-    l_run[c] = 0.f;
+    l_run[c] = m_run[c] = 0.f;
+    ref[c] = false;
   }
+  auto chain = [&] { return ref[0] || ref[QB - 1]; };
+  // the first scores of a block
+  auto look = [&](int c, const f32x16& s) {
+    ref[c] = __builtin_amdgcn_ballot_w64(!(fabsf(across_halves(largest(s), max_of)) <= S_PLAIN)) != 0ull;
+  };
+  auto passed = [&] {
+    bool over = false;
+#pragma unroll
+    for (int c = 0; c < QB; ++c) over = over || !(l_run[c] <= L_MAX);
+    return __builtin_amdgcn_ballot_w64(over) != 0ull;
+  };
+  // after a tile: a reference that brings normalisers to 1 .. 2 for a block in which one has left the range
+  auto settle = [&](int c) {
+    if (ref[c] || __builtin_amdgcn_ballot_w64(!(l_run[c] <= L_MAX)) == 0ull) return;
+    const int up = __builtin_amdgcn_frexp_expf(across_halves(l_run[c], sum_of)) - 1;
+    ref[c] = true;
+    m_run[c] = (float)up;
+    l_run[c] = __builtin_amdgcn_ldexpf(l_run[c], -up);
+#pragma unroll
+    for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[c][ot][e] = __builtin_amdgcn_ldexpf(o[c][ot][e], -up);
+  };
 
-  // operand addresses in a stage: the second 32 rows have the chunks permuted and lie 4 KB further
-  int ka[KS], va[4];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) ka[ks] = k_off<HD>(l32, 2 * ks + half);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) va[c] = v_off(l32, 2 * c + half);
   // keys / values of half t of a tile
   auto read_keys = [&](const unsigned char* st, int t, bf16x8 (&kf)[KS]) {
 #pragma unroll
@@ -468,19 +525,10 @@ __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_k
     constexpr bool LAST = decltype(last_c)::value;
     const unsigned char* v_st = smem + v_stage(kt);
     const unsigned char* k_st = smem + k_stage(kt + 1);
-    auto turn = [&] {
-      if (kt + 1 >= n_tiles) return;
-      publish(kt + 1);
-      if (kt + 2 < n_tiles) request(kt + 2);
-    };
-    if (!wave_has_queries) {
-      turn();
-      return;
-    }
     float psum[QB];
 #pragma unroll
     for (int c = 0; c < QB; ++c) psum[c] = 0.f;
-    step(s0, s1, v_st, 0, psum, yes, turn, [&] { if (!LAST) read_keys(k_st, 0, kf); });
+    step(s0, s1, v_st, 0, psum, yes, [&] { turn(kt); }, [&] { if (!LAST) read_keys(k_st, 0, kf); });
     if constexpr (LAST) step(s1, s0, v_st, 1, psum, no, nothing, nothing);
     else step(s1, s0, v_st, 1, psum, yes, nothing, [&] { read_keys(k_st, 1, kf); });
 #pragma unroll
@@ -494,20 +542,27 @@ __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_k
   if (n_tiles > 1) wait_dma_but<4>();            // tile 1 may still be on its way
   if (n_tiles > 1) __syncthreads();
   else publish(0);
-  if (n_full > 0) {
-    if (wave_has_queries) {
-      read_keys(smem, 0, kf);
+  int kt = 0;                                    // the next tile
+  if (n_full > 0 && wave_has_queries) {
+    read_keys(smem, 0, kf);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
+    for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-        for (int c = 0; c < QB; ++c) score_mfma(s0[c], c, ks, kf);
-      read_keys(smem, 1, kf);
+      for (int c = 0; c < QB; ++c) score_mfma(s0[c], c, ks, kf);
+    read_keys(smem, 1, kf);
+#pragma unroll
+    for (int c = 0; c < QB; ++c) look(c, s0[c]);
+    bool plain = !chain();
+    while (plain && kt + 1 < n_full) {
+      full_tile(kt++, no);
+      plain = !passed();
     }
-    for (int kt = 0; kt + 1 < n_full; ++kt) full_tile(kt, no);
-    full_tile(n_full - 1, yes);
+    if (plain) full_tile(kt++, yes);
+#pragma unroll
+    for (int c = 0; c < QB; ++c) settle(c);
   }
   const int rest = a.Lk - n_full * KTILE;
-  if (rest > 0 && wave_has_queries) {            // the last, part-filled tile, published by the tile before it
+  if (rest > 0 && wave_has_queries && !chain()) {    // the last, part-filled tile, published by the tile before it
     const unsigned char* k_st = smem + k_stage(n_full);
     float psum[QB];
 #pragma unroll
@@ -523,72 +578,64 @@ __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_k
       for (int c = 0; c < QB; ++c)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          if (t * 32 + 8 * (e >> 2) + 4 * half + (e & 3) >= rest) s0[c][e] = -__builtin_huge_valf();
+          if (8 * (e >> 2) + (e & 3) >= rest - 32 * t - 4 * half) s0[c][e] = -__builtin_huge_valf();
       if (t) step(s0, s1, smem + v_stage(n_full), 1, psum, no, nothing, nothing);
       else step(s0, s1, smem + v_stage(n_full), 0, psum, no, nothing, nothing);
     }
 #pragma unroll
-    for (int c = 0; c < QB; ++c) l_run[c] += psum[c];
+    for (int c = 0; c < QB; ++c) {
+      l_run[c] += psum[c];
+      settle(c);
+    }
+    ++kt;
   }
 
-  // ---- blocks whose sums left the range: online softmax with a reference exponent ----
-  float l_tot[QB];
-  bool again[QB], any = false;
+  // ---- the rest of the tiles where a block has a reference; waves without queries only fetch ----
+  bool work[QB];
 #pragma unroll
-  for (int c = 0; c < QB; ++c) {
-    l_tot[c] = l_run[c] + __shfl_xor(l_run[c], 32, WAVE);
-    float most = 0.f, least = 1.f;               // of the lane's sums; NaN as soon as one of them is
+  for (int c = 0; c < QB; ++c) work[c] = wave_has_queries;
+  // tile kt for N blocks from C0 on
+  auto chained = [&](int kt, auto c0_c, auto n_c) {
+    constexpr int C0 = decltype(c0_c)::value, N = decltype(n_c)::value;
+    const unsigned char* k_st = smem + k_stage(kt);
+    const unsigned char* v_st = smem + v_stage(kt);
+    const int left = a.Lk - kt * KTILE;
+    f32x16 s[N][2];
 #pragma unroll
-    for (int ot = 0; ot < 2; ++ot)
+    for (int t = 0; t < 2; ++t) {
+      read_keys(k_st, t, kf);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) most = __builtin_elementwise_maximum(most, __builtin_fabsf(o[c][ot][e]));
-    if (__builtin_amdgcn_ballot_w64(l_tot[c] < 1.f) != 0ull)
+      for (int n = 0; n < N; ++n) {
+        const float neg_m = -m_run[C0 + n];
 #pragma unroll
-      for (int ot = 0; ot < 2; ++ot)
+        for (int e = 0; e < 16; ++e) s[n][t][e] = neg_m;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) least = __builtin_elementwise_minimum(least, __builtin_fabsf(o[c][ot][e]));
-    const bool sound = l_tot[c] >= L_MIN && l_tot[c] <= L_MAX && most < __builtin_huge_valf() && (l_tot[c] >= 1.f || least >= O_MIN);
-    again[c] = wave_has_queries && __builtin_amdgcn_ballot_w64(!sound) != 0ull;
-    any = any || again[c];
-  }
-  if (__syncthreads_or(any ? 1 : 0)) {
-    float m_run[QB];
-#pragma unroll
-    for (int c = 0; c < QB; ++c)
-      if (again[c]) {
-        o[c][0] = o[c][1] = f32x16{};
-        l_run[c] = m_run[c] = 0.f;
+        for (int ks = 0; ks < KS; ++ks) s[n][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[C0 + n][ks], s[n][t], 0, 0, 0);
       }
-    // a key tile for block c; `left`: keys from the tile's first on
-    auto general = [&](int kt, int c, int left) {
-      const unsigned char* k_st = smem + k_stage(kt);
-      const unsigned char* v_st = smem + v_stage(kt);
-      f32x16 s[2];
-      bf16x8 pf[2][2], vf[2][2];
-      const float neg_m = -m_run[c];
+    }
+    if (left < KTILE) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        read_keys(k_st, t, kf);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) s[t][e] = neg_m;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[c][ks], s[t], 0, 0, 0);
-      }
-      if (left < KTILE) {
+      for (int n = 0; n < N; ++n)
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
           for (int e = 0; e < 16; ++e)
-            if (t * 32 + 8 * (e >> 2) + 4 * half + (e & 3) >= left) s[t][e] = -__builtin_huge_valf();
-      }
-      float mx = s[0][0];
+            if (8 * (e >> 2) + (e & 3) >= left - 32 * t - 4 * half) s[n][t][e] = -__builtin_huge_valf();
+    }
+    float mx[N];
+    bool raise = false;
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int n = 0; n < N; ++n) {
+      mx[n] = fmaxf(largest(s[n][0]), largest(s[n][1]));
+      raise = raise || (ref[C0 + n] && (kt == 0 || __builtin_amdgcn_ballot_w64(mx[n] > 8.0f) != 0ull));
+    }
+    if (raise)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[t][e]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-      if (kt == 0 || __builtin_amdgcn_ballot_w64(mx > 8.0f) != 0ull) {
-        const float delta = kt == 0 ? mx : fmaxf(mx, 0.f);               // the first tile sets the reference
+      for (int n = 0; n < N; ++n) {
+        const int c = C0 + n;
+        if (!ref[c] || (kt > 0 && __builtin_amdgcn_ballot_w64(mx[n] > 8.0f) == 0ull)) continue;
+        const float top = across_halves(mx[n], max_of);
+        const float delta = kt == 0 ? top : fmaxf(top, 0.f);             // the first tile sets the reference
         const float alpha = kt == 0 ? 1.0f : __builtin_amdgcn_exp2f(-delta);
         m_run[c] += delta;
         l_run[c] *= alpha;
@@ -599,45 +646,105 @@ __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_k
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) s[t][e] -= delta;
+          for (int e = 0; e < 16; ++e) s[n][t][e] -= delta;
       }
+    bf16x8 pf[N][2][2], vf[2][2];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
       float psum = 0.f;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) probability_pair(s[t], pf[t], i);
+        for (int i = 0; i < 8; ++i) probability_pair(s[n][t], pf[n][t], i);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) psum = add_pair(pf[t], i, psum);
+        for (int i = 0; i < 8; ++i) psum = add_pair(pf[n][t], i, psum);
       }
-      l_run[c] += psum;
+      l_run[C0 + n] += psum;
+    }
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        read_values(v_st, t, vf);
+    for (int t = 0; t < 2; ++t) {
+      read_values(v_st, t, vf);
+#pragma unroll
+      for (int n = 0; n < N; ++n)
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-          for (int ot = 0; ot < 2; ++ot) o[c][ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[jj][ot], pf[t][jj], o[c][ot], 0, 0, 0);
-      }
-    };
-    request(0);
-    for (int kt = 0; kt < n_tiles; ++kt) {
-      publish(kt);
-      if (kt + 1 < n_tiles) request(kt + 1);
-#pragma unroll
-      for (int c = 0; c < QB; ++c)
-        if (again[c]) general(kt, c, a.Lk - kt * KTILE);
+          for (int ot = 0; ot < 2; ++ot)
+            o[C0 + n][ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[jj][ot], pf[n][t][jj], o[C0 + n][ot], 0, 0, 0);
     }
 #pragma unroll
-    for (int c = 0; c < QB; ++c)
-      if (again[c]) l_tot[c] = l_run[c] + __shfl_xor(l_run[c], 32, WAVE);
+    for (int n = 0; n < N; ++n) settle(C0 + n);
+  };
+  const bool kept = n_tiles <= 2;                // all tiles stay where they are
+  float l_tot[QB];
+  for (bool last_round = false;; last_round = true) {
+    if (kt < n_tiles) {
+      int lane_here = lane;
+      asm volatile("" : "+v"(lane_here));        // computed anew: nothing is carried here through the loop above
+      addresses(lane_here);
+    }
+    for (; kt < n_tiles; ++kt) {
+      constexpr std::integral_constant<int, 0> c0{};
+      constexpr std::integral_constant<int, 1> c1{};
+      if (QB == 2 && work[0] && work[QB - 1]) {
+        chained(kt, c0, std::integral_constant<int, QB>{});
+      } else {
+        if (work[0]) chained(kt, c0, c1);
+        if constexpr (QB == 2)
+          if (work[1]) chained(kt, c1, c1);
+      }
+      if (!kept || !last_round) turn(kt);
+    }
+    bool again[QB];
+#pragma unroll
+    for (int c = 0; c < QB; ++c) {
+      l_tot[c] = across_halves(l_run[c], sum_of);
+      float most[4] = {0.f, 0.f, 0.f, 0.f}, least = 1.f;     // of the lane's sums; NaN as soon as one of them is
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int ot = 0; ot < 2; ++ot)
+          most[ot + (e & 2)] = __builtin_elementwise_maximum(most[ot + (e & 2)], __builtin_fabsf(o[c][ot][e]));
+      most[0] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(most[0], most[1]), __builtin_elementwise_maximum(most[2], most[3]));
+      if (__builtin_amdgcn_ballot_w64(l_tot[c] < 1.f) != 0ull)
+#pragma unroll
+        for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) least = __builtin_elementwise_minimum(least, __builtin_fabsf(o[c][ot][e]));
+      const bool sound = l_tot[c] >= L_MIN && l_tot[c] <= L_MAX && most[0] < __builtin_huge_valf() && (l_tot[c] >= 1.f || least >= O_MIN);
+      again[c] = wave_has_queries && __builtin_amdgcn_ballot_w64(!sound) != 0ull;
+    }
+    bool more = !last_round && (again[0] || again[QB - 1]);
+    if (!kept && !last_round) {                  // all waves fetch
+      if (lane == 0) left_over[wave] = more ? 1 : 0;
+      __syncthreads();
+      more = (left_over[0] | left_over[1] | left_over[2] | left_over[3]) != 0;
+    }
+    if (!more) break;
+    kt = 0;
+#pragma unroll
+    for (int c = 0; c < QB; ++c) {
+      work[c] = again[c];
+      if (!again[c]) continue;
+      o[c][0] = o[c][1] = f32x16{};
+      l_run[c] = m_run[c] = 0.f;
+      ref[c] = true;
+    }
+    if (!kept) {
+      request(0);
+      request(1);
+      publish(0);
+    }
   }
   if (!wave_has_queries) return;
 
   // ---- normalise and store: lane holds head-dim rows 8*(e/4) + 4*half + e%4 of its queries ----
+  int lane_out = lane;
+  asm volatile("" : "+v"(lane_out));
 #pragma unroll
   for (int c = 0; c < QB; ++c) {
     const float inv = 1.0f / l_tot[c];
-    const int qr = q0 + 32 * c + l32;
+    const int qr = q0 + 32 * c + (lane_out & 31);
     if (qr < a.Lq) {
       uint16_t* op = (a.split > 0) ? (qr < a.split ? a.out + ((int64_t)b * a.split + qr) * a.ldo + h * HD
                                                    : a.out2 + ((int64_t)b * (a.Lq - a.split) + qr - a.split) * a.ldo + h * HD)
@@ -649,7 +756,7 @@ __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_k
           bf16x4 w;
 #pragma unroll
           for (int t = 0; t < 4; ++t) w[t] = (__bf16)(o[c][ot][4 * q + t] * inv);
-          *reinterpret_cast<bf16x4*>(op + ot * 32 + 8 * q + 4 * half) = w;
+          *reinterpret_cast<bf16x4*>(op + ot * 32 + 8 * q + 4 * (lane_out >> 5)) = w;
         }
     }
   }

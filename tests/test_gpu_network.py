@@ -197,7 +197,7 @@ def test_network_attention_outside_the_range_of_plain_probabilities(lib, offset,
 
 # values so large or so small that beside a normaliser inside the range of plain probabilities (2^offset and more) their products
 # leave fp32's range: the reference exponent of the online softmax keeps them
-@pytest.mark.parametrize("offset,exponent", [(50.0, 80), (30.0, 110), (0.0, 115), (-50.0, -85), (-20.0, -115), (-58.0, -75)])
+@pytest.mark.parametrize("offset,exponent", [(50.0, 80), (30.0, 110), (0.0, 115), (-38.0, -112), (-20.0, -115), (-58.0, -100)])
 @pytest.mark.parametrize("Lk", [13, 128, 331])
 def test_network_attention_with_values_of_any_size(lib, offset, exponent, Lk):
     say(f"network attention, scores moved by {offset}, values of size 2^{exponent}, {Lk} keys")
@@ -214,3 +214,60 @@ def test_network_attention_with_values_of_any_size(lib, offset, exponent, Lk):
     assert np.isfinite(outs[0]).all()
     # probabilities and outputs are rounded to bf16 (2^-9 relative)
     assert np.max(np.abs(outs[0] - want)) < 1.5e-2 * np.max(np.abs(want))
+
+
+# One key far above the others for one block of 32 queries: inside the range in which probabilities are taken as they are, past it
+# in a tile that fp32 still holds (the block goes on with a reference), and in one it does not (the block is done again), in the first
+# half of the first tile, later, and in the part-filled last tile
+@pytest.mark.parametrize("score", [50.0, 70.0, 100.0, 140.0, 600.0])
+@pytest.mark.parametrize("Lk,key", [(64, 40), (331, 3), (331, 63), (331, 130), (331, 255), (331, 328), (90, 77), (192, 64)])
+def test_network_attention_with_one_key_far_above_the_others(lib, score, Lk, key):
+    say(f"network attention, key {key} of {Lk} at {score}")
+    rng = np.random.default_rng(Lk + key)
+    B, Lq, heads, hd = 1, 300, 1, 64
+    scale = np.float32(1.4426950408889634 / math.sqrt(hd))
+    q = workloads.bf16_round(rng.standard_normal((B, Lq, hd), dtype=np.float32) * scale)
+    k = workloads.bf16_round(rng.standard_normal((B, Lk, hd), dtype=np.float32))
+    v = workloads.bf16_round(rng.standard_normal((B, Lk, hd), dtype=np.float32))
+    q[:, :, 5], k[:, :, 5] = 0.0, 0.0
+    k[0, key, 5] = score
+    plain = _network_attention(lib, q, k, v, heads, 1)
+    q[0, 128:160, 5] = np.linspace(0.5, 1.0, 32)                   # not all of the block's queries leave the range
+    q = workloads.bf16_round(q)
+    want = dit.attention(q.astype(np.float64) / float(scale), k.astype(np.float64), v.astype(np.float64), heads)
+    got = _network_attention(lib, q, k, v, heads, 1)
+    assert np.isfinite(got).all()
+    # fp32 scores of size 600 (ulp 6e-5) do not show beside probabilities and outputs rounded to bf16 (2^-9 relative)
+    assert np.max(np.abs(got - want)) < 1.5e-2 * np.max(np.abs(want))
+    others = np.ones((B, Lq), bool)
+    others[0, 128:160] = False
+    np.testing.assert_array_equal(got[others], plain[others])      # nobody else notices
+    np.testing.assert_array_equal(_network_attention(lib, q, k, v, heads, 2), got)
+
+
+@pytest.mark.parametrize("B,Lq,Lk,heads", [(48, 1178, 1178, 24), (24, 1024, 1024, 12), (24, 1024, 77, 12)])
+def test_sharp_attention_takes_little_longer_than_flat(lib, B, Lq, Lk, heads):
+    """Scores of standard deviation 29 in log2 units (largest of a row 60 to 100), which need a reference exponent, against scores of
+    1.4: 1.31, 1.21 and 1.10 times as long (2.2, 2.1 and 1.4 times when every block was done twice)."""
+    say(f"sharp attention, time, {B} x {heads} heads x {Lq} on {Lk}")
+    D, Lkpad = heads * 64, (Lk + 63) // 64 * 64
+    g = torch.Generator(device=DEV)
+    g.manual_seed(Lk)
+    rand = lambda *s: torch.randn(*s, device=DEV, generator=g)
+    bits = lambda t: t.to(torch.bfloat16).view(torch.int16)
+    q, k, vt = rand(B, Lq, D) * (1.4426950408889634 / 8), bits(rand(B, Lk, D)), bits(rand(B, D, Lkpad))
+    out = torch.zeros(B, Lq, D, dtype=torch.int16, device=DEV)
+    micros = []
+    for gain in (1.0, 20.0):
+        qb = bits(q * gain)
+        a, b, best = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), 1e9
+        for _ in range(6):
+            a.record()
+            for _ in range(10):
+                lib.pg_attention_network(qb, k, vt, out, B, Lq, Lk, Lkpad, heads, 64, 0)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 100)
+        micros.append(best)
+    say(f"  flat {micros[0]:.1f} us, sharp {micros[1]:.1f} us")
+    assert micros[1] < (1.6 if Lk > 100 else 1.25) * micros[0]
