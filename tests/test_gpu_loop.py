@@ -276,6 +276,29 @@ def test_network_time_does_not_depend_on_the_grouping(lib):
     assert many < 1.6 * few
 
 
+def test_projection_time_does_not_depend_on_the_sequence_length(lib):
+    """4096 token rows of a 512-wide network as 256 trajectories of 16 tokens and as 16 of 256: the same products (1.05 times; 1.17
+    when the values of groups of rows that span several trajectories were stored token by token)."""
+    say("network forward, time of the products with short sequences")
+    def milliseconds(P, N, H, W):
+        cfg = workloads.get_config("cfg1")
+        cfg.update(P=P, N=N, H=H, W=W, D=512, heads=8, blocks=8, T=1, schedule=[[] for _ in range(P)], Li=H * W // 4, d=4 * H * W)
+        w = workloads.make_weights(cfg)
+        ctx, buf = _gpu_ctx(lib, cfg, w, workloads.make_inputs(cfg, w))
+        lib.pg_init_group(ctx, 5)
+        best = 1e9
+        for _ in range(8):
+            lib.pg_profile_begin(1000)
+            lib.pg_net_forward(ctx, 0)
+            best = min(best, lib.pg_profile_read(0)["ms"])
+            lib.pg_profile_end()
+        lib.pg_destroy(ctx)
+        return best
+    short, long = milliseconds(8, 32, 8, 8), milliseconds(1, 16, 32, 32)
+    say(f"  16 tokens {1e3 * short:.0f} us, 256 tokens {1e3 * long:.0f} us")
+    assert short < 1.1 * long
+
+
 def _sharpen_attention(w, kind, gain):
     """Makes the attention decide the network output: with weights of 0.02 the softmax is nearly flat and its branch small, and a
     wrong value order or a missing key tile moves u by less than its tolerance.  With sharp scores and values and outputs four
