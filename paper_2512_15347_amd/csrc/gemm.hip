@@ -454,7 +454,10 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
         }
       }
     };
-    if (row_w + BM / WM <= MM && col_w + CW <= n_rm) slabs(std::true_type{});
+    // Plain fp32 output keeps its masks: rows that do not end on a 128-byte line share lines with their neighbours, and waves with and
+    // without masks in one workgroup get further apart in them (24576 x 1000 x 256 36.9 us, with masks alone 34.6; no difference
+    // for 1024 or 2048 columns).
+    if (EPI != EPI_F32 && row_w + BM / WM <= MM && col_w + CW <= n_rm) slabs(std::true_type{});
     else slabs(std::false_type{});
     return;
   }
