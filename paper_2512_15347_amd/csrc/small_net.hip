@@ -379,17 +379,28 @@ __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArg
                          });
 }
 
-// Whatever fits the LDS of a compute unit runs here, however many trajectories are active (so that a trajectory's result does not
-// depend on the batch).  A step with two blocks, us, a launch per layer / here:
+// What fits the LDS of a compute unit runs here; however many trajectories are still active, so that a trajectory's result does not
+// change with the prunes of its group or with the steps that are evaluated together.  A step with two blocks, us, a launch per
+// layer / here:
 //   width 128,  64 tokens:   4 trajectories  99 / 49   256: 173 / 58   4096: 1424 / 584
 //   width 128,  90 tokens:   4 trajectories 100 / 60   256: 219 / 71   4096: 2031 / 754
 //   width  64, 184 tokens:   4 trajectories  95 / 59   256: 243 / 70   4096: 2578 / 740
-//   width 128,  16 tokens:   4 trajectories  95 / 41   256: 111 / 48   4096:  456 / 442
-// Width 192 and 256, built the same way, were slower with 8 to 16 trajectories (width 256, 32 tokens, 4 blocks: 185 / 211): there a
-// compute unit's reading of the weights (1.6 MB a block) is the longer part.
+// A workgroup costs as much for 1 token as for 32, its smallest tile, where a launch per layer takes its time by the row.  So of up to
+// 16 tokens (width 64: 14) only groups of few trajectories in all do, the number from which the layers are faster being about
+// 1400 + 18 L^2 (width 64) and 896 + 8 L^2 (width 128).  Loops of three steps, us, a launch per layer / here:
+//   width  64,  1 token:  1536 trajectories 339 / 334, 4096 443 / 778    8 tokens: 2560 520 / 511, 4096 668 / 776
+//   width  64, 12 tokens: 4096 trajectories 793 / 776, 8192 1349 / 1502  15 tokens: 8192 1571 / 1498, 16384 3069 / 2990
+//   width 128,  1 token:   768 trajectories 346 / 299, 4096 628 / 1409   8 tokens: 1280 505 / 478, 4096 961 / 1399
+//   width 128, 16 tokens: 2560 trajectories 939 / 907, 4096 1314 / 1404  18 tokens: 4096 1589 / 1403, 16384 5387 / 5475
+// Built for the two kinds of network whose blocks have this one sequence of layers.  Width 192 and 256, built the same way, were
+// slower with 8 to 16 trajectories (width 256, 32 tokens, 4 blocks: 185 / 211): there a compute unit's reading of the weights (1.6 MB a
+// block) is the longer part.
 bool small_net_takes(const pg_ctx* c) {
   const pg_config& f = c->cfg;
-  return (f.net_kind == PG_NET_ADALN || f.net_kind == PG_NET_JOINT) && (f.D == 64 || f.D == 128) && f.C <= 16 && tiles_for(f.D, c->L) > 0;
+  if ((f.net_kind != PG_NET_ADALN && f.net_kind != PG_NET_JOINT) || (f.D != 64 && f.D != 128) || f.C > 16 || tiles_for(f.D, c->L) == 0)
+    return false;
+  const int64_t L2 = (int64_t)c->L * c->L;
+  return f.D == 64 ? c->L > 14 || c->M0 <= 1400 + 18 * L2 : c->L > 16 || c->M0 <= 896 + 8 * L2;
 }
 
 template <int D, int HD, int T>

@@ -375,6 +375,43 @@ def test_network_output_of_narrow_networks(lib, kind, D, heads, C, H, W, Lc):
     _check_sharp_network(lib, cfg, kind, 7 if L > 1 else 1, (0, 2, 3, 5))
 
 
+# few tokens: the number of trajectories up to which one workgroup each evaluates them, and one group more
+@pytest.mark.parametrize("kind,D,P,N,H,W,Lc", [
+    ("adaln", 128, 15, 60, 2, 2, 0), ("adaln", 128, 16, 60, 2, 2, 0), ("joint", 64, 40, 43, 2, 6, 1), ("joint", 64, 41, 43, 2, 6, 1),
+    ("adaln", 128, 46, 64, 8, 8, 0), ("adaln", 128, 47, 64, 8, 8, 0)])
+def test_network_output_of_many_short_sequences(lib, kind, D, P, N, H, W, Lc):
+    say(f"narrow network {kind} width {D}, {P} x {N} trajectories of {H * W // 4 + Lc} tokens")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind=kind, P=P, N=N, C=4, H=H, W=W, D=D, heads=2, Lc=Lc, Dc=D if Lc else 0, blocks=2, T=1, schedule=[[] for _ in range(P)],
+               Li=H * W // 4, d=4 * H * W)
+    _check_sharp_network(lib, cfg, kind, 7 if H * W > 4 else 1, (0, 1, N, P * N // 2, P * N - 1))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_time_of_narrow_networks_goes_with_their_tokens(lib, D):
+    """4096 trajectories of 4 tokens against 4096 of 32 (0.68 and 0.55 times; 1.0 when one workgroup evaluated either)."""
+    say(f"narrow network of width {D}, time with few tokens")
+    def micros(H, W):
+        cfg = workloads.get_config("cfg1")
+        cfg.update(P=64, N=64, H=H, W=W, D=D, heads=2, blocks=2, T=1, schedule=[[] for _ in range(64)], Li=H * W // 4, d=4 * H * W)
+        w = workloads.make_weights(cfg)
+        ctx, buf = _gpu_ctx(lib, cfg, w, workloads.make_inputs(cfg, w))
+        lib.pg_init_group(ctx, 5)
+        a, b, best = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), 1e9
+        for _ in range(6):
+            a.record()
+            for _ in range(5):
+                lib.pg_net_forward(ctx, 0)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 200)
+        lib.pg_destroy(ctx)
+        return best
+    few, many = micros(4, 4), micros(8, 16)
+    say(f"  4 tokens {few:.0f} us, 32 tokens {many:.0f} us")
+    assert few < 0.85 * many
+
+
 # enough trajectories and tokens for the 64-queries-per-wave attention (four query tiles of 128 against two of 256, 1.67 rounds
 # against one): whole key tiles (484 + 28 tokens), a last tile that ends in its second (484 + 26) or first (462 + 18) half,
 # separate streams (462 + 26)
