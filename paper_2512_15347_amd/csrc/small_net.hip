@@ -411,7 +411,11 @@ static pg_status launch_small(const SmallNetArgs& a, hipStream_t s) {
                                (int)lds_bytes(D, T)));
     attr_set = true;
   }
+  // the whole network as one product: its layers' flops and its attention's
+  const double rows = (double)a.M * a.L, image = (double)a.M * a.Li;
+  const int rec = prof_open(PROF_GEMM, a.blocks * rows * (24.0 * D * D + 4.0 * a.L * D) + 16.0 * image * D * a.C, s);
   small_net_kernel<D, HD, T><<<dim3(a.M), dim3(THREADS), lds_bytes(D, T), s>>>(a);
+  prof_close(rec, s);
   PG_LAUNCH_CHECK("small_net_kernel");
   return PG_OK;
 }

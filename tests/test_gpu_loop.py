@@ -375,6 +375,29 @@ def test_network_output_of_narrow_networks(lib, kind, D, heads, C, H, W, Lc):
     _check_sharp_network(lib, cfg, kind, 7 if L > 1 else 1, (0, 2, 3, 5))
 
 
+@pytest.mark.parametrize("kind,D,P,N,H,W,Lc", [("adaln", 128, 1, 8, 16, 16, 0), ("joint", 64, 2, 3, 10, 10, 39), ("joint", 192, 1, 3, 10, 10, 6),
+                                                ("adaln", 128, 20, 60, 2, 2, 0)])
+def test_profile_counts_the_work_of_a_network(lib, kind, D, P, N, H, W, Lc):
+    """Networks in one launch and with a launch per layer: the brackets of kinds 0 and 1 together hold all the flops of an evaluation."""
+    say(f"profile of a network {kind} width {D}, {P * N} trajectories")
+    cfg = workloads.get_config("cfg3_small")
+    Li = H * W // 4
+    cfg.update(kind=kind, P=P, N=N, C=4, H=H, W=W, D=D, heads=2 if D < 192 else 3, Lc=Lc, Dc=64 if Lc else 0, blocks=2, T=1,
+               schedule=[[] for _ in range(P)], Li=Li, d=4 * H * W)
+    w = workloads.make_weights(cfg)
+    ctx, buf = _gpu_ctx(lib, cfg, w, workloads.make_inputs(cfg, w))
+    lib.pg_init_group(ctx, 5)
+    lib.pg_profile_begin(1000)
+    lib.pg_net_forward(ctx, 0)
+    products, attention = lib.pg_profile_read(0), lib.pg_profile_read(1)
+    lib.pg_profile_end()
+    lib.pg_destroy(ctx)
+    L, M = Li + Lc, P * N
+    want = M * (2 * (24 * L * D * D + 4 * L * L * D) + 2 * 2 * Li * D * 16)      # the context's projection belongs to pg_init_group
+    assert products["work"] + attention["work"] == want
+    assert products["launches"] >= 1 and products["ms"] > 0
+
+
 # few tokens: the number of trajectories up to which one workgroup each evaluates them, and one group more
 @pytest.mark.parametrize("kind,D,P,N,H,W,Lc", [
     ("adaln", 128, 15, 60, 2, 2, 0), ("adaln", 128, 16, 60, 2, 2, 0), ("joint", 64, 40, 43, 2, 6, 1), ("joint", 64, 41, 43, 2, 6, 1),
