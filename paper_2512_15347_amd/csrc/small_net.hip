@@ -216,11 +216,12 @@ __device__ __forceinline__ void attention(const uint16_t* qk, const uint16_t* vt
 
 template <int D, int HD, int T>
 __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
+  // of a fixed size, so that no launch depends on an attribute that a process would have to set once per device
+  static_assert(lds_bytes(D, T) <= LDS_MAX, "fits");
+  __shared__ __align__(16) unsigned char smem[lds_bytes(D, T)];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lk = lane >> 4;
   constexpr int L16 = T * 16, vp = v_pitch(T);
-  static_assert(lds_bytes(D, T) <= LDS_MAX, "fits");
   float* h = reinterpret_cast<float*>(smem);                           // [L16][D + 4]
   float* md = h + L16 * h_pitch(D);                                    // [6 D] modulation vectors of the block
   uint16_t* act = reinterpret_cast<uint16_t*>(md + 6 * D);             // [L16][D + 8]
@@ -405,16 +406,10 @@ bool small_net_takes(const pg_ctx* c) {
 
 template <int D, int HD, int T>
 static pg_status launch_small(const SmallNetArgs& a, hipStream_t s) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    PG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(small_net_kernel<D, HD, T>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds_bytes(D, T)));
-    attr_set = true;
-  }
   // the whole network as one product: its layers' flops and its attention's
   const double rows = (double)a.M * a.L, image = (double)a.M * a.Li;
   const int rec = prof_open(PROF_GEMM, a.blocks * rows * (24.0 * D * D + 4.0 * a.L * D) + 16.0 * image * D * a.C, s);
-  small_net_kernel<D, HD, T><<<dim3(a.M), dim3(THREADS), lds_bytes(D, T), s>>>(a);
+  small_net_kernel<D, HD, T><<<dim3(a.M), dim3(THREADS), 0, s>>>(a);
   prof_close(rec, s);
   PG_LAUNCH_CHECK("small_net_kernel");
   return PG_OK;
