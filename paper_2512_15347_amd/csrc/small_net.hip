@@ -277,9 +277,9 @@ __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArg
   }
   for (int i = tid; i < (L16 - a.Li) * (D / 4); i += THREADS) {
     const int j = i / (D / 4), k = i - j * (D / 4);
-    const float4 z = {0.f, 0.f, 0.f, 0.f};
-    *reinterpret_cast<float4*>(h + (a.Li + j) * h_pitch(D) + 4 * k) =
-        j < a.Lc ? reinterpret_cast<const float4*>(a.ctx_h)[((int64_t)g * a.Lc + j) * (D / 4) + k] : z;
+    float4 v = {0.f, 0.f, 0.f, 0.f};
+    if (j < a.Lc) v = reinterpret_cast<const float4*>(a.ctx_h)[((int64_t)g * a.Lc + j) * (D / 4) + k];
+    *reinterpret_cast<float4*>(h + (a.Li + j) * h_pitch(D) + 4 * k) = v;
   }
   put_vectors();
   __syncthreads();
