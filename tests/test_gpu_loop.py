@@ -18,8 +18,18 @@ def say(msg):
     print(msg, flush=True)
 
 
+def _config(name):
+    """The named configuration; `<name>_layers` has its network of width 128 widened to 256, which takes a launch per layer where one
+    workgroup evaluates the narrow one whole."""
+    if not name.endswith("_layers"):
+        return workloads.get_config(name)
+    cfg = workloads.get_config(name[:-len("_layers")])
+    cfg.update(D=256, heads=2 * cfg["heads"], Dc=256 if cfg["Lc"] else 0)
+    return cfg
+
+
 def _oracle(name, seed, **kw):
-    cfg = workloads.get_config(name)
+    cfg = _config(name)
     w = workloads.make_weights(cfg)
     inp = workloads.make_inputs(cfg, w)
     s = cfg["sampler"]
@@ -344,8 +354,9 @@ def _check_sharp_network(lib, cfg, kind, gain, trajectories):
     lib.pg_destroy(ctx)
 
 
-# token counts that store the transposed values in units of four, in pairs (30 image tokens before the context's) and one by one
-# (35; context rows of 13, 21, 27 and 77 tokens), at both head widths
+# the rows of the cross and dual-stream networks take a launch per layer, with token counts that store the transposed values in units
+# of four (64 and 32 tokens; context rows of 16 after 64) and one by one (35 and 30; context rows of 13, 18, 21 and 77); those of the
+# other two kinds one workgroup evaluates whole
 @pytest.mark.parametrize("kind,H,W,Lc,heads,gain", [
     ("adaln", 16, 16, 0, 4, 7), ("adaln", 10, 14, 0, 4, 10), ("cross", 10, 14, 13, 2, 7), ("cross", 16, 16, 77, 2, 7),
     ("joint", 10, 14, 26, 2, 7), ("joint", 16, 16, 27, 2, 7), ("mmdit", 10, 14, 18, 2, 1), ("mmdit", 10, 12, 21, 2, 1),
@@ -354,6 +365,19 @@ def test_network_output_with_sharp_attention(lib, kind, H, W, Lc, heads, gain):
     say(f"sharp attention {kind} {H}x{W} Lc={Lc}")
     cfg = workloads.get_config("cfg3_small")
     cfg.update(kind=kind, P=2, N=5, H=H, W=W, D=128, heads=heads, Lc=Lc, Dc=128 if Lc else 0, blocks=1, T=1, schedule=[[], []],
+               Li=H * W // 4, d=4 * H * W)
+    _check_sharp_network(lib, cfg, kind, gain, (0, 4, 5, 9))
+
+
+# a launch per layer for the other two kinds, too, at both head widths: units of four (64 tokens, 30 before 26 that make 56 of them),
+# and one by one (35; 91)
+@pytest.mark.parametrize("kind,H,W,Lc,heads,gain", [
+    ("adaln", 16, 16, 0, 6, 7), ("adaln", 10, 14, 0, 3, 10), ("joint", 10, 12, 26, 3, 7), ("joint", 16, 16, 27, 3, 7),
+    ("joint", 10, 14, 26, 6, 7), ("cross", 10, 14, 13, 6, 7), ("mmdit", 8, 16, 16, 6, 1)])
+def test_network_output_with_sharp_attention_in_layers(lib, kind, H, W, Lc, heads, gain):
+    say(f"sharp attention, width 192, {kind} {H}x{W} Lc={Lc}")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind=kind, P=2, N=5, H=H, W=W, D=192, heads=heads, Lc=Lc, Dc=128 if Lc else 0, blocks=1, T=1, schedule=[[], []],
                Li=H * W // 4, d=4 * H * W)
     _check_sharp_network(lib, cfg, kind, gain, (0, 4, 5, 9))
 
@@ -477,7 +501,7 @@ def test_network_output_of_a_trajectory_does_not_depend_on_the_batch(lib, kind):
     np.testing.assert_array_equal(u[64][:5], u[5])
 
 
-@pytest.mark.parametrize("name", ["cfg1", "cfg2_small", "cfg3_small", "cfg4_small", "cfg3_mmdit_small"])
+@pytest.mark.parametrize("name", ["cfg1", "cfg2_small", "cfg3_small", "cfg4_small", "cfg3_mmdit_small", "cfg1_layers", "cfg4_small_layers"])
 def test_full_loop_with_own_network(lib, name):
     """Free-running library loop against the free-running oracle: the survivor sets must be the
     oracle's (the seeds used here leave no near-tie), floats within the stated tolerances."""
@@ -584,13 +608,14 @@ def test_sample_group_is_repeatable_and_seed_dependent(lib):
     lib.pg_destroy(ctx)
 
 
-def test_whole_loop_replays_from_a_hip_graph(lib):
+@pytest.mark.parametrize("name", ["cfg1", "cfg4_small_layers"])
+def test_whole_loop_replays_from_a_hip_graph(lib, name):
     """The one-call loop copies nothing from the host and never waits for the device, so it can be recorded into a
     HIP graph (a caller that must not pay 2 400 launches per tiny group does that).  Every replay, with eager work
     of the library and synchronisations in between, must give the eager loop's result bit for bit."""
-    name, seed = "cfg1", 4242
+    seed = 4242
     say(f"graph capture {name}")
-    cfg = workloads.get_config(name)
+    cfg = _config(name)
     w = workloads.make_weights(cfg); inp = workloads.make_inputs(cfg, w)
     ctx, buf = _gpu_ctx(lib, cfg, w, inp)
     P = cfg["P"]
@@ -622,13 +647,13 @@ def test_whole_loop_replays_from_a_hip_graph(lib):
     lib.pg_destroy(ctx)
 
 
-@pytest.mark.parametrize("name", ["cfg1", "cfg2_small", "cfg3_small", "cfg3_mmdit_small"])
+@pytest.mark.parametrize("name", ["cfg1", "cfg2_small", "cfg3_small", "cfg3_mmdit_small", "cfg1_layers", "cfg3_small_layers"])
 def test_first_run_recorded_but_not_yet_replayed(lib, name):
     """A context whose first run is recorded into a HIP graph: an eager run before any replay gives what a context that was never
     captured gives, and so does the replay.  (The workspace starts as NaN patterns, so nothing can pass on its old contents.)"""
     seed = 91
     say(f"capture first {name}")
-    cfg = workloads.get_config(name)
+    cfg = _config(name)
     w = workloads.make_weights(cfg); inp = workloads.make_inputs(cfg, w)
     c, keep = lib.make_config(cfg, probe_bias=inp["probe_b"])
     runs = []

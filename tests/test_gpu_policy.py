@@ -15,8 +15,7 @@ def say(msg):
     print(msg, flush=True)
 
 
-def _setup(lib, name, seed):
-    cfg = workloads.get_config(name)
+def _setup(lib, cfg, seed):
     w = workloads.make_weights(cfg); inp = workloads.make_inputs(cfg, w)
     s = cfg["sampler"]
     tables = (sampler.flow_sde_tables(cfg["T"], s["a"]) if s["kind"] == "flow"
@@ -28,7 +27,7 @@ def _setup(lib, name, seed):
     lib.pg_bind(ctx, buf)
     lib.pg_sample_group(ctx, seed)
     lib.pg_check(ctx)
-    return cfg, w, inp, tables, rec, ctx, buf
+    return w, inp, tables, rec, ctx, buf
 
 
 def _dev_weights(lib, ctx, cfg, w):
@@ -38,8 +37,29 @@ def _dev_weights(lib, ctx, cfg, w):
 @pytest.mark.parametrize("name", ["cfg1", "cfg2_small", "cfg4_small", "cfg3_mmdit_small"])
 def test_trajectory_record_and_policy_ratio(lib, name):
     say(f"policy ratio {name}")
-    seed = 31
-    cfg, w, inp, tables, rec, ctx, buf = _setup(lib, name, seed)
+    _check_record_and_ratio(lib, workloads.get_config(name), 31)
+
+
+# Several stored steps in one evaluation of the network, for several groups with prompts, contexts and survivors of their own: as many
+# steps together as the buffers hold, a last batch that is shorter (3 + 1 steps; 4 + 2 where only the vectors of four steps fit and
+# the buffers hold five); all four kinds, and the two that one workgroup evaluates whole at both widths of that kind.  (With four or
+# six steps no log-prob lies near zero, where a relative tolerance would ask too much of it.)
+@pytest.mark.parametrize("kind,D,heads,P,N,Lc,T,keep", [
+    ("joint", 64, 2, 3, 8, 9, 4, (3, 2, 3)), ("adaln", 128, 4, 3, 8, 0, 4, (2, 4, 2)), ("joint", 256, 4, 3, 8, 9, 4, (3, 2, 3)),
+    ("adaln", 256, 8, 3, 8, 0, 4, (2, 4, 2)), ("mmdit", 256, 4, 3, 8, 9, 4, (2, 3, 3)), ("mmdit", 128, 4, 3, 8, 13, 4, (3, 2, 2)),
+    ("cross", 192, 3, 3, 8, 9, 4, (3, 3, 2)), ("joint", 192, 3, 16, 5, 4, 6, (1,) * 16), ("adaln", 64, 1, 16, 5, 0, 6, (1,) * 16)])
+def test_policy_ratio_of_several_steps_together(lib, kind, D, heads, P, N, Lc, T, keep):
+    say(f"policy ratio, several steps together, {kind} width {D}, {P} groups")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind=kind, P=P, N=N, C=4, H=16, W=16, T=T, D=D, heads=heads, blocks=2, Lc=Lc, Dc=64 if Lc else 0, Li=64, d=4 * 256,
+               schedule=[[(g % 3, keep[g] + 1), (3, keep[g])] if g % 2 else [(1 + g % 3, keep[g])] for g in range(P)])
+    together = min(T, 64 // P, P * N // sum(keep))
+    assert together in (3, 4) and T % together
+    _check_record_and_ratio(lib, cfg, 31)
+
+
+def _check_record_and_ratio(lib, cfg, seed):
+    w, inp, tables, rec, ctx, buf = _setup(lib, cfg, seed)
     P, N, T = cfg["P"], cfg["N"], cfg["T"]
     M0 = P * N
     ids = rec["orig_id"]
