@@ -1,4 +1,6 @@
-// Softmax attention of the network on bf16 MFMA (self, joint and cross variants share this kernel).
+// Softmax attention on bf16 MFMA, the same code for self, joint and cross attention.  Two kernels: attention_kernel, first below, for
+// head width 32 and for the public entry point, whose values are in natural key order; attention_fast_kernel for head width 64
+// inside the network.  What follows describes the first, and the layout that both share.
 //
 // One workgroup = 4 wavefronts = 128 queries of one (batch, head); each wavefront owns 32 queries and
 // walks the keys in tiles of 64 staged through LDS.  The score tile is computed TRANSPOSED,
@@ -535,13 +537,13 @@ __global__ __launch_bounds__(ATT_THREADS, QB == 2 ? 2 : 3) void attention_fast_k
     for (int c = 0; c < QB; ++c) l_run[c] += psum[c];
   };
 
+  // The queries are here before the loop (a wait inside it would be one for the next tile, too), and with them the first two tiles,
+  // which were asked for before them: loads return in order.
 #pragma unroll
-  for (int c = 0; c < QB; ++c)                   // the queries are here before the loop (a wait inside it would be one for the next tile, too)
+  for (int c = 0; c < QB; ++c)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) pin(qf[c][ks]);
-  if (n_tiles > 1) wait_dma_but<4>();            // tile 1 may still be on its way
-  if (n_tiles > 1) __syncthreads();
-  else publish(0);
+  publish(0);
   int kt = 0;                                    // the next tile
   if (n_full > 0 && wave_has_queries) {
     read_keys(smem, 0, kf);

@@ -17,8 +17,6 @@ __device__ __forceinline__ void dma16(uint32_t off, const void* base, uint32_t l
 }
 // wait until none of this wave's loads is in flight
 __device__ __forceinline__ void wait_dma() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-// wait until at most N of them are (they arrive in order)
-template <int N> __device__ __forceinline__ void wait_dma_but() { __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4) << 14); }
 
 // Where token t of a transposed value row is stored: in every 16 tokens the second and third group of four change places,
 // which puts the eight tokens that a lane of the attention kernel multiplies at a time (4 h .. 4 h + 3 and 8 + 4 h .. 8 + 4 h + 3,

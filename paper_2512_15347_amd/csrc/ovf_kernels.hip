@@ -210,8 +210,9 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
 // ---- many groups: one lane per group ----
 // The wave-per-group form needs about 400 wave instructions per group, most of them cross-lane traffic (an all-pairs rank and
 // four fp64 scans by shuffles): 2^20 groups of 64 -> 16 took 1.53 ms, here 0.14 (64 groups in 2812 vector, 162 LDS and 29 load
-// instructions; with two waves per SIMD, 231 registers, the vector ALU issues in 0.53 of the cycles, some instruction is active in
-// 0.71, and a wave waits for memory and LDS for 0.40 of its time: instructions and exposed latency bound it together).  What
+// instructions; with two waves per SIMD the vector ALU issues in 0.53 of the cycles, some instruction is active in 0.71, and a wave
+// waits for memory and LDS for 0.40 of its time: instructions and exposed latency bound it together).  The kernel has 256
+// registers; up to 16 of a group take 231 of them, more than 16 spill 100.  What
 // took it from 0.21 ms (4462, 358 and 141 instructions): values stay floats in the sort, they stay in registers for the
 // thresholds instead of being staged a second time, and whole chunks are staged by direct loads.  Here a lane
 // sorts its own group in registers by a compare-exchange network (Batcher's odd-even merge sort: 543 compare-exchanges for 64

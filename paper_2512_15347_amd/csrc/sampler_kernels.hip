@@ -2,10 +2,10 @@
 // update + Gaussian log-prob (paper Eq. 13 and the policy of Eq. 19), the one-step ODE preview with
 // the linear reward proxy (Eq. 15-16), and the ragged survivor gather (Sec. 5.1, early termination).
 //
-// Work decomposition: one workgroup of 256 lanes owns one STREAM_CHUNK (4096 floats) of one
-// trajectory and moves it with 16-byte accesses; per-trajectory sums are written as one partial per
-// workgroup and finished by a second tiny kernel in a fixed order (fp64), so results do not depend
-// on scheduling.
+// Work decomposition: 256 lanes own one STREAM_CHUNK (4096 floats) of one trajectory and move it with
+// 16-byte accesses; a chunk's sum is one partial, and a trajectory's partials are added up in a fixed
+// order (fp64), so results do not depend on scheduling: by the workgroup itself where it holds all chunks
+// of a short trajectory, else by a second tiny kernel.
 #include <type_traits>
 #include "ctx.hpp"
 #include "operands.hpp"

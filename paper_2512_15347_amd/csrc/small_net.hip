@@ -1,5 +1,5 @@
-// Narrow networks on short sequences (width 64 or 128, a sequence that fits one compute unit's LDS): one workgroup evaluates the
-// whole network for one trajectory, from the latents to u, in one launch.
+// Narrow networks on short sequences (width 64 or 128, a sequence that fits one compute unit's LDS; small_net_takes): one workgroup
+// evaluates the whole network for one trajectory, from the latents to u, in one launch.
 //
 // Layer by layer such a network is a chain of launches of 3 to 5 us that each hold less than a microsecond of work (a block of
 // width 128 over 64 tokens is 27 MFLOP).  Trajectories do not depend on each other inside the network, so here nothing leaves the
@@ -7,7 +7,7 @@
 // hidden values) and the transposed values live in LDS.  A wave reads the weights of its own output columns straight from
 // global memory into registers, since no other wave of the workgroup needs the same ones.
 // What bounds it is latency: a block takes 14 us (31 layer by layer), of which the queries, keys and values are 1.8, the attention
-// 1.9, the output projection 0.9, each half of the MLP 3.3, a LayerNorm 1.0 (nine barriers).  A launch finds no weights in its
+// 1.9, the output projection 0.9, each half of the MLP 3.3, a LayerNorm 1.0 (ten barriers).  A launch finds no weights in its
 // L2, so every layer's are asked for one to three phases before they are used: asked for one unit of work ahead, a block took 22 us.
 // The sequence length is a template parameter in steps, so that all operand reads of a phase are in flight together (16 us with
 // loops over the row tiles).
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArg
   float* md = h + L16 * h_pitch(D);                                    // [6 D] modulation vectors of the block
   uint16_t* act = reinterpret_cast<uint16_t*>(md + 6 * D);             // [L16][D + 8]
   uint16_t* qk = act + L16 * a_pitch(D);                               // [L16][2 D + 8]: queries | keys, then half the hidden values
-  uint16_t* vt = qk + L16 * q_pitch(D);                                // [D][up32(L) + 8]
+  uint16_t* vt = qk + L16 * q_pitch(D);                                // [D][16 T + 8]
   uint16_t* bs = vt + D * vp;                                          // [9 D] biases of the block: qkv, out, fc1, fc2
   const int m = blockIdx.x, g = a.group_of[m], row = a.mod_of[m];
   const int Wp = a.W / 2, HW = a.H * a.W;
