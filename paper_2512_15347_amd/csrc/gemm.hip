@@ -104,7 +104,8 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
   static_assert(CW == 32 || CW == 64, "the epilogue handles 32 or 64 columns per wave");
   static_assert((BM / WM) % MI == 0 && (BM / WM) % 8 == 0, "wave rows");
   constexpr int A_BYTES = BM * BK * 2, W_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + W_BYTES;
-  extern __shared__ __align__(16) unsigned char smem[];
+  // of a fixed size, so that no launch depends on an attribute that a process would have to set once per device
+  __shared__ __align__(16) unsigned char smem[2 * STAGE_BYTES];
   const int per_xcd = gridDim.x / XCDS;
   const int b = (blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS;
   // ---- which output tile: XCD-aware, banded raster ----
@@ -488,18 +489,11 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
 
 template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE = false, int NPROB>
 static pg_status launch_tile(const GemmBatch<NPROB>& batch, hipStream_t s) {
-  constexpr int LDS = 2 * (BM + BN) * BK * 2;
-  static bool attr_set = false;
-  if (!attr_set) {
-    PG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_kernel<EPI, BM, BN, WM, WN, MINW, WIDE, NPROB>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
-    attr_set = true;
-  }
   int tiles_m = 0;
   for (const GemmArgs& g : batch.g) tiles_m += (g.M + BM - 1) / BM;
   const int tiles = tiles_m * ((batch.g[0].N + BN - 1) / BN);
   const int grid = (tiles + XCDS - 1) / XCDS * XCDS;
-  gemm_kernel<EPI, BM, BN, WM, WN, MINW, WIDE, NPROB><<<dim3(grid), dim3(64 * WM * WN), LDS, s>>>(batch);
+  gemm_kernel<EPI, BM, BN, WM, WN, MINW, WIDE, NPROB><<<dim3(grid), dim3(64 * WM * WN), 0, s>>>(batch);
   PG_LAUNCH_CHECK("gemm_kernel");
   return PG_OK;
 }
