@@ -20,7 +20,7 @@ PEAK_HBM_GBS = 8000.0
 PEAK_VALU_LANE_OPS = 256 * 64 * 2.4e9       # vector-ALU issue roofline: 256 compute units x 64 lanes x 2.4 GHz
 # Vector-ALU instructions per latent element of the two kernels that the Philox / Box-Muller arithmetic bounds, as
 # the SQ_INSTS_VALU counter reads them (profiles/attention_and_streaming_kernels_issue_counters.txt)
-VALU_OPS_PER_ELEMENT = {"init_latents": 20.81, "sde_step_bf16": 33.94}
+VALU_OPS_PER_ELEMENT = {"init_latents": 20.81, "sde_step_bf16": 33.38}
 
 DESCRIPTIONS = {
     "cfg1": "tiny flow group 8->4, DiT 64 tok x 128 x 2 blocks",
