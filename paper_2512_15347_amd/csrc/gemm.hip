@@ -2,10 +2,10 @@
 // network evaluation of every denoising step spends its time (the noise-prediction row of the paper's
 // cost table, Sec. 6.2).  Built around the 16x16x32 bf16 MFMA:
 //   both operands are K-contiguous; 16-byte chunks go from global memory straight into LDS (no register
-//   staging), two LDS stages of 64 columns, one barrier per K step; the requests for tile kt+2 are
-//   interleaved with the MFMAs that follow the barrier, and so are the reads of the operand fragments, which
-//   are double buffered in registers and read one MFMA slab ahead, also across the barrier; the K loop
-//   itself holds no branch (the last two steps are peeled);
+//   staging), a ring of two or three LDS stages of 64 columns per operand, one barrier per K step; the requests for
+//   the tiles that take a freed stage are interleaved with the MFMAs that follow the barrier, and so are the reads of
+//   the operand fragments, which are double buffered in registers and read one MFMA slab ahead, also across the
+//   barrier; the K loop itself holds no branch (the last steps are peeled);
 //   chunk positions are XOR-swizzled so that the 16-byte operand reads are bank-conflict free while the
 //   direct loads still write 1 KB contiguous per instruction;
 //   the epilogue goes through an LDS transpose so that every lane stores 16 contiguous bytes, with the
@@ -17,7 +17,13 @@
 // smaller instruction also allows 16-row steps, so that every tile height keeps a 2 x 4 arrangement of waves.  Four waves with
 // 128 x 128 wave tiles and accumulators in AGPRs read a third less from LDS, but one wave per SIMD exposes the epilogue:
 // 0.92 ms (0.855 against 0.872 ms at K = 6144, N = 1536).  Storing the accumulators without the pass through LDS: 1.03 ms.
-// Several tile shapes are instantiated (workgroup tile BM x BN x 64, WM x WN wavefronts); the launcher
+// A K step of a small tile, and of a large one whose rows come from beyond the L2, is shorter than a load takes (about 1 us under
+// load), so two stages leave every step waiting: with a third one of both operands, or of A alone where LDS holds no more (192
+// and 224 rows; 256 rows have no room), us before / now: 1296 x 1344 x 5376 + residual 48.4 / 29.9 (128 x 64), 648 x 384 x 1536
+// 13.8 / 8.8 (64 x 64), 24576 x 768 x 3072 140.4 / 121.0 (160 rows), 18848 x 1536 x 6144 318 / 297 and 56544 rows 916 / 865
+// (224 rows).  Six or eight stages of the small tiles are slower than three (35 and 48 us at the first shape): one workgroup
+// per compute unit.
+// Several tile shapes are instantiated (workgroup tile BM x BN x 64, WM x WN wavefronts, SA and SW stages); the launcher
 // picks one (pick_tile).
 #include <cmath>
 #include <cstdlib>
@@ -97,15 +103,18 @@ __device__ __forceinline__ GemmArgs chosen(const GemmBatch<2>& b, bool second) {
 // tile (14136 x 1536 x 1536: 85.9 -> 82.3), nothing of taller ones (one slab of a 224-row tile spills: 437 -> 446 us).
 constexpr int prefetched_slabs(int bm, int slabs) { return bm >= 224 ? 0 : bm == 192 ? 1 : slabs; }
 
-template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE, int NPROB>
+template <int EPI, int BM, int BN, int WM, int WN, int MINW, int SA, int SW, bool WIDE, int NPROB>
 __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatch<NPROB> batch) {
   constexpr int WAVES = WM * WN;
   constexpr int CW = BN / WN, FM = BM / WM / MI, FN = CW / MI, FR = FM + FN, MF = FM * FN;   // columns, fragments, MFMAs of a wave
   static_assert(CW == 32 || CW == 64, "the epilogue handles 32 or 64 columns per wave");
   static_assert((BM / WM) % MI == 0 && (BM / WM) % 8 == 0, "wave rows");
-  constexpr int A_BYTES = BM * BK * 2, W_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + W_BYTES;
+  // SA tiles of A and SW of W in LDS
+  static_assert(SA == SW || (SA == 3 && SW == 2), "the counts of requests under way are worked out for these");
+  constexpr int A_BYTES = BM * BK * 2, W_BYTES = BN * BK * 2, W_AT = SA * A_BYTES;
+  constexpr int BIAS_AT = W_AT + SW * W_BYTES, BIAS_BYTES = BN < 128 ? 256 : 2 * BN;    // whole requests of 128 columns
   // of a fixed size, so that no launch depends on an attribute that a process would have to set once per device
-  __shared__ __align__(16) unsigned char smem[2 * STAGE_BYTES];
+  __shared__ __align__(16) unsigned char smem[BIAS_AT + BIAS_BYTES];
   const int per_xcd = gridDim.x / XCDS;
   const int b = (blockIdx.x % XCDS) * per_xcd + blockIdx.x / XCDS;
   // ---- which output tile: XCD-aware, banded raster ----
@@ -132,14 +141,6 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
   const int lr = lane % MI, lk = lane / MI;
 
   const int row_w = m0 + wm * (BM / WM), col_w = n0 + wn * CW;       // first row and column of this wave
-  // The accumulators start at the bias: in each 16x16 tile a lane holds one column, so it is one value per tile, loaded while
-  // the first operands are under way, instead of an add per result in the epilogue.
-  float bias[FN];
-#pragma unroll
-  for (int j = 0; j < FN; ++j) {
-    const int col = col_w + j * MI + lr;
-    bias[j] = PB && col < NN ? bf16_to_f32(PB[col]) : 0.f;
-  }
   f32x4v acc[FM][FN];
   // EPI_RESID: PF slabs of 32 rows of the residual stream are loaded while the last one and a half K steps run (rows and columns
   // past the end repeat existing ones)
@@ -159,8 +160,10 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
   };
 
   {
-    // ---- global -> LDS directly: a stage is N_REG regions of 1 KB (8 tile rows), dealt to the waves in turn ----
-    constexpr int RPR = 64 / CH, A_REG = BM / RPR, N_REG = (BM + BN) / RPR, PER_WAVE = (N_REG + WAVES - 1) / WAVES;
+    // ---- global -> LDS directly: a tile is regions of 1 KB (8 rows of it), dealt to the waves in turn, W's before A's ----
+    constexpr int RPR = 64 / CH, A_REG = BM / RPR, W_REG = BN / RPR;
+    constexpr int A_PER = (A_REG + WAVES - 1) / WAVES, W_PER = (W_REG + WAVES - 1) / WAVES, PER_WAVE = A_PER + W_PER;
+    constexpr int A_LOW = A_REG / WAVES, W_LOW = W_REG / WAVES;    // what every wave has at least
     const int nk = a.K / BK;
     uint32_t g_off[WIDE ? 1 : PER_WAVE];
     const uint16_t* g_base[PER_WAVE];                // WIDE: per lane; else wave-uniform
@@ -168,9 +171,8 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
     const uint32_t lds_base = (uint32_t)(uintptr_t)smem;
 #pragma unroll
     for (int i = 0; i < PER_WAVE; ++i) {
-      const int g = min(wave + i * WAVES, N_REG - 1);  // wave-uniform
-      const bool is_w = g >= A_REG;
-      const int rg = is_w ? g - A_REG : g;
+      const bool is_w = i < W_PER;
+      const int rg = is_w ? min(wave + i * WAVES, W_REG - 1) : min(wave + (i - W_PER) * WAVES, A_REG - 1);  // wave-uniform
       const int row = rg * RPR + lane / CH;
       const int ch = (lane % CH) ^ swz(row);
       const int r = is_w ? min(row, NN - 1 - n0) : min(row, MM - 1 - m0);
@@ -180,12 +182,13 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
         g_base[i] = is_w ? PW + (int64_t)n0 * LDW : PA + (int64_t)m0 * LDA;
         g_off[WIDE ? 0 : i] = ((uint32_t)r * (uint32_t)(is_w ? LDW : LDA) + (uint32_t)(ch * 8)) * 2u;
       }
-      g_lds[i] = __builtin_amdgcn_readfirstlane(lds_base + (is_w ? A_BYTES : 0) + rg * 1024);
+      g_lds[i] = __builtin_amdgcn_readfirstlane(lds_base + (is_w ? W_AT : 0) + rg * 1024);
     }
-    // request region i of K tile `kt`
-    auto request = [&](int i, int kt) {
-      if ((i + 1) * WAVES > N_REG && wave + i * WAVES >= N_REG) return;      // the last one of an uneven deal
-      const uint32_t dst = g_lds[i] + (kt & 1) * STAGE_BYTES;
+    // request region i of K tile `kt` into the stage of its ring that starts `at` bytes in
+    auto request = [&](int i, int kt, int at) {
+      if (i < W_PER ? (i + 1) * WAVES > W_REG && wave + i * WAVES >= W_REG
+                    : (i - W_PER + 1) * WAVES > A_REG && wave + (i - W_PER) * WAVES >= A_REG) return;      // the last one of an uneven deal
+      const uint32_t dst = g_lds[i] + at;
       if (WIDE) dma16_wide(g_base[i] + kt * BK, dst);
       else dma16(g_off[WIDE ? 0 : i], g_base[i] + kt * BK, dst);
     };
@@ -193,30 +196,38 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
     constexpr int SLABS = BK / KS;
     static_assert(SLABS == 2, "fragment buffers alternate per slab");
     const int pa0 = lds_off(wm * (BM / WM) + lr, lk), pa1 = lds_off(wm * (BM / WM) + lr, KS / 8 + lk);
-    const int pw0 = A_BYTES + lds_off(wn * CW + lr, lk), pw1 = A_BYTES + lds_off(wn * CW + lr, KS / 8 + lk);
+    const int pw0 = W_AT + lds_off(wn * CW + lr, lk), pw1 = W_AT + lds_off(wn * CW + lr, KS / 8 + lk);
+    struct Stage { int a, w; };                      // bytes into the two rings
+    auto after = [&](Stage t) {
+      return Stage{t.a + A_BYTES == SA * A_BYTES ? 0 : t.a + A_BYTES, t.w + W_BYTES == SW * W_BYTES ? 0 : t.w + W_BYTES};
+    };
     bf16x8 fr[2][FR];
-    auto fetch = [&](int stage, int ks, int buf, int f) {
-      const int at = f < FN ? (ks ? pw1 : pw0) + f * MI * CH * 16 : (ks ? pa1 : pa0) + (f - FN) * MI * CH * 16;
-      fr[buf][f] = *reinterpret_cast<const bf16x8*>(smem + at + stage * STAGE_BYTES);
+    auto fetch = [&](Stage t, int ks, int buf, int f) {
+      const int at = f < FN ? (ks ? pw1 : pw0) + f * MI * CH * 16 + t.w : (ks ? pa1 : pa0) + (f - FN) * MI * CH * 16 + t.a;
+      fr[buf][f] = *reinterpret_cast<const bf16x8*>(smem + at);
     };
     // One request after every EVERY-th MFMA and one fragment read after every FEV-th: a wave's request waits for the
     // texture path, which takes 1 KB every ~20 cycles, and in a burst the MFMAs queued behind it would wait too.
     static_assert(MF >= FR && MF >= PER_WAVE, "every fragment and every request has an MFMA to follow");
     constexpr int FEV = MF / FR, EVERY = MF / PER_WAVE;
-    // K step kt.  At its last slab every read of its stage has been issued and awaited, so the barrier that publishes tile
-    // kt+1 and frees the stage is passed before that slab's MFMAs; the first slab of tile kt+1 is read, and tile kt+2
-    // requested (REQ), while they run.
-    auto step = [&](int kt, auto req_c, auto next_c) {
-      constexpr bool REQ = decltype(req_c)::value, NEXT = decltype(next_c)::value;
+    // K step kt, whose tiles lie at `cur`, the next one's at `next`.  At its last slab every read of its stage has been issued and
+    // awaited, so the barrier that publishes tile kt+1 and frees the stage is passed before that slab's MFMAs; the first slab
+    // of tile kt+1 is read, and the tiles that take the place of this one's are requested (REQ_W, REQ_A), while they run.
+    // LEFT: requests of a wave that may still be under way when the ones of tile kt+1 have to have ended (-1: there is none).
+    auto step = [&](int kt, Stage cur, Stage next, auto req_w, auto req_a, auto left_c) {
+      constexpr bool REQ_W = decltype(req_w)::value, REQ_A = decltype(req_a)::value;
+      constexpr int LEFT = decltype(left_c)::value;
+      constexpr bool NEXT = LEFT >= 0;
 #pragma unroll
       for (int ks = 0; ks < SLABS; ++ks) {
         const bool last = ks + 1 == SLABS;
         if (last && NEXT) {
-          wait_dma();
+          wait_dma<NEXT ? LEFT : 0>();
           __syncthreads();
-          if (!REQ) prefetch();
+          if (!REQ_W && LEFT == 0) prefetch();
         }
-        const int stage = (last ? kt + 1 : kt) & 1, to = (ks + 1) & 1;
+        const Stage from = last ? next : cur;
+        const int to = (ks + 1) & 1;
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_setprio(1);
         int q = 0;
@@ -227,12 +238,12 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[ks & 1][FN + i], fr[ks & 1][j], acc[i][j], 0, 0, 0);
             if ((!last || NEXT) && q % FEV == 0 && q / FEV < FR) {
               __builtin_amdgcn_sched_barrier(0);
-              fetch(stage, last ? 0 : ks + 1, to, q / FEV);
+              fetch(from, last ? 0 : ks + 1, to, q / FEV);
               __builtin_amdgcn_sched_barrier(0);
             }
-            if (REQ && last && q % EVERY == EVERY - 1 && q / EVERY < PER_WAVE) {
+            if (last && q % EVERY == EVERY - 1 && q / EVERY < PER_WAVE && (q / EVERY < W_PER ? REQ_W : REQ_A)) {
               __builtin_amdgcn_sched_barrier(0);
-              request(q / EVERY, kt + 2);
+              request(q / EVERY, kt + (q / EVERY < W_PER ? SW : SA), q / EVERY < W_PER ? cur.w : cur.a);
               __builtin_amdgcn_sched_barrier(0);
             }
             ++q;
@@ -240,24 +251,58 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
         __builtin_amdgcn_s_setprio(0);
       }
     };
-#pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i) request(i, 0);
-    wait_dma();
-    __syncthreads();
-    if (nk > 1) {
-#pragma unroll
-      for (int i = 0; i < PER_WAVE; ++i) request(i, 1);
+    // The bias goes the same way as the operands, in front of them: a load into registers would be awaited with everything
+    // that was requested after it.
+    if (PB && wave * 128 < BN) {
+      const int c = n0 + wave * 128 + 2 * lane;      // N is even
+      dma4((uint32_t)min(c, NN - 2) * 2u, PB, lds_base + BIAS_AT + wave * 256);
     }
+    static_assert(WAVES * 128 >= BN, "a wave asks for 128 columns of the bias");
 #pragma unroll
-    for (int f = 0; f < FR; ++f) fetch(0, 0, 0, f);
+    for (int t = 0; t < SA; ++t)
+      if (t < nk)
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < PER_WAVE; ++i) {
+          if (i < W_PER && t < SW) request(i, t, t * W_BYTES);
+          if (i >= W_PER) request(i, t, t * A_BYTES);
+        }
+    if (nk >= SA) wait_dma<(SA - 1) * A_LOW + (SW - 1) * W_LOW>();
+    else wait_dma();
+    __syncthreads();
 #pragma unroll
-      for (int j = 0; j < FN; ++j) acc[i][j] = f32x4v{bias[j], bias[j], bias[j], bias[j]};
-    for (int kt = 0; kt + 2 < nk; ++kt) step(kt, std::true_type{}, std::true_type{});
-    if (nk > 1) step(nk - 2, std::false_type{}, std::true_type{});
-    else prefetch();
-    step(nk - 1, std::false_type{}, std::false_type{});
+    for (int f = 0; f < FR; ++f) fetch(Stage{0, 0}, 0, 0, f);
+    // The accumulators start at the bias: in each 16x16 tile a lane holds one column, so it is one value per tile instead of an
+    // add per result in the epilogue.
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int cl = wn * CW + j * MI + lr;
+      const float v = PB && n0 + cl < NN ? bf16_to_f32(*reinterpret_cast<const uint16_t*>(smem + BIAS_AT + 2 * cl)) : 0.f;
+#pragma unroll
+      for (int i = 0; i < FM; ++i) acc[i][j] = f32x4v{v, v, v, v};
+    }
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    constexpr int LEFT = (SW - 2) * W_LOW + (SA == SW ? SW - 2 : SW - 1) * A_LOW;   // of a wave, behind those of tile kt+1
+    Stage cur{0, 0};
+    int kt = 0;
+    auto run = [&](auto req_w, auto req_a, auto left_c) {
+      const Stage next = after(cur);
+      step(kt, cur, next, req_w, req_a, left_c);
+      cur = next;
+      ++kt;
+    };
+    while (kt + SA < nk) run(yes, yes, int_tag<LEFT>{});
+    if (SA > SW && kt + SA == nk) run(yes, no, int_tag<LEFT>{});
+    // the last SW steps, or all of them where there are fewer: T tiles behind kt+1
+    auto drain = [&](auto&& self, auto t_c) -> void {
+      constexpr int T = decltype(t_c)::value;
+      if constexpr (T >= -1) {
+        if (T == -1 && nk == 1) prefetch();
+        if (kt + 2 + T == nk) run(no, no, int_tag<(T > 0 ? T * (A_LOW + W_LOW) : T)>{});
+        self(self, int_tag<T - 1>{});
+      }
+    };
+    drain(drain, int_tag<SW - 2>{});
   }
 
   // ---- epilogue: in each 16x16 accumulator tile a lane holds ONE column (lr) and rows 4 lk + t ----
@@ -267,7 +312,7 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
     constexpr int EST = CW + 4;                      // staging row stride in floats: 4 rows down are 16 banks on
     constexpr int VP = 72;                           // pitch of the transposed staging in bf16: 64 tokens + 8 (16-byte aligned rows)
     constexpr int STG = CW * VP * 2;                 // staging bytes per wave
-    static_assert(32 * EST * 4 <= STG && WAVES * STG <= 2 * STAGE_BYTES, "the staging areas fit");
+    static_assert(32 * EST * 4 <= STG && WAVES * STG <= BIAS_AT, "the staging areas fit");
     __syncthreads();                                 // every wave has finished reading the last stage
     float* stg = reinterpret_cast<float*>(smem + wave * STG);
     int lane_e = lane;
@@ -309,7 +354,6 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
           const int traj_w = row0 / a.L, tok_w = row0 - traj_w * a.L, at_w = a.tok_off + tok_w;     // wave-uniform
           if (all_v && row0 + nt * MI <= MM && tok_w + nt * MI <= a.L && (at_w & 1) == 0) {
             // the whole group is one trajectory's: 8 bytes per lane, or two pairs where its tokens start in the middle of four
-            const int at = at_w + t4;
             uint16_t* dst = a.vt + ((int64_t)traj_w * Dv + (col_w - n_rm) + csub) * a.Lpad;
             const uint16_t* src = stg16 + csub * VP + t4;
             const int64_t step_v = (int64_t)rpa * a.Lpad;
@@ -487,52 +531,52 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void gemm_kernel(const GemmBatc
   }
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int MINW, bool WIDE = false, int NPROB>
+template <int EPI, int BM, int BN, int WM, int WN, int MINW, int SA, int SW, bool WIDE = false, int NPROB>
 static pg_status launch_tile(const GemmBatch<NPROB>& batch, hipStream_t s) {
   int tiles_m = 0;
   for (const GemmArgs& g : batch.g) tiles_m += (g.M + BM - 1) / BM;
   const int tiles = tiles_m * ((batch.g[0].N + BN - 1) / BN);
   const int grid = (tiles + XCDS - 1) / XCDS * XCDS;
-  gemm_kernel<EPI, BM, BN, WM, WN, MINW, WIDE, NPROB><<<dim3(grid), dim3(64 * WM * WN), 0, s>>>(batch);
+  gemm_kernel<EPI, BM, BN, WM, WN, MINW, SA, SW, WIDE, NPROB><<<dim3(grid), dim3(64 * WM * WN), 0, s>>>(batch);
   PG_LAUNCH_CHECK("gemm_kernel");
   return PG_OK;
 }
 
 // Tile choice: the shape with the smallest estimated time.  A compute unit works through w = tiles / 256 tiles (the last
-// round, part empty, counts half as empty as it is: tiles of a long launch drift apart), each a fixed part (prologue and
-// epilogue; a read-modify-write of the residual stream costs three times a bf16 store) and K / 64 steps.  Microseconds per
-// step measured with the chip full and nearly idle (what limits a full chip is power and the operand traffic, a nearly
-// idle one the latency of a step):
-//   tile             full                   idle         tiles per compute unit
-//   BM x 256   0.00553 (BM + 64)    0.55 of that    1     (256: 42.5 us per round of K = 1536, 192: 33.7)
-//   128 x 128   0.52 (0.64 alone)   0.36            2
-//   128 x  64   0.30                0.28            3
-//    64 x  64   0.18                0.18            4
-// The 64-column tiles are for launches that would otherwise leave most of the chip without work or with one long K loop per
-// compute unit: 512 x 128 x 512 takes 12.0 us with 128 x 256 tiles and 5.5 with 64 x 64; 4096 x 1024 x 1024 23.3 and 16.2
-// (128 x 64).
-struct TileShape { int bm, bn; double full, idle; };
-constexpr TileShape TILES[7] = {
-    {256, 256, 0.00553 * 320, 0.00304 * 320}, {192, 256, 0.00553 * 256, 0.00304 * 256},
-    {128, 128, 0.52, 0.36}, {160, 256, 0.00553 * 224, 0.00304 * 224}, {224, 256, 0.00553 * 288, 0.00304 * 288},
-    {128, 64, 0.30, 0.28}, {64, 64, 0.18, 0.18}};
+// round, part empty, counts half as empty as it is: tiles of a long launch drift apart), each an edge (prologue and epilogue,
+// by what the epilogue does) and K / 64 steps; where it holds several tiles at a time (`several`), a lone one's steps take
+// their latency (`idle`) whatever else there is, otherwise they rise from `idle` to `full` as the chip fills.  The constants are
+// microseconds fitted to every tile's time at 620 shapes (16 to 280000 rows, widths 64 to 1536, all layers of the network); over
+// these the chosen tile is on average 3 % behind the best one (by the constants before, among the tiles there were, 11 %).
+struct TileShape { int bm, bn; bool several; double fixed, resid, qkv, out, idle, full; };
+constexpr TileShape TILES[9] = {
+    {256, 256, false, 0, 11.1, 9.9, 6.2, 1.31, 1.47},
+    {192, 256, false, 0, 8.9, 8.2, 5.6, 0.29, 1.14},
+    {128, 128, true, 3.3, 3.3, 3.0, 1.4, 0.56, 0.49},
+    {160, 256, false, 0, 7.4, 8.0, 5.6, 0.68, 0.99},
+    {224, 256, false, 0, 10.8, 9.0, 5.9, 0.96, 1.32},
+    {128, 64, true, 3.8, 2.1, 1.6, 0.94, 0.21, 0.28},
+    {64, 64, true, 4.4, 0.84, 0.34, 0.16, 0.26, 0.19},
+    {128, 256, false, 0, 6.9, 7.1, 5.3, 0.55, 0.81},
+    {64, 64, true, 4.4, 0.87, 0.46, 0.28, 0.16, 0.18}};
 template <int NPROB>
 static int pick_tile(const GemmBatch<NPROB>& batch, int epilogue) {
   const GemmArgs& a = batch.g[0];
-  const double nk = a.K / BK, edge = epilogue == EPI_RESID ? 12.0 : 4.0;
+  const double nk = a.K / BK;
   const bool whole_heads = epilogue == EPI_QKV && a.norm_hd > 32;   // the fused norm needs a whole head inside one wave's columns
   int best = 0;
   double best_us = 0.0;
-  for (int i = 0; i < 7; ++i) {
+  for (int i = 0; i < 9; ++i) {
     const TileShape& t = TILES[i];
     if (whole_heads && t.bm == 64) continue;      // 32 columns per wave
     double tile_rows = 0.0;
     for (const GemmArgs& g : batch.g) tile_rows += ceil((double)g.M / t.bm);
     const double load = tile_rows * ceil((double)a.N / t.bn) / 256.0;
     const double w = load <= 1.0 ? 1.0 : 0.5 * (load + ceil(load));
-    const double full = t.bm == 128 && t.bn == 128 && load <= 1.0 ? 0.64 : t.full;
-    const double step = t.idle + (full - t.idle) * fmin(1.0, load / 0.75);
-    const double us = w * (edge * t.bm * t.bn / 65536.0 + 0.3 + nk * step);
+    const double edge = epilogue == EPI_RESID ? t.resid : epilogue == EPI_QKV ? t.qkv : t.out;
+    const double full = t.bm == 256 && a.K > a.N ? 1.08 * t.full : t.full;    // two tiles of A ahead are too few for a cold A
+    const double alone = t.several ? t.idle : t.idle + (full - t.idle) * fmin(1.0, load / 0.75);
+    const double us = t.fixed + fmax(edge + nk * alone, w * (edge + nk * full));
     if (i == 0 || us < best_us) { best = i; best_us = us; }
   }
   return best;
@@ -542,15 +586,17 @@ template <int EPI, int NPROB>
 static pg_status launch_one(const GemmBatch<NPROB>& batch, hipStream_t s) {
   // operand rows so far apart that their byte offsets inside a tile need 64 bits (pg_gemm_bf16 alone takes any)
   if constexpr (EPI == EPI_F32)
-    if (batch.g[0].lda > NARROW_LD || batch.g[0].ldw > NARROW_LD) return launch_tile<EPI_F32, 128, 128, 2, 2, 2, true>(batch, s);
+    if (batch.g[0].lda > NARROW_LD || batch.g[0].ldw > NARROW_LD) return launch_tile<EPI_F32, 128, 128, 2, 2, 2, 2, 2, true>(batch, s);
   switch (pick_tile(batch, EPI)) {
-    case 0: return launch_tile<EPI, 256, 256, 2, 4, 2>(batch, s);
-    case 1: return launch_tile<EPI, 192, 256, 2, 4, 2>(batch, s);
-    case 2: return launch_tile<EPI, 128, 128, 2, 2, 2>(batch, s);
-    case 3: return launch_tile<EPI, 160, 256, 2, 4, 2>(batch, s);
-    case 4: return launch_tile<EPI, 224, 256, 2, 4, 2>(batch, s);
-    case 5: return launch_tile<EPI, 128, 64, 4, 1, 3>(batch, s);
-    default: return launch_tile<EPI, 64, 64, 2, 2, 4>(batch, s);
+    case 0: return launch_tile<EPI, 256, 256, 2, 4, 2, 2, 2>(batch, s);
+    case 1: return launch_tile<EPI, 192, 256, 2, 4, 2, 3, 2>(batch, s);
+    case 2: return launch_tile<EPI, 128, 128, 2, 2, 2, 2, 2>(batch, s);
+    case 3: return launch_tile<EPI, 160, 256, 2, 4, 2, 3, 3>(batch, s);
+    case 4: return launch_tile<EPI, 224, 256, 2, 4, 2, 3, 2>(batch, s);
+    case 5: return launch_tile<EPI, 128, 64, 4, 1, 2, 3, 3>(batch, s);
+    case 6: return launch_tile<EPI, 64, 64, 2, 2, 4, 2, 2>(batch, s);
+    case 7: return launch_tile<EPI, 128, 256, 2, 4, 2, 3, 3>(batch, s);
+    default: return launch_tile<EPI, 64, 64, 2, 2, 3, 3, 3>(batch, s);
   }
 }
 

@@ -15,8 +15,16 @@ namespace pg {
 __device__ __forceinline__ void dma16(uint32_t off, const void* base, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr) : "memory");
 }
-// wait until none of this wave's loads is in flight
-__device__ __forceinline__ void wait_dma() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+// 4 bytes per lane, 256 a wave
+__device__ __forceinline__ void dma4(uint32_t off, const void* base, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds_addr) : "memory");
+}
+// wait until no more than LEFT of this wave's loads are in flight (they complete in order)
+template <int LEFT = 0>
+__device__ __forceinline__ void wait_dma() {
+  static_assert(LEFT < 64, "six bits count them");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (LEFT & 15) | (LEFT >> 4) << 14);
+}
 
 // Where token t of a transposed value row is stored: in every 16 tokens the second and third group of four change places,
 // which puts the eight tokens that a lane of the attention kernel multiplies at a time (4 h .. 4 h + 3 and 8 + 4 h .. 8 + 4 h + 3,

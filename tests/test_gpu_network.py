@@ -48,6 +48,14 @@ def test_gemm_tiles_with_short_k(lib, M, N, K):
     test_gemm_matches_oracle_linear(lib, M, N, K)
 
 
+# every tile with fewer K steps than its operands have stages in LDS, as many, and more: 256 x 256 (two stages of either operand), 192
+# and 224 rows (three of A, two of W), 160 rows and 128 x 256 (three), 128 x 128 (two), 128 x 64 and 64 x 64 (three)
+@pytest.mark.parametrize("M,N", [(28673, 260), (14337, 516), (16385, 516), (12289, 516), (14337, 260), (5121, 516), (4097, 260), (70, 68)])
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 7])
+def test_gemm_stages_in_lds(lib, M, N, steps):
+    test_gemm_matches_oracle_linear(lib, M, N, 64 * steps)
+
+
 @pytest.mark.parametrize("ld", [1 << 23, (1 << 23) + 64])
 def test_gemm_rows_far_apart(lib, ld):
     """Row strides on both sides of what a 32-bit byte offset inside a tile can express."""
