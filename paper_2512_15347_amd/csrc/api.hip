@@ -5,6 +5,7 @@
 #include <cstring>
 #include <new>
 #include "ctx.hpp"
+#include "small_net.hpp"
 
 namespace pg {
 
@@ -193,7 +194,7 @@ static pg_status plan_workspace(pg_ctx* c) {
   c->ws_sched = take(sizeof(int32_t) * c->sched_table.size());                  // the funnel, uploaded by pg_bind
   c->ws_tin = take(sizeof(double) * c->cfg.T);                                  // network times of the steps
   c->ws_emb = take(c->cfg.net_kind == PG_NET_NONE ? 0 : sizeof(float) * 256 * (size_t)c->cfg.T);   // their embeddings
-  c->ws_logr = take(sizeof(double) * (size_t)c->cfg.T * c->M0);                 // fp64 log-ratios of pg_policy_ratio
+  c->ws_logr = take(sizeof(double) * (size_t)c->cfg.T * c->M0);                 // fp64 log-ratios of pg_policy_ratio; sums of sample_rows
   c->ws_net = off;
   PG_TRY(net_plan(c));
   c->ws_total = align256(off + c->net.total);
@@ -684,8 +685,63 @@ extern "C" pg_status pg_policy_ratio(pg_ctx* c, const uint16_t* weights_new, dou
                           clip_eps, ratio, J, s);
 }
 
+// The loop of a narrow network whose rows are spread over workgroups: the launch that ends an evaluation makes the sampler's update
+// and starts the next evaluation; after a prune, and where the modulation vectors of more steps have to be made first, the launch
+// that starts an evaluation makes the update.
+static pg_status sample_rows(pg_ctx* c, hipStream_t s) {
+  const pg_config& f = c->cfg;
+  const int together = c->net.mod_steps;
+  double* sums = (double*)ws(c, c->ws_logr);
+  PG_TRY(launch_noise_sums(c->M0, f.T, c->d, c->seed, sums, s));
+  auto update = [&](int step) {
+    return RowsUpdate{(float)c->A[step], (float)c->B[step], (float)c->C[step], (uint32_t)c->seed, (uint32_t)(c->seed >> 32), (uint32_t)step,
+                      c->pending_gather ? c->buf.sel_idx : nullptr, c->buf.orig_id[c->cur_id], c->buf.x[1 - c->cur_x],
+                      c->buf.x_hist ? c->buf.x_hist + (size_t)(step + 1) * c->M0 * c->d : nullptr, sums + (size_t)step * c->M0,
+                      LogProb{nullptr, c->buf.logp_hist + (size_t)step * c->M0, c->buf.logp_sum,
+                              (double)c->d * (std::log(c->C[step]) + 0.5 * std::log(2.0 * M_PI))}};
+  };
+  auto updated = [&](int step) {
+    c->cur_x = 1 - c->cur_x;
+    c->steps_done = step + 1;
+    c->pending_gather = c->net_fresh = false;
+    c->updates += c->M;
+  };
+  bool begin = true, owed = false;                    // start the evaluation; the update before it is still to be made
+  for (int step = 0; step < f.T; ++step) {
+    if (step % together == 0) PG_TRY(net_modulate(c, step, std::min(together, f.T - step), c->buf.weights, s));
+    const bool checkpoint = c->is_checkpoint[step], last = step + 1 == f.T;
+    RowsUpdate before, after;
+    RowsPass pass{};
+    pass.begin = begin;
+    if (owed) {
+      before = update(step - 1);
+      pass.before = &before; pass.x_before = c->buf.x[c->cur_x];
+      updated(step - 1);
+    }
+    pass.x = c->buf.x[c->cur_x];
+    const bool moves = !checkpoint && (last || (step + 1) % together != 0);
+    if (moves) {
+      after = update(step);
+      pass.after = &after; pass.start_next = !last;
+    }
+    PG_TRY(net_rows(c, NetBatch{c->M, pass.x, c->buf.group_of, c->buf.group_of, step % together}, pass, c->buf.weights, s));
+    c->net_fresh = true;
+    c->evals += c->M;
+    begin = !moves;
+    owed = !moves && !last;
+    if (moves) updated(step);
+    if (checkpoint) PG_TRY(pg_prune(c, step, s));
+    if (last && !moves) PG_TRY(pg_step(c, step, s));
+  }
+  return PG_OK;
+}
+
 extern "C" pg_status pg_sample_group(pg_ctx* c, uint64_t seed, void* stream) {
   PG_TRY(pg_init_group(c, seed, stream));
+  if (c->cfg.net_kind != PG_NET_NONE && small_rows_takes(c)) {
+    PG_TRY(sample_rows(c, (hipStream_t)stream));
+    return pg_advantages(c, stream);
+  }
   const int together = c->cfg.net_kind == PG_NET_NONE ? c->cfg.T : c->net.mod_steps;   // steps whose modulation vectors are made at once
   for (int s = 0; s < c->cfg.T; ++s) {
     if (c->cfg.net_kind != PG_NET_NONE && s % together == 0)

@@ -8,6 +8,7 @@ struct WeightSlot { int64_t offset; int32_t rows, cols, ld; };
 struct NetPlan {             // byte offsets into the workspace for the network's activations
   size_t h, act, qkv, vt, att, hid, tok, mod, cond, rows, ctx_h, ckv, ckvt, total;
   int mod_steps;             // steps whose modulation vectors fit in `mod`
+  size_t rows_h, rows_qk[2], rows_vt[2];   // narrow networks of few trajectories: rows of 16-row tiles (RowsArgs)
 };
 
 struct pg_ctx {
@@ -37,6 +38,7 @@ struct pg_ctx {
   int steps_done = 0;                     // steps taken since pg_init_group
   bool advantages_done = false;
   bool context_ready = false;             // step-independent network precomputation done
+  int rows_buffer = 0;                    // which of NetPlan::rows_qk / rows_vt the next block reads
   // The funnel as the schedule fixes it: row s = k[P] | new_offsets[P+1] of a prune at step s when every earlier
   // prune followed the schedule.  Uploaded into the workspace once (pg_bind), so a prune needs no host -> device copy.
   std::vector<int32_t> sched_table;       // [T][2P+1]
@@ -66,6 +68,8 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
                           float* logp_sum, const int32_t* src, const int32_t* orig_id, int64_t n_traj, int64_t d,
                           double A, double B, double C, uint64_t seed, uint32_t step, float* partials,
                           float* hist_next, hipStream_t s);
+// sums[t, id] = sum over the noise that step t draws for trajectory id, t < steps (latents of at most four chunks)
+pg_status launch_noise_sums(int M0, int steps, int64_t d, uint64_t seed, double* sums, hipStream_t s);
 pg_status launch_transition_logprob(const float* x, const float* u, const float* x_next_by_id,
                                     const int32_t* orig_id, int64_t n_traj, int64_t d, double A, double B, double C,
                                     uint64_t seed, uint32_t step, float* logp_by_id, double* log_ratio_by_id,

@@ -285,6 +285,11 @@ pg_status net_plan(pg_ctx* c) {
     n.ckv = take((size_t)f.blocks * f.P * f.Lc * D * 2);
     n.ckvt = take((size_t)f.blocks * f.P * D * Lcpad * 2);
   }
+  if (small_rows_takes(c)) {
+    const size_t rows = (size_t)c->M0 * small_rows_tiles(c) * 16, pairs = (size_t)c->M0 * ((small_rows_tiles(c) + 1) & ~1) * 16;
+    n.rows_h = take(rows * D * 4);
+    for (int i = 0; i < 2; ++i) { n.rows_qk[i] = take(rows * 2 * D * 2); n.rows_vt[i] = take(pairs * D * 2); }
+  }
   n.total = off;
   return PG_OK;
 }
@@ -422,6 +427,55 @@ pg_status net_batch_steps(pg_ctx* c, int steps, NetBatch* batch, hipStream_t s) 
   return PG_OK;
 }
 
+namespace {
+// what the narrow networks' kernels are given; mod, fmod: vectors of the batch's first row
+SmallNetArgs small_args(const pg_ctx* c, const Net& n, const NetBatch& batch, const float* mod, const float* fmod) {
+  const pg_config& f = c->cfg;
+  auto layer = [&](int w, int b) { return SmallLayer{n.w(w), n.w(b), n.ld(w)}; };
+  SmallNetArgs a{};
+  a.x = batch.x; a.u = c->buf.u; a.group_of = batch.group_of; a.mod_of = batch.mod_of; a.M = batch.M;
+  a.C = f.C; a.H = f.H; a.W = f.W; a.Li = c->Li; a.Lc = c->L - c->Li; a.L = c->L; a.blocks = f.blocks;
+  if (a.Lc) a.ctx_h = n.at<float>(c->net.ctx_h);
+  a.embed = layer(PG_W_PE_W, PG_W_PE_B); a.qkv = layer(PG_W_QKV_W, PG_W_QKV_B); a.out = layer(PG_W_O_W, PG_W_O_B);
+  a.fc1 = layer(PG_W_FC1_W, PG_W_FC1_B); a.fc2 = layer(PG_W_FC2_W, PG_W_FC2_B); a.fin = layer(PG_W_F_W, PG_W_F_B);
+  a.pos = n.w(PG_W_POS); a.mod = mod; a.fmod = fmod; a.block_stride = c->block_stride;
+  a.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)(f.D / f.heads)));
+  return a;
+}
+}  // namespace
+
+pg_status net_rows(pg_ctx* c, const NetBatch& batch, const RowsPass& pass, const uint16_t* weights, hipStream_t s) {
+  const pg_config& f = c->cfg;
+  Net n{c, s, (char*)c->buf.workspace + c->ws_net, weights};
+  const ModPlan mp = mod_plan(c, n);
+  const int64_t row = (int64_t)std::max(0, batch.mod_row) * f.P;
+  const int hd = f.D / f.heads;
+  const SmallNetArgs net = small_args(c, n, batch, mp.mod + row * mp.ld, mp.fmod + row * 2 * f.D);
+  RowsArgs a{};
+  a.hs = n.at<float>(c->net.rows_h);
+  auto launch = [&](int block, int to, bool start, const float* x, const RowsUpdate* update) -> pg_status {
+    a.qk_in = n.at<uint16_t>(c->net.rows_qk[1 - to]); a.vt_in = n.at<uint16_t>(c->net.rows_vt[1 - to]);
+    a.qk_out = n.at<uint16_t>(c->net.rows_qk[to]); a.vt_out = n.at<uint16_t>(c->net.rows_vt[to]);
+    c->rows_buffer = to;
+    a.x = x;
+    a.mod_next = net.mod + (block < 0 ? 0 : f.P * mp.ld);
+    a.update = update != nullptr;
+    if (update) a.up = *update;
+    return launch_small_rows(net, a, f.D, hd, block, start, s);
+  };
+  // the evaluation as one product: its layers' flops and its attention's
+  const double rows = (double)batch.M * c->L, image = (double)batch.M * c->Li;
+  const int rec = prof_open(PROF_GEMM, f.blocks * rows * (24.0 * f.D * f.D + 4.0 * c->L * f.D) + 16.0 * image * f.D * f.C, s);
+  pg_status st = PG_OK;
+  if (pass.begin) st = launch(-1, 0, true, pass.before ? pass.x_before : pass.x, pass.before);
+  for (int b = 0; b < f.blocks && st == PG_OK; ++b) {
+    const bool last = b + 1 == f.blocks;
+    st = launch(b, 1 - c->rows_buffer, last && pass.start_next, pass.x, last ? pass.after : nullptr);
+  }
+  prof_close(rec, s);
+  return st;
+}
+
 pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t* weights, hipStream_t s) {
   const pg_config& f = c->cfg;
   Net n{c, s, (char*)c->buf.workspace + c->ws_net, weights};
@@ -469,17 +523,10 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
     if (own_step) PG_TRY(launch_modulation(c, n, mp, 1));
   }
 
-  // ---- narrow networks on short sequences: the rest in one launch ----
+  // ---- narrow networks on short sequences: the rest in one launch, or one per block ----
   if (small) {
-    auto layer = [&](int w, int b) { return SmallLayer{n.w(w), n.w(b), n.ld(w)}; };
-    SmallNetArgs a{};
-    a.x = batch.x; a.u = c->buf.u; a.group_of = group_of; a.mod_of = mod_of; a.M = M;
-    a.C = f.C; a.H = f.H; a.W = f.W; a.Li = Li; a.Lc = L - Li; a.L = L; a.blocks = f.blocks;
-    if (a.Lc) a.ctx_h = n.at<float>(pl.ctx_h);
-    a.embed = layer(PG_W_PE_W, PG_W_PE_B); a.qkv = layer(PG_W_QKV_W, PG_W_QKV_B); a.out = layer(PG_W_O_W, PG_W_O_B);
-    a.fc1 = layer(PG_W_FC1_W, PG_W_FC1_B); a.fc2 = layer(PG_W_FC2_W, PG_W_FC2_B); a.fin = layer(PG_W_F_W, PG_W_F_B);
-    a.pos = n.w(PG_W_POS); a.mod = mod; a.fmod = fmod; a.block_stride = c->block_stride; a.scale_log2 = scale_log2;
-    return launch_small_net(a, D, hd, s);
+    if (small_rows_takes(c)) return net_rows(c, batch, RowsPass{batch.x, true, nullptr, nullptr, nullptr, false}, weights, s);
+    return launch_small_net(small_args(c, n, batch, mod, fmod), D, hd, s);
   }
 
   // ---- patch embedding (+ position table) ----

@@ -8,6 +8,7 @@
 // of a short trajectory, else by a second tiny kernel.
 #include <type_traits>
 #include "ctx.hpp"
+#include "logprob.hpp"
 #include "operands.hpp"
 #include "philox.hpp"
 
@@ -81,15 +82,6 @@ static void with_groups(int chunks, F launch) {
   else if (chunks == 1) launch(groups_tag<1>{});
   else if (chunks == 2) launch(groups_tag<2>{});
   else launch(groups_tag<ROW_GROUPS>{});
-}
-
-struct LogProb { float* logp; float* hist; float* sum; double log_norm; };
-// logp[r] = -1/2 s - d (ln C + 1/2 ln 2 pi); history and running sum by original id
-__device__ __forceinline__ void finish_logprob(const LogProb& o, int r, int id, double s) {
-  const float lp = (float)(-0.5 * s - o.log_norm);
-  if (o.logp) o.logp[r] = lp;
-  if (o.hist) o.hist[id] = lp;
-  if (o.sum) o.sum[id] += lp;
 }
 
 // x_out[r] = A x[q] + B u[q] + C xi, q = src ? src[r] : r; sum xi^2 per trajectory.  GROUPS 0: a workgroup per chunk,
@@ -189,6 +181,27 @@ __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_st
     const float t = block_sum_256(acc);
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
   }
+}
+
+// sums[t, r] = sum xi^2 over the noise of step t for original id r, t = blockIdx.y: what a step's log-prob is made of, in the order of
+// sde_step_kernel.  The noise depends on seed, step and id alone, so a loop whose updates are spread over several workgroups of a
+// trajectory takes its sums from here instead of putting them together at every step (64 tokens of 4 channels, 8 trajectories,
+// ten steps: one launch of 3 us).
+template <int GROUPS>
+__global__ __launch_bounds__(GROUPS * STREAM_THREADS) void noise_sums_kernel(int d4, int chunks, uint32_t k0, uint32_t k1,
+                                                                             double* __restrict__ sums) {
+  const int r = blockIdx.x, step = blockIdx.y;
+  const int c = threadIdx.x / STREAM_THREADS, lane256 = threadIdx.x & (STREAM_THREADS - 1);
+  float acc = 0.f;
+#pragma unroll
+  for (int it = 0; it < STREAM_ITERS; ++it) {
+    const int e4 = c * (STREAM_CHUNK / 4) + it * STREAM_THREADS + lane256;
+    if (e4 < d4) {
+      const f32x4 z = philox_normal4((uint32_t)e4, (uint32_t)step, (uint32_t)r, STREAM_STEP, k0, k1);
+      acc += (z.x * z.x + z.y * z.y) + (z.z * z.z + z.w * z.w);
+    }
+  }
+  row_sum<GROUPS>(chunks, acc, [&](double s) { sums[(size_t)step * gridDim.x + r] = s; });
 }
 
 // The kernels that finish a sum are pure latency, once per step: one wavefront per trajectory (a lane that walked its
@@ -413,6 +426,19 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
   prof_close(rec, stream);
   PG_LAUNCH_CHECK("sde_step_kernel");
   return row ? PG_OK : launch_logprob_finish(partials, chunks, n_traj, orig_id, out, stream);
+}
+
+pg_status launch_noise_sums(int M0, int steps, int64_t d, uint64_t seed, double* sums, hipStream_t stream) {
+  const int chunks = (int)chunks_per_traj(d);
+  if (d % 4 || chunks > ROW_GROUPS) return fail(PG_ESHAPE, "noise sums: latent size %lld", (long long)d);
+  with_groups(chunks, [&](auto groups) {
+    constexpr int G = decltype(groups)::value;
+    if constexpr (G > 0)
+      noise_sums_kernel<G><<<dim3((unsigned)M0, (unsigned)steps), dim3(G * STREAM_THREADS), 0, stream>>>(
+          (int)(d / 4), chunks, (uint32_t)seed, (uint32_t)(seed >> 32), sums);
+  });
+  PG_LAUNCH_CHECK("noise_sums_kernel");
+  return PG_OK;
 }
 
 pg_status launch_transition_logprob(const float* x, const float* u, const float* x_next_by_id,

@@ -422,6 +422,57 @@ def test_profile_counts_the_work_of_a_network(lib, kind, D, P, N, H, W, Lc):
     assert products["launches"] >= 1 and products["ms"] > 0
 
 
+# a workgroup per 16 rows and the update inside the network's launches (few trajectories) against a workgroup per trajectory and an
+# update of its own (many): one row tile, odd and even numbers of them, tiles of context rows alone, both head widths, odd patch rows,
+# one and three blocks, modulation vectors of a few steps at a time (many groups)
+@pytest.mark.parametrize("kind,D,heads,C,H,W,Lc,blocks,P", [
+    ("adaln", 128, 4, 4, 16, 16, 0, 2, 1), ("joint", 128, 2, 4, 10, 10, 40, 1, 2), ("joint", 128, 4, 16, 14, 12, 54, 3, 1),
+    ("adaln", 128, 2, 3, 8, 8, 0, 2, 3), ("joint", 128, 2, 4, 6, 6, 24, 2, 33), ("joint", 64, 2, 4, 10, 10, 39, 2, 1),
+    ("joint", 64, 1, 16, 16, 46, 8, 1, 1), ("adaln", 64, 2, 4, 4, 18, 0, 3, 2), ("adaln", 64, 1, 4, 16, 28, 0, 2, 9)])
+def test_narrow_loops_by_rows_and_by_trajectories_agree(lib, kind, D, heads, C, H, W, Lc, blocks, P):
+    L = H * W // 4 + Lc
+    say(f"narrow loop {kind} width {D}, {L} tokens, {P} groups")
+    cfg = workloads.get_config("cfg3_small")
+    first = [(1, 3), (4, 2)]
+    cfg.update(kind=kind, P=P, N=4, C=C, H=H, W=W, D=D, heads=heads, Lc=Lc, Dc=D if Lc else 0, blocks=blocks, T=6,
+               schedule=[first] + [[]] * (P - 1), Li=H * W // 4, d=C * H * W)
+    many = dict(cfg, P=300, schedule=[first] + [[]] * 299)
+    w = workloads.make_weights(cfg)
+    inp = workloads.make_inputs(many, w)
+    seed, ctx, runs = 31, {}, []
+    for name, c in (("few", cfg), ("many", many)):
+        part = {k: v[:c["P"]] if k in ("y", "ctx") and v is not None else v for k, v in inp.items()}
+        cc, keep = lib.make_config(c, probe_bias=part["probe_b"])
+        ctx[name] = lib.pg_create(cc)
+        buf = lib.Buffers(ctx[name], c, inputs=part, weights_flat=lib.pack_weights(ctx[name], c, w), keep_history=name == "few")
+        buf.workspace.fill_(255)
+        lib.pg_bind(ctx[name], buf)
+        for whole in (True, False) if name == "few" else (True,):
+            if whole:
+                lib.pg_sample_group(ctx[name], seed)
+            else:
+                lib.pg_init_group(ctx[name], seed)
+                for s in range(6):
+                    lib.pg_net_forward(ctx[name], s)
+                    if s in (1, 4):
+                        lib.pg_prune(ctx[name], s)
+                    lib.pg_step(ctx[name], s)
+                lib.pg_advantages(ctx[name])
+            lib.pg_check(ctx[name])
+            st = lib.pg_state(ctx[name], c["P"])
+            M = 2 + 4 * (P - 1)                          # survivors of the groups that both contexts have
+            runs.append(dict(x=buf.x[st["cur_x"]][:M].clone(), u=buf.u[:M].clone(), ids=buf.orig_id[st["cur_id"]][:M].clone(),
+                             hist=buf.logp_hist[:, :4 * P].clone().view(torch.int32), sum=buf.logp_sum[:4 * P].clone(),
+                             rewards=buf.rewards[:M].clone()))
+            if name == "few":
+                runs[-1]["record"] = buf.x_hist.clone()
+        lib.pg_destroy(ctx[name])
+    for k in runs[1]:
+        assert torch.equal(runs[0][k].view(torch.int32), runs[1][k].view(torch.int32)), f"one call and step by step: {k}"
+    for k in runs[2]:
+        assert torch.equal(runs[0][k], runs[2][k]), f"by rows and by trajectories: {k}"
+
+
 # few tokens: the number of trajectories up to which one workgroup each evaluates them, and one group more
 @pytest.mark.parametrize("kind,D,P,N,H,W,Lc", [
     ("adaln", 128, 15, 60, 2, 2, 0), ("adaln", 128, 16, 60, 2, 2, 0), ("joint", 64, 40, 43, 2, 6, 1), ("joint", 64, 41, 43, 2, 6, 1),
