@@ -5,9 +5,10 @@
 // quadratic in one member's value, so some optimum is "j lowest and k-j highest".
 // Two decompositions for groups of at most 64 members (the paper's groups, cf. the group-size
 // ablation), both with the same order of fp64 additions and therefore the same bits:
-//   few groups: one 64-lane wavefront owns one group: ranks by all-pairs comparison from LDS, fp64
-//   prefix sums by a six-step shuffle-up scan, k+1 candidate scores in lanes 0..k, a butterfly
-//   arg-max, a ballot for the survivor mask;
+//   few groups: one 64-lane wavefront owns one group: ranks by all-pairs comparison from LDS (the slot decides only
+//   where values are equal), fp64 prefix sums by a six-step scan, k+1 candidate scores in lanes 0..k, a butterfly
+//   arg-max, a ballot for the survivor mask.  4096 groups of 64 are four waves per SIMD, whose instructions bound it:
+//   9.9 us with the slot in every comparison and scans and arg-max by shuffles through LDS, 7.8 here;
 //   many groups: one LANE owns one group (ovf_select_lanes_kernel below).
 #include <algorithm>
 #include <mutex>
@@ -24,16 +25,35 @@ constexpr int SCAN_BLOCK = SCAN_THREADS * SCAN_ITEMS;
 
 __device__ __forceinline__ double shfl_up_f64(double v, int delta) { return __shfl_up(v, delta, WAVE); }
 
-// Inclusive prefix sum across the wave by the doubling recurrence: after the pass with distance dd
-// lane i holds the sum of lanes max(0, i-2dd+1) .. i.  The order of additions is part of the
-// library's bit-exactness contract.
-__device__ __forceinline__ double wave_scan_f64(double a, int lane) {
+// Inclusive prefix sums of four values across the wave by the doubling recurrence: after the pass with distance dd lane i holds
+// the sum of lanes max(0, i-2dd+1) .. i.  The order of additions is part of the library's bit-exactness contract.  A lane
+// that has no partner adds +0, which changes nothing: no sum here is -0.  Distances 1, 2 and 4 are that many shifts by one lane, 16
+// and 32 exchanges of rows, without the shuffles through LDS that 8 takes.
+template <class Shift>
+__device__ __forceinline__ double add_shifted(double v, Shift shift) {
+  const uint64_t w = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = shift((uint32_t)w), hi = shift((uint32_t)(w >> 32));
+  return __dadd_rn(v, __builtin_bit_cast(double, (uint64_t)hi << 32 | lo));
+}
+template <int LANES> __device__ __forceinline__ uint32_t shifted(uint32_t v) {          // by 1, 2 or 4 lanes, zeros move in
 #pragma unroll
-  for (int dd = 1; dd < WAVE; dd <<= 1) {
-    const double t = shfl_up_f64(a, dd);
-    if (lane >= dd) a = __dadd_rn(a, t);
-  }
-  return a;
+  for (int i = 0; i < LANES; ++i) v = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, true);
+  return v;
+}
+__device__ __forceinline__ void wave_scans(double& a, double& b, double& c, double& d) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  auto all = [&](auto shift) { a = add_shifted(a, shift); b = add_shifted(b, shift); c = add_shifted(c, shift); d = add_shifted(d, shift); };
+  all([](uint32_t v) { return shifted<1>(v); });
+  all([](uint32_t v) { return shifted<2>(v); });
+  all([](uint32_t v) { return shifted<4>(v); });
+  const int at8 = 4 * (lane - 8);
+  all([&](uint32_t v) { const uint32_t t = (uint32_t)__builtin_amdgcn_ds_bpermute(at8, (int)v); return lane >= 8 ? t : 0u; });
+  all([&](uint32_t v) {                              // rows 1 and 3 get rows 0 and 2, row 2 gets row 1
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const auto q = __builtin_amdgcn_permlane32_swap(r[1], r[1], false, false);
+    return lane & 16 ? (uint32_t)r[0] : lane & 32 ? (uint32_t)q[0] : 0u;
+  });
+  all([&](uint32_t v) { const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false); return lane & 32 ? (uint32_t)q[0] : 0u; });
 }
 
 // A group whose size or count the selection cannot take (size outside 1..limit, k outside 1..size): its mask is
@@ -123,17 +143,58 @@ __device__ __forceinline__ bool bad_group(int n, int k) { return (n < 1 || n > W
 // the first k slots (1 <= k <= 64)
 __device__ __forceinline__ uint64_t first_slots(int k) { return k == WAVE ? ~0ull : (1ull << k) - 1ull; }
 
-// Optimal Variance Filtering of one group by one wavefront: the survivor mask, in every lane; `vals`, `sorted`: 64 floats of LDS
-// of this wave.
-__device__ __forceinline__ uint64_t survivors_by_wave(const float* __restrict__ rewards, int b, int n, int k, float* vals,
-                                                      float* sorted, int32_t* __restrict__ status) {
+// the lane's reward of a group (anything past its end)
+__device__ __forceinline__ float reward_of_lane(const float* __restrict__ rewards, int b, int n) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  return lane < n ? rewards[b + lane] : 0.0f;
+}
+
+// the better of two candidates: the larger score, the smaller index of equal ones
+__device__ __forceinline__ void keep_better(double& score, int& best, double os, int ob) {
+  const bool other = os > score || (os == score && ob < best);
+  score = other ? os : score;
+  best = other ? ob : best;
+}
+__device__ __forceinline__ double from_halves(uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo); }
+// the best candidate of the wave, in every lane: a butterfly inside rows of 16 lanes by data-parallel primitives (see head_sum), then
+// over the rows
+template <int CTRL> __device__ __forceinline__ uint32_t permuted(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
+}
+template <int CTRL> __device__ __forceinline__ void best_of_permuted(double& score, int& best) {
+  const uint64_t w = __builtin_bit_cast(uint64_t, score);
+  keep_better(score, best, from_halves(permuted<CTRL>((uint32_t)w), permuted<CTRL>((uint32_t)(w >> 32))), (int)permuted<CTRL>((uint32_t)best));
+}
+template <bool HALVES> __device__ __forceinline__ void best_of_rows(double& score, int& best) {
+  const uint64_t w = __builtin_bit_cast(uint64_t, score);
+  auto swap = [](uint32_t v) {
+    if (HALVES) return __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    else return __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  };
+  const auto lo = swap((uint32_t)w), hi = swap((uint32_t)(w >> 32)), b = swap((uint32_t)best);
+  score = from_halves((uint32_t)lo[0], (uint32_t)hi[0]);             // one of the two is the lane's own
+  best = (int)b[0];
+  keep_better(score, best, from_halves((uint32_t)lo[1], (uint32_t)hi[1]), (int)b[1]);
+}
+__device__ __forceinline__ void wave_best(double& score, int& best) {
+  best_of_permuted<0xB1>(score, best);
+  best_of_permuted<0x4E>(score, best);
+  best_of_permuted<0x141>(score, best);
+  best_of_permuted<0x140>(score, best);
+  best_of_rows<false>(score, best);
+  best_of_rows<true>(score, best);
+}
+
+// Optimal Variance Filtering of one group by one wavefront: the survivor mask, in every lane; `raw`: reward_of_lane; `vals`,
+// `sorted`: 64 floats of LDS of this wave.
+__device__ __forceinline__ uint64_t survivors_by_wave(float raw, int n, int k, float* vals, float* sorted, int32_t* __restrict__ status) {
   const int lane = threadIdx.x & (WAVE - 1);
   if (n < 1 || n > WAVE || k < 1 || k > n) {        // nothing to select: empty mask
     if (lane == 0 && bad_group(n, k)) atomicOr(status, 2);
     return 0ull;
   }
   const bool live = lane < n;
-  const float v = live ? rewards[b + lane] + 0.0f : 0.0f;  // -0.0 becomes +0.0
+  const float v = live ? raw + 0.0f : 0.0f;          // -0.0 becomes +0.0
   const bool bad = live && !(__builtin_fabsf(v) <= 3.4028234663852886e38f);
   if (__ballot(bad) != 0ull || k == n) {
     // k == n keeps everything; a non-finite reward is flagged and the first k slots are kept so
@@ -149,20 +210,21 @@ __device__ __forceinline__ uint64_t survivors_by_wave(const float* __restrict__ 
   int rank = 0;
   for (int l = 0; l < n; l += 4) {
     const float4 q = *reinterpret_cast<const float4*>(vals + l);
-    rank += (q.x < v || (q.x == v && l < lane)) ? 1 : 0;
-    rank += (q.y < v || (q.y == v && l + 1 < lane)) ? 1 : 0;
-    rank += (q.z < v || (q.z == v && l + 2 < lane)) ? 1 : 0;
-    rank += (q.w < v || (q.w == v && l + 3 < lane)) ? 1 : 0;
+    rank += q.x < v ? 1 : 0;
+    rank += q.y < v ? 1 : 0;
+    rank += q.z < v ? 1 : 0;
+    rank += q.w < v ? 1 : 0;
   }
+  // members with equal values have the same count of smaller ones so far, and the counts add up to less than 0 + 1 + .. + n - 1
+  if ((int)wave_allsum(live ? (float)rank : 0.f) != n * (n - 1) / 2)
+    for (int l = 0; l < n; ++l) rank += vals[l] == v && l < lane ? 1 : 0;
   if (live) sorted[rank] = v;
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
   const double y = (double)sorted[lane];                           // ascending, zero padded
   const double z = live ? (double)sorted[n - 1 - lane] : 0.0;      // descending, zero padded
-  const double s_lo = wave_scan_f64(y, lane);
-  const double s_lo2 = wave_scan_f64(__dmul_rn(y, y), lane);
-  const double s_hi = wave_scan_f64(z, lane);
-  const double s_hi2 = wave_scan_f64(__dmul_rn(z, z), lane);
+  double s_lo = y, s_lo2 = __dmul_rn(y, y), s_hi = z, s_hi2 = __dmul_rn(z, z);
+  wave_scans(s_lo, s_lo2, s_hi, s_hi2);
   // candidate j (lane j, 0 <= j <= k <= 63): j lowest + (k - j) highest
   const int j = lane;
   const int m = k - j;                                              // taken from the top
@@ -176,13 +238,7 @@ __device__ __forceinline__ uint64_t survivors_by_wave(const float* __restrict__ 
   double score = __dsub_rn(__dmul_rn((double)k, s2), __dmul_rn(s1, s1));
   int best = j;
   if (j > k) score = -__builtin_huge_val();
-  // arg-max, ties to the smaller j
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const double os = __shfl_xor(score, o, WAVE);
-    const int ob = __shfl_xor(best, o, WAVE);
-    if (os > score || (os == score && ob < best)) { score = os; best = ob; }
-  }
+  wave_best(score, best);                            // arg-max, ties to the smaller j
   return __ballot(live && (rank < best || rank >= n - (k - best)));
 }
 
@@ -194,14 +250,14 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void ovf_select_kernel(
   __shared__ __align__(16) float vals[OVF_WAVES][WAVE];
   __shared__ float sorted[OVF_WAVES][WAVE];
   __shared__ int part[OVF_WAVES];
-  const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = threadIdx.x & (WAVE - 1);
   const int g = blockIdx.x * OVF_WAVES + wv;
+  const bool have = g < n_groups;                   // the same in the whole wave
+  const int b = have ? offsets[g] : 0, n = have ? offsets[g + 1] - b : 0, k = have ? kk[g] : 0;
+  const float v = reward_of_lane(rewards, b, n);
   const int out0 = place_group<FROM>(kk, sums, g, n_groups, new_offsets, part);
-  if (g >= n_groups) return;                        // whole wave leaves together
-  const int b = offsets[g];
-  const int n = offsets[g + 1] - b;
-  const int k = kk[g];
-  const uint64_t mask = survivors_by_wave(rewards, b, n, k, vals[wv], sorted[wv], status);
+  if (!have) return;                                // whole wave leaves together
+  const uint64_t mask = survivors_by_wave(v, n, k, vals[wv], sorted[wv], status);
   if (lane == 0) masks[g] = mask;
   if (bad_group(n, k)) fill_bad_group(sel_idx, out0, b, n, k, lane, WAVE);
   else if ((mask >> lane) & 1ull) sel_idx[out0 + __popcll(mask & ((1ull << lane) - 1ull))] = b + lane;
@@ -245,7 +301,7 @@ __device__ __forceinline__ void sort_registers(float (&v)[N]) {
   }
 }
 
-// inclusive prefix sums by the doubling recurrence (see wave_scan_f64)
+// inclusive prefix sums by the doubling recurrence (see wave_scans)
 template <int K, int DD = 1>
 __device__ __forceinline__ void scan_registers(double (&a)[K]) {
   if constexpr (DD < K) {
@@ -474,7 +530,8 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void counts_and_rest_kernel(
   uint64_t left = __ballot(lane >= own && lane < own + per_wave && have && by_wave(n, k, odd));
   for (; left; left &= left - 1ull) {
     const int i = __builtin_ctzll(left);
-    const uint64_t mask = survivors_by_wave(rewards, __shfl(b, i, WAVE), __shfl(n, i, WAVE), __shfl(k, i, WAVE), vals[wv], sorted[wv],
+    const int ni = __shfl(n, i, WAVE);
+    const uint64_t mask = survivors_by_wave(reward_of_lane(rewards, __shfl(b, i, WAVE), ni), ni, __shfl(k, i, WAVE), vals[wv], sorted[wv],
                                             status);
     if (lane == 0) masks[chunk + i] = mask;
   }
