@@ -125,19 +125,25 @@ def _check(status):
 
 def _ptr(t):
     """Device (or host) address of a torch tensor / None."""
-    if t is None:
-        return None
-    if isinstance(t, int):
+    if t is None or t.__class__ is int:
         return t
     assert t.is_contiguous(), "the C ABI takes contiguous buffers"
     return t.data_ptr()
 
 
+_current_stream = None
+
+
 def _stream(stream):
-    if stream is None:
+    if stream is not None:
+        return stream if isinstance(stream, int) else stream.cuda_stream
+    global _current_stream
+    if _current_stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
-    return stream if isinstance(stream, int) else stream.cuda_stream
+        # the handle alone, without the stream object around it, which costs more than the launch of a small kernel
+        device, raw = torch.cuda.current_device, torch._C._cuda_getCurrentRawStream
+        _current_stream = lambda: raw(device())
+    return _current_stream()
 
 
 # ---------------------------------------------------------------- context-level calls
