@@ -195,6 +195,7 @@ static pg_status plan_workspace(pg_ctx* c) {
   c->ws_tin = take(sizeof(double) * c->cfg.T);                                  // network times of the steps
   c->ws_emb = take(c->cfg.net_kind == PG_NET_NONE ? 0 : sizeof(float) * 256 * (size_t)c->cfg.T);   // their embeddings
   c->ws_logr = take(sizeof(double) * (size_t)c->cfg.T * c->M0);                 // fp64 log-ratios of pg_policy_ratio; sums of sample_rows
+  c->ws_arrived = take(sizeof(uint64_t) * (size_t)c->M0);                       // sums of a step's log-probs under way
   c->ws_net = off;
   PG_TRY(net_plan(c));
   c->ws_total = align256(off + c->net.total);
@@ -295,7 +296,8 @@ extern "C" pg_status pg_create(const pg_config* cfg, pg_ctx** out) {
   // the funnel when every prune follows the schedule: row s = counts kept at step s | their exclusive scan
   {
     const int P = f.P, row = 2 * P + 1;
-    c->sched_table.assign((size_t)T * row, 0);
+    c->sched_table.assign((size_t)T * row + P + 1, 0);
+    for (int g = 0; g <= P; ++g) c->sched_table[(size_t)T * row + g] = g * f.N;
     std::vector<int> size(P, f.N);
     for (int s = 0; s < T; ++s) {
       int32_t* k = c->sched_table.data() + (size_t)s * row;
@@ -432,9 +434,10 @@ extern "C" pg_status pg_init_group(pg_ctx* c, uint64_t seed, void* stream) {
   c->pending_gather = false; c->net_fresh = false;
   c->evals = 0; c->updates = 0; c->steps_done = 0; c->advantages_done = false;
   for (int g = 0; g <= f.P; ++g) c->offsets[g] = g * f.N;
-  PG_TRY(launch_init_state(f.P, f.N, c->buf.group_offsets, c->buf.orig_id[0], c->buf.group_of, c->buf.logp_hist,
-                           (size_t)f.T * c->M0, c->buf.logp_sum, c->buf.status, s));
-  PG_TRY(pg_init_latents(c->buf.x[0], c->buf.orig_id[0], c->M0, c->d, seed, stream));
+  const bool rows = f.net_kind != PG_NET_NONE && small_rows_takes(c);             // sample_rows takes the sums of the noise from here
+  PG_TRY(launch_init_group(c->buf.x[0], f.P, f.N, c->d, seed, rows ? (double*)ws(c, c->ws_logr) : nullptr, f.T, c->buf.group_offsets,
+                           c->buf.orig_id[0], c->buf.group_of, c->buf.logp_hist, (size_t)f.T * c->M0, c->buf.logp_sum, c->buf.status,
+                           (uint64_t*)ws(c, c->ws_arrived), s));
   if (c->buf.x_hist)
     PG_HIP(hipMemcpyAsync(c->buf.x_hist, c->buf.x[0], sizeof(float) * (size_t)c->M0 * c->d, hipMemcpyDeviceToDevice, s));
   if (f.net_kind != PG_NET_NONE && !c->context_ready) {
@@ -465,16 +468,20 @@ extern "C" pg_status pg_net_forward(pg_ctx* c, int32_t step, void* stream) {
   return forward_step(c, step, -1, (hipStream_t)stream);
 }
 
+static void pruned(pg_ctx* c, const std::vector<int>& new_off) {
+  c->cur_id = 1 - c->cur_id;
+  c->offsets = new_off;
+  c->M = new_off[c->cfg.P];
+  c->pending_gather = true;
+}
+
 // shared tail of pg_prune / pg_prune_forced once sel_idx is on the device; new_off_dev: the new offsets [device]
 static pg_status finish_prune(pg_ctx* c, const std::vector<int>& new_off, const int32_t* new_off_dev, hipStream_t s) {
   const int P = c->cfg.P;
   const int M_new = new_off[P];
   PG_TRY(launch_pack_state(c->buf.orig_id[c->cur_id], c->buf.sel_idx, M_new, c->buf.orig_id[1 - c->cur_id], new_off_dev, P,
                            c->buf.group_offsets, c->buf.group_of, s));
-  c->cur_id = 1 - c->cur_id;
-  c->offsets = new_off;
-  c->M = M_new;
-  c->pending_gather = true;
+  pruned(c, new_off);
   return PG_OK;
 }
 
@@ -513,6 +520,20 @@ static pg_status prune_common(pg_ctx* c, int step, const uint64_t* forced, uint6
     PG_HIP(hipMemcpy(ws(c, c->ws_newoff), new_off.data(), sizeof(int32_t) * (P + 1), hipMemcpyHostToDevice));
     k_dev = (const int32_t*)ws(c, c->ws_k);
     off_dev = (const int32_t*)ws(c, c->ws_newoff);
+  }
+  // the usual case: sizes before and after are the schedule's, and the whole prune is one launch behind the rewards'
+  const size_t rows = 2 * (size_t)P + 1, old_at = step ? (step - 1) * rows + P : f.T * rows;
+  if (!forced && on_schedule && std::equal(c->offsets.begin(), c->offsets.end(), c->sched_table.begin() + old_at)) {
+    GroupEndArgs a{};
+    a.x = c->buf.x[c->cur_x]; a.u = c->Qv[step] != 0.0 ? c->buf.u : nullptr; a.w = c->buf.probe_w;
+    a.Pc = c->Pv[step]; a.Qc = a.u ? c->Qv[step] : 0.0; a.bias = f.probe_bias;
+    a.partials = (float*)ws(c, c->ws_partials); a.rewards = c->buf.rewards; a.offsets = (const int32_t*)ws(c, c->ws_sched) + old_at;
+    a.k = k_dev; a.new_offsets = off_dev; a.masks = c->buf.masks; a.sel_idx = c->buf.sel_idx; a.status = c->buf.status;
+    a.ids_in = c->buf.orig_id[c->cur_id]; a.ids_out = c->buf.orig_id[1 - c->cur_id]; a.group_of = c->buf.group_of;
+    a.offsets_out = c->buf.group_offsets;
+    PG_TRY(launch_group_end(a, P, f.N, c->M, c->d, s));
+    pruned(c, new_off);
+    return PG_OK;
   }
   PG_TRY(pg_preview_reward(c->buf.x[c->cur_x], c->buf.u, c->buf.probe_w, c->buf.rewards, c->M, c->d,
                            c->Pv[step], c->Qv[step], f.probe_bias, (float*)ws(c, c->ws_partials), s));
@@ -571,7 +592,8 @@ extern "C" pg_status pg_step(pg_ctx* c, int32_t step, void* stream) {
                          c->buf.logp_hist + (size_t)step * c->M0, c->buf.logp_sum,
                          c->pending_gather ? c->buf.sel_idx : nullptr, c->buf.orig_id[c->cur_id], c->M, c->d,
                          c->A[step], c->B[step], c->C[step], c->seed, (uint32_t)step,
-                         (float*)ws(c, c->ws_partials), hist_next, (hipStream_t)stream));
+                         (float*)ws(c, c->ws_partials), hist_next, sums_on_arrival(c->d) ? (uint64_t*)ws(c, c->ws_arrived) : nullptr,
+                         (hipStream_t)stream));
   c->steps_done = step + 1;
   c->cur_x = 1 - c->cur_x;
   c->pending_gather = false;
@@ -585,9 +607,10 @@ extern "C" pg_status pg_advantages(pg_ctx* c, void* stream) {
   if (c->pending_gather) return fail(PG_ESCHED, "pg_advantages: a prune is waiting for its pg_step");
   if (c->steps_done != c->cfg.T)
     return fail(PG_ESCHED, "pg_advantages: %d of %d steps taken (Eq. 18 is on the final latents)", c->steps_done, c->cfg.T);
-  PG_TRY(pg_preview_reward(c->buf.x[c->cur_x], nullptr, c->buf.probe_w, c->buf.rewards, c->M, c->d, 1.0, 0.0,
-                           c->cfg.probe_bias, (float*)ws(c, c->ws_partials), stream));
-  PG_TRY(pg_group_advantages(c->buf.rewards, c->buf.group_offsets, c->cfg.P, c->cfg.adv_eps, c->buf.adv, stream));
+  GroupEndArgs a{};
+  a.x = c->buf.x[c->cur_x]; a.w = c->buf.probe_w; a.Pc = 1.0; a.bias = c->cfg.probe_bias; a.partials = (float*)ws(c, c->ws_partials);
+  a.rewards = c->buf.rewards; a.offsets = c->buf.group_offsets; a.eps = c->cfg.adv_eps; a.adv = c->buf.adv;
+  PG_TRY(launch_group_end(a, c->cfg.P, c->cfg.N, c->M, c->d, (hipStream_t)stream));
   c->advantages_done = true;
   return PG_OK;
 }
@@ -691,8 +714,7 @@ extern "C" pg_status pg_policy_ratio(pg_ctx* c, const uint16_t* weights_new, dou
 static pg_status sample_rows(pg_ctx* c, hipStream_t s) {
   const pg_config& f = c->cfg;
   const int together = c->net.mod_steps;
-  double* sums = (double*)ws(c, c->ws_logr);
-  PG_TRY(launch_noise_sums(c->M0, f.T, c->d, c->seed, sums, s));
+  const double* sums = (const double*)ws(c, c->ws_logr);         // by pg_init_group
   auto update = [&](int step) {
     return RowsUpdate{(float)c->A[step], (float)c->B[step], (float)c->C[step], (uint32_t)c->seed, (uint32_t)(c->seed >> 32), (uint32_t)step,
                       c->pending_gather ? c->buf.sel_idx : nullptr, c->buf.orig_id[c->cur_id], c->buf.x[1 - c->cur_x],

@@ -23,7 +23,7 @@ struct pg_ctx {
   int64_t block_stride = 0, weights_numel = 0;
   // workspace plan
   size_t ws_partials = 0, ws_k = 0, ws_newoff = 0, ws_forced = 0, ws_sched = 0, ws_tin = 0, ws_emb = 0,
-         ws_logr = 0, ws_net = 0,
+         ws_logr = 0, ws_arrived = 0, ws_net = 0,
          ws_total = 0;
   NetPlan net{};
   // bound buffers
@@ -41,7 +41,7 @@ struct pg_ctx {
   int rows_buffer = 0;                    // which of NetPlan::rows_qk / rows_vt the next block reads
   // The funnel as the schedule fixes it: row s = k[P] | new_offsets[P+1] of a prune at step s when every earlier
   // prune followed the schedule.  Uploaded into the workspace once (pg_bind), so a prune needs no host -> device copy.
-  std::vector<int32_t> sched_table;       // [T][2P+1]
+  std::vector<int32_t> sched_table;       // [T][2P+1], then the offsets of the full groups [P+1]
   // pinned host slot for the counts pg_select_final takes per call (2P+1 ints), and the event that tells when the
   // copy out of it has run (the host waits on it before writing the slot again)
   int32_t* staging = nullptr;
@@ -67,7 +67,14 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
 pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* logp, float* logp_hist,
                           float* logp_sum, const int32_t* src, const int32_t* orig_id, int64_t n_traj, int64_t d,
                           double A, double B, double C, uint64_t seed, uint32_t step, float* partials,
-                          float* hist_next, hipStream_t s);
+                          float* hist_next, uint64_t* arrived, hipStream_t s);
+bool sums_on_arrival(int64_t d);                                 // whether an update of such latents may be given `arrived`
+// the preview's rewards; `unfinished`: partial sums are left to be added up, where that is not done here
+pg_status launch_preview(const float* x, const float* u, const float* w, float* rewards, int64_t n_traj, int64_t d, double Pc, double Qc,
+                         double bias, float* partials, bool* unfinished, hipStream_t s);
+pg_status launch_init_group(float* x, int P, int N, int64_t d, uint64_t seed, double* sums, int steps, int32_t* offsets, int32_t* ids,
+                            int32_t* group_of, float* logp_hist, size_t hist_n, float* logp_sum, int32_t* status, uint64_t* arrived,
+                            hipStream_t s);
 // sums[t, id] = sum over the noise that step t draws for trajectory id, t < steps (latents of at most four chunks)
 pg_status launch_noise_sums(int M0, int steps, int64_t d, uint64_t seed, double* sums, hipStream_t s);
 pg_status launch_transition_logprob(const float* x, const float* u, const float* x_next_by_id,
@@ -79,8 +86,14 @@ pg_status launch_surrogate(const double* log_ratio, const float* adv, const int3
                            float* J, hipStream_t s);
 // small launches (ovf_kernels.hip)
 pg_status launch_fill_u32(void* p, uint32_t v, size_t n, hipStream_t s);
-pg_status launch_init_state(int P, int N, int32_t* offsets, int32_t* ids, int32_t* group_of, float* logp_hist, size_t hist_n,
-                            float* logp_sum, int32_t* status, hipStream_t s);
+// rewards of the groups, then the selection and packing (k set) or the advantages
+struct GroupEndArgs {
+  const float* x; const float* u; const float* w; double Pc, Qc, bias; float* partials; float* rewards; const int32_t* offsets;
+  const int32_t* k; const int32_t* new_offsets; uint64_t* masks; int32_t* sel_idx; int32_t* status;
+  const int32_t* ids_in; int32_t* ids_out; int32_t* group_of; int32_t* offsets_out;
+  double eps; float* adv;
+};
+pg_status launch_group_end(GroupEndArgs& a, int P, int N, int M, int64_t d, hipStream_t s);
 pg_status launch_pack_state(const int32_t* ids_in, const int32_t* sel, int n_out, int32_t* ids_out, const int32_t* new_offsets,
                             int P, int32_t* offsets, int32_t* group_of, hipStream_t s);
 pg_status launch_gather_ids(const int32_t* in, const int32_t* sel, int n_out, int32_t* out, hipStream_t s);

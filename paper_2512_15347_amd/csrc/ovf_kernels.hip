@@ -12,7 +12,8 @@
 //   many groups: one LANE owns one group (ovf_select_lanes_kernel below).
 #include <algorithm>
 #include <mutex>
-#include "common.hpp"
+#include <type_traits>
+#include "ctx.hpp"
 #include "operands.hpp"
 #include "philox.hpp"
 
@@ -816,6 +817,103 @@ __global__ __launch_bounds__(OVF_WAVES * WAVE) void uniform_select_kernel(
   }
 }
 
+// ---- the end of a checkpoint or of a run in one launch: a workgroup per group (of at most 64 members, the loop's) gets its rewards, and
+// its first wave selects and packs, or forms the advantages.  A launch less is 4 to 6 us less of a prune, of which a loop of short
+// trajectories has three: rewards, selection, packing. ----
+// Where the rewards come from: REWARDS_READY, what the caller has; REWARDS_PARTIAL, the partial sums of preview_reward_kernel, at
+// most 16 to a trajectory, a lane each, added in the order of reward_finish_kernel; REWARDS_DIRECT, the latents, four members of one
+// chunk at a time, summed in the order of preview_reward_kernel.
+enum RewardsFrom { REWARDS_READY, REWARDS_PARTIAL, REWARDS_DIRECT };
+constexpr int PARTIALS_MAX = 16, DIRECT_GROUPS = 4;
+struct GroupEnd {
+  const float* x; const float* u; const float* w; int d4; float Pc, Qc;      // REWARDS_DIRECT; u NULL: not used
+  const float* partials; int chunks;
+  double bias;
+  float* rewards;
+  const int32_t* offsets;                          // of the members
+  // selection: counts and offsets of the survivors, where they go
+  const int32_t* k; const int32_t* new_offsets; uint64_t* masks; int32_t* sel_idx; int32_t* status;
+  const int32_t* ids_in; int32_t* ids_out; int32_t* group_of; int32_t* offsets_out; int P;
+  double eps; float* adv;                          // advantages
+};
+// sum of `chunks` <= 16 partials by one lane, as wave_sum_of adds them: neighbours 8, 4, 2 and 1 apart
+__device__ __forceinline__ double sum_of_partials(const float* __restrict__ p, int chunks) {
+  double v[PARTIALS_MAX];
+#pragma unroll
+  for (int c = 0; c < PARTIALS_MAX; ++c) v[c] = (double)p[min(c, chunks - 1)];
+#pragma unroll
+  for (int c = 0; c < PARTIALS_MAX; ++c) v[c] = c < chunks ? 0.0 + v[c] : 0.0;
+#pragma unroll
+  for (int o = PARTIALS_MAX / 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int c = 0; c < o; ++c) v[c] = __dadd_rn(v[c], v[c + o]);
+  return v[0];
+}
+template <int FROM, bool SELECT>
+__global__ __launch_bounds__(FROM == REWARDS_DIRECT ? DIRECT_GROUPS * STREAM_THREADS : WAVE) void group_end_kernel(const GroupEnd a) {
+  __shared__ __align__(16) float vals[WAVE];
+  __shared__ float sorted[WAVE], reward[WAVE];
+  const int g = blockIdx.x, lane = threadIdx.x & (WAVE - 1);
+  const int b = a.offsets[g], n = a.offsets[g + 1] - b;
+  float v = 0.f;
+  if (FROM == REWARDS_DIRECT) {
+    __shared__ float part[DIRECT_GROUPS][4];
+    const int q = threadIdx.x / STREAM_THREADS, lane256 = threadIdx.x & (STREAM_THREADS - 1);
+    for (int i0 = 0; i0 < n; i0 += DIRECT_GROUPS) {
+      const int i = min(i0 + q, n - 1);
+      const f32x4* xr = reinterpret_cast<const f32x4*>(a.x) + (size_t)(b + i) * a.d4;
+      const f32x4* ur = reinterpret_cast<const f32x4*>(a.u) + (size_t)(b + i) * a.d4;
+      float acc = 0.f;
+#pragma unroll
+      for (int it = 0; it < STREAM_ITERS; ++it) {
+        const int e4 = it * STREAM_THREADS + lane256;
+        if (e4 < a.d4) {
+          const f32x4 xv = xr[e4], wv = reinterpret_cast<const f32x4*>(a.w)[e4];
+          f32x4 h;
+          if (a.u) {
+            const f32x4 uv = ur[e4];
+            h.x = a.Pc * xv.x + a.Qc * uv.x; h.y = a.Pc * xv.y + a.Qc * uv.y;
+            h.z = a.Pc * xv.z + a.Qc * uv.z; h.w = a.Pc * xv.w + a.Qc * uv.w;
+          } else {
+            h.x = a.Pc * xv.x; h.y = a.Pc * xv.y; h.z = a.Pc * xv.z; h.w = a.Pc * xv.w;
+          }
+          acc += (wv.x * h.x + wv.y * h.y) + (wv.z * h.z + wv.w * h.w);
+        }
+      }
+      acc = wave_allsum(acc);
+      if (lane == 0) part[q][(threadIdx.x / WAVE) & 3] = acc;
+      __syncthreads();
+      if (lane256 == 0 && i0 + q < n) reward[i0 + q] = (float)(a.bias + (double)((part[q][0] + part[q][1]) + (part[q][2] + part[q][3])));
+      __syncthreads();
+    }
+    if (threadIdx.x >= WAVE) return;
+    if (lane < n) v = reward[lane];
+  } else if (lane < n) {
+    v = FROM == REWARDS_PARTIAL ? (float)(a.bias + sum_of_partials(a.partials + (size_t)(b + lane) * a.chunks, a.chunks)) : a.rewards[b + lane];
+  }
+  if (FROM != REWARDS_READY && lane < n) a.rewards[b + lane] = v;
+  if (SELECT) {
+    const int k = a.k[g], out0 = a.new_offsets[g];
+    if (lane == 0) {
+      a.offsets_out[g] = out0;
+      if (g == a.P - 1) a.offsets_out[a.P] = a.new_offsets[a.P];
+    }
+    const uint64_t mask = survivors_by_wave(v, n, k, vals, sorted, a.status);
+    if (lane == 0) a.masks[g] = mask;
+    if ((mask >> lane) & 1ull) {
+      const int at = out0 + __popcll(mask & ((1ull << lane) - 1ull));
+      a.sel_idx[at] = b + lane;
+      a.ids_out[at] = a.ids_in[b + lane];
+      a.group_of[at] = g;
+    }
+  } else {                                           // as group_advantages_kernel
+    const double mu = wave_allsum_f64(lane < n ? 0.0 + (double)v : 0.0) / (double)n;
+    const double dv = (double)v - mu;
+    const double sigma = sqrt(wave_allsum_f64(lane < n ? 0.0 + dv * dv : 0.0) / (double)n);
+    if (lane < n) a.adv[b + lane] = (float)(dv / (sigma + a.eps));
+  }
+}
+
 // ---- group diagnostics: sigma_G (population) and the share of members within delta sigma_G of the
 // group mean (the clustered region of Eq. 7); one wave per group, any group size ----
 __global__ __launch_bounds__(OVF_WAVES * WAVE) void group_stats_kernel(
@@ -850,22 +948,6 @@ __global__ void gather_ids_kernel(const int32_t* __restrict__ ids_in, const int3
                                   int n_out, int32_t* __restrict__ ids_out) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r < n_out) ids_out[r] = ids_in[sel[r]];
-}
-
-// What a run starts from, in one launch: offsets of the full groups, ids, group of every row, no log-prob yet (NaN), zero
-// sums, clear status.  (Five fills and a copy of a few microseconds each before.)
-__global__ void init_state_kernel(int P, int N, int32_t* __restrict__ offsets, int32_t* __restrict__ ids,
-                                  int32_t* __restrict__ group_of, uint32_t* __restrict__ logp_hist, size_t hist_n,
-                                  float* __restrict__ logp_sum, int32_t* __restrict__ status) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
-  if (i < 4) status[i] = 0;
-  for (size_t g = i; g <= (size_t)P; g += stride) offsets[g] = (int32_t)g * N;
-  for (size_t r = i; r < (size_t)P * N; r += stride) {
-    ids[r] = (int32_t)r;
-    group_of[r] = (int32_t)(r / N);
-    logp_sum[r] = 0.f;
-  }
-  for (size_t j = i; j < hist_n; j += stride) logp_hist[j] = 0x7FC00000u;
 }
 
 // After a selection: ids, group and offsets of the packed survivors (group of a row: binary search in the new offsets)
@@ -911,20 +993,36 @@ pg_status launch_fill_u32(void* p, uint32_t v, size_t n, hipStream_t s) {
   return PG_OK;
 }
 
-pg_status launch_init_state(int P, int N, int32_t* offsets, int32_t* ids, int32_t* group_of, float* logp_hist, size_t hist_n,
-                            float* logp_sum, int32_t* status, hipStream_t s) {
-  const size_t n = std::max(hist_n, (size_t)P * N) + 1;
-  init_state_kernel<<<dim3((unsigned)std::min<size_t>((n + 255) / 256, 1024)), dim3(256), 0, s>>>(
-      P, N, offsets, ids, group_of, (uint32_t*)logp_hist, hist_n, logp_sum, status);
-  PG_LAUNCH_CHECK("init_state_kernel");
-  return PG_OK;
-}
-
 pg_status launch_pack_state(const int32_t* ids_in, const int32_t* sel, int n_out, int32_t* ids_out, const int32_t* new_offsets,
                             int P, int32_t* offsets, int32_t* group_of, hipStream_t s) {
   pack_state_kernel<<<dim3((std::max(n_out, 1) + 255) / 256), dim3(256), 0, s>>>(ids_in, sel, n_out, ids_out, new_offsets, P,
                                                                                 offsets, group_of);
   PG_LAUNCH_CHECK("pack_state_kernel");
+  return PG_OK;
+}
+
+// Rewards of a run's groups from the latents, then the selection (k set) or the advantages.  The members' latents go through the
+// group's own workgroup where it has little to read: 12 members of 1024 elements take it 2 us, 64 of 4096 more than the launches saved.
+pg_status launch_group_end(GroupEndArgs& a, int P, int N, int M, int64_t d, hipStream_t s) {
+  GroupEnd e{a.x, a.u, a.w, (int)(d / 4), (float)a.Pc, (float)a.Qc, a.partials, (int)chunks_per_traj(d), a.bias, a.rewards, a.offsets,
+             a.k, a.new_offsets, a.masks, a.sel_idx, a.status, a.ids_in, a.ids_out, a.group_of, a.offsets_out, P, a.eps, a.adv};
+  int from = REWARDS_DIRECT;
+  if ((int64_t)N * d > 16384 || e.chunks > 1) {
+    bool unfinished = false;
+    PG_TRY(launch_preview(a.x, a.u, a.w, a.rewards, M, d, a.Pc, a.Qc, a.bias, a.partials, e.chunks <= PARTIALS_MAX ? &unfinished : nullptr, s));
+    from = unfinished ? REWARDS_PARTIAL : REWARDS_READY;
+  }
+  auto run = [&](auto select) {
+    constexpr bool SELECT = decltype(select)::value;
+    if (from == REWARDS_DIRECT) group_end_kernel<REWARDS_DIRECT, SELECT><<<dim3(P), dim3(DIRECT_GROUPS * STREAM_THREADS), 0, s>>>(e);
+    else if (from == REWARDS_PARTIAL) group_end_kernel<REWARDS_PARTIAL, SELECT><<<dim3(P), dim3(WAVE), 0, s>>>(e);
+    else group_end_kernel<REWARDS_READY, SELECT><<<dim3(P), dim3(WAVE), 0, s>>>(e);
+  };
+  const int rec = from == REWARDS_DIRECT ? prof_open(PROF_PREVIEW, (a.u ? 8.0 : 4.0) * (double)M * (double)d, s) : -1;
+  if (a.k) run(std::true_type{});
+  else run(std::false_type{});
+  prof_close(rec, s);
+  PG_LAUNCH_CHECK("group_end_kernel");
   return PG_OK;
 }
 

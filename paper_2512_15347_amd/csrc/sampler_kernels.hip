@@ -6,6 +6,7 @@
 // 16-byte accesses; a chunk's sum is one partial, and a trajectory's partials are added up in a fixed
 // order (fp64), so results do not depend on scheduling: by the workgroup itself where it holds all chunks
 // of a short trajectory, else by a second tiny kernel.
+#include <algorithm>
 #include <type_traits>
 #include "ctx.hpp"
 #include "logprob.hpp"
@@ -26,17 +27,19 @@ __device__ __forceinline__ float block_sum_256(float v) {
   return t;
 }
 
-__global__ __launch_bounds__(STREAM_THREADS) void init_latents_kernel(
-    float* __restrict__ x, const int32_t* __restrict__ orig_id, int d4, int chunks, uint32_t k0,
-    uint32_t k1) {
-  const int r = blockIdx.x / chunks, c = blockIdx.x - r * chunks;
-  const uint32_t id = (uint32_t)orig_id[r];
+__device__ __forceinline__ void init_chunk(float* __restrict__ x, int r, int c, uint32_t id, int d4, uint32_t k0, uint32_t k1) {
   f32x4* xr = reinterpret_cast<f32x4*>(x) + (size_t)r * d4;
 #pragma unroll
   for (int it = 0; it < STREAM_ITERS; ++it) {
     const int e4 = c * (STREAM_CHUNK / 4) + it * STREAM_THREADS + threadIdx.x;
     if (e4 < d4) xr[e4] = philox_normal4((uint32_t)e4, 0u, id, STREAM_INIT, k0, k1);
   }
+}
+__global__ __launch_bounds__(STREAM_THREADS) void init_latents_kernel(
+    float* __restrict__ x, const int32_t* __restrict__ orig_id, int d4, int chunks, uint32_t k0,
+    uint32_t k1) {
+  const int r = blockIdx.x / chunks;
+  init_chunk(x, r, blockIdx.x - r * chunks, (uint32_t)orig_id[r], d4, k0, k1);
 }
 
 // ---- sums over a trajectory: one partial per chunk of STREAM_CHUNK elements (256 lanes), added up in fp64 in a fixed order ----
@@ -85,13 +88,15 @@ static void with_groups(int chunks, F launch) {
 }
 
 // x_out[r] = A x[q] + B u[q] + C xi, q = src ? src[r] : r; sum xi^2 per trajectory.  GROUPS 0: a workgroup per chunk,
-// which leaves its partial; else a workgroup of GROUPS x 256 lanes per trajectory.
+// which leaves its partial, or adds it to `arrived` (one word per row, 0 before and after); else a workgroup of GROUPS x 256 lanes
+// per trajectory.
+constexpr int ARRIVED_SHIFT = 52;                  // 12 bits of count above 24 of whole and 28 of fractional sum
 template <int GROUPS>
 __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_step_kernel(
     const float* __restrict__ x, const float* __restrict__ u, float* __restrict__ x_out,
     const int32_t* __restrict__ src, const int32_t* __restrict__ orig_id, int d4, int chunks, float A,
     float B, float C, uint32_t k0, uint32_t k1, uint32_t step, float* __restrict__ partials,
-    float* __restrict__ hist_next, const LogProb out) {
+    float* __restrict__ hist_next, const LogProb out, uint64_t* __restrict__ arrived) {
   const int r = GROUPS ? blockIdx.x : blockIdx.x / chunks, c = GROUPS ? threadIdx.x / STREAM_THREADS : blockIdx.x - r * chunks;
   const int lane256 = GROUPS > 1 ? threadIdx.x & (STREAM_THREADS - 1) : threadIdx.x;
   const int q = src ? src[r] : r;
@@ -129,7 +134,19 @@ __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_st
     row_sum<GROUPS>(chunks, acc, [&](double s) { finish_logprob(out, r, (int)id, s); });
   } else {
     const float t = block_sum_256(acc);
-    if (threadIdx.x == 0) partials[blockIdx.x] = t;
+    if (threadIdx.x != 0) return;
+    if (!arrived) {
+      partials[blockIdx.x] = t;
+      return;
+    }
+    // The workgroup that adds its share last has the sum: no second launch, which a step paid 4 us for.  Sum and number of shares are
+    // one 64-bit word, so that nothing else has to be ordered.  In units of 2^-28 a share of 2^-4 and more is exact, and the sum then
+    // the one that fp64 gives, whatever the order (a share that small, of a last chunk of a few elements, is off by 2^-29 at most).
+    const uint64_t share = (uint64_t)__double2ull_rn((double)t * 268435456.0);
+    const uint64_t before = __hip_atomic_fetch_add(arrived + r, (1ull << ARRIVED_SHIFT) + share, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((int)(before >> ARRIVED_SHIFT) + 1 != chunks) return;
+    __hip_atomic_store(arrived + r, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // for the next step
+    finish_logprob(out, r, (int)id, (double)((before & ((1ull << ARRIVED_SHIFT) - 1)) + share) * (1.0 / 268435456.0));
   }
 }
 
@@ -187,20 +204,23 @@ __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_st
 // sde_step_kernel.  The noise depends on seed, step and id alone, so a loop whose updates are spread over several workgroups of a
 // trajectory takes its sums from here instead of putting them together at every step (64 tokens of 4 channels, 8 trajectories,
 // ten steps: one launch of 3 us).
-template <int GROUPS>
-__global__ __launch_bounds__(GROUPS * STREAM_THREADS) void noise_sums_kernel(int d4, int chunks, uint32_t k0, uint32_t k1,
-                                                                             double* __restrict__ sums) {
-  const int r = blockIdx.x, step = blockIdx.y;
-  const int c = threadIdx.x / STREAM_THREADS, lane256 = threadIdx.x & (STREAM_THREADS - 1);
+__device__ __forceinline__ float noise_square_sum(int c, int lane256, int d4, uint32_t step, uint32_t id, uint32_t k0, uint32_t k1) {
   float acc = 0.f;
 #pragma unroll
   for (int it = 0; it < STREAM_ITERS; ++it) {
     const int e4 = c * (STREAM_CHUNK / 4) + it * STREAM_THREADS + lane256;
     if (e4 < d4) {
-      const f32x4 z = philox_normal4((uint32_t)e4, (uint32_t)step, (uint32_t)r, STREAM_STEP, k0, k1);
+      const f32x4 z = philox_normal4((uint32_t)e4, step, id, STREAM_STEP, k0, k1);
       acc += (z.x * z.x + z.y * z.y) + (z.z * z.z + z.w * z.w);
     }
   }
+  return acc;
+}
+template <int GROUPS>
+__global__ __launch_bounds__(GROUPS * STREAM_THREADS) void noise_sums_kernel(int d4, int chunks, uint32_t k0, uint32_t k1,
+                                                                             double* __restrict__ sums) {
+  const int r = blockIdx.x, step = blockIdx.y;
+  const float acc = noise_square_sum(threadIdx.x / STREAM_THREADS, threadIdx.x & (STREAM_THREADS - 1), d4, (uint32_t)step, (uint32_t)r, k0, k1);
   row_sum<GROUPS>(chunks, acc, [&](double s) { sums[(size_t)step * gridDim.x + r] = s; });
 }
 
@@ -407,7 +427,7 @@ static pg_status launch_logprob_finish(const float* partials, int chunks, int64_
 pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* logp, float* logp_hist,
                           float* logp_sum, const int32_t* src, const int32_t* orig_id, int64_t n_traj, int64_t d,
                           double A, double B, double C, uint64_t seed, uint32_t step, float* partials,
-                          float* hist_next, hipStream_t stream) {
+                          float* hist_next, uint64_t* arrived, hipStream_t stream) {
   PG_TRY(check_stream_shape(n_traj, d));
   if (n_traj == 0) return PG_OK;
   if (!x || !u || !x_out || !orig_id || !partials) return fail(PG_EINVAL, "pg_sde_step_logprob: null pointer");
@@ -421,11 +441,72 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
     constexpr int G = decltype(groups)::value;
     sde_step_kernel<G><<<dim3((unsigned)(G ? n_traj : n_traj * chunks)), dim3((G ? G : 1) * STREAM_THREADS), 0, stream>>>(
         x, u, x_out, src, orig_id, (int)(d / 4), chunks, (float)A, (float)B, (float)C, (uint32_t)seed, (uint32_t)(seed >> 32), step,
-        partials, hist_next, out);
+        partials, hist_next, out, arrived);
   });
   prof_close(rec, stream);
   PG_LAUNCH_CHECK("sde_step_kernel");
-  return row ? PG_OK : launch_logprob_finish(partials, chunks, n_traj, orig_id, out, stream);
+  return row || arrived ? PG_OK : launch_logprob_finish(partials, chunks, n_traj, orig_id, out, stream);
+}
+
+// A sum of d squared normals is below 23 d (a pair's is -2 ln u, u >= 2^-33).
+bool sums_on_arrival(int64_t d) { return 23 * d < (1 << 24) && chunks_per_traj(d) < (1 << (64 - ARRIVED_SHIFT)); }
+
+pg_status launch_noise_sums(int M0, int steps, int64_t d, uint64_t seed, double* sums, hipStream_t stream);
+
+// What a run starts from, in one launch: initial latents by chunk (ids are the rows), then, 256 lanes a workgroup, the sums of the noise
+// of `steps` steps where they are asked for (latents of one chunk), then the state: offsets of the full groups, ids, group of
+// every row, no log-prob yet (NaN), zero sums, clear status and counts.  (Two launches, with the noise three, of 2 to 3 us before.)
+struct InitGroup {
+  float* x; int d4, chunks; uint32_t k0, k1;
+  double* sums; int steps;
+  int P, N; int32_t* offsets; int32_t* ids; int32_t* group_of; uint32_t* logp_hist; size_t hist_n; float* logp_sum; int32_t* status;
+  uint64_t* arrived;
+  int latent_blocks, noise_blocks;
+};
+__global__ __launch_bounds__(STREAM_THREADS) void init_group_kernel(const InitGroup a) {
+  int blk = blockIdx.x;
+  if (blk < a.latent_blocks) {
+    const int r = blk / a.chunks;
+    init_chunk(a.x, r, blk - r * a.chunks, (uint32_t)r, a.d4, a.k0, a.k1);
+    return;
+  }
+  blk -= a.latent_blocks;
+  if (blk < a.noise_blocks) {
+    const int M0 = a.P * a.N, step = blk / M0, r = blk - step * M0;
+    const float acc = noise_square_sum(0, threadIdx.x, a.d4, (uint32_t)step, (uint32_t)r, a.k0, a.k1);
+    row_sum<1>(1, acc, [&](double s) { a.sums[(size_t)step * M0 + r] = s; });
+    return;
+  }
+  blk -= a.noise_blocks;
+  const size_t i = (size_t)blk * STREAM_THREADS + threadIdx.x;
+  const size_t stride = (size_t)(gridDim.x - a.latent_blocks - a.noise_blocks) * STREAM_THREADS;
+  if (i < 4) a.status[i] = 0;
+  for (size_t g = i; g <= (size_t)a.P; g += stride) a.offsets[g] = (int32_t)g * a.N;
+  for (size_t r = i; r < (size_t)a.P * a.N; r += stride) {
+    a.ids[r] = (int32_t)r;
+    a.group_of[r] = (int32_t)(r / a.N);
+    a.logp_sum[r] = 0.f;
+    a.arrived[r] = 0;
+  }
+  for (size_t j = i; j < a.hist_n; j += stride) a.logp_hist[j] = 0x7FC00000u;
+}
+
+// `sums`: see launch_noise_sums, or NULL
+pg_status launch_init_group(float* x, int P, int N, int64_t d, uint64_t seed, double* sums, int steps, int32_t* offsets, int32_t* ids,
+                            int32_t* group_of, float* logp_hist, size_t hist_n, float* logp_sum, int32_t* status, uint64_t* arrived,
+                            hipStream_t s) {
+  const int64_t M0 = (int64_t)P * N;
+  PG_TRY(check_stream_shape(M0, d));
+  const int chunks = (int)chunks_per_traj(d);
+  const bool noise_here = sums && chunks == 1 && M0 * steps <= (1 << 24);
+  InitGroup a{x, (int)(d / 4), chunks, (uint32_t)seed, (uint32_t)(seed >> 32), sums, steps, P, N, offsets, ids, group_of,
+              (uint32_t*)logp_hist, hist_n, logp_sum, status, arrived, (int)(M0 * chunks), noise_here ? (int)(M0 * steps) : 0};
+  const size_t n = std::max(hist_n, (size_t)M0) + 1;
+  const int64_t blocks = (int64_t)a.latent_blocks + a.noise_blocks + (int64_t)std::min<size_t>((n + 255) / 256, 1024);
+  if (blocks > INT32_MAX) return fail(PG_ESHAPE, "n_traj * ceil(d/4096) exceeds the grid limit");
+  init_group_kernel<<<dim3((unsigned)blocks), dim3(STREAM_THREADS), 0, s>>>(a);
+  PG_LAUNCH_CHECK("init_group_kernel");
+  return sums && !noise_here ? launch_noise_sums((int)M0, steps, d, seed, sums, s) : PG_OK;
 }
 
 pg_status launch_noise_sums(int M0, int steps, int64_t d, uint64_t seed, double* sums, hipStream_t stream) {
@@ -476,7 +557,7 @@ extern "C" pg_status pg_sde_step_logprob(const float* x, const float* u, float* 
                                          double B, double C, uint64_t seed, uint32_t step,
                                          float* partials, void* stream) {
   return launch_sde_step(x, u, x_out, logp, logp_hist, logp_sum, src, orig_id, n_traj, d, A, B, C, seed, step,
-                         partials, nullptr, (hipStream_t)stream);
+                         partials, nullptr, nullptr, (hipStream_t)stream);
 }
 
 extern "C" pg_status pg_sde_step_logprob_bf16(const uint16_t* x, const uint16_t* u, uint16_t* x_out, float* logp,
@@ -504,16 +585,15 @@ extern "C" pg_status pg_sde_step_logprob_bf16(const uint16_t* x, const uint16_t*
   return row ? PG_OK : launch_logprob_finish(partials, chunks, n_traj, orig_id, out, stream);
 }
 
-extern "C" pg_status pg_preview_reward(const float* x, const float* u, const float* w, float* rewards,
-                                       int64_t n_traj, int64_t d, double Pc, double Qc, double bias,
-                                       float* partials, void* stream) {
+namespace pg {
+pg_status launch_preview(const float* x, const float* u, const float* w, float* rewards, int64_t n_traj, int64_t d, double Pc, double Qc,
+                         double bias, float* partials, bool* unfinished, hipStream_t s) {
   PG_TRY(check_stream_shape(n_traj, d));
   if (n_traj == 0) return PG_OK;
   if (!x || !w || !rewards || !partials) return fail(PG_EINVAL, "pg_preview_reward: null pointer");
   if (!u && Qc != 0.0) return fail(PG_EINVAL, "pg_preview_reward: u is NULL but Qc = %g", Qc);
   const int chunks = (int)chunks_per_traj(d);
   const bool with_u = u && Qc != 0.0;
-  hipStream_t s = (hipStream_t)stream;
   const bool row = row_per_workgroup(n_traj, chunks);
   const int rec = prof_open(PROF_PREVIEW, (with_u ? 8.0 : 4.0) * (double)n_traj * (double)d, s);
   with_groups(row ? chunks : 0, [&](auto groups) {
@@ -524,11 +604,19 @@ extern "C" pg_status pg_preview_reward(const float* x, const float* u, const flo
   });
   prof_close(rec, s);
   PG_LAUNCH_CHECK("preview_reward_kernel");
-  if (row) return PG_OK;
+  if (unfinished) *unfinished = !row;
+  if (row || unfinished) return PG_OK;
   reward_finish_kernel<<<dim3((unsigned)((n_traj + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS * WAVE), 0, s>>>(
       partials, chunks, (int)n_traj, bias, rewards);
   PG_LAUNCH_CHECK("reward_finish_kernel");
   return PG_OK;
+}
+}  // namespace pg
+
+extern "C" pg_status pg_preview_reward(const float* x, const float* u, const float* w, float* rewards,
+                                       int64_t n_traj, int64_t d, double Pc, double Qc, double bias,
+                                       float* partials, void* stream) {
+  return launch_preview(x, u, w, rewards, n_traj, d, Pc, Qc, bias, partials, nullptr, (hipStream_t)stream);
 }
 
 extern "C" pg_status pg_compact_gather(const float* x, float* out, const int32_t* src, int64_t n_out,

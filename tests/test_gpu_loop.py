@@ -473,6 +473,71 @@ def test_narrow_loops_by_rows_and_by_trajectories_agree(lib, kind, D, heads, C, 
         assert torch.equal(runs[0][k], runs[2][k]), f"by rows and by trajectories: {k}"
 
 
+# The loop's launches (a prune's and the advantages' rewards by group, a step's log-probs by the last workgroup to arrive) against the
+# entry points of the single kernels: latents of one chunk with little and with more to read for a group, of 2 with many trajectories,
+# of 5, 16 and 17 chunks, and too large for the sums by arrival
+@pytest.mark.parametrize("P,N,C,H,W", [(3, 4, 4, 32, 32), (3, 5, 4, 32, 32), (2, 64, 4, 2, 2), (9, 64, 4, 32, 34), (2, 6, 4, 64, 72),
+                                       (2, 4, 16, 64, 64), (1, 3, 16, 66, 64), (1, 3, 16, 214, 214)])
+def test_loop_launches_against_the_single_kernels(lib, P, N, C, H, W):
+    d, T, seed, M0 = C * H * W, 3, 77, P * N
+    say(f"loop launches {P} x {N} latents of {d}")
+    cfg = workloads.get_config("cfg1")
+    cfg.update(P=P, N=N, C=C, H=H, W=W, T=T, schedule=[[(0, N - 1), (1, 1)]] + [[(1, max(1, N // 2))]] * (P - 1), Li=H * W // 4, d=d)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    c, keep = lib.make_config(cfg, probe_bias=0.25, net=False)
+    ctx = lib.pg_create(c)
+    buf = lib.Buffers(ctx, cfg)
+    buf.workspace.fill_(255)
+    buf.u.normal_(generator=g)
+    buf.probe_w.normal_(generator=g)
+    lib.pg_bind(ctx, buf)
+    lib.pg_init_group(ctx, seed)
+    for s in range(T):
+        lib.pg_net_forward(ctx, s)
+        if s < 2:
+            lib.pg_prune(ctx, s)
+        lib.pg_step(ctx, s)
+    lib.pg_advantages(ctx)
+    lib.pg_check(ctx)
+    tab = lib.pg_get_tables(ctx, T)
+    ints = lambda v: torch.tensor(v, dtype=torch.int32, device=DEV)
+    ids, sizes = torch.arange(M0, dtype=torch.int32, device=DEV), [N] * P
+    x, other = torch.empty(M0, d, device=DEV), torch.empty(M0, d, device=DEV)
+    lib.pg_init_latents(x, ids, seed)
+    partials = torch.empty(lib.pg_step_scratch_floats(M0, d), device=DEV)
+    rewards, logp = torch.zeros(M0, device=DEV), torch.zeros(M0, device=DEV)
+    hist, total = torch.full((T, M0), float("nan"), device=DEV), torch.zeros(M0, device=DEV)
+    status, scratch = torch.zeros(4, dtype=torch.int32, device=DEV), torch.zeros(lib.pg_ovf_scratch_ints(P), dtype=torch.int32, device=DEV)
+    offsets, masks = ints([N * i for i in range(P + 1)]), torch.zeros(P, dtype=torch.int64, device=DEV)
+    for s in range(T):
+        sel, M = None, sum(sizes)
+        if s < 2:
+            lib.pg_preview_reward(x, buf.u, buf.probe_w, rewards, M, d, tab["P"][s], tab["Q"][s], 0.25, partials)
+            sizes = [dict(cfg["schedule"][i]).get(s, n) for i, n in enumerate(sizes)]
+            M = sum(sizes)
+            sel, new = torch.zeros(M, dtype=torch.int32, device=DEV), torch.zeros(P + 1, dtype=torch.int32, device=DEV)
+            lib.pg_ovf_select(rewards, offsets, ints(sizes), P, masks, sel, new, status, scratch)
+            ids, offsets = ids[sel.long()].contiguous(), new
+        lib.pg_sde_step_logprob(x, buf.u, other, logp, hist[s], total, sel, ids, M, d, tab["A"][s], tab["B"][s], tab["C"][s], seed, s, partials)
+        x, other = other, x
+    adv = torch.zeros(M0, device=DEV)
+    lib.pg_preview_reward(x, None, buf.probe_w, rewards, M, d, 1.0, 0.0, 0.25, partials)
+    lib.pg_group_advantages(rewards, offsets, P, 1e-6, adv)
+    torch.cuda.synchronize()
+    st = lib.pg_state(ctx, P)
+    assert st["M"] == M and st["offsets"] == offsets.tolist()
+    groups = torch.cat([torch.full((n,), i, dtype=torch.int32) for i, n in enumerate(sizes)])
+    for name, got, want in (("x", buf.x[st["cur_x"]][:M], x[:M]), ("ids", buf.orig_id[st["cur_id"]][:M], ids), ("masks", buf.masks, masks),
+                            ("offsets", buf.group_offsets, offsets), ("groups", buf.group_of[:M], groups.to(DEV)),
+                            ("rewards", buf.rewards[:M], rewards[:M]), ("adv", buf.adv[:M], adv[:M]), ("sum", buf.logp_sum, total),
+                            ("hist", buf.logp_hist, hist)):
+        if name == "adv":                                # a group of one has no spread: 0 / (0 + eps)
+            assert torch.isfinite(got).all()
+        assert torch.equal(got.contiguous().view(torch.int32), want.contiguous().view(torch.int32)), name
+    lib.pg_destroy(ctx)
+
+
 # few tokens: the number of trajectories up to which one workgroup each evaluates them, and one group more
 @pytest.mark.parametrize("kind,D,P,N,H,W,Lc", [
     ("adaln", 128, 15, 60, 2, 2, 0), ("adaln", 128, 16, 60, 2, 2, 0), ("joint", 64, 40, 43, 2, 6, 1), ("joint", 64, 41, 43, 2, 6, 1),
