@@ -27,6 +27,30 @@ __device__ __forceinline__ float block_sum_256(float v) {
   return t;
 }
 
+// A workgroup per chunk of the update has a lane for every 16 bytes: bound by HBM, which a sweep of many waves with one access of each
+// array serves best (1024 x 262144 update, 3.2 GB: 539 us with four accesses of each array in a lane of 256, 500 us so, 6.5 TB/s;
+// two inputs and one output without arithmetic take 505 and 497, in waves of their own 471, but their sums would be 16 to a chunk).
+// The bf16 storage keeps four waves: its Philox blocks bound it as much as memory (267 us; a lane per access 269, two chunks to a
+// workgroup 279).
+constexpr int CHUNK_THREADS = STREAM_CHUNK / 4;
+// Sum over the lanes of such a workgroup, in the order of four accesses by each of 256 lanes (block_sum_256); valid in lane 0 of wave
+// 0, the other waves are done.
+__device__ __forceinline__ float chunk_sum(float v) {
+  __shared__ float part[CHUNK_THREADS];
+  part[threadIdx.x] = v;
+  __syncthreads();
+  if (threadIdx.x >= WAVE) return 0.f;
+  float w[STREAM_THREADS / WAVE];
+#pragma unroll
+  for (int i = 0; i < STREAM_THREADS / WAVE; ++i) {
+    float s = 0.f;
+#pragma unroll
+    for (int it = 0; it < STREAM_ITERS; ++it) s += part[it * STREAM_THREADS + i * WAVE + threadIdx.x];
+    w[i] = wave_allsum(s);
+  }
+  return (w[0] + w[1]) + (w[2] + w[3]);
+}
+
 __device__ __forceinline__ void init_chunk(float* __restrict__ x, int r, int c, uint32_t id, int d4, uint32_t k0, uint32_t k1) {
   f32x4* xr = reinterpret_cast<f32x4*>(x) + (size_t)r * d4;
 #pragma unroll
@@ -92,24 +116,25 @@ static void with_groups(int chunks, F launch) {
 // per trajectory.
 constexpr int ARRIVED_SHIFT = 52;                  // 12 bits of count above 24 of whole and 28 of fractional sum
 template <int GROUPS>
-__global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_step_kernel(
+__global__ __launch_bounds__(GROUPS ? GROUPS * STREAM_THREADS : CHUNK_THREADS) void sde_step_kernel(
     const float* __restrict__ x, const float* __restrict__ u, float* __restrict__ x_out,
     const int32_t* __restrict__ src, const int32_t* __restrict__ orig_id, int d4, int chunks, float A,
     float B, float C, uint32_t k0, uint32_t k1, uint32_t step, float* __restrict__ partials,
     float* __restrict__ hist_next, const LogProb out, uint64_t* __restrict__ arrived) {
+  constexpr int ITERS = GROUPS ? STREAM_ITERS : 1, LANES = GROUPS ? STREAM_THREADS : CHUNK_THREADS;
   const int r = GROUPS ? blockIdx.x : blockIdx.x / chunks, c = GROUPS ? threadIdx.x / STREAM_THREADS : blockIdx.x - r * chunks;
-  const int lane256 = GROUPS > 1 ? threadIdx.x & (STREAM_THREADS - 1) : threadIdx.x;
+  const int at = GROUPS > 1 ? threadIdx.x & (STREAM_THREADS - 1) : threadIdx.x;
   const int q = src ? src[r] : r;
   const uint32_t id = (uint32_t)orig_id[r];
   f32x4* hn = hist_next ? reinterpret_cast<f32x4*>(hist_next) + (size_t)id * d4 : nullptr;
   const f32x4* xq = reinterpret_cast<const f32x4*>(x) + (size_t)q * d4;
   const f32x4* uq = reinterpret_cast<const f32x4*>(u) + (size_t)q * d4;
   f32x4* xo = reinterpret_cast<f32x4*>(x_out) + (size_t)r * d4;
-  f32x4 xv[STREAM_ITERS], uv[STREAM_ITERS];
-  int e4[STREAM_ITERS];
+  f32x4 xv[ITERS], uv[ITERS];
+  int e4[ITERS];
 #pragma unroll
-  for (int it = 0; it < STREAM_ITERS; ++it) {
-    e4[it] = c * (STREAM_CHUNK / 4) + it * STREAM_THREADS + lane256;
+  for (int it = 0; it < ITERS; ++it) {
+    e4[it] = c * (STREAM_CHUNK / 4) + it * LANES + at;
     if (e4[it] < d4) {
       xv[it] = __builtin_nontemporal_load(xq + e4[it]);
       uv[it] = __builtin_nontemporal_load(uq + e4[it]);
@@ -117,7 +142,7 @@ __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_st
   }
   float acc = 0.f;
 #pragma unroll
-  for (int it = 0; it < STREAM_ITERS; ++it) {
+  for (int it = 0; it < ITERS; ++it) {
     if (e4[it] < d4) {
       const f32x4 z = philox_normal4((uint32_t)e4[it], step, id, STREAM_STEP, k0, k1);
       f32x4 o;
@@ -133,7 +158,7 @@ __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * STREAM_THREADS) void sde_st
   if constexpr (GROUPS > 0) {
     row_sum<GROUPS>(chunks, acc, [&](double s) { finish_logprob(out, r, (int)id, s); });
   } else {
-    const float t = block_sum_256(acc);
+    const float t = chunk_sum(acc);
     if (threadIdx.x != 0) return;
     if (!arrived) {
       partials[blockIdx.x] = t;
@@ -439,7 +464,7 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
   const int rec = prof_open(PROF_SDE_STEP, 12.0 * (double)n_traj * (double)d, stream);
   with_groups(row ? chunks : 0, [&](auto groups) {
     constexpr int G = decltype(groups)::value;
-    sde_step_kernel<G><<<dim3((unsigned)(G ? n_traj : n_traj * chunks)), dim3((G ? G : 1) * STREAM_THREADS), 0, stream>>>(
+    sde_step_kernel<G><<<dim3((unsigned)(G ? n_traj : n_traj * chunks)), dim3(G ? G * STREAM_THREADS : CHUNK_THREADS), 0, stream>>>(
         x, u, x_out, src, orig_id, (int)(d / 4), chunks, (float)A, (float)B, (float)C, (uint32_t)seed, (uint32_t)(seed >> 32), step,
         partials, hist_next, out, arrived);
   });
