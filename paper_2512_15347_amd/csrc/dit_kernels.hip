@@ -17,6 +17,7 @@
 #include "ctx.hpp"
 #include "gemm.hpp"
 #include "operands.hpp"
+#include "row_chain.hpp"
 #include "small_net.hpp"
 
 namespace pg {
@@ -622,21 +623,53 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
     }
   }
 
+  // attention over the prompt's context tokens
+  auto cross_attention = [&](int b) -> pg_status {
+    AttnArgs a{};
+    a.q = qk; a.ldq = D;
+    a.k = n.at<uint16_t>(pl.ckv) + (size_t)b * P * f.Lc * D; a.ldk = D; a.k_bstride = (int64_t)f.Lc * D;
+    a.vt = n.at<uint16_t>(pl.ckvt) + (size_t)b * P * D * Lcpad; a.vt_bstride = (int64_t)D * Lcpad; a.Lkpad = Lcpad;
+    a.out = att; a.ldo = D; a.kv_map = group_of;
+    a.B = M; a.Lq = L; a.Lk = f.Lc; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1; a.v_swapped = 1;
+    return launch_attention(a, hd, s);
+  };
+  const bool chain = !dual && row_chain_takes(D, c->M0);   // what lies between two attentions in one launch
   for (int b = 0; b < (dual ? 0 : f.blocks); ++b) {
     const float* mb = mod + (size_t)b * 6 * D;     // shift1, scale1, gate1, shift2, scale2, gate2
     // attention sub-block
-    PG_TRY(layer_norm(mb, mb + D, mod_ld, R, L));
-    {
+    if (!chain || b == 0) {
+      PG_TRY(layer_norm(mb, mb + D, mod_ld, R, L));
       GemmArgs g{};
       g.A = act; g.lda = D; g.W = n.w(PG_W_QKV_W, b); g.ldw = n.ld(PG_W_QKV_W); g.bias = n.w(PG_W_QKV_B, b);
       g.M = R; g.N = 3 * D; g.K = D; g.outb = qk; g.ldob = 2 * D; g.vt = vt; g.v_start = 2 * D; g.Lpad = Lpad; g.L = L;
       g.out_scale = scale_log2; g.scale_cols = D;   // queries leave the projection already in the softmax's log2 units
       PG_TRY(launch_gemm(g, EPI_QKV, s));
+    }
+    {
       AttnArgs a{};
       a.q = qk; a.ldq = 2 * D; a.k = qk + D; a.ldk = 2 * D; a.k_bstride = (int64_t)L * 2 * D;
       a.vt = vt; a.vt_bstride = (int64_t)D * Lpad; a.Lkpad = Lpad; a.out = att; a.ldo = D;
       a.B = M; a.Lq = L; a.Lk = L; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1; a.v_swapped = 1;
       PG_TRY(launch_attention(a, hd, s));
+    }
+    if (chain) {
+      const bool last = b + 1 == f.blocks;
+      ChainArgs r{};
+      r.att = att; r.h = h; r.qk = qk; r.vt = vt; r.mod_ld = mod_ld; r.mod_of = mod_of; r.M = M; r.L = L; r.Lpad = Lpad; r.out_scale = scale_log2;
+      r.o_w = n.w(PG_W_O_W, b); r.o_b = n.w(PG_W_O_B, b); r.gate1 = mb + 2 * D;
+      if (f.net_kind == PG_NET_CROSS) {
+        r.next_w = n.w(PG_W_CQ_W, b); r.next_b = n.w(PG_W_CQ_B, b);
+        PG_TRY(launch_row_chain(r, D, CHAIN_QUERIES, s));
+        PG_TRY(cross_attention(b));
+        r.o_w = n.w(PG_W_CO_W, b); r.o_b = n.w(PG_W_CO_B, b); r.gate1 = nullptr;
+      }
+      r.norm1 = mb + 3 * D; r.gate2 = mb + 5 * D; r.norm2 = mb + 6 * D;
+      r.fc1_w = n.w(PG_W_FC1_W, b); r.fc1_b = n.w(PG_W_FC1_B, b); r.fc2_w = n.w(PG_W_FC2_W, b); r.fc2_b = n.w(PG_W_FC2_B, b);
+      if (!last) { r.next_w = n.w(PG_W_QKV_W, b + 1); r.next_b = n.w(PG_W_QKV_B, b + 1); }
+      PG_TRY(launch_row_chain(r, D, last ? CHAIN_LAST : CHAIN_BLOCK, s));
+      continue;
+    }
+    {
       GemmArgs o{};
       o.A = att; o.lda = D; o.W = n.w(PG_W_O_W, b); o.ldw = n.ld(PG_W_O_W); o.bias = n.w(PG_W_O_B, b);
       o.M = R; o.N = D; o.K = D; o.outf = h; o.ldo = D; o.L = L; o.gate = mb + 2 * D; o.gate_ld = mod_ld;
@@ -651,13 +684,7 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
       g.M = R; g.N = D; g.K = D; g.outb = qk; g.ldob = D;
       g.out_scale = scale_log2; g.scale_cols = D;
       PG_TRY(launch_gemm(g, EPI_BF16, s));
-      AttnArgs a{};
-      a.q = qk; a.ldq = D;
-      a.k = n.at<uint16_t>(pl.ckv) + (size_t)b * P * f.Lc * D; a.ldk = D; a.k_bstride = (int64_t)f.Lc * D;
-      a.vt = n.at<uint16_t>(pl.ckvt) + (size_t)b * P * D * Lcpad; a.vt_bstride = (int64_t)D * Lcpad; a.Lkpad = Lcpad;
-      a.out = att; a.ldo = D; a.kv_map = group_of;
-      a.B = M; a.Lq = L; a.Lk = f.Lc; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1; a.v_swapped = 1;
-      PG_TRY(launch_attention(a, hd, s));
+      PG_TRY(cross_attention(b));
       GemmArgs o{};
       o.A = att; o.lda = D; o.W = n.w(PG_W_CO_W, b); o.ldw = n.ld(PG_W_CO_W); o.bias = n.w(PG_W_CO_B, b);
       o.M = R; o.N = D; o.K = D; o.outf = h; o.ldo = D; o.L = L; o.gate = nullptr; o.group_of = group_of;

@@ -1,0 +1,27 @@
+// The layers between two attentions of a block, which work on a row at a time, in one launch.
+#pragma once
+#include "common.hpp"
+
+namespace pg {
+
+// What follows an attention: the output projection with its residual sum, and then
+enum ChainKind {
+  CHAIN_QUERIES = 0,   // LayerNorm and the queries of the cross-attention
+  CHAIN_BLOCK = 1,     // LayerNorm, MLP with its residual sum, LayerNorm and queries | keys | values of the next block
+  CHAIN_LAST = 2       // LayerNorm, MLP with its residual sum
+};
+struct ChainArgs {
+  const uint16_t* att; float* h;                   // attention's output and the residual stream, [M L, D]
+  uint16_t* qk; uint16_t* vt;                      // CHAIN_QUERIES: [M L, D]; CHAIN_BLOCK: [M L, 2 D] and transposed values (EPI_QKV)
+  const uint16_t* o_w; const uint16_t* o_b; const uint16_t* fc1_w; const uint16_t* fc1_b; const uint16_t* fc2_w; const uint16_t* fc2_b;
+  const uint16_t* next_w; const uint16_t* next_b;  // rows of D (fc2: 4 D) columns, no padding
+  // of modulation row 0: gate of the projection (NULL: 1), shift and scale of the LayerNorm behind it (NULL: 0, 0), gate of the MLP,
+  // shift and scale of the next block
+  const float* gate1; const float* norm1; const float* gate2; const float* norm2; int64_t mod_ld; const int32_t* mod_of;
+  int M, L, Lpad;
+  float out_scale;                                 // of the queries
+};
+bool row_chain_takes(int D, int64_t M);            // whether networks of this width, for at most M trajectories, run that way
+pg_status launch_row_chain(const ChainArgs& a, int D, ChainKind kind, hipStream_t s);
+
+}  // namespace pg

@@ -399,6 +399,42 @@ def test_network_output_of_narrow_networks(lib, kind, D, heads, C, H, W, Lc):
     _check_sharp_network(lib, cfg, kind, 7 if L > 1 else 1, (0, 2, 3, 5))
 
 
+# the layers between two attentions in one launch (widths 128, 192, 256), with 16 rows to a workgroup (few trajectories) and 32 (many):
+# one token, whole tiles of either height and one token more, both head widths, one to three blocks; a trajectory's output is the
+# same bits either way
+@pytest.mark.parametrize("kind,D,heads,H,W,Lc,blocks", [
+    ("adaln", 192, 3, 2, 2, 0, 2), ("adaln", 256, 4, 8, 8, 0, 3), ("adaln", 192, 6, 8, 16, 0, 1), ("joint", 256, 8, 8, 16, 1, 2),
+    ("joint", 128, 2, 14, 14, 48, 2), ("joint", 192, 3, 10, 6, 2, 2), ("cross", 128, 4, 2, 2, 1, 3), ("cross", 192, 6, 6, 22, 13, 2),
+    ("cross", 256, 4, 10, 14, 77, 1), ("cross", 128, 2, 16, 16, 5, 2)])
+def test_network_output_of_rows_between_attentions(lib, kind, D, heads, H, W, Lc, blocks):
+    L = H * W // 4 + (Lc if kind == "joint" else 0)
+    say(f"rows between attentions, {kind} width {D}, {L} tokens, {blocks} blocks")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind=kind, P=2, N=3, H=H, W=W, D=D, heads=heads, Lc=Lc, Dc=128 if Lc else 0, blocks=blocks, T=1, schedule=[[], []],
+               Li=H * W // 4, d=4 * H * W)
+    # scores grow as gain^2 D, and with them what rounding does to them: as sharp as 7 makes width 128 (7 at width 256, two blocks,
+    # is off by 2.1e-2 with a launch per layer, too)
+    gain = 7 * (128 / D) ** 0.5 if L > 1 else 1
+    _check_sharp_network(lib, cfg, kind, gain, (0, 5))
+    N = min(64, 256 // (2 * ((L + 15) // 16)) + 1)
+    P = 256 // (N * ((L + 15) // 16)) + 1
+    many = dict(cfg, P=P, N=N, schedule=[[]] * P)
+    w = workloads.make_weights(cfg)
+    _sharpen_attention(w, kind, gain)
+    inp = workloads.make_inputs(many, w)
+    outs = []
+    for c in (dict(cfg, P=1), many):
+        part = {k: v[:c["P"]] if k in ("y", "ctx") and v is not None else v for k, v in inp.items()}
+        ctx, buf = _gpu_ctx(lib, c, w, part)
+        buf.workspace.fill_(255)
+        lib.pg_bind(ctx, buf)
+        lib.pg_init_group(ctx, 77)
+        lib.pg_net_forward(ctx, 0)
+        outs.append(buf.u[:3].clone().view(torch.int32))
+        lib.pg_destroy(ctx)
+    assert torch.equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("kind,D,P,N,H,W,Lc", [("adaln", 128, 1, 8, 16, 16, 0), ("joint", 64, 2, 3, 10, 10, 39), ("joint", 192, 1, 3, 10, 10, 6),
                                                 ("adaln", 128, 20, 60, 2, 2, 0)])
 def test_profile_counts_the_work_of_a_network(lib, kind, D, P, N, H, W, Lc):
