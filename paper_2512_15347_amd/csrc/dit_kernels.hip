@@ -569,6 +569,8 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
                      Ri, mods[1] + slot * D, mods[1] + (slot + 1) * D, f.Lc});
   };
 
+  const bool chain = row_chain_takes(D, c->M0);     // what lies between two attentions in one launch
+
   // ---- dual-stream blocks: two planes (image rows, context rows), joint q | k and V^T ----
   if (dual) {
     float* hs[2] = {h, h + (size_t)Ri * D};
@@ -584,8 +586,8 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
     for (int b = 0; b < f.blocks; ++b) {
       const float* mbs[2] = {mod + (size_t)b * 6 * D, cmod + (size_t)b * 6 * D};
       GemmArgs g[2];
-      PG_TRY(layer_norm_pair(mbs, 0));
-      for (int st = 0; st < 2; ++st) {
+      if (!chain || b == 0) PG_TRY(layer_norm_pair(mbs, 0));
+      for (int st = 0; st < 2 && (!chain || b == 0); ++st) {
         g[st] = GemmArgs{};
         g[st].A = acts[st]; g[st].lda = D; g[st].W = n.w(W_QKV[st], b); g[st].ldw = n.ld(W_QKV[st]); g[st].bias = n.w(B_QKV[st], b);
         g[st].M = rows[st]; g[st].N = 3 * D; g[st].K = D; g[st].outb = qk; g[st].ldob = 2 * D; g[st].vt = vt; g[st].v_start = 2 * D;
@@ -594,13 +596,29 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
         g[st].norm_hd = hd; g[st].qn_g = n.w(W_QN[st], b); g[st].kn_g = n.w(W_KN[st], b);
         g[st].out_scale = scale_log2; g[st].scale_cols = D;
       }
-      PG_TRY(launch_gemm_pair(g[0], g[1], EPI_QKV, s));
+      if (!chain || b == 0) PG_TRY(launch_gemm_pair(g[0], g[1], EPI_QKV, s));
       AttnArgs a{};
       a.q = qk; a.ldq = 2 * D; a.k = qk + D; a.ldk = 2 * D; a.k_bstride = (int64_t)L * 2 * D;
       a.vt = vt; a.vt_bstride = (int64_t)D * Lpad; a.Lkpad = Lpad; a.out = atts[0]; a.ldo = D;
       a.split = Li; a.out2 = atts[1];
       a.B = M; a.Lq = L; a.Lk = L; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1; a.v_swapped = 1;
       PG_TRY(launch_attention(a, hd, s));
+      if (chain) {                                   // the context's rows are not used any more after the last block
+        const bool last = b + 1 == f.blocks;
+        ChainArgs r{};
+        r.qk = qk; r.vt = vt; r.mod_ld = mod_ld; r.mod_of = mod_of; r.M = M; r.Lpad = Lpad; r.out_scale = scale_log2; r.norm_hd = last ? 0 : hd;
+        for (int st = 0; st < (last ? 1 : 2); ++st) {
+          ChainStream& t = r.s[st];
+          t.att = atts[st]; t.h = hs[st]; t.L = Ls[st];
+          t.o_w = n.w(W_O[st], b); t.o_b = n.w(B_O[st], b); t.fc1_w = n.w(W_FC1[st], b); t.fc1_b = n.w(B_FC1[st], b);
+          t.fc2_w = n.w(W_FC2[st], b); t.fc2_b = n.w(B_FC2[st], b);
+          t.gate1 = mbs[st] + 2 * D; t.norm1 = mbs[st] + 3 * D; t.gate2 = mbs[st] + 5 * D; t.norm2 = mbs[st] + 6 * D;
+          if (last) break;
+          t.next_w = n.w(W_QKV[st], b + 1); t.next_b = n.w(B_QKV[st], b + 1); t.qn_g = n.w(W_QN[st], b + 1); t.kn_g = n.w(W_KN[st], b + 1);
+        }
+        PG_TRY(launch_row_chain(r, D, last ? CHAIN_LAST : CHAIN_BLOCK, s));
+        continue;
+      }
       // the layers that add into the residual stream: `gate` is the slot of their gates among the modulation vectors
       auto residual = [&](uint16_t* const* in, int K, const int* W, const int* B, int gate) -> pg_status {
         for (int st = 0; st < 2; ++st) {
@@ -633,7 +651,6 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
     a.B = M; a.Lq = L; a.Lk = f.Lc; a.heads = f.heads; a.scale_log2 = scale_log2; a.q_prescaled = 1; a.v_swapped = 1;
     return launch_attention(a, hd, s);
   };
-  const bool chain = !dual && row_chain_takes(D, c->M0);   // what lies between two attentions in one launch
   for (int b = 0; b < (dual ? 0 : f.blocks); ++b) {
     const float* mb = mod + (size_t)b * 6 * D;     // shift1, scale1, gate1, shift2, scale2, gate2
     // attention sub-block
@@ -655,17 +672,18 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
     if (chain) {
       const bool last = b + 1 == f.blocks;
       ChainArgs r{};
-      r.att = att; r.h = h; r.qk = qk; r.vt = vt; r.mod_ld = mod_ld; r.mod_of = mod_of; r.M = M; r.L = L; r.Lpad = Lpad; r.out_scale = scale_log2;
-      r.o_w = n.w(PG_W_O_W, b); r.o_b = n.w(PG_W_O_B, b); r.gate1 = mb + 2 * D;
+      ChainStream& t = r.s[0];
+      r.qk = qk; r.vt = vt; r.mod_ld = mod_ld; r.mod_of = mod_of; r.M = M; r.Lpad = Lpad; r.out_scale = scale_log2;
+      t.att = att; t.h = h; t.L = L; t.o_w = n.w(PG_W_O_W, b); t.o_b = n.w(PG_W_O_B, b); t.gate1 = mb + 2 * D;
       if (f.net_kind == PG_NET_CROSS) {
-        r.next_w = n.w(PG_W_CQ_W, b); r.next_b = n.w(PG_W_CQ_B, b);
+        t.next_w = n.w(PG_W_CQ_W, b); t.next_b = n.w(PG_W_CQ_B, b);
         PG_TRY(launch_row_chain(r, D, CHAIN_QUERIES, s));
         PG_TRY(cross_attention(b));
-        r.o_w = n.w(PG_W_CO_W, b); r.o_b = n.w(PG_W_CO_B, b); r.gate1 = nullptr;
+        t.o_w = n.w(PG_W_CO_W, b); t.o_b = n.w(PG_W_CO_B, b); t.gate1 = nullptr;
       }
-      r.norm1 = mb + 3 * D; r.gate2 = mb + 5 * D; r.norm2 = mb + 6 * D;
-      r.fc1_w = n.w(PG_W_FC1_W, b); r.fc1_b = n.w(PG_W_FC1_B, b); r.fc2_w = n.w(PG_W_FC2_W, b); r.fc2_b = n.w(PG_W_FC2_B, b);
-      if (!last) { r.next_w = n.w(PG_W_QKV_W, b + 1); r.next_b = n.w(PG_W_QKV_B, b + 1); }
+      t.norm1 = mb + 3 * D; t.gate2 = mb + 5 * D; t.norm2 = mb + 6 * D;
+      t.fc1_w = n.w(PG_W_FC1_W, b); t.fc1_b = n.w(PG_W_FC1_B, b); t.fc2_w = n.w(PG_W_FC2_W, b); t.fc2_b = n.w(PG_W_FC2_B, b);
+      if (!last) { t.next_w = n.w(PG_W_QKV_W, b + 1); t.next_b = n.w(PG_W_QKV_B, b + 1); }
       PG_TRY(launch_row_chain(r, D, last ? CHAIN_LAST : CHAIN_BLOCK, s));
       continue;
     }

@@ -1,6 +1,6 @@
 // The layers between two attentions of a block (output projection, residual sum, LayerNorm, MLP, LayerNorm, queries / keys / values
 // of the next block) for networks of width 128, 192 and 256: a workgroup takes 16 or 32 rows of one trajectory through all of them in
-// one launch.
+// one launch.  In the dual-stream network a workgroup's rows are image or context tokens, with the weights of their stream.
 //
 // Layer by layer each of them is a launch of 4 to 8 us with a microsecond of work in it (six of them and their gaps: 40 us).  They need
 // nothing but their own rows, so the residual stream stays in registers, operands and hidden values in LDS, and what a workgroup
@@ -76,7 +76,7 @@ struct Weights {
   }
   // The launch's weights into the L2 of this XCD: its workgroups (every eighth of the grid) touch a share of the 128-byte lines each.
   // They all run through the weights side by side, so without this nearly every piece of theirs was waited for from beyond the L2.
-  template <int KIND> __device__ __forceinline__ void warm(const ChainArgs& a, unsigned char* touched, int wave) const {
+  template <int KIND> __device__ __forceinline__ void warm(const ChainStream& a, unsigned char* touched, int wave) const {
     constexpr int LOADS = D * D * 2 / (128 * 64);    // of 64 lines, for the weights of a product
     const int id = blockIdx.y * gridDim.x + blockIdx.x, wgs = (gridDim.x * gridDim.y + 7) / 8;
     const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)touched);
@@ -173,8 +173,9 @@ __device__ __forceinline__ void normalise(const float* h, uint16_t* act, const f
   }
 }
 
-template <int D, int KIND, int RT>
-__global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(const ChainArgs a) {
+// DUAL: two streams with weights of their own, and normalised queries and keys
+template <int D, int KIND, int RT, bool DUAL>
+__global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(const ChainArgs args) {
   using C = Chain<D, RT>;
   constexpr bool MLP = KIND != CHAIN_QUERIES, NEXT = KIND != CHAIN_LAST;
   constexpr int ROWS = 16 * RT, NB = KIND == CHAIN_QUERIES ? 2 : KIND == CHAIN_BLOCK ? 9 : 6;     // biases in units of D
@@ -184,12 +185,18 @@ __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(cons
   __shared__ __align__(16) float md[4 * D];          // shift, scale of the LayerNorm, shift, scale of the next block
   __shared__ __align__(16) uint16_t bs[NB * D];      // projection, [fc1, fc2,] next
   __shared__ __align__(16) unsigned char touched[256];
+  __shared__ float squares[DUAL ? C::WAVES * ROWS : 1];     // of a wave's columns
   float* hl = reinterpret_cast<float*>(both);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lr = lane & 15, lk = lane >> 4, m = blockIdx.y, t0 = blockIdx.x * ROWS;
+  const int tiles0 = DUAL ? (args.s[0].L + ROWS - 1) / ROWS : 0;
+  const bool second = DUAL && (int)blockIdx.x >= tiles0;
+  const ChainStream a = second ? args.s[1] : args.s[0];
+  const int lr = lane & 15, lk = lane >> 4, m = blockIdx.y, t0 = (blockIdx.x - (second ? tiles0 : 0)) * ROWS;
   const int n0 = wave * 32 + 4 * lk;                 // the lane's columns: n0 .. n0 + 3 and 16 further
   const int64_t row0 = (int64_t)m * a.L;
-  const int64_t mod_row = (int64_t)a.mod_of[m] * a.mod_ld;
+  const int64_t mod_row = (int64_t)args.mod_of[m] * args.mod_ld;
+  const int L_all = DUAL ? args.s[0].L + args.s[1].L : a.L, tok0 = second ? args.s[0].L : 0;       // the stream's tokens among all
+  const int64_t all0 = (int64_t)m * L_all + tok0;
 
   // ---- asked for at once, in the order of use; rows past the end repeat the last one ----
   constexpr int AV = ROWS * D / 8 / C::THREADS;      // 16-byte chunks of attention's output per thread: RT
@@ -279,7 +286,37 @@ __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(cons
     for (int t = 0; t < RT; ++t)
       if (t0 + 16 * t + lr < a.L)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) put4(dst + (row0 + t0 + 16 * t + lr) * ld + n0 + 16 * c, acc[c][t] * scale);
+        for (int c = 0; c < 2; ++c) put4(dst + (all0 + t0 + 16 * t + lr) * ld + n0 + 16 * c, acc[c][t] * scale);
+  };
+  // RMS norm of the rows' heads, which are the columns of this wave or of this one and its neighbour
+  auto normalise_heads = [&](const uint16_t* g) {
+    float ss[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      ss[t] = 0.f;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const f32x4v v = acc[c][t];
+        ss[t] += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+      }
+      ss[t] = across_rows(ss[t], [](float x, float y) { return x + y; });
+    }
+    if (args.norm_hd == 64) {
+      __syncthreads();                               // the sums before these have been read
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+        if (lk == 0) squares[wave * ROWS + 16 * t + lr] = ss[t];
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < RT; ++t) ss[t] = squares[(wave & ~1) * ROWS + 16 * t + lr] + squares[(wave | 1) * ROWS + 16 * t + lr];
+    }
+    const float inv_hd = args.norm_hd == 64 ? 1.f / 64.f : 1.f / 32.f;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const f32x4v scale = four_of(g + ((n0 + 16 * c) & (args.norm_hd - 1)));
+#pragma unroll
+      for (int t = 0; t < RT; ++t) acc[c][t] = acc[c][t] * (rsqrtf(ss[t] * inv_hd + 1e-6f) * scale);
+    }
   };
 
   start(acc, bs);
@@ -294,7 +331,7 @@ __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(cons
     store_stream();
     start(acc, bs + D);
     weights.template product<true>(w_next, w_next, false, act, x, acc);
-    store_rows(a.qk, D, a.out_scale);
+    store_rows(args.qk, D, args.out_scale);
   } else {
     f32x4v sum[2][RT];
     start(sum, bs + 5 * D);
@@ -330,7 +367,8 @@ __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(cons
       for (int i = 0; i < 2; ++i) {                  // queries, keys
         start(acc, bs + (6 + i) * D);
         weights.template product<false>(part(i), part(i + 1), true, act, x, acc);
-        store_rows(a.qk + i * D, 2 * D, i ? 1.f : a.out_scale);
+        if constexpr (DUAL) normalise_heads(i ? a.kn_g : a.qn_g);
+        store_rows(args.qk + i * D, 2 * D, i ? 1.f : args.out_scale);
       }
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -339,34 +377,36 @@ __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(cons
         for (int t = 0; t < RT; ++t) acc[c][t] = f32x4v{b, b, b, b};
       }
       weights.template product<false, true>(part(2), part(2), false, act, x, acc);
-      // tokens past the end, too: a value row has room for whole tiles, and attention takes nothing from there
+      // tokens past the end, too, where nobody else's follow: a value row has room for whole tiles, and attention takes nothing from there
 #pragma unroll
       for (int c = 0; c < 2; ++c)
 #pragma unroll
-        for (int t = 0; t < RT; ++t)
-          put4(a.vt + ((int64_t)m * D + wave * 32 + 16 * c + lr) * a.Lpad + value_slot(t0 + 16 * t + 4 * lk), acc[c][t]);
+        for (int t = 0; t < RT; ++t) {
+          uint16_t* row = args.vt + ((int64_t)m * D + wave * 32 + 16 * c + lr) * args.Lpad;
+          const int tok = t0 + 16 * t + 4 * lk;
+          if (!DUAL || ((tok0 & 3) == 0 && tok + 4 <= a.L)) put4(row + value_slot(tok0 + tok), acc[c][t]);
+          else
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (tok + e < a.L) row[value_slot(tok0 + tok + e)] = (uint16_t)pack_bf16x2(acc[c][t][e], 0.f);
+        }
     }
   }
 }
 
-template <int D, int KIND, int RT>
-pg_status launch_kind(const ChainArgs& a, hipStream_t s) {
-  row_chain_kernel<D, KIND, RT><<<dim3((unsigned)((a.L + 16 * RT - 1) / (16 * RT)), (unsigned)a.M), dim3(Chain<D, RT>::THREADS), 0, s>>>(a);
+template <int D, int KIND, bool DUAL>
+pg_status launch_rows(const ChainArgs& a, hipStream_t s) {
+  auto tiles = [&](int rows) { return (unsigned)((a.s[0].L + rows - 1) / rows + (DUAL ? (a.s[1].L + rows - 1) / rows : 0)); };
+  if ((int64_t)a.M * tiles(16) <= 256) row_chain_kernel<D, KIND, 1, DUAL><<<dim3(tiles(16), (unsigned)a.M), dim3(2 * D), 0, s>>>(a);
+  else row_chain_kernel<D, KIND, 2, DUAL><<<dim3(tiles(32), (unsigned)a.M), dim3(2 * D), 0, s>>>(a);
   PG_LAUNCH_CHECK("row_chain_kernel");
   return PG_OK;
 }
-template <int D, int KIND>
-pg_status launch_rows(const ChainArgs& a, hipStream_t s) {
-  return a.M * (int64_t)((a.L + 15) / 16) <= 256 ? launch_kind<D, KIND, 1>(a, s) : launch_kind<D, KIND, 2>(a, s);
-}
 template <int D>
 pg_status launch_width(const ChainArgs& a, ChainKind kind, hipStream_t s) {
-  switch (kind) {
-    case CHAIN_QUERIES: return launch_rows<D, CHAIN_QUERIES>(a, s);
-    case CHAIN_BLOCK: return launch_rows<D, CHAIN_BLOCK>(a, s);
-    case CHAIN_LAST: return launch_rows<D, CHAIN_LAST>(a, s);
-  }
-  return fail(PG_EINVAL, "row chain: kind %d", (int)kind);
+  if (kind == CHAIN_QUERIES) return launch_rows<D, CHAIN_QUERIES, false>(a, s);
+  if (kind == CHAIN_LAST) return launch_rows<D, CHAIN_LAST, false>(a, s);
+  return a.s[1].L > 0 ? launch_rows<D, CHAIN_BLOCK, true>(a, s) : launch_rows<D, CHAIN_BLOCK, false>(a, s);
 }
 }  // namespace
 
@@ -375,17 +415,25 @@ pg_status launch_width(const ChainArgs& a, ChainKind kind, hipStream_t s) {
 //   width 192:  4 of 64 598 / 469, 64 of 256 1250 / 862, x 256 of 256 2040 / 1646, x 768 of 256 5598 / 4735
 //   width 256: 16 of 100 727 / 601, 64 of 256 1386 / 1036, x 256 of 256 2529 / 2154, x 576 of 256 5159 / 4742
 //   cross-attention: width 192, 9 of 88 876 / 630, width 256, 36 of 290 1687 / 1359, 4 of 88 960 / 875
+//   dual-stream: width 128, 8 of 200 682 / 436, width 192, 64 of 256 1298 / 896, width 256, 4 of 88 695 / 678, 64 of 256 1420 / 1078
 // A width of 320 won in a band of sizes alone (64 of 256 1683 / 1448, 4 of 88 722 / 880, x 384 of 256 4903 / 5480), and so did 384.
 bool row_chain_takes(int D, int64_t M) { return (D == 128 || D == 192 || D == 256) && M <= 65535; }     // the limit is the grid's
 
 pg_status launch_row_chain(const ChainArgs& a, int D, ChainKind kind, hipStream_t s) {
-  if (!row_chain_takes(D, a.M) || !a.att || !a.h || !a.o_w || !a.o_b || a.M < 1 || a.L < 1 || !a.mod_of ||
-      (kind != CHAIN_QUERIES && (!a.fc1_w || !a.fc1_b || !a.fc2_w || !a.fc2_b || !a.gate2)) ||
-      (kind != CHAIN_LAST && (!a.next_w || !a.next_b || !a.qk)) ||
-      (kind == CHAIN_BLOCK && (!a.vt || !a.norm2 || a.Lpad % 64 || a.Lpad < a.L)))
-    return fail(PG_ESHAPE, "row chain: width %d, %d x %d rows", D, a.M, a.L);
+  const bool dual = a.s[1].L > 0;
+  const int L = a.s[0].L + a.s[1].L;
+  bool complete = row_chain_takes(D, a.M) && a.M >= 1 && a.mod_of && (kind == CHAIN_LAST || a.qk) &&
+                  (kind != CHAIN_BLOCK || (a.vt && a.Lpad % 64 == 0 && a.Lpad >= L)) && (dual ? kind == CHAIN_BLOCK : a.norm_hd == 0) &&
+                  (!dual || a.norm_hd == 32 || a.norm_hd == 64);
+  for (int i = 0; i < (dual ? 2 : 1); ++i) {
+    const ChainStream& c = a.s[i];
+    complete = complete && c.L >= 1 && c.att && c.h && c.o_w && c.o_b && (kind == CHAIN_LAST || (c.next_w && c.next_b)) &&
+               (kind == CHAIN_QUERIES || (c.fc1_w && c.fc1_b && c.fc2_w && c.fc2_b && c.gate2)) && (kind != CHAIN_BLOCK || c.norm2) &&
+               (!dual || (c.qn_g && c.kn_g));
+  }
+  if (!complete) return fail(PG_ESHAPE, "row chain: width %d, %d x %d rows", D, a.M, L);
   const double n = kind == CHAIN_QUERIES ? 2 : kind == CHAIN_BLOCK ? 12 : 9;
-  const int rec = prof_open(PROF_GEMM, n * 2.0 * a.M * a.L * D * D, s);
+  const int rec = prof_open(PROF_GEMM, n * 2.0 * a.M * L * D * D, s);
   const pg_status st = D == 128 ? launch_width<128>(a, kind, s) : D == 192 ? launch_width<192>(a, kind, s) : launch_width<256>(a, kind, s);
   prof_close(rec, s);
   return st;

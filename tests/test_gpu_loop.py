@@ -400,14 +400,15 @@ def test_network_output_of_narrow_networks(lib, kind, D, heads, C, H, W, Lc):
 
 
 # the layers between two attentions in one launch (widths 128, 192, 256), with 16 rows to a workgroup (few trajectories) and 32 (many):
-# one token, whole tiles of either height and one token more, both head widths, one to three blocks; a trajectory's output is the
-# same bits either way
+# one token, whole tiles of either height and one token more, both head widths, one to three blocks, and of the dual-stream network
+# context tokens that follow a whole number of fours (32, 16; 34) and that do not (35, 21); a trajectory's output is the same bits either way
 @pytest.mark.parametrize("kind,D,heads,H,W,Lc,blocks", [
     ("adaln", 192, 3, 2, 2, 0, 2), ("adaln", 256, 4, 8, 8, 0, 3), ("adaln", 192, 6, 8, 16, 0, 1), ("joint", 256, 8, 8, 16, 1, 2),
     ("joint", 128, 2, 14, 14, 48, 2), ("joint", 192, 3, 10, 6, 2, 2), ("cross", 128, 4, 2, 2, 1, 3), ("cross", 192, 6, 6, 22, 13, 2),
-    ("cross", 256, 4, 10, 14, 77, 1), ("cross", 128, 2, 16, 16, 5, 2)])
+    ("cross", 256, 4, 10, 14, 77, 1), ("cross", 128, 2, 16, 16, 5, 2), ("mmdit", 192, 6, 8, 16, 16, 2), ("mmdit", 128, 2, 10, 14, 18, 3),
+    ("mmdit", 256, 4, 8, 8, 1, 2), ("mmdit", 256, 8, 14, 6, 33, 2), ("mmdit", 192, 3, 4, 34, 31, 2), ("mmdit", 128, 4, 2, 2, 2, 1)])
 def test_network_output_of_rows_between_attentions(lib, kind, D, heads, H, W, Lc, blocks):
-    L = H * W // 4 + (Lc if kind == "joint" else 0)
+    L = H * W // 4 + (Lc if kind in ("joint", "mmdit") else 0)
     say(f"rows between attentions, {kind} width {D}, {L} tokens, {blocks} blocks")
     cfg = workloads.get_config("cfg3_small")
     cfg.update(kind=kind, P=2, N=3, H=H, W=W, D=D, heads=heads, Lc=Lc, Dc=128 if Lc else 0, blocks=blocks, T=1, schedule=[[], []],
