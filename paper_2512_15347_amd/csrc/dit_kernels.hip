@@ -593,8 +593,8 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
     for (int b = 0; b < f.blocks; ++b) {
       const float* mbs[2] = {mod + (size_t)b * 6 * D, cmod + (size_t)b * 6 * D};
       GemmArgs g[2];
-      if (!chain || b == 0) PG_TRY(layer_norm_pair(mbs, 0));
-      for (int st = 0; st < 2 && (!chain || b == 0); ++st) {
+      if (!chain) PG_TRY(layer_norm_pair(mbs, 0));
+      for (int st = 0; st < 2 && !chain; ++st) {
         g[st] = GemmArgs{};
         g[st].A = acts[st]; g[st].lda = D; g[st].W = n.w(W_QKV[st], b); g[st].ldw = n.ld(W_QKV[st]); g[st].bias = n.w(B_QKV[st], b);
         g[st].M = rows[st]; g[st].N = 3 * D; g[st].K = D; g[st].outb = qk; g[st].ldob = 2 * D; g[st].vt = vt; g[st].v_start = 2 * D;
@@ -603,7 +603,18 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
         g[st].norm_hd = hd; g[st].qn_g = n.w(W_QN[st], b); g[st].kn_g = n.w(W_KN[st], b);
         g[st].out_scale = scale_log2; g[st].scale_cols = D;
       }
-      if (!chain || b == 0) PG_TRY(launch_gemm_pair(g[0], g[1], EPI_QKV, s));
+      ChainArgs r{};
+      r.qk = qk; r.vt = vt; r.mod_ld = mod_ld; r.mod_of = mod_of; r.M = M; r.Lpad = Lpad; r.out_scale = scale_log2; r.norm_hd = hd;
+      auto projection = [&](int st, int block, const float* norm) {
+        ChainStream& t = r.s[st];
+        t.h = hs[st]; t.L = Ls[st]; t.norm2 = norm;
+        t.next_w = n.w(W_QKV[st], block); t.next_b = n.w(B_QKV[st], block); t.qn_g = n.w(W_QN[st], block); t.kn_g = n.w(W_KN[st], block);
+      };
+      if (!chain) PG_TRY(launch_gemm_pair(g[0], g[1], EPI_QKV, s));
+      else if (b == 0) {
+        for (int st = 0; st < 2; ++st) projection(st, 0, mbs[st]);
+        PG_TRY(launch_row_chain(r, D, CHAIN_START, s));
+      }
       AttnArgs a{};
       a.q = qk; a.ldq = 2 * D; a.k = qk + D; a.ldk = 2 * D; a.k_bstride = (int64_t)L * 2 * D;
       a.vt = vt; a.vt_bstride = (int64_t)D * Lpad; a.Lkpad = Lpad; a.out = atts[0]; a.ldo = D;
@@ -612,16 +623,14 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
       PG_TRY(launch_attention(a, hd, s));
       if (chain) {                                   // the context's rows are not used any more after the last block
         const bool last = b + 1 == f.blocks;
-        ChainArgs r{};
-        r.qk = qk; r.vt = vt; r.mod_ld = mod_ld; r.mod_of = mod_of; r.M = M; r.Lpad = Lpad; r.out_scale = scale_log2; r.norm_hd = last ? 0 : hd;
+        if (last) { r.norm_hd = 0; r.s[1].L = 0; }
         for (int st = 0; st < (last ? 1 : 2); ++st) {
           ChainStream& t = r.s[st];
+          if (!last) projection(st, b + 1, mbs[st] + 6 * D);
           t.att = atts[st]; t.h = hs[st]; t.L = Ls[st];
           t.o_w = n.w(W_O[st], b); t.o_b = n.w(B_O[st], b); t.fc1_w = n.w(W_FC1[st], b); t.fc1_b = n.w(B_FC1[st], b);
           t.fc2_w = n.w(W_FC2[st], b); t.fc2_b = n.w(B_FC2[st], b);
-          t.gate1 = mbs[st] + 2 * D; t.norm1 = mbs[st] + 3 * D; t.gate2 = mbs[st] + 5 * D; t.norm2 = mbs[st] + 6 * D;
-          if (last) break;
-          t.next_w = n.w(W_QKV[st], b + 1); t.next_b = n.w(B_QKV[st], b + 1); t.qn_g = n.w(W_QN[st], b + 1); t.kn_g = n.w(W_KN[st], b + 1);
+          t.gate1 = mbs[st] + 2 * D; t.norm1 = mbs[st] + 3 * D; t.gate2 = mbs[st] + 5 * D;
         }
         PG_TRY(launch_row_chain(r, D, last ? CHAIN_LAST : CHAIN_BLOCK, s));
         continue;
@@ -661,7 +670,18 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
   for (int b = 0; b < (dual ? 0 : f.blocks); ++b) {
     const float* mb = mod + (size_t)b * 6 * D;     // shift1, scale1, gate1, shift2, scale2, gate2
     // attention sub-block
-    if (!chain || b == 0) {
+    ChainArgs r{};
+    r.qk = qk; r.vt = vt; r.mod_ld = mod_ld; r.mod_of = mod_of; r.M = M; r.Lpad = Lpad; r.out_scale = scale_log2;
+    ChainStream& t = r.s[0];
+    t.h = h; t.L = L;
+    auto projection = [&](int block, const float* norm) {
+      t.norm2 = norm; t.next_w = n.w(PG_W_QKV_W, block); t.next_b = n.w(PG_W_QKV_B, block);
+    };
+    if (chain && b == 0) {
+      projection(0, mb);
+      PG_TRY(launch_row_chain(r, D, CHAIN_START, s));
+    }
+    if (!chain) {
       PG_TRY(layer_norm(mb, mb + D, mod_ld, R, L));
       GemmArgs g{};
       g.A = act; g.lda = D; g.W = n.w(PG_W_QKV_W, b); g.ldw = n.ld(PG_W_QKV_W); g.bias = n.w(PG_W_QKV_B, b);
@@ -678,19 +698,16 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
     }
     if (chain) {
       const bool last = b + 1 == f.blocks;
-      ChainArgs r{};
-      ChainStream& t = r.s[0];
-      r.qk = qk; r.vt = vt; r.mod_ld = mod_ld; r.mod_of = mod_of; r.M = M; r.Lpad = Lpad; r.out_scale = scale_log2;
-      t.att = att; t.h = h; t.L = L; t.o_w = n.w(PG_W_O_W, b); t.o_b = n.w(PG_W_O_B, b); t.gate1 = mb + 2 * D;
+      t.att = att; t.o_w = n.w(PG_W_O_W, b); t.o_b = n.w(PG_W_O_B, b); t.gate1 = mb + 2 * D;
       if (f.net_kind == PG_NET_CROSS) {
         t.next_w = n.w(PG_W_CQ_W, b); t.next_b = n.w(PG_W_CQ_B, b);
         PG_TRY(launch_row_chain(r, D, CHAIN_QUERIES, s));
         PG_TRY(cross_attention(b));
         t.o_w = n.w(PG_W_CO_W, b); t.o_b = n.w(PG_W_CO_B, b); t.gate1 = nullptr;
       }
-      t.norm1 = mb + 3 * D; t.gate2 = mb + 5 * D; t.norm2 = mb + 6 * D;
+      t.norm1 = mb + 3 * D; t.gate2 = mb + 5 * D;
       t.fc1_w = n.w(PG_W_FC1_W, b); t.fc1_b = n.w(PG_W_FC1_B, b); t.fc2_w = n.w(PG_W_FC2_W, b); t.fc2_b = n.w(PG_W_FC2_B, b);
-      if (!last) { t.next_w = n.w(PG_W_QKV_W, b + 1); t.next_b = n.w(PG_W_QKV_B, b + 1); }
+      if (!last) projection(b + 1, mb + 6 * D);
       PG_TRY(launch_row_chain(r, D, last ? CHAIN_LAST : CHAIN_BLOCK, s));
       continue;
     }

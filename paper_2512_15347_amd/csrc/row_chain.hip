@@ -1,6 +1,7 @@
 // The layers between two attentions of a block (output projection, residual sum, LayerNorm, MLP, LayerNorm, queries / keys / values
-// of the next block) for networks of width 128, 192 and 256: a workgroup takes 16 or 32 rows of one trajectory through all of them in
-// one launch.  In the dual-stream network a workgroup's rows are image or context tokens, with the weights of their stream.
+// of the next block; in front of the first attention the last two) for networks of width 128, 192 and 256: a workgroup takes 16 or 32
+// rows of one trajectory through all of them in one launch.  In the dual-stream network a workgroup's rows are image or context
+// tokens, with the weights of their stream.
 //
 // Layer by layer each of them is a launch of 4 to 8 us with a microsecond of work in it (six of them and their gaps: 40 us).  They need
 // nothing but their own rows, so the residual stream stays in registers, operands and hidden values in LDS, and what a workgroup
@@ -24,7 +25,7 @@ typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 
 namespace {
 // products of a launch, each [rows, D] x [D, D]^T: the projection, then fc1 and fc2 by quarters of the hidden values, then the next ones
-template <int KIND> constexpr int products() { return KIND == CHAIN_QUERIES ? 2 : KIND == CHAIN_BLOCK ? 12 : 9; }
+template <int KIND> constexpr int products() { return KIND == CHAIN_QUERIES ? 2 : KIND == CHAIN_BLOCK ? 12 : KIND == CHAIN_LAST ? 9 : 3; }
 
 template <int D, int RT> struct Chain {
   static constexpr int WAVES = D / 32, THREADS = 64 * WAVES;
@@ -82,7 +83,8 @@ struct Weights {
     const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)touched);
     for (int k = id / 8 * C::WAVES + wave; k < products<KIND>() * LOADS; k += wgs * C::WAVES) {
       const int p = k / LOADS;
-      const uint16_t* base = p == 0 ? a.o_w : KIND == CHAIN_QUERIES ? a.next_w : p < 5 ? a.fc1_w + (p - 1) * D * D
+      const uint16_t* base = KIND == CHAIN_START ? a.next_w + p * D * D : p == 0 ? a.o_w
+                             : KIND == CHAIN_QUERIES ? a.next_w : p < 5 ? a.fc1_w + (p - 1) * D * D
                              : p < 9 ? a.fc2_w + (p - 5) * D * D : a.next_w + (p - 9) * D * D;
       dma4(lane * 128u, base + (k - p * LOADS) * 64 * 64, to);
     }
@@ -177,13 +179,13 @@ __device__ __forceinline__ void normalise(const float* h, uint16_t* act, const f
 template <int D, int KIND, int RT, bool DUAL>
 __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(const ChainArgs args) {
   using C = Chain<D, RT>;
-  constexpr bool MLP = KIND != CHAIN_QUERIES, NEXT = KIND != CHAIN_LAST;
-  constexpr int ROWS = 16 * RT, NB = KIND == CHAIN_QUERIES ? 2 : KIND == CHAIN_BLOCK ? 9 : 6;     // biases in units of D
+  constexpr bool START = KIND == CHAIN_START, MLP = KIND == CHAIN_BLOCK || KIND == CHAIN_LAST, NEXT = KIND == CHAIN_BLOCK || START;
+  constexpr int ROWS = 16 * RT, NB = KIND == CHAIN_QUERIES ? 2 : KIND == CHAIN_BLOCK ? 9 : KIND == CHAIN_LAST ? 6 : 3;     // biases in units of D
   __shared__ __align__(16) unsigned char ring[C::WAVES * C::SLOTS * C::PIECE];
   __shared__ __align__(16) unsigned char both[ROWS * C::PITCH * 4];      // residual stream for the LayerNorm | hidden values, two quarters
   __shared__ __align__(16) uint16_t act[ROWS * C::PITCH];
   __shared__ __align__(16) float md[4 * D];          // shift, scale of the LayerNorm, shift, scale of the next block
-  __shared__ __align__(16) uint16_t bs[NB * D];      // projection, [fc1, fc2,] next
+  __shared__ __align__(16) uint16_t bs[NB * D];      // [projection,] [fc1, fc2,] [next]
   __shared__ __align__(16) unsigned char touched[256];
   __shared__ float squares[DUAL ? C::WAVES * ROWS : 1];     // of a wave's columns
   float* hl = reinterpret_cast<float*>(both);
@@ -202,15 +204,15 @@ __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(cons
   constexpr int AV = ROWS * D / 8 / C::THREADS;      // 16-byte chunks of attention's output per thread: RT
   u32x4v av[AV];
 #pragma unroll
-  for (int i = 0; i < AV; ++i) {
+  for (int i = 0; i < AV && !START; ++i) {
     const int e = i * C::THREADS + tid, r = e / (D / 8), c = e - r * (D / 8);
     av[i] = *reinterpret_cast<const u32x4v*>(a.att + (row0 + min(t0 + r, a.L - 1)) * D + 8 * c);
   }
   u32x4v bias_in = {0u, 0u, 0u, 0u};
   const int bi = 8 * tid;                            // of the biases one after another
   if (bi < NB * D) {
-    const uint16_t* p = bi < D ? a.o_b + bi : !MLP ? a.next_b + bi - D : bi < 5 * D ? a.fc1_b + bi - D : bi < 6 * D ? a.fc2_b + bi - 5 * D
-                                                                                                                : a.next_b + bi - 6 * D;
+    const uint16_t* p = START ? a.next_b + bi : bi < D ? a.o_b + bi : !MLP ? a.next_b + bi - D
+                        : bi < 5 * D ? a.fc1_b + bi - D : bi < 6 * D ? a.fc2_b + bi - 5 * D : a.next_b + bi - 6 * D;
     bias_in = *reinterpret_cast<const u32x4v*>(p);
   }
   f32x4v h[2][RT];
@@ -225,12 +227,12 @@ __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(cons
   if (tid < D) {                                     // of 4 D modulation values
     const int i = 4 * tid;
     if (i < 2 * D) { if (a.norm1) vec = *reinterpret_cast<const f32x4v*>(a.norm1 + mod_row + i); }
-    else if (KIND == CHAIN_BLOCK) vec = *reinterpret_cast<const f32x4v*>(a.norm2 + mod_row + i - 2 * D);
+    else if (NEXT) vec = *reinterpret_cast<const f32x4v*>(a.norm2 + mod_row + i - 2 * D);
   }
   f32x4v gate1[2], gate2[2];
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
-    gate1[c] = a.gate1 ? *reinterpret_cast<const f32x4v*>(a.gate1 + mod_row + n0 + 16 * c) : f32x4v{1.f, 1.f, 1.f, 1.f};
+    if (!START) gate1[c] = a.gate1 ? *reinterpret_cast<const f32x4v*>(a.gate1 + mod_row + n0 + 16 * c) : f32x4v{1.f, 1.f, 1.f, 1.f};
     if (MLP) gate2[c] = *reinterpret_cast<const f32x4v*>(a.gate2 + mod_row + n0 + 16 * c);
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -239,17 +241,17 @@ __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(cons
   const Source<false> w_out{a.o_w + wave * 32 * D}, w_next{a.next_w + wave * 32 * D};
   auto w_fc1 = [&](int j) { return Source<false>{a.fc1_w + (j * D + wave * 32) * D}; };
   auto w_fc2 = [&](int j) { return Source<true>{a.fc2_w + wave * 32 * 4 * D + j * D}; };
-  weights.begin(w_out);
+  weights.begin(START ? w_next : w_out);
   weights.template warm<KIND>(a, touched, wave);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < AV; ++i) {
+  for (int i = 0; i < AV && !START; ++i) {
     const int e = i * C::THREADS + tid, r = e / (D / 8), c = e - r * (D / 8);
     *reinterpret_cast<u32x4v*>(act + r * C::PITCH + 8 * c) = av[i];
   }
   if (bi < NB * D) *reinterpret_cast<u32x4v*>(bs + bi) = bias_in;
   if (tid < D) *reinterpret_cast<f32x4v*>(md + 4 * tid) = vec;
-  __syncthreads();
+  if (!START) __syncthreads();
 
   f32x4v acc[2][RT];
   typename Weights<D, RT>::Rows x;
@@ -319,20 +321,23 @@ __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(cons
     }
   };
 
-  start(acc, bs);
-  weights.template product<true>(w_out, MLP ? w_fc1(0) : w_next, true, act, x, acc);
-  add_to_stream(gate1, acc);
-  stream_to_lds();
-  __syncthreads();
-  normalise<D, RT>(hl, act, md, md + D);
-  __syncthreads();
+  if constexpr (!START) {
+    start(acc, bs);
+    weights.template product<true>(w_out, MLP ? w_fc1(0) : w_next, true, act, x, acc);
+    add_to_stream(gate1, acc);
+    stream_to_lds();
+    __syncthreads();
+    normalise<D, RT>(hl, act, md, md + D);
+    __syncthreads();
+  }
 
   if constexpr (KIND == CHAIN_QUERIES) {
     store_stream();
     start(acc, bs + D);
     weights.template product<true>(w_next, w_next, false, act, x, acc);
     store_rows(args.qk, D, args.out_scale);
-  } else {
+  }
+  if constexpr (MLP) {
     f32x4v sum[2][RT];
     start(sum, bs + 5 * D);
     weights.read_all_rows(act, x);
@@ -354,43 +359,43 @@ __global__ __launch_bounds__(2 * D, D == 128 ? 2 : 1) void row_chain_kernel(cons
     }
     add_to_stream(gate2, sum);
     if constexpr (!NEXT) store_stream();
-    if constexpr (NEXT) {
-      __syncthreads();                               // the hidden values have been read
-      stream_to_lds();
-      __syncthreads();
-      normalise<D, RT>(hl, act, md + 2 * D, md + 3 * D);
-      __syncthreads();
-      store_stream();                                // behind the last barrier, which would wait for it and for the ring's loads
-      weights.read_all_rows(act, x);
-      auto part = [&](int i) { return Source<false>{w_next.w + i * D * D}; };
+    else __syncthreads();                            // the hidden values have been read
+  }
+  if constexpr (NEXT) {
+    stream_to_lds();
+    __syncthreads();
+    normalise<D, RT>(hl, act, md + 2 * D, md + 3 * D);
+    __syncthreads();
+    if (!START) store_stream();                      // behind the last barrier, which would wait for it and for the ring's loads
+    weights.read_all_rows(act, x);
+    auto part = [&](int i) { return Source<false>{w_next.w + i * D * D}; };
 #pragma unroll 1
-      for (int i = 0; i < 2; ++i) {                  // queries, keys
-        start(acc, bs + (6 + i) * D);
-        weights.template product<false>(part(i), part(i + 1), true, act, x, acc);
-        if constexpr (DUAL) normalise_heads(i ? a.kn_g : a.qn_g);
-        store_rows(args.qk + i * D, 2 * D, i ? 1.f : args.out_scale);
-      }
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const float b = bf16_to_f32(bs[8 * D + wave * 32 + 16 * c + lr]);
-#pragma unroll
-        for (int t = 0; t < RT; ++t) acc[c][t] = f32x4v{b, b, b, b};
-      }
-      weights.template product<false, true>(part(2), part(2), false, act, x, acc);
-      // tokens past the end, too, where nobody else's follow: a value row has room for whole tiles, and attention takes nothing from there
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int t = 0; t < RT; ++t) {
-          uint16_t* row = args.vt + ((int64_t)m * D + wave * 32 + 16 * c + lr) * args.Lpad;
-          const int tok = t0 + 16 * t + 4 * lk;
-          if (!DUAL || ((tok0 & 3) == 0 && tok + 4 <= a.L)) put4(row + value_slot(tok0 + tok), acc[c][t]);
-          else
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (tok + e < a.L) row[value_slot(tok0 + tok + e)] = (uint16_t)pack_bf16x2(acc[c][t][e], 0.f);
-        }
+    for (int i = 0; i < 2; ++i) {                    // queries, keys
+      start(acc, bs + (NB - 3 + i) * D);
+      weights.template product<false>(part(i), part(i + 1), true, act, x, acc);
+      if constexpr (DUAL) normalise_heads(i ? a.kn_g : a.qn_g);
+      store_rows(args.qk + i * D, 2 * D, i ? 1.f : args.out_scale);
     }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const float b = bf16_to_f32(bs[(NB - 1) * D + wave * 32 + 16 * c + lr]);
+#pragma unroll
+      for (int t = 0; t < RT; ++t) acc[c][t] = f32x4v{b, b, b, b};
+    }
+    weights.template product<false, true>(part(2), part(2), false, act, x, acc);
+    // tokens past the end, too, where nobody else's follow: a value row has room for whole tiles, and attention takes nothing from there
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        uint16_t* row = args.vt + ((int64_t)m * D + wave * 32 + 16 * c + lr) * args.Lpad;
+        const int tok = t0 + 16 * t + 4 * lk;
+        if (!DUAL || ((tok0 & 3) == 0 && tok + 4 <= a.L)) put4(row + value_slot(tok0 + tok), acc[c][t]);
+        else
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (tok + e < a.L) row[value_slot(tok0 + tok + e)] = (uint16_t)pack_bf16x2(acc[c][t][e], 0.f);
+      }
   }
 }
 
@@ -406,6 +411,7 @@ template <int D>
 pg_status launch_width(const ChainArgs& a, ChainKind kind, hipStream_t s) {
   if (kind == CHAIN_QUERIES) return launch_rows<D, CHAIN_QUERIES, false>(a, s);
   if (kind == CHAIN_LAST) return launch_rows<D, CHAIN_LAST, false>(a, s);
+  if (kind == CHAIN_START) return a.s[1].L > 0 ? launch_rows<D, CHAIN_START, true>(a, s) : launch_rows<D, CHAIN_START, false>(a, s);
   return a.s[1].L > 0 ? launch_rows<D, CHAIN_BLOCK, true>(a, s) : launch_rows<D, CHAIN_BLOCK, false>(a, s);
 }
 }  // namespace
@@ -420,19 +426,18 @@ pg_status launch_width(const ChainArgs& a, ChainKind kind, hipStream_t s) {
 bool row_chain_takes(int D, int64_t M) { return (D == 128 || D == 192 || D == 256) && M <= 65535; }     // the limit is the grid's
 
 pg_status launch_row_chain(const ChainArgs& a, int D, ChainKind kind, hipStream_t s) {
-  const bool dual = a.s[1].L > 0;
+  const bool dual = a.s[1].L > 0, next = kind == CHAIN_BLOCK || kind == CHAIN_START, mlp = kind == CHAIN_BLOCK || kind == CHAIN_LAST;
   const int L = a.s[0].L + a.s[1].L;
   bool complete = row_chain_takes(D, a.M) && a.M >= 1 && a.mod_of && (kind == CHAIN_LAST || a.qk) &&
-                  (kind != CHAIN_BLOCK || (a.vt && a.Lpad % 64 == 0 && a.Lpad >= L)) && (dual ? kind == CHAIN_BLOCK : a.norm_hd == 0) &&
-                  (!dual || a.norm_hd == 32 || a.norm_hd == 64);
+                  (!next || (a.vt && a.Lpad % 64 == 0 && a.Lpad >= L)) && (dual ? next && (a.norm_hd == 32 || a.norm_hd == 64) : a.norm_hd == 0);
   for (int i = 0; i < (dual ? 2 : 1); ++i) {
     const ChainStream& c = a.s[i];
-    complete = complete && c.L >= 1 && c.att && c.h && c.o_w && c.o_b && (kind == CHAIN_LAST || (c.next_w && c.next_b)) &&
-               (kind == CHAIN_QUERIES || (c.fc1_w && c.fc1_b && c.fc2_w && c.fc2_b && c.gate2)) && (kind != CHAIN_BLOCK || c.norm2) &&
-               (!dual || (c.qn_g && c.kn_g));
+    complete = complete && c.L >= 1 && c.h && (kind == CHAIN_START || (c.att && c.o_w && c.o_b)) &&
+               (kind == CHAIN_LAST || (c.next_w && c.next_b)) && (!mlp || (c.fc1_w && c.fc1_b && c.fc2_w && c.fc2_b && c.gate2)) &&
+               (!next || c.norm2) && (!dual || (c.qn_g && c.kn_g));
   }
   if (!complete) return fail(PG_ESHAPE, "row chain: width %d, %d x %d rows", D, a.M, L);
-  const double n = kind == CHAIN_QUERIES ? 2 : kind == CHAIN_BLOCK ? 12 : 9;
+  const double n = kind == CHAIN_QUERIES ? 2 : kind == CHAIN_BLOCK ? 12 : kind == CHAIN_LAST ? 9 : 3;
   const int rec = prof_open(PROF_GEMM, n * 2.0 * a.M * L * D * D, s);
   const pg_status st = D == 128 ? launch_width<128>(a, kind, s) : D == 192 ? launch_width<192>(a, kind, s) : launch_width<256>(a, kind, s);
   prof_close(rec, s);

@@ -8,7 +8,8 @@ namespace pg {
 enum ChainKind {
   CHAIN_QUERIES = 0,   // LayerNorm and the queries of the cross-attention
   CHAIN_BLOCK = 1,     // LayerNorm, MLP with its residual sum, LayerNorm and queries | keys | values of the next block
-  CHAIN_LAST = 2       // LayerNorm, MLP with its residual sum
+  CHAIN_LAST = 2,      // LayerNorm, MLP with its residual sum
+  CHAIN_START = 3      // and, in front of the first one: LayerNorm and queries | keys | values of the first block
 };
 struct ChainStream {
   const uint16_t* att; float* h;                   // attention's output and the residual stream, [M L, D]
@@ -21,8 +22,8 @@ struct ChainStream {
   int L;                                           // rows of a trajectory
 };
 struct ChainArgs {
-  ChainStream s[2];                                // the second one with L > 0: CHAIN_BLOCK, its tokens follow the first one's
-  uint16_t* qk; uint16_t* vt;                      // CHAIN_QUERIES: [M L, D]; CHAIN_BLOCK: [M L, 2 D] and transposed values (EPI_QKV), L of both
+  ChainStream s[2];                                // the second one with L > 0: CHAIN_BLOCK or CHAIN_START, its tokens follow the first one's
+  uint16_t* qk; uint16_t* vt;                      // CHAIN_QUERIES: [M L, D]; CHAIN_BLOCK, CHAIN_START: [M L, 2 D] and transposed values (EPI_QKV), L of both
   int64_t mod_ld; const int32_t* mod_of;
   int M, Lpad;
   float out_scale;                                 // of the queries
