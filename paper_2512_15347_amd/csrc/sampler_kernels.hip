@@ -112,16 +112,17 @@ static void with_groups(int chunks, F launch) {
 }
 
 // x_out[r] = A x[q] + B u[q] + C xi, q = src ? src[r] : r; sum xi^2 per trajectory.  GROUPS 0: a workgroup per chunk,
-// which leaves its partial, or adds it to `arrived` (one word per row, 0 before and after); else a workgroup of GROUPS x 256 lanes
-// per trajectory.
+// which leaves its partial, or adds it to `arrived` (one word per row, 0 before and after), with a lane for every 16 bytes (WIDE) or
+// 256 lanes, the same sums in the same order; else a workgroup of GROUPS x 256 lanes per trajectory.
 constexpr int ARRIVED_SHIFT = 52;                  // 12 bits of count above 24 of whole and 28 of fractional sum
-template <int GROUPS>
-__global__ __launch_bounds__(GROUPS ? GROUPS * STREAM_THREADS : CHUNK_THREADS) void sde_step_kernel(
+constexpr int step_lanes(int groups, bool wide) { return groups || !wide ? STREAM_THREADS : CHUNK_THREADS; }     // of a chunk
+template <int GROUPS, bool WIDE>
+__global__ __launch_bounds__((GROUPS ? GROUPS : 1) * step_lanes(GROUPS, WIDE)) void sde_step_kernel(
     const float* __restrict__ x, const float* __restrict__ u, float* __restrict__ x_out,
     const int32_t* __restrict__ src, const int32_t* __restrict__ orig_id, int d4, int chunks, float A,
     float B, float C, uint32_t k0, uint32_t k1, uint32_t step, float* __restrict__ partials,
     float* __restrict__ hist_next, const LogProb out, uint64_t* __restrict__ arrived) {
-  constexpr int ITERS = GROUPS ? STREAM_ITERS : 1, LANES = GROUPS ? STREAM_THREADS : CHUNK_THREADS;
+  constexpr int LANES = step_lanes(GROUPS, WIDE), ITERS = STREAM_CHUNK / 4 / LANES;
   const int r = GROUPS ? blockIdx.x : blockIdx.x / chunks, c = GROUPS ? threadIdx.x / STREAM_THREADS : blockIdx.x - r * chunks;
   const int at = GROUPS > 1 ? threadIdx.x & (STREAM_THREADS - 1) : threadIdx.x;
   const int q = src ? src[r] : r;
@@ -158,7 +159,9 @@ __global__ __launch_bounds__(GROUPS ? GROUPS * STREAM_THREADS : CHUNK_THREADS) v
   if constexpr (GROUPS > 0) {
     row_sum<GROUPS>(chunks, acc, [&](double s) { finish_logprob(out, r, (int)id, s); });
   } else {
-    const float t = chunk_sum(acc);
+    float t;
+    if constexpr (WIDE) t = chunk_sum(acc);
+    else t = block_sum_256(acc);
     if (threadIdx.x != 0) return;
     if (!arrived) {
       partials[blockIdx.x] = t;
@@ -449,6 +452,10 @@ static pg_status launch_logprob_finish(const float* partials, int chunks, int64_
   return PG_OK;
 }
 
+// Whether the update of chunks has a lane for every 16 bytes: where a launch may have so many (HIP takes less than 2^32 of them; with
+// 256 a chunk four times as many trajectories).
+static bool lane_per_access(int64_t n_traj, int chunks) { return n_traj * chunks < (1ll << 32) / CHUNK_THREADS; }
+
 pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* logp, float* logp_hist,
                           float* logp_sum, const int32_t* src, const int32_t* orig_id, int64_t n_traj, int64_t d,
                           double A, double B, double C, uint64_t seed, uint32_t step, float* partials,
@@ -464,9 +471,14 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
   const int rec = prof_open(PROF_SDE_STEP, 12.0 * (double)n_traj * (double)d, stream);
   with_groups(row ? chunks : 0, [&](auto groups) {
     constexpr int G = decltype(groups)::value;
-    sde_step_kernel<G><<<dim3((unsigned)(G ? n_traj : n_traj * chunks)), dim3(G ? G * STREAM_THREADS : CHUNK_THREADS), 0, stream>>>(
-        x, u, x_out, src, orig_id, (int)(d / 4), chunks, (float)A, (float)B, (float)C, (uint32_t)seed, (uint32_t)(seed >> 32), step,
-        partials, hist_next, out, arrived);
+    auto launch = [&](auto wide) {
+      constexpr bool WIDE = decltype(wide)::value;
+      sde_step_kernel<G, WIDE><<<dim3((unsigned)(G ? n_traj : n_traj * chunks)), dim3((G ? G : 1) * step_lanes(G, WIDE)), 0, stream>>>(
+          x, u, x_out, src, orig_id, (int)(d / 4), chunks, (float)A, (float)B, (float)C, (uint32_t)seed, (uint32_t)(seed >> 32), step,
+          partials, hist_next, out, arrived);
+    };
+    if (G || !lane_per_access(n_traj, chunks)) launch(std::false_type{});
+    else if constexpr (G == 0) launch(std::true_type{});
   });
   prof_close(rec, stream);
   PG_LAUNCH_CHECK("sde_step_kernel");

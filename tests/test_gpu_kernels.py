@@ -111,6 +111,27 @@ def test_sums_over_a_trajectory_do_not_depend_on_the_batch(lib, d):
     assert np.isfinite(results[0][1]).all() and np.abs(results[0][4]).min() > 0
 
 
+@pytest.mark.parametrize("d", [4100, 8192])
+def test_sde_step_of_very_many_chunks(lib, d):
+    """2^22 chunks of two to a trajectory: more than a launch has lanes for with one for every 16 bytes.  The sources repeat, so that
+    the output alone is large (32 and 64 GiB); rows all over it against a call of their own."""
+    n, few = 1 << 21, 64
+    say(f"update of {n} trajectories of {d}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d)
+    x, u = (torch.randn(few, d, device=DEV, generator=g) for _ in range(2))
+    ids = torch.arange(n, dtype=torch.int32, device=DEV)
+    rows = torch.tensor([0, 1, 2, few + 3, n // 2 - 1, n // 2, n - 2, n - 1], device=DEV)
+    got = []
+    for some in (ids, ids[rows]):
+        m = len(some)
+        out, lp, part = torch.empty(m, d, device=DEV), torch.zeros(m, device=DEV), torch.zeros(lib.pg_step_scratch_floats(m, d), device=DEV)
+        lib.pg_sde_step_logprob(x, u, out, lp, None, None, some % few, some, m, d, 0.9, -0.2, 0.3, 7, 2, part)
+        got.append((out, lp) if m < n else (out[rows], lp[rows]))
+        del out
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 @pytest.mark.parametrize("n,d,gather", [(4, 1024, False), (3, 4096 * 2 + 520, False), (12, 4096 + 256, True)])
 def test_sde_step_bf16_storage_matches_oracle(lib, n, d, gather):
     """Storage variant: bf16 latents and network output in, bf16 latents out.  The oracle takes the same
