@@ -2,8 +2,8 @@
 // update + Gaussian log-prob (paper Eq. 13 and the policy of Eq. 19), the one-step ODE preview with
 // the linear reward proxy (Eq. 15-16), and the ragged survivor gather (Sec. 5.1, early termination).
 //
-// Work decomposition: 256 lanes own one STREAM_CHUNK (4096 floats) of one trajectory and move it with
-// 16-byte accesses; a chunk's sum is one partial, and a trajectory's partials are added up in a fixed
+// Work decomposition: 256 lanes (of the update in chunks mostly 1024) own one STREAM_CHUNK (4096 floats) of one trajectory and move it
+// with 16-byte accesses; a chunk's sum is one partial, and a trajectory's partials are added up in a fixed
 // order (fp64), so results do not depend on scheduling: by the workgroup itself where it holds all chunks
 // of a short trajectory, else by a second tiny kernel.
 #include <algorithm>
@@ -27,9 +27,11 @@ __device__ __forceinline__ float block_sum_256(float v) {
   return t;
 }
 
-// A workgroup per chunk of the update has a lane for every 16 bytes: bound by HBM, which a sweep of many waves with one access of each
-// array serves best (1024 x 262144 update, 3.2 GB: 539 us with four accesses of each array in a lane of 256, 500 us so, 6.5 TB/s;
-// two inputs and one output without arithmetic take 505 and 497, in waves of their own 471, but their sums would be 16 to a chunk).
+// A workgroup per chunk of the update has a lane for every 16 bytes (lane_per_access): bound by HBM, which a sweep of many waves with
+// one access of each array serves best (1024 x 262144 update, 3.2 GB: 506 to 546 us with four accesses of each array in a lane of
+// 256, 487 to 516 us so, by where the arrays lie and from box to box, always 3 to 6 % apart; 6.2 to 6.6 TB/s, the plain copy
+// 6.0 to 6.25.  Two inputs and one output without arithmetic take 505 and 497, in waves of their own 471, but their sums would be 16
+// to a chunk).
 // The bf16 storage keeps four waves: its Philox blocks bound it as much as memory (267 us; a lane per access 269, two chunks to a
 // workgroup 279).
 constexpr int CHUNK_THREADS = STREAM_CHUNK / 4;
@@ -453,8 +455,15 @@ static pg_status launch_logprob_finish(const float* partials, int chunks, int64_
 }
 
 // Whether the update of chunks has a lane for every 16 bytes: where a launch may have so many (HIP takes less than 2^32 of them; with
-// 256 a chunk four times as many trajectories).
-static bool lane_per_access(int64_t n_traj, int chunks) { return n_traj * chunks < (1ll << 32) / CHUNK_THREADS; }
+// 256 a chunk four times as many trajectories), and where few of them would have nothing to do.  A last chunk of a few elements
+// costs 1024 lanes as much as a whole one, 256 lanes less: us with 256 / 1024 for trajectories of two chunks 4096 x 4100
+// 49.3 / 54.9, 8192 x 5120 96.5 / 102.6, x 6144 109.4 / 111.8, x 7168 125.5 / 120.0, of three 8192 x 8448 136.9 / 141.5,
+// x 10240 167.2 / 159.6, of four x 12544 209.5 / 215.2, x 13312 220.0 / 221.6, x 14336 243.2 / 231.6, of five x 16388
+// 283.4 / 268.1, of six x 20484 385 / 360.
+static bool lane_per_access(int64_t n_traj, int64_t d) {
+  const int64_t chunks = chunks_per_traj(d);
+  return n_traj * chunks < (1ll << 32) / CHUNK_THREADS && (chunks > 4 || 6 * d >= 5 * chunks * STREAM_CHUNK);
+}
 
 pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* logp, float* logp_hist,
                           float* logp_sum, const int32_t* src, const int32_t* orig_id, int64_t n_traj, int64_t d,
@@ -477,7 +486,7 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
           x, u, x_out, src, orig_id, (int)(d / 4), chunks, (float)A, (float)B, (float)C, (uint32_t)seed, (uint32_t)(seed >> 32), step,
           partials, hist_next, out, arrived);
     };
-    if (G || !lane_per_access(n_traj, chunks)) launch(std::false_type{});
+    if (G || !lane_per_access(n_traj, d)) launch(std::false_type{});
     else if constexpr (G == 0) launch(std::true_type{});
   });
   prof_close(rec, stream);

@@ -111,6 +111,26 @@ def test_sums_over_a_trajectory_do_not_depend_on_the_batch(lib, d):
     assert np.isfinite(results[0][1]).all() and np.abs(results[0][4]).min() > 0
 
 
+# the update has 256 lanes to a chunk where less than five sixths of 1024 would have work, else 1024: last chunks on either side of that and of
+# one access alone; the same bits as a workgroup per trajectory, which takes few of at most four chunks, else against the oracle
+@pytest.mark.parametrize("d", [4100, 6824, 6828, 8188, 8196, 10236, 10240, 12292, 13652, 13656, 16380, 16388, 20484])
+def test_update_does_not_depend_on_the_lanes_of_a_chunk(lib, d):
+    say(f"update of chunks, d={d}")
+    if d > 4 * 4096:
+        return _step_case(lib, 3, d, seed=5, step=1, A=0.93, B=-0.21, Cc=0.31)
+    n = 513
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d)
+    x, u = (torch.randn(n, d, device=DEV, generator=g) for _ in range(2))
+    ids = torch.arange(n, dtype=torch.int32, device=DEV)
+    part = torch.zeros(lib.pg_step_scratch_floats(n, d), device=DEV)
+    outs = [(torch.zeros(m, d, device=DEV), torch.zeros(m, device=DEV)) for m in (n, 512)]
+    for out, lp in outs:
+        lib.pg_sde_step_logprob(x, u, out, lp, None, None, None, ids, len(lp), d, 0.9, -0.2, 0.3, 7, 2, part)
+    for many, few in zip(*outs):
+        assert torch.equal(many[:512].view(torch.int32), few.view(torch.int32))
+
+
 @pytest.mark.parametrize("d", [4100, 8192])
 def test_sde_step_of_very_many_chunks(lib, d):
     """2^22 chunks of two to a trajectory: more than a launch has lanes for with one for every 16 bytes.  The sources repeat, so that
