@@ -548,10 +548,20 @@ pg_status launch_init_group(float* x, int P, int N, int64_t d, uint64_t seed, do
   InitGroup a{x, (int)(d / 4), chunks, (uint32_t)seed, (uint32_t)(seed >> 32), sums, steps, P, N, offsets, ids, group_of,
               (uint32_t*)logp_hist, hist_n, logp_sum, status, arrived, (int)(M0 * chunks), noise_here ? (int)(M0 * steps) : 0};
   const size_t n = std::max(hist_n, (size_t)M0) + 1;
-  const int64_t blocks = (int64_t)a.latent_blocks + a.noise_blocks + (int64_t)std::min<size_t>((n + 255) / 256, 1024);
-  if (blocks > INT32_MAX) return fail(PG_ESHAPE, "n_traj * ceil(d/4096) exceeds the grid limit");
-  init_group_kernel<<<dim3((unsigned)blocks), dim3(STREAM_THREADS), 0, s>>>(a);
-  PG_LAUNCH_CHECK("init_group_kernel");
+  const int state_blocks = (int)std::min<size_t>((n + 255) / 256, 1024);
+  const auto launch = [&](int64_t blocks) -> pg_status {
+    init_group_kernel<<<dim3((unsigned)blocks), dim3(STREAM_THREADS), 0, s>>>(a);
+    PG_LAUNCH_CHECK("init_group_kernel");
+    return PG_OK;
+  };
+  const int64_t blocks = (int64_t)a.latent_blocks + a.noise_blocks;
+  if ((blocks + state_blocks) * STREAM_THREADS < 1ll << 32) {
+    PG_TRY(launch(blocks + state_blocks));
+  } else {                                           // a launch takes less than 2^32 lanes: the latents may need all of them
+    PG_TRY(launch(blocks));
+    a.latent_blocks = a.noise_blocks = 0;
+    PG_TRY(launch(state_blocks));
+  }
   return sums && !noise_here ? launch_noise_sums((int)M0, steps, d, seed, sums, s) : PG_OK;
 }
 

@@ -575,6 +575,29 @@ def test_loop_launches_against_the_single_kernels(lib, P, N, C, H, W):
     lib.pg_destroy(ctx)
 
 
+def test_start_of_very_many_trajectories(lib):
+    """16,777,152 trajectories: their latents take a launch's last lanes, and the state of the run has to find others."""
+    P, N, d = 262143, 64, 4
+    say(f"start of {P} x {N} trajectories")
+    cfg = workloads.get_config("cfg1")
+    cfg.update(P=P, N=N, C=1, H=2, W=2, T=1, schedule=[[]] * P, Li=1, d=d)
+    c, keep = lib.make_config(cfg, net=False)
+    ctx = lib.pg_create(c)
+    buf = lib.Buffers(ctx, cfg)
+    for t in (buf.x[0], buf.orig_id[0], buf.group_of, buf.group_offsets, buf.logp_hist, buf.logp_sum, buf.status):
+        t.fill_(9)
+    lib.pg_bind(ctx, buf)
+    lib.pg_init_group(ctx, 3)
+    torch.cuda.synchronize()
+    ids = torch.arange(P * N, dtype=torch.int32, device=DEV)
+    x = torch.empty(P * N, d, device=DEV)
+    lib.pg_init_latents(x, ids, 3)
+    assert torch.equal(buf.x[0], x) and torch.equal(buf.orig_id[0], ids) and torch.equal(buf.group_of, ids // N)
+    assert torch.equal(buf.group_offsets, torch.arange(P + 1, dtype=torch.int32, device=DEV) * N)
+    assert buf.logp_hist.isnan().all() and not buf.logp_sum.any() and not buf.status.any()
+    lib.pg_destroy(ctx)
+
+
 # few tokens: the number of trajectories up to which one workgroup each evaluates them, and one group more
 @pytest.mark.parametrize("kind,D,P,N,H,W,Lc", [
     ("adaln", 128, 15, 60, 2, 2, 0), ("adaln", 128, 16, 60, 2, 2, 0), ("joint", 64, 40, 43, 2, 6, 1), ("joint", 64, 41, 43, 2, 6, 1),
