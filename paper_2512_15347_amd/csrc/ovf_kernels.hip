@@ -1001,13 +1001,20 @@ pg_status launch_pack_state(const int32_t* ids_in, const int32_t* sel, int n_out
   return PG_OK;
 }
 
-// Rewards of a run's groups from the latents, then the selection (k set) or the advantages.  The members' latents go through the
-// group's own workgroup where it has little to read: 12 members of 1024 elements take it 2 us, 64 of 4096 more than the launches saved.
+// Rewards of a run's groups from the latents, then the selection (k set) or the advantages.  REWARDS_DIRECT saves the preview's launch but
+// takes a group's members four at a time, 0.4 us for each four (advantages) and 1.2 us (selection, which reads u too), with 1024 lanes
+// to a group.  us, a preview of its own / direct, groups x members of d elements: selection 64 x 4 of 16 10.8 / 8.0, of 1024
+// 10.7 / 8.4, of 4096 11.4 / 12.5, 64 x 12 of 1024 10.6 / 12.3, 64 x 64 of 16 12.2 / 26.8, 2048 x 4 of 16 14.0 / 18.7; advantages
+// 64 x 4 of 16 9.6 / 6.2, of 4096 9.6 / 8.3, 64 x 24 of 256 9.6 / 7.8, 64 x 64 of 256 9.4 / 12.3, 512 x 12 of 1024 10.4 / 10.2,
+// 2048 x 12 of 16 13.3 / 16.7.
+static bool rewards_direct(const GroupEndArgs& a, int P, int N, int64_t d) {
+  return P <= 512 && d <= STREAM_CHUNK && (a.k ? N <= 8 && N * d <= 8192 : N <= 24 && N * d <= 16384);
+}
 pg_status launch_group_end(GroupEndArgs& a, int P, int N, int M, int64_t d, hipStream_t s) {
   GroupEnd e{a.x, a.u, a.w, (int)(d / 4), (float)a.Pc, (float)a.Qc, a.partials, (int)chunks_per_traj(d), a.bias, a.rewards, a.offsets,
              a.k, a.new_offsets, a.masks, a.sel_idx, a.status, a.ids_in, a.ids_out, a.group_of, a.offsets_out, P, a.eps, a.adv};
   int from = REWARDS_DIRECT;
-  if ((int64_t)N * d > 16384 || e.chunks > 1) {
+  if (!rewards_direct(a, P, N, d)) {
     bool unfinished = false;
     PG_TRY(launch_preview(a.x, a.u, a.w, a.rewards, M, d, a.Pc, a.Qc, a.bias, a.partials, e.chunks <= PARTIALS_MAX ? &unfinished : nullptr, s));
     from = unfinished ? REWARDS_PARTIAL : REWARDS_READY;

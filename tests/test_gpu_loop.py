@@ -598,6 +598,44 @@ def test_start_of_very_many_trajectories(lib):
     lib.pg_destroy(ctx)
 
 
+def test_prune_and_advantages_of_very_many_groups(lib):
+    """2^22 groups of three: more than a launch has lanes for with a large workgroup for each.  Of three members the lowest and the
+    highest stay."""
+    P, N, d = 1 << 22, 3, 4
+    say(f"prune and advantages of {P} x {N}")
+    cfg = workloads.get_config("cfg1")
+    cfg.update(P=P, N=N, C=1, H=2, W=2, T=1, schedule=[[(0, 2)]] * P, Li=1, d=d)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(8)
+    c, keep = lib.make_config(cfg, net=False)
+    ctx = lib.pg_create(c)
+    buf = lib.Buffers(ctx, cfg)
+    buf.u.normal_(generator=g)
+    buf.probe_w.normal_(generator=g)
+    lib.pg_bind(ctx, buf)
+    lib.pg_init_group(ctx, 3)
+    lib.pg_net_forward(ctx, 0)
+    lib.pg_prune(ctx, 0)
+    torch.cuda.synchronize()
+    r = buf.rewards.view(P, N)
+    # groups whose order of two rewards is not strict are not looked at
+    strict = (r.sort(1).values.diff(dim=1) > 0).all(1)
+    kept = (1 << r.argmin(1)) | (1 << r.argmax(1))
+    assert strict.float().mean() > 0.99 and torch.equal(buf.masks[strict], kept[strict])
+    assert torch.equal(buf.group_offsets, 2 * torch.arange(P + 1, dtype=torch.int32, device=DEV))
+    assert torch.equal(buf.group_of[:2 * P], torch.arange(2 * P, dtype=torch.int32, device=DEV) // 2)
+    del r, strict, kept
+    lib.pg_step(ctx, 0)
+    lib.pg_advantages(ctx)
+    lib.pg_check(ctx)
+    r = buf.rewards[:2 * P].view(P, 2).double()
+    half = (r[:, :1] - r[:, 1:]).abs() / 2
+    want = ((r - r.mean(1, keepdim=True)) / (half + 1e-6)).float()
+    # fp32 results of fp64 arithmetic on the same rewards: half a unit of numbers up to 1, and of the comparison's
+    assert (buf.adv[:2 * P].view(P, 2) - want).abs().max() < 2.0 ** -23
+    lib.pg_destroy(ctx)
+
+
 # few tokens: the number of trajectories up to which one workgroup each evaluates them, and one group more
 @pytest.mark.parametrize("kind,D,P,N,H,W,Lc", [
     ("adaln", 128, 15, 60, 2, 2, 0), ("adaln", 128, 16, 60, 2, 2, 0), ("joint", 64, 40, 43, 2, 6, 1), ("joint", 64, 41, 43, 2, 6, 1),
