@@ -592,7 +592,7 @@ extern "C" pg_status pg_step(pg_ctx* c, int32_t step, void* stream) {
                          c->buf.logp_hist + (size_t)step * c->M0, c->buf.logp_sum,
                          c->pending_gather ? c->buf.sel_idx : nullptr, c->buf.orig_id[c->cur_id], c->M, c->d,
                          c->A[step], c->B[step], c->C[step], c->seed, (uint32_t)step,
-                         (float*)ws(c, c->ws_partials), hist_next, sums_on_arrival(c->d) ? (uint64_t*)ws(c, c->ws_arrived) : nullptr,
+                         (float*)ws(c, c->ws_partials), hist_next, sums_on_arrival(c->M, c->d) ? (uint64_t*)ws(c, c->ws_arrived) : nullptr,
                          (hipStream_t)stream));
   c->steps_done = step + 1;
   c->cur_x = 1 - c->cur_x;

@@ -68,7 +68,7 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
                           float* logp_sum, const int32_t* src, const int32_t* orig_id, int64_t n_traj, int64_t d,
                           double A, double B, double C, uint64_t seed, uint32_t step, float* partials,
                           float* hist_next, uint64_t* arrived, hipStream_t s);
-bool sums_on_arrival(int64_t d);                                 // whether an update of such latents may be given `arrived`
+bool sums_on_arrival(int64_t n_traj, int64_t d);                 // whether an update may be given `arrived`
 // the preview's rewards; `unfinished`: partial sums are left to be added up, where that is not done here
 pg_status launch_preview(const float* x, const float* u, const float* w, float* rewards, int64_t n_traj, int64_t d, double Pc, double Qc,
                          double bias, float* partials, bool* unfinished, hipStream_t s);

@@ -494,8 +494,15 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
   return row || arrived ? PG_OK : launch_logprob_finish(partials, chunks, n_traj, orig_id, out, stream);
 }
 
-// A sum of d squared normals is below 23 d (a pair's is -2 ln u, u >= 2^-33).
-bool sums_on_arrival(int64_t d) { return 23 * d < (1 << 24) && chunks_per_traj(d) < (1 << (64 - ARRIVED_SHIFT)); }
+// Whether an update of so many trajectories may be given `arrived`.  The shares of a trajectory arrive at one word one after another, so
+// it pays for few chunks and small launches only.  us with a second launch / by arrival, trajectories x chunks: 384 x 5 22.7 / 20.4,
+// 1024 x 5 43.6 / 42.2, 4096 x 5 147.8 / 160.9, 4096 x 4 135.2 / 141.7, 96 x 16 21.3 / 20.2, 384 x 16 56.5 / 57.6, 1024 x 16
+// 134.7 / 138.3, 16 x 32 12.4 / 12.1, 96 x 32 33.5 / 33.3, 16 x 64 17.0 / 20.8, 96 x 64 56.0 / 61.0, 96 x 173 135 / 164.
+// (A sum of d squared normals is below 23 d, 2^22 here: a pair's is -2 ln u, u >= 2^-33.)
+bool sums_on_arrival(int64_t n_traj, int64_t d) {
+  const int64_t chunks = chunks_per_traj(d);
+  return chunks <= 32 && n_traj * chunks <= 5120;
+}
 
 pg_status launch_noise_sums(int M0, int steps, int64_t d, uint64_t seed, double* sums, hipStream_t stream);
 

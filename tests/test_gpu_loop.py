@@ -575,6 +575,13 @@ def test_loop_launches_against_the_single_kernels(lib, P, N, C, H, W):
     lib.pg_destroy(ctx)
 
 
+# log-probs by the last workgroup to arrive and by a second launch, on either side of where one gives way to the other: 5120 chunks in
+# a launch (1024 x 5, the last of them of four elements; the launches after the prunes have fewer) and 32 of a trajectory
+@pytest.mark.parametrize("P,N,C,H,W", [(16, 64, 1, 2, 8194), (41, 25, 1, 2, 8194), (2, 4, 16, 64, 128), (2, 4, 16, 64, 130)])
+def test_loop_sums_by_arrival_and_by_a_launch(lib, P, N, C, H, W):
+    test_loop_launches_against_the_single_kernels(lib, P, N, C, H, W)
+
+
 def test_start_of_very_many_trajectories(lib):
     """16,777,152 trajectories: their latents take a launch's last lanes, and the state of the run has to find others."""
     P, N, d = 262143, 64, 4
