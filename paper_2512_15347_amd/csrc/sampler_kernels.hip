@@ -116,7 +116,7 @@ static void with_groups(int chunks, F launch) {
 // x_out[r] = A x[q] + B u[q] + C xi, q = src ? src[r] : r; sum xi^2 per trajectory.  GROUPS 0: a workgroup per chunk,
 // which leaves its partial, or adds it to `arrived` (one word per row, 0 before and after), with a lane for every 16 bytes (WIDE) or
 // 256 lanes, the same sums in the same order; else a workgroup of GROUPS x 256 lanes per trajectory.
-constexpr int ARRIVED_SHIFT = 52;                  // 12 bits of count above 24 of whole and 28 of fractional sum
+constexpr int ARRIVED_SHIFT = 58, ARRIVED_UNIT = 36;   // 6 bits of count above 22 of whole and 36 of fractional sum
 constexpr int step_lanes(int groups, bool wide) { return groups || !wide ? STREAM_THREADS : CHUNK_THREADS; }     // of a chunk
 template <int GROUPS, bool WIDE>
 __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * step_lanes(GROUPS, WIDE)) void sde_step_kernel(
@@ -170,13 +170,15 @@ __global__ __launch_bounds__((GROUPS ? GROUPS : 1) * step_lanes(GROUPS, WIDE)) v
       return;
     }
     // The workgroup that adds its share last has the sum: no second launch, which a step paid 4 us for.  Sum and number of shares are
-    // one 64-bit word, so that nothing else has to be ordered.  In units of 2^-28 a share of 2^-4 and more is exact, and the sum then
-    // the one that fp64 gives, whatever the order (a share that small, of a last chunk of a few elements, is off by 2^-29 at most).
-    const uint64_t share = (uint64_t)__double2ull_rn((double)t * 268435456.0);
+    // one 64-bit word, so that nothing else has to be ordered.  In units of 2^-36 a share of 2^-13 and more is exact, and the sum then
+    // the one that fp64 gives, whatever the order (a share that small, of a last chunk of a few elements, is off by 2^-37 at most, which
+    // is what fp64 rounds sums of 65536 and more to, too).
+    constexpr double UNITS = (double)(1ull << ARRIVED_UNIT);
+    const uint64_t share = (uint64_t)__double2ull_rn((double)t * UNITS);
     const uint64_t before = __hip_atomic_fetch_add(arrived + r, (1ull << ARRIVED_SHIFT) + share, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((int)(before >> ARRIVED_SHIFT) + 1 != chunks) return;
     __hip_atomic_store(arrived + r, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // for the next step
-    finish_logprob(out, r, (int)id, (double)((before & ((1ull << ARRIVED_SHIFT) - 1)) + share) * (1.0 / 268435456.0));
+    finish_logprob(out, r, (int)id, (double)((before & ((1ull << ARRIVED_SHIFT) - 1)) + share) * (1.0 / UNITS));
   }
 }
 
@@ -498,9 +500,10 @@ pg_status launch_sde_step(const float* x, const float* u, float* x_out, float* l
 // it pays for few chunks and small launches only.  us with a second launch / by arrival, trajectories x chunks: 384 x 5 22.7 / 20.4,
 // 1024 x 5 43.6 / 42.2, 4096 x 5 147.8 / 160.9, 4096 x 4 135.2 / 141.7, 96 x 16 21.3 / 20.2, 384 x 16 56.5 / 57.6, 1024 x 16
 // 134.7 / 138.3, 16 x 32 12.4 / 12.1, 96 x 32 33.5 / 33.3, 16 x 64 17.0 / 20.8, 96 x 64 56.0 / 61.0, 96 x 173 135 / 164.
-// (A sum of d squared normals is below 23 d, 2^22 here: a pair's is -2 ln u, u >= 2^-33.)
 bool sums_on_arrival(int64_t n_traj, int64_t d) {
   const int64_t chunks = chunks_per_traj(d);
+  // a sum of d squared normals is below 23 d: a pair's is -2 ln u, u >= 2^-33
+  static_assert(23 * 32 * STREAM_CHUNK < 1 << (ARRIVED_SHIFT - ARRIVED_UNIT) && 32 < 1 << (64 - ARRIVED_SHIFT), "sum and count have room");
   return chunks <= 32 && n_traj * chunks <= 5120;
 }
 
