@@ -425,17 +425,16 @@ extern "C" pg_status pg_state(const pg_ctx* c, int32_t* M, int32_t* cur_x, int32
 
 static char* ws(pg_ctx* c, size_t off) { return (char*)c->buf.workspace + off; }
 
-extern "C" pg_status pg_init_group(pg_ctx* c, uint64_t seed, void* stream) {
+// `sums`: with the sums of all steps' noise for sample_rows, in ws_logr
+static pg_status init_group(pg_ctx* c, uint64_t seed, bool sums, hipStream_t s) {
   if (!c || !c->bound) return fail(PG_EINVAL, "pg_init_group: context not bound");
-  hipStream_t s = (hipStream_t)stream;
   const pg_config& f = c->cfg;
   c->seed = seed;
   c->M = c->M0; c->cur_x = 0; c->cur_id = 0;
   c->pending_gather = false; c->net_fresh = false;
   c->evals = 0; c->updates = 0; c->steps_done = 0; c->advantages_done = false;
   for (int g = 0; g <= f.P; ++g) c->offsets[g] = g * f.N;
-  const bool rows = f.net_kind != PG_NET_NONE && small_rows_takes(c);             // sample_rows takes the sums of the noise from here
-  PG_TRY(launch_init_group(c->buf.x[0], f.P, f.N, c->d, seed, rows ? (double*)ws(c, c->ws_logr) : nullptr, f.T, c->buf.group_offsets,
+  PG_TRY(launch_init_group(c->buf.x[0], f.P, f.N, c->d, seed, sums ? (double*)ws(c, c->ws_logr) : nullptr, f.T, c->buf.group_offsets,
                            c->buf.orig_id[0], c->buf.group_of, c->buf.logp_hist, (size_t)f.T * c->M0, c->buf.logp_sum, c->buf.status,
                            (uint64_t*)ws(c, c->ws_arrived), s));
   if (c->buf.x_hist)
@@ -450,6 +449,8 @@ extern "C" pg_status pg_init_group(pg_ctx* c, uint64_t seed, void* stream) {
   c->initialised = true;
   return PG_OK;
 }
+
+extern "C" pg_status pg_init_group(pg_ctx* c, uint64_t seed, void* stream) { return init_group(c, seed, false, (hipStream_t)stream); }
 
 // mod_row: see NetBatch
 static pg_status forward_step(pg_ctx* c, int step, int mod_row, hipStream_t s) {
@@ -714,7 +715,7 @@ extern "C" pg_status pg_policy_ratio(pg_ctx* c, const uint16_t* weights_new, dou
 static pg_status sample_rows(pg_ctx* c, hipStream_t s) {
   const pg_config& f = c->cfg;
   const int together = c->net.mod_steps;
-  const double* sums = (const double*)ws(c, c->ws_logr);         // by pg_init_group
+  const double* sums = (const double*)ws(c, c->ws_logr);         // by init_group
   auto update = [&](int step) {
     return RowsUpdate{(float)c->A[step], (float)c->B[step], (float)c->C[step], (uint32_t)c->seed, (uint32_t)(c->seed >> 32), (uint32_t)step,
                       c->pending_gather ? c->buf.sel_idx : nullptr, c->buf.orig_id[c->cur_id], c->buf.x[1 - c->cur_x],
@@ -759,8 +760,10 @@ static pg_status sample_rows(pg_ctx* c, hipStream_t s) {
 }
 
 extern "C" pg_status pg_sample_group(pg_ctx* c, uint64_t seed, void* stream) {
-  PG_TRY(pg_init_group(c, seed, stream));
-  if (c->cfg.net_kind != PG_NET_NONE && small_rows_takes(c)) {
+  if (!c) return fail(PG_EINVAL, "pg_sample_group: null context");
+  const bool rows = c->cfg.net_kind != PG_NET_NONE && small_rows_takes(c);
+  PG_TRY(init_group(c, seed, rows, (hipStream_t)stream));
+  if (rows) {
     PG_TRY(sample_rows(c, (hipStream_t)stream));
     return pg_advantages(c, stream);
   }

@@ -575,6 +575,24 @@ def test_loop_launches_against_the_single_kernels(lib, P, N, C, H, W):
     lib.pg_destroy(ctx)
 
 
+@pytest.mark.parametrize("C,H,W", [(4, 16, 16), (16, 16, 20)])
+def test_init_group_draws_the_initial_latents_alone(lib, C, H, W):
+    """A narrow network's run, whose loop in one call wants sums of the noise of all steps: they are not made for a caller who goes step by
+    step.  Of the scratch memory nothing but a word per trajectory is written."""
+    P, N, T = 1, 8, 40
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind="adaln", P=P, N=N, C=C, H=H, W=W, D=64, heads=2, Lc=0, Dc=0, blocks=1, T=T, schedule=[[]], Li=H * W // 4, d=C * H * W)
+    w = workloads.make_weights(cfg)
+    ctx, buf = _gpu_ctx(lib, cfg, w, workloads.make_inputs(cfg, w))
+    words = buf.workspace[:buf.workspace.numel() // 8 * 8].view(torch.int64)
+    before = words.clone()
+    lib.pg_init_group(ctx, 5)
+    torch.cuda.synchronize()
+    written = int((words != before).sum())
+    lib.pg_destroy(ctx)
+    assert written <= N + 1, f"{written} words written"
+
+
 # log-probs by the last workgroup to arrive and by a second launch, on either side of where one gives way to the other: 5120 chunks in
 # a launch (1024 x 5, the last of them of four elements; the launches after the prunes have fewer) and 32 of a trajectory
 @pytest.mark.parametrize("P,N,C,H,W", [(16, 64, 1, 2, 8194), (41, 25, 1, 2, 8194), (2, 4, 16, 64, 128), (2, 4, 16, 64, 130)])
