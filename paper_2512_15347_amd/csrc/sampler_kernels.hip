@@ -554,7 +554,7 @@ pg_status launch_init_group(float* x, int P, int N, int64_t d, uint64_t seed, do
   const int64_t M0 = (int64_t)P * N;
   PG_TRY(check_stream_shape(M0, d));
   const int chunks = (int)chunks_per_traj(d);
-  const bool noise_here = sums && chunks == 1 && M0 * steps <= (1 << 24);
+  const bool noise_here = sums && chunks == 1 && M0 * steps <= (1 << 23);    // a launch has room for less than 2^24 workgroups
   InitGroup a{x, (int)(d / 4), chunks, (uint32_t)seed, (uint32_t)(seed >> 32), sums, steps, P, N, offsets, ids, group_of,
               (uint32_t*)logp_hist, hist_n, logp_sum, status, arrived, (int)(M0 * chunks), noise_here ? (int)(M0 * steps) : 0};
   const size_t n = std::max(hist_n, (size_t)M0) + 1;

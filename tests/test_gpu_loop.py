@@ -593,6 +593,29 @@ def test_init_group_draws_the_initial_latents_alone(lib, C, H, W):
     assert written <= N + 1, f"{written} words written"
 
 
+@pytest.mark.parametrize("M0,T,C,H,W", [(1, 65600, 16, 16, 18), (128, 65536, 4, 2, 2), (256, 65536, 4, 2, 2)])
+def test_narrow_loop_of_very_many_steps(lib, M0, T, C, H, W):
+    """As many steps times trajectories as one launch makes the sums of the noise for, and more: log-probs of the first steps, the last ones
+    and those around 32768 and 65536 as one update gives them."""
+    d = C * H * W
+    say(f"{T} steps of {M0} trajectories of {d}")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind="adaln", P=1 if M0 < 64 else M0 // 64, N=min(M0, 64), C=C, H=H, W=W, D=64, heads=2, Lc=0, Dc=0, blocks=1, T=T, Li=H * W // 4, d=d,
+               schedule=[[]] * (1 if M0 < 64 else M0 // 64))
+    w = workloads.make_weights(cfg)
+    ctx, buf = _gpu_ctx(lib, cfg, w, workloads.make_inputs(cfg, w))
+    lib.pg_sample_group(ctx, 5)
+    lib.pg_check(ctx)
+    C_s = lib.pg_get_tables(ctx, T)["C"]
+    lib.pg_destroy(ctx)
+    x, ids = torch.zeros(M0, d, device=DEV), torch.arange(M0, dtype=torch.int32, device=DEV)
+    out, logp, part = torch.zeros(M0, d, device=DEV), torch.zeros(M0, device=DEV), torch.zeros(lib.pg_step_scratch_floats(M0, d), device=DEV)
+    for s in (0, 1, 32767, 32768, 65535, 65536, T - 1):
+        if s < T:
+            lib.pg_sde_step_logprob(x, x, out, logp, None, None, None, ids, M0, d, 1.0, 0.0, float(C_s[s]), 5, s, part)
+            assert torch.equal(buf.logp_hist[s], logp), s
+
+
 # log-probs by the last workgroup to arrive and by a second launch, on either side of where one gives way to the other: 5120 chunks in
 # a launch (1024 x 5, the last of them of four elements; the launches after the prunes have fewer) and 32 of a trajectory
 @pytest.mark.parametrize("P,N,C,H,W", [(16, 64, 1, 2, 8194), (41, 25, 1, 2, 8194), (2, 4, 16, 64, 128), (2, 4, 16, 64, 130)])
