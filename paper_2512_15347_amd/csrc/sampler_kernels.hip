@@ -421,7 +421,9 @@ __global__ __launch_bounds__(256) void surrogate_kernel(const double* __restrict
 static pg_status check_stream_shape(int64_t n_traj, int64_t d) {
   if (n_traj < 0 || d <= 0) return fail(PG_EINVAL, "n_traj = %lld, d = %lld", (long long)n_traj, (long long)d);
   if (d % 4 != 0) return fail(PG_ESHAPE, "latent size d = %lld must be a multiple of 4", (long long)d);
-  if (d / 4 > INT32_MAX || n_traj * chunks_per_traj(d) > INT32_MAX)
+  // a launch takes less than 2^32 lanes; of more, HIP refuses a multiple of 2^32 and starts the remainder of any other number
+  constexpr int64_t MOST = (1ll << 32) / STREAM_THREADS;
+  if (d / 4 > INT32_MAX || n_traj >= MOST || n_traj * chunks_per_traj(d) >= MOST)
     return fail(PG_ESHAPE, "n_traj * ceil(d/4096) exceeds the grid limit");
   return PG_OK;
 }
@@ -456,12 +458,12 @@ static pg_status launch_logprob_finish(const float* partials, int chunks, int64_
   return PG_OK;
 }
 
-// Whether the update of chunks has a lane for every 16 bytes: where a launch may have so many (HIP takes less than 2^32 of them; with
-// 256 a chunk four times as many trajectories), and where few of them would have nothing to do.  A last chunk of a few elements
-// costs 1024 lanes as much as a whole one, 256 lanes less: us with 256 / 1024 for trajectories of two chunks 4096 x 4100
-// 49.3 / 54.9, 8192 x 5120 96.5 / 102.6, x 6144 109.4 / 111.8, x 7168 125.5 / 120.0, of three 8192 x 8448 136.9 / 141.5,
-// x 10240 167.2 / 159.6, of four x 12544 209.5 / 215.2, x 13312 220.0 / 221.6, x 14336 243.2 / 231.6, of five x 16388
-// 283.4 / 268.1, of six x 20484 385 / 360.
+// Whether the update of chunks has a lane for every 16 bytes: where a launch may have so many (HIP takes less than 2^32 of them; with 256
+// a chunk four times as many trajectories, see check_stream_shape), and where few of them would have nothing to do.  A last chunk of a
+// few elements costs 1024 lanes as much as a whole one, 256 lanes less: us with 256 / 1024 for trajectories of two chunks 4096 x 4100
+// 49.3 / 54.9, 8192 x 5120 96.5 / 102.6, x 6144 109.4 / 111.8, x 7168 125.5 / 120.0, of three 8192 x 8448 136.9 / 141.5, x 10240 167.2 /
+// 159.6, of four x 12544 209.5 / 215.2, x 13312 220.0 / 221.6, x 14336 243.2 / 231.6, of five x 16388 283.4 / 268.1, of six x 20484 385 /
+// 360.
 static bool lane_per_access(int64_t n_traj, int64_t d) {
   const int64_t chunks = chunks_per_traj(d);
   return n_traj * chunks < (1ll << 32) / CHUNK_THREADS && (chunks > 4 || 6 * d >= 5 * chunks * STREAM_CHUNK);

@@ -193,6 +193,18 @@ def test_context_free_argument_checks_need_no_gpu():
     assert "null" in pg.pg_last_error().lower() or len(pg.pg_last_error()) > 0
 
 
+@pytest.mark.parametrize("n,d,fits", [((1 << 24) - 1, 4, True), (1 << 24, 4, False), ((1 << 24) + 1000, 4, False), (1 << 62, 4, False),
+                                      ((1 << 23) - 1, 4100, True), ((1 << 23) + 1, 4100, False), (1, 1 << 38, False)])
+def test_more_chunks_than_a_launch_has_lanes_for_are_refused(n, d, fits):
+    """2^24 workgroups of 256 lanes: HIP starts the remainder over 2^32 lanes without an error.  What fits gets as far as its null pointers."""
+    lib = C.CDLL(pg.LIB_PATH)
+    n, d, f, z = C.c_int64(n), C.c_int64(d), C.c_double(1.0), None
+    calls = (lib.pg_init_latents(z, z, n, d, C.c_uint64(0), z),
+             lib.pg_sde_step_logprob(z, z, z, z, z, z, z, z, n, d, f, f, f, C.c_uint64(0), C.c_uint32(0), z, z),
+             lib.pg_preview_reward(z, z, z, z, n, d, f, f, f, z, z), lib.pg_compact_gather(z, z, z, n, d, z))
+    assert all(status == (pg.PG_EINVAL if fits else pg.PG_ESHAPE) for status in calls), calls
+
+
 def test_attention_refuses_value_rows_that_end_inside_a_tile():
     """The kernels read value rows in whole tiles of 64 keys: a shorter padding is an error before anything is launched."""
     for kernel in (0, 1, 2):
