@@ -576,7 +576,7 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
                      Ri, mods[1] + slot * D, mods[1] + (slot + 1) * D, f.Lc});
   };
 
-  const bool chain = row_chain_takes(D, c->M0);     // what lies between two attentions in one launch
+  const bool chain = row_chain_takes(D, c->M0, dual ? Li : L, dual ? f.Lc : 0);     // what lies between two attentions in one launch
 
   // ---- dual-stream blocks: two planes (image rows, context rows), joint q | k and V^T ----
   if (dual) {

@@ -424,12 +424,28 @@ pg_status launch_width(const ChainArgs& a, ChainKind kind, hipStream_t s) {
 //   cross-attention: width 192, 9 of 88 876 / 630, width 256, 36 of 290 1687 / 1359, 4 of 88 960 / 875
 //   dual-stream: width 128, 8 of 200 682 / 436, width 192, 64 of 256 1298 / 896, width 256, 4 of 88 695 / 678, 64 of 256 1420 / 1078
 // A width of 320 won in a band of sizes alone (64 of 256 1683 / 1448, 4 of 88 722 / 880, x 384 of 256 4903 / 5480), and so did 384.
-bool row_chain_takes(int D, int64_t M) { return (D == 128 || D == 192 || D == 256) && M <= 65535; }     // the limit is the grid's
+//
+// Its time goes with the workgroups, that of a launch per layer with the rows, and a trajectory's last workgroup may have few: us a
+// launch per layer / here, two blocks, width 192: 9344 trajectories of 16 tokens 1327 / 1687, 7488 of 20 1292 / 1464, 1472 of 100
+// 1103 / 1128, 1344 of 110 1156 / 1068, 1088 of 132 1125 / 1075; few workgroups: 1024 of 8 160 / 193, 512 of 16 141 / 127, 384 of 1
+// 100 / 105, 256 of 4 96 / 66; width 256: 1472 of 100 1417 / 1591, 1664 of 90 1512 / 1441, 4672 of 256 10966 / 10307; dual-stream, width
+// 256: 1024 of 110 and 33 1544 / 1598, 384 of 64 and 5 368 / 312.  Hence at most so many workgroups of 32 rows: a number and,
+// in thousandths, as many as the rows would fill without gaps, fitted to 557 sizes of 16 to 1200000 rows.  Of these 9 are slower here
+// than by layer (by 11 % at most, 320 trajectories of 4 tokens) and 7 would be faster (by 6 %).
+struct ChainLimit { int wgs, fill; };
+constexpr ChainLimit CHAIN_LIMIT[3][2] = {{{950, 1625}, {1025, 2650}}, {{310, 1180}, {525, 1325}}, {{225, 1050}, {350, 1175}}};   // one stream, two
+bool row_chain_has(int D, int64_t M) { return (D == 128 || D == 192 || D == 256) && M <= 65535; }       // of trajectories
+bool row_chain_takes(int D, int64_t M, int L, int L2) {
+  if (!row_chain_has(D, M)) return false;
+  auto wgs = [&](int rows) { return M * ((L + rows - 1) / rows + (L2 + rows - 1) / rows); };
+  const ChainLimit most = CHAIN_LIMIT[D / 64 - 2][L2 > 0];
+  return wgs(16) <= 256 || 32000 * (wgs(32) - most.wgs) <= most.fill * M * (L + L2);      // up to 256, a compute unit each
+}
 
 pg_status launch_row_chain(const ChainArgs& a, int D, ChainKind kind, hipStream_t s) {
   const bool dual = a.s[1].L > 0, next = kind == CHAIN_BLOCK || kind == CHAIN_START, mlp = kind == CHAIN_BLOCK || kind == CHAIN_LAST;
   const int L = a.s[0].L + a.s[1].L;
-  bool complete = row_chain_takes(D, a.M) && a.M >= 1 && a.mod_of && (kind == CHAIN_LAST || a.qk) &&
+  bool complete = row_chain_has(D, a.M) && a.M >= 1 && a.mod_of && (kind == CHAIN_LAST || a.qk) &&
                   (!next || (a.vt && a.Lpad % 64 == 0 && a.Lpad >= L)) && (dual ? next && (a.norm_hd == 32 || a.norm_hd == 64) : a.norm_hd == 0);
   for (int i = 0; i < (dual ? 2 : 1); ++i) {
     const ChainStream& c = a.s[i];

@@ -29,7 +29,8 @@ struct ChainArgs {
   float out_scale;                                 // of the queries
   int norm_hd;                                     // head width of queries and keys that are RMS-normalised (EPI_QKV), or 0
 };
-bool row_chain_takes(int D, int64_t M);            // whether networks of this width, for at most M trajectories, run that way
+// whether networks of this width, for at most M trajectories of L (and L2, of the second stream) tokens, run that way
+bool row_chain_takes(int D, int64_t M, int L, int L2);
 pg_status launch_row_chain(const ChainArgs& a, int D, ChainKind kind, hipStream_t s);
 
 }  // namespace pg

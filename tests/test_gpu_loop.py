@@ -436,6 +436,26 @@ def test_network_output_of_rows_between_attentions(lib, kind, D, heads, H, W, Lc
     assert torch.equal(outs[0], outs[1])
 
 
+# what lies between two attentions in one launch or in a launch per layer, on either side of where one gives way to the other; token counts
+# that store the transposed values in units of four and one by one
+@pytest.mark.parametrize("kind,D,heads,H,W,Lc,P,N,rows", [
+    ("adaln", 256, 4, 10, 14, 0, 6, 44, True), ("adaln", 256, 4, 10, 14, 0, 5, 53, False), ("cross", 128, 4, 6, 6, 5, 33, 53, True),
+    ("cross", 128, 4, 6, 6, 5, 35, 50, False), ("mmdit", 192, 3, 4, 4, 3, 6, 51, True), ("mmdit", 192, 3, 4, 4, 3, 7, 44, False),
+    ("adaln", 192, 6, 8, 10, 0, 20, 59, True), ("adaln", 192, 6, 8, 10, 0, 197, 6, False), ("mmdit", 256, 4, 10, 14, 18, 6, 55, True),
+    ("mmdit", 256, 4, 10, 14, 18, 9, 37, False)])
+def test_network_output_by_rows_and_by_layers(lib, kind, D, heads, H, W, Lc, P, N, rows):
+    say(f"by rows or by layers, {kind} width {D}, {P * N} trajectories")
+    cfg = workloads.get_config("cfg3_small")
+    cfg.update(kind=kind, P=P, N=N, H=H, W=W, D=D, heads=heads, Lc=Lc, Dc=128 if Lc else 0, blocks=2, T=1, schedule=[[]] * P,
+               Li=H * W // 4, d=4 * H * W)
+    lib.pg_profile_begin(1000)
+    _check_sharp_network(lib, cfg, kind, 7 * (128 / D) ** 0.5 if H * W > 16 else 1, (0, N, P * N - 1))
+    launches = lib.pg_profile_read(0)["launches"]
+    lib.pg_profile_end()
+    before = 1 + (cfg["blocks"] - 1 if kind == "cross" else 0) if Lc else 0      # the context's projections
+    assert (launches - before <= 2 * 2 + 3) == rows, launches
+
+
 @pytest.mark.parametrize("kind,D,P,N,H,W,Lc", [("adaln", 128, 1, 8, 16, 16, 0), ("joint", 64, 2, 3, 10, 10, 39), ("joint", 192, 1, 3, 10, 10, 6),
                                                 ("adaln", 128, 20, 60, 2, 2, 0)])
 def test_profile_counts_the_work_of_a_network(lib, kind, D, P, N, H, W, Lc):
