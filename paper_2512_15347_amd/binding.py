@@ -125,7 +125,7 @@ def _check(status):
 
 def _ptr(t):
     """Device (or host) address of a torch tensor / None."""
-    if t is None or t.__class__ is int:
+    if t is None or isinstance(t, int):
         return t
     assert t.is_contiguous(), "the C ABI takes contiguous buffers"
     return t.data_ptr()

@@ -205,6 +205,14 @@ def test_more_chunks_than_a_launch_has_lanes_for_are_refused(n, d, fits):
     assert all(status == (pg.PG_EINVAL if fits else pg.PG_ESHAPE) for status in calls), calls
 
 
+def test_addresses_of_any_integer_type_are_taken():
+    class Address(int):
+        pass
+    import enum
+    assert pg._ptr(None) is None and pg._ptr(4096) == 4096 and pg._ptr(Address(4096)) == 4096
+    assert pg._ptr(enum.IntEnum("E", {"A": 64}).A) == 64 and pg._ptr(False) == 0
+
+
 def test_attention_refuses_value_rows_that_end_inside_a_tile():
     """The kernels read value rows in whole tiles of 64 keys: a shorter padding is an error before anything is launched."""
     for kernel in (0, 1, 2):
