@@ -140,9 +140,10 @@ def _stream(stream):
     global _current_stream
     if _current_stream is None:
         import torch
-        # the handle alone, without the stream object around it, which costs more than the launch of a small kernel
-        device, raw = torch.cuda.current_device, torch._C._cuda_getCurrentRawStream
-        _current_stream = lambda: raw(device())
+        # the handle alone, without the stream object around it, which costs more than the launch of a small kernel; torch keeps this
+        # function to itself
+        device, raw = torch.cuda.current_device, getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _current_stream = (lambda: raw(device())) if raw else (lambda: torch.cuda.current_stream().cuda_stream)
     return _current_stream()
 
 

@@ -213,6 +213,16 @@ def test_addresses_of_any_integer_type_are_taken():
     assert pg._ptr(enum.IntEnum("E", {"A": 64}).A) == 64 and pg._ptr(False) == 0
 
 
+def test_current_stream_without_torchs_own_function(monkeypatch):
+    import types
+
+    import torch
+    monkeypatch.setattr(pg, "_current_stream", None)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=77))
+    assert pg._stream(None) == 77 and pg._stream(5) == 5
+
+
 def test_attention_refuses_value_rows_that_end_inside_a_tile():
     """The kernels read value rows in whole tiles of 64 keys: a shorter padding is an error before anything is launched."""
     for kernel in (0, 1, 2):
