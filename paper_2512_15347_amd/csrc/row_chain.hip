@@ -76,11 +76,17 @@ struct Weights {
   template <int I = 0> __device__ __forceinline__ void begin(Source<false> p) const {
     if constexpr (I < C::SLOTS) { request<I>(p); begin<I + 1>(p); }
   }
-  // The launch's weights into the L2 of this XCD: its workgroups (every eighth of the grid) touch a share of the 128-byte lines each.
-  // They all run through the weights side by side, so without this nearly every piece of theirs was waited for from beyond the L2.
+  // The launch's weights (of the workgroup's stream) into the L2 of this XCD: its workgroups (every eighth of the grid) touch a share of
+  // the 128-byte lines each.  They all run through the weights side by side, so without this nearly every piece of theirs was waited
+  // for from beyond the L2.  The first product waits for these loads, too, so where few workgroups would have many each they are left
+  // out: four blocks of width 256, 1, 4, 8, 64 trajectories of one stream and 100, 100, 256, 256 tokens, us with / without them 179 / 139,
+  // 145 / 139, 143.6 / 144.7, 154 / 156; from eight workgroups to an XCD on they pay.  In the dual-stream network a share is that of the
+  // workgroup's number among all, so some lines of either stream stay cold; every workgroup touching those of both streams takes
+  // longer (8 of 128 tokens 138.5 / 144.8, 4 of 88 156 / 163).
   template <int KIND> __device__ __forceinline__ void warm(const ChainStream& a, unsigned char* touched, int wave) const {
     constexpr int LOADS = D * D * 2 / (128 * 64);    // of 64 lines, for the weights of a product
     const int id = blockIdx.y * gridDim.x + blockIdx.x, wgs = (gridDim.x * gridDim.y + 7) / 8;
+    if (wgs < 8) return;
     const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)touched);
     for (int k = id / 8 * C::WAVES + wave; k < products<KIND>() * LOADS; k += wgs * C::WAVES) {
       const int p = k / LOADS;
