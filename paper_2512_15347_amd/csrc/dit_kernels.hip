@@ -533,7 +533,7 @@ pg_status net_forward(pg_ctx* c, int step, const NetBatch& batch, const uint16_t
 
   // ---- narrow networks on short sequences: the rest in one launch, or one per block ----
   if (small) {
-    if (small_rows_takes(c)) return net_rows(c, batch, RowsPass{batch.x, true, nullptr, nullptr, nullptr, false}, weights, s);
+    if (small_rows_evaluates(c, M)) return net_rows(c, batch, RowsPass{batch.x, true, nullptr, nullptr, nullptr, false}, weights, s);
     return launch_small_net(small_args(c, n, batch, mod, fmod), D, hd, s);
   }
 

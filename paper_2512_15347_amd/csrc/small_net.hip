@@ -857,19 +857,30 @@ pg_status launch_small_net(const SmallNetArgs& a, int D, int hd, hipStream_t s) 
   return hd == 32 ? launch_width<32>(a, D, s) : launch_width<64>(a, D, s);
 }
 
-
 int small_rows_tiles(const pg_ctx* c) { return (c->L + 15) / 16; }
 
 // A launch per block pays while its workgroups are about as many as the compute units hold; with more, they read the weights more
-// often than one workgroup per trajectory does.  Loops of six steps and two blocks, us, one workgroup per trajectory / per 16 rows:
-//   width 128,  64 tokens: 16 row tiles in the context 295 / 193, 256: 296 / 222,  512: 303 / 306, 1024: 317 / 487
-//   width 128,  90 tokens:                         24: 353 / 194, 384: 360 / 296,  768: 367 / 402
-//   width  64,  64 tokens:                         16: 186 / 161, 256: 194 / 184,  512: 197 / 211
-//   width  64, 178 tokens:                         48: 337 / 186, 768: 349 / 334, 1536: 352 / 497
-//   up to 16 tokens: width 128 512: 370 / 289, 1024: 649 / 486; width 64 512: 243 / 183, 1024: 405 / 268, 2048: 688 / 693
+// often than one workgroup per trajectory does.  A compute unit holds one of width 128, two of width 64, so the lines lie at 256 and 512
+// workgroups; a loop takes more of them than an evaluation alone, since its updates cost no launch, and one of few tokens fewer, since
+// one workgroup per trajectory then is a short launch.  How many times as fast as one workgroup per trajectory, loops of six steps with a
+// prune / evaluations alone, of 1, 2 and 4 blocks, row tiles x trajectories:
+//   width 128, 2 tiles: 256 1.25 1.28 1.24 / 1.03 1.07 1.08, 288 1.09 1.03 0.96 / 0.82 0.79 0.75
+//              4 tiles: 256 1.54 1.46 1.43 / 1.23 1.22 1.19, 512 1.21 1.13 1.03 / 0.84 0.82 0.80, 544 0.91 0.80 0.75 / 0.73 0.69 0.64
+//              6 tiles: 504 1.37 1.34 1.25 / 0.99 0.98 0.96, 528 1.08 0.97 0.91 / 0.80 0.82 0.76
+//   width  64, 2 tiles: 128 1.22 1.07 1.04 / 0.97 0.96 0.98, 256 1.20 1.05 1.01 / 1.07 0.99 0.87, 288 1.11 1.03 0.94 / 0.95 0.88 0.85
+//              4 tiles: 128 1.27 1.22 1.15 / 1.04 0.94 0.99, 256 1.26 1.21 1.11 / 1.01 0.98 0.94, 352 1.19 1.05 0.93 / 0.88 0.85 0.78
+//              8 tiles: 512 1.40 1.32 1.23 / 1.05 1.03 1.00, 544 1.26 1.19 1.06 / 0.91 0.87 0.82, 768 1.20 1.07 0.97 / 0.85 0.85 0.81
+//             12 tiles: 480 1.67 1.57 1.50 / 1.13 1.16 1.14, 768 1.24 1.14 1.04 / 0.91 0.94 0.89
+//   up to 16 tokens: width 128 512 1.45 1.36 1.36 / 1.24 1.35 1.34, 896 1.43 1.43 1.44 / 1.40 1.43 1.44; width 64 128 1.26 1.16 1.10 /
+//              1.01 0.99 1.06, 896 1.59 1.60 1.66 / 1.48 1.55 1.64
 bool small_rows_takes(const pg_ctx* c) {
-  const int tiles = small_rows_tiles(c), most = tiles == 1 ? 1024 : c->cfg.D == 64 ? 256 + 42 * tiles : 384 + 32 * tiles;
+  const int tiles = small_rows_tiles(c);
+  const int most = tiles == 1 ? 1024 : c->cfg.D == 64 ? (tiles <= 4 ? 256 : tiles < 8 ? 512 : 64 * tiles) : tiles == 2 ? 256 : 512;
   return small_net_takes(c) && chunks_per_traj(c->d) <= 4 && (int64_t)c->M0 * tiles <= most;
+}
+bool small_rows_evaluates(const pg_ctx* c, int M) {
+  const int tiles = small_rows_tiles(c);
+  return small_rows_takes(c) && (int64_t)M * tiles <= (tiles == 1 ? 1024 : tiles > 4 ? 512 : c->cfg.D == 64 ? 128 : 256);
 }
 
 template <int D, int HD, int T, int KIND>

@@ -49,7 +49,8 @@ struct RowsArgs {
   int update;                                      // whether `up` is made
   RowsUpdate up;
 };
-bool small_rows_takes(const pg_ctx* c);
+bool small_rows_takes(const pg_ctx* c);                // whether a loop in one call runs that way
+bool small_rows_evaluates(const pg_ctx* c, int M);     // whether an evaluation of M trajectories alone does (the same bits either way)
 int small_rows_tiles(const pg_ctx* c);
 // block -1: a step's first rows; start: the last block's launch starts the next step (an update goes with it).  The caller sets x, hs,
 // the buffers, mod_next and the update.

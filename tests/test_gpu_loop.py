@@ -530,6 +530,15 @@ def test_narrow_loops_by_rows_and_by_trajectories_agree(lib, kind, D, heads, C, 
         assert torch.equal(runs[0][k], runs[2][k]), f"by rows and by trajectories: {k}"
 
 
+# on either side of where a loop, and where an evaluation alone, of narrow networks takes a workgroup per 16 rows: 2, 4 and 6 row tiles of
+# width 128, 4, 8 and 12 of width 64
+@pytest.mark.parametrize("D,H,W,P", [(128, 8, 12, 32), (128, 8, 12, 33), (128, 16, 16, 16), (128, 16, 16, 17), (128, 16, 16, 32), (128, 16, 24, 21),
+                                     (128, 16, 24, 22), (64, 16, 16, 8), (64, 16, 16, 9), (64, 16, 16, 16), (64, 16, 16, 17), (64, 16, 32, 16),
+                                     (64, 16, 32, 17), (64, 16, 46, 16), (64, 16, 46, 17)])
+def test_narrow_loops_on_either_side_of_the_rows_limits(lib, D, H, W, P):
+    test_narrow_loops_by_rows_and_by_trajectories_agree(lib, "adaln", D, 2, 4, H, W, 0, 2, P)
+
+
 # The loop's launches (a prune's and the advantages' rewards by group, a step's log-probs by the last workgroup to arrive) against the
 # entry points of the single kernels: latents of one chunk with little and with more to read for a group, of 2 with many trajectories,
 # of 5, 16 and 17 chunks, and too large for the sums by arrival
