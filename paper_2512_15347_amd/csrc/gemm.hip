@@ -550,19 +550,19 @@ static pg_status launch_tile(const GemmBatch<NPROB>& batch, hipStream_t s) {
 // round, part empty, counts half as empty as it is: tiles of a long launch drift apart), each an edge (prologue and epilogue,
 // by what the epilogue does) and K / 64 steps; where it holds several tiles at a time (`several`), a lone one's steps take
 // their latency (`idle`) whatever else there is, otherwise they rise from `idle` to `full` as the chip fills.  The constants are
-// microseconds fitted to every tile's time at 620 shapes (16 to 280000 rows, widths 64 to 1536, all layers of the network); over
-// these the chosen tile is on average 3 % behind the best one (by the constants before, among the tiles there were, 11 %).
+// microseconds fitted to every tile's time in 1892 layers (256 to 450000 rows, 16 widths from 64 to 1536); with the chosen tile a block
+// of the network takes 0.2 % longer than with the best one, layer by layer, and 8 % at most.
 struct TileShape { int bm, bn; bool several; double fixed, resid, qkv, out, idle, full; };
 constexpr TileShape TILES[9] = {
-    {256, 256, false, 0, 11.1, 9.9, 6.2, 1.31, 1.47},
-    {192, 256, false, 0, 8.9, 8.2, 5.6, 0.29, 1.14},
-    {128, 128, true, 3.3, 3.3, 3.0, 1.4, 0.56, 0.49},
-    {160, 256, false, 0, 7.4, 8.0, 5.6, 0.68, 0.99},
-    {224, 256, false, 0, 10.8, 9.0, 5.9, 0.96, 1.32},
-    {128, 64, true, 3.8, 2.1, 1.6, 0.94, 0.21, 0.28},
-    {64, 64, true, 4.4, 0.84, 0.34, 0.16, 0.26, 0.19},
-    {128, 256, false, 0, 6.9, 7.1, 5.3, 0.55, 0.81},
-    {64, 64, true, 4.4, 0.87, 0.46, 0.28, 0.16, 0.18}};
+    {256, 256, false, 0, 11.7, 11.3, 7.16, 1.76, 1.44},
+    {192, 256, false, 0, 8.42, 8.79, 6.22, 0.396, 1.14},
+    {128, 128, true, 3.41, 2.58, 1.98, 1.66, 0.83, 0.479},
+    {160, 256, false, 0, 7.29, 8.98, 5.48, 0.801, 0.969},
+    {224, 256, false, 0, 10.2, 9.5, 6.72, 0.976, 1.32},
+    {128, 64, true, 3.76, 2.04, 1.5, 1.24, 0.23, 0.28},
+    {64, 64, true, 4.13, 0.844, 0.295, 0.131, 0.304, 0.196},
+    {128, 256, false, 0, 7.28, 9.94, 5.89, 0.457, 0.763},
+    {64, 64, true, 4.3, 0.897, 0.413, 0.293, 0.204, 0.169}};
 template <int NPROB>
 static int pick_tile(const GemmBatch<NPROB>& batch, int epilogue) {
   const GemmArgs& a = batch.g[0];
