@@ -317,6 +317,15 @@ pg_status pg_gemm_bf16(const uint16_t *A, int64_t lda, const uint16_t *W, int64_
                        const uint16_t *bias, float *C, int64_t ldc, int64_t M, int64_t N, int64_t K,
                        void *stream);
 
+/* Test hooks: the same product with one of the launcher's tiles, 1 to 9 (256 x 256, 192 x 256, 128 x 128, 160 x 256, 224 x 256, 128 x 64,
+ * 64 x 64, 128 x 256 and 64 x 64 with three stages of either operand), 0 is the launcher's choice for these sizes, which pg_gemm_tile
+ * tells without a launch (0 for sizes below 1).  accumulate: C += A W^T + bias, as the layers that add into the residual stream.  The
+ * result does not depend on the tile. */
+int32_t pg_gemm_tile(int64_t M, int64_t N, int64_t K, int32_t accumulate);
+pg_status pg_gemm_bf16_tile(const uint16_t *A, int64_t lda, const uint16_t *W, int64_t ldw,
+                            const uint16_t *bias, float *C, int64_t ldc, int64_t M, int64_t N, int64_t K,
+                            int32_t accumulate, int32_t tile, void *stream);
+
 /* Softmax attention on MFMA, exposed for unit parity: q [B, Lq, heads*hd], k [B, Lk, heads*hd]
  * row-major bf16; vt [B, heads*hd, Lk_pad] (values transposed, Lk_pad = Lk rounded up to 64);
  * out [B, Lq, heads*hd] bf16; hd 32 or 64; logits scaled by 1/sqrt(hd). */

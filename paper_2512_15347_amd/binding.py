@@ -99,6 +99,8 @@ _SIGNATURES = {
     "pg_compact_gather": (_i32, [_vp, _vp, _vp, _i64, _i64, _vp]),
     "pg_group_advantages": (_i32, [_vp, _vp, _i32, _f64, _vp, _vp]),
     "pg_gemm_bf16": (_i32, [_vp, _i64, _vp, _i64, _vp, _vp, _i64, _i64, _i64, _i64, _vp]),
+    "pg_gemm_tile": (_i32, [_i64, _i64, _i64, _i32]),
+    "pg_gemm_bf16_tile": (_i32, [_vp, _i64, _vp, _i64, _vp, _vp, _i64, _i64, _i64, _i64, _i32, _i32, _vp]),
     "pg_attention_bf16": (_i32, [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _vp]),
     "pg_attention_kernel": (_i32, [_i32] * 5),
     "pg_attention_network": (_i32, [_vp, _vp, _vp, _vp] + [_i32] * 7 + [_vp]),
@@ -424,6 +426,14 @@ def pg_group_advantages(rewards, group_offsets, n_groups, eps, adv, stream=None)
 
 def pg_gemm_bf16(A, lda, W, ldw, bias, Cout, ldc, M, N, K, stream=None):
     _check(_lib.pg_gemm_bf16(_ptr(A), lda, _ptr(W), ldw, _ptr(bias), _ptr(Cout), ldc, M, N, K, _stream(stream)))
+
+
+def pg_gemm_tile(M, N, K, accumulate=False):
+    return int(_lib.pg_gemm_tile(M, N, K, int(accumulate)))
+
+
+def pg_gemm_bf16_tile(A, lda, W, ldw, bias, Cout, ldc, M, N, K, accumulate=False, tile=0, stream=None):
+    _check(_lib.pg_gemm_bf16_tile(_ptr(A), lda, _ptr(W), ldw, _ptr(bias), _ptr(Cout), ldc, M, N, K, int(accumulate), tile, _stream(stream)))
 
 
 def pg_attention_bf16(q, k, vt, out, B, Lq, Lk, heads, hd, stream=None):

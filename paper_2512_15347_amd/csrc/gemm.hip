@@ -587,11 +587,11 @@ static int pick_tile(const GemmBatch<NPROB>& batch, int epilogue) {
 }
 
 template <int EPI, int NPROB>
-static pg_status launch_one(const GemmBatch<NPROB>& batch, hipStream_t s) {
+static pg_status launch_one(const GemmBatch<NPROB>& batch, hipStream_t s, int tile = 0) {
   // operand rows so far apart that their byte offsets inside a tile need 64 bits (pg_gemm_bf16 alone takes any)
   if constexpr (EPI == EPI_F32)
     if (batch.g[0].lda > NARROW_LD || batch.g[0].ldw > NARROW_LD) return launch_tile<EPI_F32, 128, 128, 2, 2, 2, 2, 2, true>(batch, s);
-  switch (pick_tile(batch, EPI)) {
+  switch (tile ? tile - 1 : pick_tile(batch, EPI)) {
     case 0: return launch_tile<EPI, 256, 256, 2, 4, 2, 2, 2>(batch, s);
     case 1: return launch_tile<EPI, 192, 256, 2, 4, 2, 3, 2>(batch, s);
     case 2: return launch_tile<EPI, 128, 128, 2, 2, 2, 2, 2>(batch, s);
@@ -638,7 +638,7 @@ static pg_status check_gemm(const GemmArgs& a, int epilogue) {
 static int raster_band(int N) { return (N + 255) / 256 <= 6 ? GROUP_M / 2 : GROUP_M; }
 static double gemm_flops(const GemmArgs& a) { return 2.0 * a.M * (double)a.N * (a.k_algo > 0 ? a.k_algo : a.K); }
 
-pg_status launch_gemm(const GemmArgs& a_in, int epilogue, hipStream_t s) {
+pg_status launch_gemm(const GemmArgs& a_in, int epilogue, hipStream_t s, int tile) {
   GemmBatch<1> batch{{a_in}};
   GemmArgs& a = batch.g[0];
   a.group_m = raster_band(a.N);
@@ -647,12 +647,12 @@ pg_status launch_gemm(const GemmArgs& a_in, int epilogue, hipStream_t s) {
   const int rec = prof_open(PROF_GEMM, gemm_flops(a), s);
   pg_status st = PG_EINVAL;
   switch (epilogue) {
-    case EPI_F32: st = launch_one<EPI_F32>(batch, s); break;
+    case EPI_F32: st = launch_one<EPI_F32>(batch, s, tile); break;
     case EPI_EMBED: st = launch_one<EPI_EMBED>(batch, s); break;
     case EPI_BF16: st = launch_one<EPI_BF16>(batch, s); break;
     case EPI_QKV: st = launch_one<EPI_QKV>(batch, s); break;
     case EPI_GELU: st = launch_one<EPI_GELU>(batch, s); break;
-    case EPI_RESID: st = launch_one<EPI_RESID>(batch, s); break;
+    case EPI_RESID: st = launch_one<EPI_RESID>(batch, s, tile); break;
     case EPI_UNPATCH: st = launch_one<EPI_UNPATCH>(batch, s); break;
     default: st = fail(PG_EINVAL, "unknown GEMM epilogue %d", epilogue);
   }
@@ -729,15 +729,36 @@ extern "C" pg_status pg_mfma_probe(int32_t blocks, int32_t iters, float operand_
   return PG_OK;
 }
 
-extern "C" pg_status pg_gemm_bf16(const uint16_t* A, int64_t lda, const uint16_t* W, int64_t ldw,
-                                  const uint16_t* bias, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
-                                  void* stream) {
+// C = A W^T + bias, or C += it
+static pg_status plain_gemm(const uint16_t* A, int64_t lda, const uint16_t* W, int64_t ldw, const uint16_t* bias, float* C, int64_t ldc,
+                            int64_t M, int64_t N, int64_t K, bool accumulate, int tile, hipStream_t s) {
   if (M < 0 || N < 0 || M > INT32_MAX || N > INT32_MAX || K > INT32_MAX) return fail(PG_EINVAL, "pg_gemm_bf16: bad sizes");
   if (M == 0 || N == 0) return PG_OK;
   if (!C || ldc < N) return fail(PG_EINVAL, "pg_gemm_bf16: bad output");
   GemmArgs a{};
   a.A = A; a.lda = lda; a.W = W; a.ldw = ldw; a.bias = bias;
-  a.M = (int)M; a.N = (int)N; a.K = (int)K;
+  a.M = (int)M; a.N = (int)N; a.K = (int)K; a.L = (int)M;
   a.outf = C; a.ldo = ldc;
-  return launch_gemm(a, EPI_F32, (hipStream_t)stream);
+  return launch_gemm(a, accumulate ? EPI_RESID : EPI_F32, s, tile);
+}
+
+extern "C" pg_status pg_gemm_bf16(const uint16_t* A, int64_t lda, const uint16_t* W, int64_t ldw,
+                                  const uint16_t* bias, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
+                                  void* stream) {
+  return plain_gemm(A, lda, W, ldw, bias, C, ldc, M, N, K, false, 0, (hipStream_t)stream);
+}
+
+extern "C" int32_t pg_gemm_tile(int64_t M, int64_t N, int64_t K, int32_t accumulate) {
+  if (M < 1 || N < 1 || K < 1 || M > INT32_MAX || N > INT32_MAX || K > INT32_MAX) return 0;
+  GemmBatch<1> batch{};
+  batch.g[0].M = (int)M; batch.g[0].N = (int)N; batch.g[0].K = (int)K;
+  return pick_tile(batch, accumulate ? EPI_RESID : EPI_F32) + 1;
+}
+
+extern "C" pg_status pg_gemm_bf16_tile(const uint16_t* A, int64_t lda, const uint16_t* W, int64_t ldw,
+                                       const uint16_t* bias, float* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
+                                       int32_t accumulate, int32_t tile, void* stream) {
+  if (tile < 0 || tile > (int)(sizeof(TILES) / sizeof(TILES[0]))) return fail(PG_EINVAL, "pg_gemm_bf16_tile: tile %d", tile);
+  if (lda > NARROW_LD || ldw > NARROW_LD) return fail(PG_ESHAPE, "pg_gemm_bf16_tile: operand rows too far apart");
+  return plain_gemm(A, lda, W, ldw, bias, C, ldc, M, N, K, accumulate != 0, tile, (hipStream_t)stream);
 }

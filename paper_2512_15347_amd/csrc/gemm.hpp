@@ -36,7 +36,7 @@ struct GemmArgs {
   int group_m;                     // tile rows per raster band (set by the launcher)
 };
 
-pg_status launch_gemm(const GemmArgs& a, int epilogue, hipStream_t s);
+pg_status launch_gemm(const GemmArgs& a, int epilogue, hipStream_t s, int tile = 0);     // tile: see pg_gemm_tile, 0: the one it names
 // two problems of equal N and K in one launch (EPI_QKV, EPI_GELU, EPI_RESID)
 pg_status launch_gemm_pair(const GemmArgs& first, const GemmArgs& second, int epilogue, hipStream_t s);
 

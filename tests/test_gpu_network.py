@@ -20,7 +20,7 @@ def bf16_dev(a):
     return torch.from_numpy(workloads.bf16_bits(a).view(np.int16)).to(DEV)
 
 
-# ragged last tiles in both directions; the launcher takes its tiles of 160, 192 and 224 rows, of 128 x 64 and of 64 x 64 here
+# ragged last tiles in both directions, by the launcher's choice
 @pytest.mark.parametrize("M,N,K", [(300, 200, 128), (2356, 384, 512), (256, 256, 64), (1, 16, 64), (777, 4608, 1536),
                                    (12251, 768, 128), (12251, 2304, 64), (12283, 3072, 128), (24571, 1532, 64),
                                    (18848, 1536, 64), (9001, 520, 192)])
@@ -40,20 +40,46 @@ def test_gemm_matches_oracle_linear(lib, M, N, K):
     assert np.max(np.abs(got - want)) < 2e-5 * math.sqrt(K) * np.max(np.abs(want)) + 1e-6
 
 
-# every tile that the launcher has (256 x 256, 224, 192 and 160 rows, 128 x 128 with one and with five K steps, 128 x 64, 64 x 64),
-# one row and column short of or past a tile
+# tiles by the launcher's choice, one row and column short of or past a tile
 @pytest.mark.parametrize("M,N,K", [(3213, 4484, 256), (14100, 1540, 192), (3697, 6140, 192), (4000, 4100, 128), (5000, 1000, 64),
                                    (4099, 1404, 320), (4097, 1020, 192), (63, 252, 64), (65, 68, 192), (64, 64, 128)])
 def test_gemm_tiles_with_short_k(lib, M, N, K):
     test_gemm_matches_oracle_linear(lib, M, N, K)
 
 
-# every tile with fewer K steps than its operands have stages in LDS, as many, and more: 256 x 256 (two stages of either operand), 192
-# and 224 rows (three of A, two of W), 160 rows and 128 x 256 (three), 128 x 128 (two), 128 x 64 and 64 x 64 (three)
+# tiles by the launcher's choice with fewer K steps than their operands have stages in LDS, as many, and more (test_gemm_tile_by_tile has
+# all of them)
 @pytest.mark.parametrize("M,N", [(28673, 260), (14337, 516), (16385, 516), (12289, 516), (14337, 260), (5121, 516), (4097, 260), (70, 68)])
 @pytest.mark.parametrize("steps", [1, 2, 3, 4, 7])
 def test_gemm_stages_in_lds(lib, M, N, steps):
     test_gemm_matches_oracle_linear(lib, M, N, 64 * steps)
+
+
+# every tile with fewer K steps than its operands have stages in LDS, as many, and more: 256 x 256 and 128 x 128 (two stages of either
+# operand), 192 and 224 rows (three of A, two of W), 160 rows, 128 x 256 and 128 x 64 (three), 64 x 64 (two; three); stored and added, with
+# rows and columns that fill no last tile, and with fewer of them than a tile has
+@pytest.mark.parametrize("tile", range(1, 10))
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 7])
+def test_gemm_tile_by_tile(lib, tile, steps):
+    K = 64 * steps
+    say(f"gemm tile {tile}, {steps} K steps")
+    for M, N in ((485, 292), (39, 20)):
+        rng = np.random.default_rng(M + steps)
+        A = workloads.bf16_round(rng.standard_normal((M, K), dtype=np.float32))
+        W = workloads.bf16_round(rng.standard_normal((N, K), dtype=np.float32) * 0.05)
+        b = workloads.bf16_round(rng.standard_normal(N, dtype=np.float32))
+        Ad, Wd, bd = bf16_dev(A), bf16_dev(W), bf16_dev(b)
+        out, chosen = (torch.full((M + 1, N), float("nan"), device=DEV) for _ in range(2))
+        lib.pg_gemm_bf16_tile(Ad, K, Wd, K, bd, out, N, M, N, K, tile=tile)
+        lib.pg_gemm_bf16(Ad, K, Wd, K, bd, chosen, N, M, N, K)
+        added = torch.randn(M + 1, N, device=DEV, generator=torch.Generator(device=DEV).manual_seed(tile))
+        before = added.clone()
+        lib.pg_gemm_bf16_tile(Ad, K, Wd, K, bd, added, N, M, N, K, accumulate=True, tile=tile)
+        want = dit.linear(A.astype(np.float64), W, b)
+        # fp32 accumulation of exact bf16 products: error ~ sqrt(K) * 2^-24 * |a||w|
+        assert np.max(np.abs(out[:M].cpu().numpy() - want)) < 2e-5 * math.sqrt(K) * np.max(np.abs(want)) + 1e-6
+        assert torch.equal(out[:M], chosen[:M]) and out[M].isnan().all()
+        assert torch.equal(added[:M], before[:M] + out[:M]) and torch.equal(added[M], before[M])
 
 
 @pytest.mark.parametrize("ld", [1 << 23, (1 << 23) + 64])

@@ -205,6 +205,19 @@ def test_more_chunks_than_a_launch_has_lanes_for_are_refused(n, d, fits):
     assert all(status == (pg.PG_EINVAL if fits else pg.PG_ESHAPE) for status in calls), calls
 
 
+def test_gemm_tile_choice_and_checks_need_no_gpu():
+    seen = {pg.pg_gemm_tile(M, N, K, acc) for acc in (0, 1) for M in (16, 700, 5000, 9001, 14337, 24576, 28673, 40000, 56544, 60000, 113088)
+            for N in (64, 260, 516, 768, 1540, 4608) for K in (64, 256, 768, 3072, 6144)}
+    assert seen == set(range(1, 10)), seen               # every tile is somebody's
+    assert pg.pg_gemm_tile(0, 64, 64) == 0 and pg.pg_gemm_tile(64, -1, 64) == 0 and pg.pg_gemm_tile(64, 64, 1 << 40) == 0
+    lib = C.CDLL(pg.LIB_PATH)
+    n, k, z = C.c_int64(64), C.c_int64(64), None
+    assert lib.pg_gemm_bf16_tile(z, k, z, k, z, z, n, n, n, k, 0, 10, z) == pg.PG_EINVAL
+    assert lib.pg_gemm_bf16_tile(z, k, z, k, z, z, n, n, n, k, 0, -1, z) == pg.PG_EINVAL
+    far = C.c_int64(1 << 40)
+    assert lib.pg_gemm_bf16_tile(z, far, z, k, z, z, n, n, n, k, 0, 1, z) == pg.PG_ESHAPE
+
+
 def test_addresses_of_any_integer_type_are_taken():
     class Address(int):
         pass
