@@ -5,8 +5,8 @@
 // quadratic in one member's value, so some optimum is "j lowest and k-j highest".
 // Two decompositions for groups of at most 64 members (the paper's groups, cf. the group-size
 // ablation), both with the same order of fp64 additions and therefore the same bits:
-//   few groups: one 64-lane wavefront owns one group: ranks by all-pairs comparison from LDS (the slot decides only
-//   where values are equal), fp64 prefix sums by a six-step scan, k+1 candidate scores in lanes 0..k, a butterfly
+//   few groups: one 64-lane wavefront owns one group: ranks by all-pairs comparison of values from LDS (equal ones
+//   are told apart afterwards), fp64 prefix sums by a six-step scan, k+1 candidate scores in lanes 0..k, a butterfly
 //   arg-max, a ballot for the survivor mask.  4096 groups of 64 are four waves per SIMD, whose instructions bound it:
 //   9.9 us with the slot in every comparison and scans and arg-max by shuffles through LDS, 7.8 here;
 //   many groups: one LANE owns one group (ovf_select_lanes_kernel below).
@@ -186,6 +186,30 @@ __device__ __forceinline__ void wave_best(double& score, int& best) {
   best_of_rows<true>(score, best);
 }
 
+// Ranks under the order (value, slot) from `rank`, the count of smaller values (-1 past the end of the group); `sorted`: 64 floats of LDS
+// of this wave.  The values that several members have are gone through one by one.  Calls of 2^20 groups 64 -> 40 with 1, 2, 12 and 32
+// different values take 888, 897, 999 and 1084 us; with a second round of comparisons, of slots where values are equal, 1221 whatever
+// the values, with value and slot compared from the start 1170, for values without ties, too (those take 875).
+__device__ __forceinline__ int ranks_by_slot(int rank, float* sorted) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  auto settle = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  if (rank >= 0) sorted[rank] = __builtin_bit_cast(float, lane);     // one member of each value stays
+  settle();
+  uint64_t left = __ballot(rank >= 0 && __builtin_bit_cast(int, sorted[max(rank, 0)]) != lane);
+  settle();
+  while (left) {
+    const int first = __builtin_amdgcn_readlane(rank, __builtin_ctzll(left));
+    const uint64_t same = __ballot(rank == first);
+    left &= ~same;
+    const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, rank));
+    if (rank == first) rank = at;
+  }
+  return rank;
+}
+
 // Optimal Variance Filtering of one group by one wavefront: the survivor mask, in every lane; `raw`: reward_of_lane; `vals`,
 // `sorted`: 64 floats of LDS of this wave.
 __device__ __forceinline__ uint64_t survivors_by_wave(float raw, int n, int k, float* vals, float* sorted, int32_t* __restrict__ status) {
@@ -217,8 +241,7 @@ __device__ __forceinline__ uint64_t survivors_by_wave(float raw, int n, int k, f
     rank += q.w < v ? 1 : 0;
   }
   // members with equal values have the same count of smaller ones so far, and the counts add up to less than 0 + 1 + .. + n - 1
-  if ((int)wave_allsum(live ? (float)rank : 0.f) != n * (n - 1) / 2)
-    for (int l = 0; l < n; ++l) rank += vals[l] == v && l < lane ? 1 : 0;
+  if ((int)wave_allsum(live ? (float)rank : 0.f) != n * (n - 1) / 2) rank = ranks_by_slot(live ? rank : -1, sorted);
   if (live) sorted[rank] = v;
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();

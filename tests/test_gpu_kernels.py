@@ -256,6 +256,26 @@ def test_ovf_stress_config_bit_exact(lib):
         np.testing.assert_array_equal(newoff, w_off)
 
 
+@pytest.mark.parametrize("groups", [40, 16400])                     # a wave each; the rest of many groups, k > 32
+def test_ovf_values_that_several_members_have(lib, groups):
+    """Groups of 1 to 64 members with one value for all, two, pairs of every value, pairs and one more, and one pair among single values."""
+    say(f"ovf ties, {groups} groups")
+    rng = np.random.default_rng(groups)
+    sizes = np.array([64, 64, 64, 63, 64, 33, 2, 40] * (groups // 8))
+    ks = np.array([40, 33, 35, 34, 63, 17, 1, 39] * (groups // 8))
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    r = np.empty(off[-1], np.float32)
+    for g, n in enumerate(sizes):
+        levels = (1, 2, 32, 32, 63, 16, 1, 12)[g % 8]
+        r[off[g]:off[g + 1]] = rng.permutation(np.arange(n) % levels) * 0.37 - 3
+    masks, sel, newoff, status = _run_ovf(lib, r, off, ks)
+    w_masks, w_sel, w_off = ovf.ovf_groups(r, off, ks)
+    assert status == 0
+    np.testing.assert_array_equal(masks, w_masks)
+    np.testing.assert_array_equal(sel, w_sel)
+    np.testing.assert_array_equal(newoff, w_off)
+
+
 def test_ovf_ragged_groups_ties_and_degenerate_k(lib):
     say("ovf ragged")
     rng = np.random.default_rng(8)
