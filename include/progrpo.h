@@ -349,8 +349,9 @@ pg_status pg_attention_network(const uint16_t *q, const uint16_t *k, const uint1
  * durations [ms] (each less the duration an empty event pair reads on that stream, measured once at
  * the first bracket), the summed algorithmic work and the number of launches.
  * kind 0: MFMA GEMM (work = 2 M N K flops; a narrow network that is evaluated in one launch counts as one of these, with the
- * flops of its products and of its attention), 1: attention (4 B heads Lq Lk hd flops),
- * 2: fused update + log-prob (12 bytes per latent element), 3: preview / reward (8 or 4 bytes per element). */
+ * flops of its products and of its attention; one that is evaluated in a launch per block, too, and the updates that pg_sample_group
+ * lets these launches make are in its time), 1: attention (4 B heads Lq Lk hd flops),
+ * 2: fused update + log-prob in a launch of its own (12 bytes per latent element), 3: preview / reward (8 or 4 bytes per element). */
 pg_status pg_profile_begin(int32_t max_records);
 pg_status pg_profile_read(int32_t kind, double *total_ms, double *total_work, int64_t *launches);
 pg_status pg_profile_end(void);

@@ -509,8 +509,6 @@ bool sums_on_arrival(int64_t n_traj, int64_t d) {
   return chunks <= 32 && n_traj * chunks <= 5120;
 }
 
-pg_status launch_noise_sums(int M0, int steps, int64_t d, uint64_t seed, double* sums, hipStream_t stream);
-
 // What a run starts from, in one launch: initial latents by chunk (ids are the rows), then, 256 lanes a workgroup, the sums of the noise
 // of `steps` steps where they are asked for (latents of one chunk), then the state: offsets of the full groups, ids, group of
 // every row, no log-prob yet (NaN), zero sums, clear status and counts.  (Two launches, with the noise three, of 2 to 3 us before.)

@@ -394,8 +394,8 @@ __global__ __launch_bounds__(THREADS, 2) void small_net_kernel(const SmallNetArg
 // A wave owns column tiles of 16 as above; every sum is formed in the order of small_net_kernel, so both give the same bits.
 // A launch takes 7.9 us (width 128, 64 tokens, 16 or 32 workgroups), with the final layer, the update and the next step's first
 // rows 10.5 us; what is left is latency: 2 us of launch, 2 us until keys, values and the first weights are there, 4 us for seven
-// phases between barriers.  The loop of 8 trajectories and ten steps takes 264 us (461 with one workgroup per trajectory and an
-// update launch per step), three groups of 12 with 90 tokens and six steps 228 us (387).
+// phases between barriers.  The loop of 8 trajectories and ten steps takes 250 us (461 with one workgroup per trajectory and an
+// update launch per step), three groups of 12 with 90 tokens and six steps 209 us (387).
 namespace {
 // What a launch does: the first rows of a step, a block with the queries / keys / values of the next one, the last block and u
 // (and the update), or that and the next step's first rows

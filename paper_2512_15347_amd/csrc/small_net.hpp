@@ -24,7 +24,7 @@ bool small_net_takes(const pg_ctx* c);
 pg_status launch_small_net(const SmallNetArgs& a, int D, int hd, hipStream_t s);
 
 // The same networks with a workgroup per 16 rows of a trajectory and a launch per block, for few trajectories
-// (small_rows_takes).  A step is rows_start (patch embedding, queries / keys / values of the first block), then one launch per
+// (small_rows_takes).  A step is ROWS_START (patch embedding, queries / keys / values of the first block), then one launch per
 // block, each with the queries / keys / values of the block after it; the last one writes u, may make the sampler's update and may
 // start the next step.
 struct RowsUpdate {                                // x_out = A x[src] + B u[src] + C xi, log-prob from the sum of xi^2
@@ -64,6 +64,5 @@ struct RowsPass {
   bool start_next;                                 // start the next step with it (the next row of the modulation vectors)
 };
 pg_status net_rows(pg_ctx* c, const NetBatch& batch, const RowsPass& pass, const uint16_t* weights, hipStream_t s);
-pg_status launch_small_rows(const RowsArgs& a, int D, int hd, hipStream_t s);
 
 }  // namespace pg

@@ -19,8 +19,8 @@ def say(msg):
 
 
 def _config(name):
-    """The named configuration; `<name>_layers` has its network of width 128 widened to 256, which takes a launch per layer where one
-    workgroup evaluates the narrow one whole."""
+    """The named configuration; `<name>_layers` has its network of width 128 widened to 256, which takes a launch for the layers between two
+    attentions where workgroups that hold a trajectory or 16 rows of it evaluate the narrow one."""
     if not name.endswith("_layers"):
         return workloads.get_config(name)
     cfg = workloads.get_config(name[:-len("_layers")])
@@ -354,9 +354,9 @@ def _check_sharp_network(lib, cfg, kind, gain, trajectories):
     lib.pg_destroy(ctx)
 
 
-# the rows of the cross and dual-stream networks take a launch per layer, with token counts that store the transposed values in units
-# of four (64 and 32 tokens; context rows of 16 after 64) and one by one (35 and 30; context rows of 13, 18, 21 and 77); those of the
-# other two kinds one workgroup evaluates whole
+# the rows of the cross and dual-stream networks take a launch between two attentions, with token counts that store the transposed values in
+# units of four (64 and 32 tokens; context rows of 16 after 64) and one by one (35 and 30; context rows of 13, 18, 21 and 77); those of the
+# other two kinds workgroups of the narrow networks evaluate
 @pytest.mark.parametrize("kind,H,W,Lc,heads,gain", [
     ("adaln", 16, 16, 0, 4, 7), ("adaln", 10, 14, 0, 4, 10), ("cross", 10, 14, 13, 2, 7), ("cross", 16, 16, 77, 2, 7),
     ("joint", 10, 14, 26, 2, 7), ("joint", 16, 16, 27, 2, 7), ("mmdit", 10, 14, 18, 2, 1), ("mmdit", 10, 12, 21, 2, 1),
@@ -369,7 +369,7 @@ def test_network_output_with_sharp_attention(lib, kind, H, W, Lc, heads, gain):
     _check_sharp_network(lib, cfg, kind, gain, (0, 4, 5, 9))
 
 
-# a launch per layer for the other two kinds, too, at both head widths: units of four (64 tokens, 30 before 26 that make 56 of them),
+# a launch between two attentions for the other two kinds, too, at both head widths: units of four (64 tokens, 30 before 26 that make 56 of them),
 # and one by one (35; 91)
 @pytest.mark.parametrize("kind,H,W,Lc,heads,gain", [
     ("adaln", 16, 16, 0, 6, 7), ("adaln", 10, 14, 0, 3, 10), ("joint", 10, 12, 26, 3, 7), ("joint", 16, 16, 27, 3, 7),
