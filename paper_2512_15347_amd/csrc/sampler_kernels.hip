@@ -32,8 +32,9 @@ __device__ __forceinline__ float block_sum_256(float v) {
 // of 256 (585 where the arrays lie at odd multiples of 4 KB) and 487 to 516 us so, by where the arrays lie and from box to box, 3 to 8 %
 // apart in calls that follow other work; 6.2 to 6.6 TB/s, the plain copy 6.0 to 6.25.  After half a second without work the clocks
 // give way under this form alone: the 4th to 25th call (2 to 12 ms on) take 520 to 605 us, then 500 again, with 256 lanes 540 from the
-// second one on, so a dozen calls after a pause take 540 to 560 us against 532.  Two inputs and one output without arithmetic take
-// 505 and 497, in waves of their own 471, but their sums would be 16 to a chunk.
+// second one on.  In a loop an update follows a network evaluation, and a dozen calls after a pause take 543 to 552 us against
+// 540.  512 lanes with two accesses each take 511 to 519 us with and without a pause.  Two inputs and one output without arithmetic
+// take 505 and 497, in waves of their own 471, but their sums would be 16 to a chunk.
 // The bf16 storage keeps four waves: its Philox blocks bound it as much as memory (267 us; a lane per access 269, two chunks to a
 // workgroup 279).
 constexpr int CHUNK_THREADS = STREAM_CHUNK / 4;
